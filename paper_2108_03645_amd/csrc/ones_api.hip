@@ -72,7 +72,7 @@ int static_scratch_of(int device, char **out) {
 // (ctx->splitters_valid).  Offsets from the block's base, which lies in the caller's workspace
 // or, for ones_generation_static, in the library's static array.
 struct ScratchLayout {
-  size_t split, thresh, bcount[2], bkeys, bidx, skeys, sidx, sbucket, pkeys, pidx, total;
+  size_t split, split_slot, thresh, bcount[2], bkeys, bidx, skeys, sidx, sbucket, total;
 };
 
 struct Layout {
@@ -84,20 +84,21 @@ struct Layout {
 // Buckets of the selection: about 16 survivors each, at most kMaxBuckets.  A bucket stores eight
 // times its fair share of the 3P/4 children and mutants (at least 256, a power of two); the
 // surplus goes to a spill list that can hold a whole pool (the general selection drops every
-// candidate, and equal scores all land in one bucket), and buckets too large for LDS are sorted
-// in a scratch pool (each takes a power-of-two slice below twice its size).  The general
-// selection re-divides the same bucket space among its own number of buckets.
-struct BucketPlan { uint32_t nb, seg, spill, pool; };
+// candidate).  The general selection re-divides the same bucket space among its own number of
+// buckets.
+struct BucketPlan { uint32_t nb, seg, spill; };
 constexpr uint32_t kMinBucketPool = 256;
+// Largest population whose selection ones_generation_static takes into the static array: the bound
+// callers know (beyond it a bucket's storage doubles); its scratch is checked against the array too.
+constexpr uint32_t kStaticMaxPopulation = 87380;
 uint32_t pow2_at_least(uint32_t v) { uint32_t n = 1; while (n < v) n <<= 1; return n; }
 BucketPlan bucket_plan(uint32_t P) {
-  if (P < kMinBucketPool) return BucketPlan{0, 0, 0, 0};      // tiny pools: one short sort is as fast
+  if (P < kMinBucketPool) return BucketPlan{0, 0, 0};      // tiny pools: one short sort is as fast
   const uint32_t K = P / 4;
   BucketPlan bp;
   bp.nb = std::min<uint32_t>(kMaxBuckets, std::max<uint32_t>(1, K / 16));
   bp.spill = P;                                            // the general selection may spill a whole pool
-  bp.pool = 2 * pow2_at_least(P);                          // every slice is a power of two below twice its bucket
-  bp.seg = std::min(pow2_at_least(std::max<uint32_t>(256, 8 * ((3 * K + bp.nb - 1) / bp.nb))), bp.pool / 4);
+  bp.seg = std::min(pow2_at_least(std::max<uint32_t>(256, 8 * ((3 * K + bp.nb - 1) / bp.nb))), pow2_at_least(P) / 2);
   return bp;
 }
 
@@ -112,15 +113,13 @@ ScratchLayout make_scratch_layout(uint32_t P) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes); return at; };
   const BucketPlan bp = bucket_plan(P);
-  S.split = take(kMaxBuckets * 8); S.thresh = take(8);
+  S.split = take(kMaxBuckets * 8); S.split_slot = take(kMaxBuckets * 4); S.thresh = take(8);
   S.bcount[0] = take(kBucketCounters * 4); S.bcount[1] = take(kBucketCounters * 4);
   S.bkeys = take(static_cast<size_t>(bp.nb) * bp.seg * 8);
   S.bidx = take(static_cast<size_t>(bp.nb) * bp.seg * 4);
   S.skeys = take(static_cast<size_t>(bp.spill) * 8);
   S.sidx = take(static_cast<size_t>(bp.spill) * 4);
   S.sbucket = take(static_cast<size_t>(bp.spill) * 4);
-  S.pkeys = take(static_cast<size_t>(bp.pool) * 8);
-  S.pidx = take(static_cast<size_t>(bp.pool) * 4);
   S.total = off;
   return S;
 }
@@ -143,7 +142,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   // single-launch generations of small pools: arrival counter + error word, scores exchanged by slot
   L.fsync = take(256);
   L.xkeys = take(fused_pool(P, Jp) ? fused_exchange_bytes(P) : 0);
-  // the selection's scratch: splitters, counters, bucket storage, spill list, scratch pool
+  // the selection's scratch: splitters, counters, bucket storage, spill list
   L.S = make_scratch_layout(P);
   L.scratch = take(L.S.total);
   L.cstart = take(Jp * 4); L.cmax = take(Jp * 4); L.info = take(Jp * 4);
@@ -379,8 +378,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.bk.spill_keys = reinterpret_cast<uint64_t *>(sc(S.skeys));
   a.bk.spill_idx = reinterpret_cast<uint32_t *>(sc(S.sidx));
   a.bk.spill_bucket = reinterpret_cast<uint32_t *>(sc(S.sbucket));
-  a.bk.pool_keys = reinterpret_cast<uint64_t *>(sc(S.pkeys));
-  a.bk.pool_idx = reinterpret_cast<uint32_t *>(sc(S.pidx));
+  a.bk.split_slot = reinterpret_cast<uint32_t *>(sc(S.split_slot));
   // the selection notes the rows the survivors keep: parents and first K slots of the next pool
   RowPlan rp;
   rp.row_of_cur = a.row_of;
@@ -708,7 +706,7 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   char *block = c->ws + c->L.scratch;
   bool static_valid = false;      // the static array holds whatever the last call on this GPU left
   if (in_static_scratch) {
-    if (c->L.S.total > ONES_STATIC_SCRATCH_BYTES) return ONES_E_STATIC_LIMIT;
+    if (c->P > kStaticMaxPopulation || c->L.S.total > ONES_STATIC_SCRATCH_BYTES) return ONES_E_STATIC_LIMIT;
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
     if (dev != c->device) return ONES_E_INVALID_ARG;

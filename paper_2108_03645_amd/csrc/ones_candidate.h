@@ -492,6 +492,7 @@ __device__ __forceinline__ void drop_in_bucket(const EvolveArgs &a, const Smem &
     uint32_t *count = ka->bk.count;
     const uint32_t seg = ka->bk.seg;
     const uint32_t slot = atomicAdd(&count[b], 1u);
+    if (slot == kManyInBucket) count[kManyFlag] = 1;
     if (slot < seg) {
       const size_t at = static_cast<size_t>(b) * seg + slot;
       ka->bk.keys[at] = bits;

@@ -66,12 +66,12 @@ __host__ __device__ inline uint32_t info_new(uint32_t w)    { return (w >> 22) &
 // Quantile buckets of the selection (valid while the job table stays the same): children and
 // mutants that beat the K-th survivor are dropped into the bucket of the survivors they fall
 // between.  nb == 0 switches the mechanism off.  A bucket stores up to seg offspring; the rare
-// surplus goes to one shared spill list, and a bucket too large for LDS is sorted in a slice of
-// a shared scratch pool.
+// surplus goes to one shared spill list.
 constexpr int kMaxBuckets = 1024;
 constexpr int kSpillCounter = kMaxBuckets;       // count[kSpillCounter]: records in the spill list
-constexpr int kPoolCounter = kMaxBuckets + 1;    // count[kPoolCounter]: scratch pool entries handed out
+constexpr int kManyFlag = kMaxBuckets + 1;       // count[kManyFlag]: a bucket was given more than kManyInBucket records
 constexpr int kBucketCounters = kMaxBuckets + 2;
+constexpr uint32_t kManyInBucket = 512;
 constexpr int kRowGroupWords = 64;               // bitmap words per entry of the free-row index (one per lane)
 struct BucketArgs {
   const uint64_t *split;      // [kMaxBuckets] score bits of survivor ranks c*K/nb, c = 1..nb-1, then +inf
@@ -82,8 +82,7 @@ struct BucketArgs {
   uint64_t       *spill_keys; // [P] surplus candidates: score bits, slot, bucket
   uint32_t       *spill_idx;
   uint32_t       *spill_bucket;
-  uint64_t       *pool_keys;  // [pool] scratch for buckets that do not fit LDS
-  uint32_t       *pool_idx;
+  uint32_t       *split_slot; // [kMaxBuckets] general selection: the pool slots that go with the splitters' scores
   uint64_t       *split_next; // splitters and threshold for the next generation (same arrays)
   uint64_t       *thresh_next;
   uint32_t        nb, seg;
@@ -219,8 +218,8 @@ inline hipError_t launch_evolve(const EvolveArgs &a, int rows, bool same_table, 
     default: return hipErrorInvalidValue;
   }
 }
-// General selection (any scores).  store: the bucket storage (count, keys, idx, spill and pool
-// arrays, split as scratch for the splitters, nb * seg entries of bucket space); used by pools
+// General selection (any scores).  store: the bucket storage (count, keys, idx and spill arrays,
+// split and split_slot as scratch for the splitters, nb * seg entries of bucket space); used by pools
 // too large for the single launch that ranks a whole pool.  slot_score: the pool's scores by slot
 // when the evolve launch wrote them all, else null (they are then looked up through the rows).
 hipError_t launch_select(const double *fit_row, const double *slot_score, const RowPlan &rp, uint32_t P, uint32_t K,

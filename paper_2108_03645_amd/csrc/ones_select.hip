@@ -128,8 +128,9 @@ __device__ __forceinline__ void note_rank(uint32_t g, uint64_t bits, uint32_t K,
 
 constexpr int kBucketThreads = 256;
 constexpr int kBucketLds = 2048;      // offspring of one bucket that are sorted in LDS
-constexpr int kBucketCount = 512;     // up to here offspring are ranked by counting, not sorted
+constexpr int kBucketCount = kManyInBucket;   // up to here offspring are ranked by counting, not sorted
 constexpr int kBucketElites = 1025;   // survivors of one bucket: at most ceil(2^18 / 256) + 1
+constexpr uint32_t kFewCrowded = 8;   // so many buckets above kBucketCount are ranked by all workgroups together
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 #pragma unroll
@@ -140,8 +141,8 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 // Ranks one bucket: offspring in (sk, si)[0..n) (padded with never-smaller keys up to npad, a
 // multiple of 8), survivors' score bits in ek[0..ne).  Writes the survivor list entries that
 // fall below K and notes the next generation's splitters.
-template <bool kElites, int kThreads, typename K64, typename I32>
-__device__ __forceinline__ void rank_bucket(K64 *sk, I32 *si, const uint64_t *ek, uint32_t n, uint32_t npad,
+template <bool kElites, int kThreads>
+__device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *si, const uint64_t *ek, uint32_t n, uint32_t npad,
                                             uint32_t ne, uint32_t e0, uint32_t off, bool sorted, uint32_t K,
                                             const BucketArgs &bk, const RowPlan &rp, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb;
@@ -216,8 +217,7 @@ __device__ __forceinline__ void rank_bucket(K64 *sk, I32 *si, const uint64_t *ek
 
 // Gathers the bucket's offspring (own storage, then its share of the spill list) into
 // (dk, di)[0..n) and pads up to npad.
-template <typename K64, typename I32>
-__device__ __forceinline__ void gather_bucket(K64 *dk, I32 *di, const BucketArgs &bk, uint32_t b, uint32_t n,
+__device__ __forceinline__ void gather_bucket(uint64_t *dk, uint32_t *di, const BucketArgs &bk, uint32_t b, uint32_t n,
                                               uint32_t npad, uint32_t *lds_counter) {
   const uint32_t tid = threadIdx.x;
   const uint32_t n_main = n < bk.seg ? n : bk.seg;
@@ -235,30 +235,135 @@ __device__ __forceinline__ void gather_bucket(K64 *dk, I32 *di, const BucketArgs
       }
     }
   }
-  __threadfence_block();
   __syncthreads();
+}
+
+// What the threads of a workgroup that handles buckets share.
+template <int kThreads>
+struct BucketShared {
+  uint64_t sk[kBucketLds];
+  uint32_t si[kBucketLds];
+  uint64_t ek[kBucketElites];
+  uint32_t red[kThreads / kLanes];
+  uint32_t below[kThreads];
+  uint32_t crowded[kMaxBuckets];       // the buckets above kBucketCount
+  uint32_t spill_cursor, n_crowded;
+};
+
+// A crowded bucket, ranked by all workgroups of the launch together: each takes an equal share of
+// the bucket's records (places of its storage, then of the spill list, whose records of other
+// buckets count for nothing) and ranks it by counting against all of them, a tile at a time; the
+// bucket's own workgroup ranks its survivors too.  Where children crowd, be it because a pool is
+// full of copies of one genome or because nearly all children beat its best members, one workgroup
+// alone took 0.2 to 1.8 ms (sorting network in global memory) for what takes all of them 10 to 50 us.
+template <bool kElites, int kThreads>
+__device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const double *fit_row, const uint32_t *parent_row,
+                                             const BucketArgs &bk, const RowPlan &rp, uint32_t K, uint32_t o, int32_t *sel) {
+  const uint32_t tid = threadIdx.x, nb = bk.nb, b = blockIdx.x;
+  uint32_t before = 0;
+  for (uint32_t c = tid; c < o; c += kThreads) before += bk.count[c];
+  before = wave_sum_u32(before);
+  __syncthreads();                                   // the shared arrays are free
+  if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
+  const uint32_t e0 = kElites ? bucket_bound(o, K, nb) : 0u, ne = kElites ? bucket_bound(o + 1, K, nb) - e0 : 0u;
+  for (uint32_t e = tid; e < ne; e += kThreads)
+    sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[parent_row[e0 + e]]));
+  __syncthreads();
+  uint32_t off = e0;
+#pragma unroll
+  for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
+  if (off >= K) return;                              // nothing of this bucket survives
+  const uint32_t n = bk.count[o], n_main = min(n, bk.seg);
+  const uint32_t places = n_main + (n > n_main ? bk.count[kSpillCounter] : 0u);
+  auto record = [&](uint32_t at, uint64_t &key, uint32_t &id) {      // a place of the bucket; id ~0: no record of it
+    key = ~0ull;
+    id = 0xFFFFFFFFu;
+    if (at < n_main) {
+      key = bk.keys[static_cast<size_t>(o) * bk.seg + at];
+      id = bk.idx[static_cast<size_t>(o) * bk.seg + at];
+    } else if (at < places && bk.spill_bucket[at - n_main] == o) {
+      key = bk.spill_keys[at - n_main];
+      id = bk.spill_idx[at - n_main];
+    }
+  };
+  const uint32_t first = static_cast<uint32_t>(static_cast<uint64_t>(places) * b / nb);
+  const uint32_t last = static_cast<uint32_t>(static_cast<uint64_t>(places) * (b + 1) / nb);
+  const uint32_t total = (last - first) + (b == o ? ne : 0u);
+  for (uint32_t base = 0; base < total; base += kThreads) {
+    // thread (i, part): element base + i against every parts-th record of a tile
+    const uint32_t m = min(total - base, static_cast<uint32_t>(kThreads)), width = pow2_at_least(m);
+    const uint32_t parts = kThreads / width, i = tid % width, part = tid / width;
+    const uint32_t mine = base + i;
+    uint64_t key = ~0ull;
+    uint32_t id = 0xFFFFFFFFu, e = 0;
+    bool offspring = false, survivor = false;
+    if (i < m) {
+      if (mine < last - first) {
+        record(first + mine, key, id);
+        offspring = id != 0xFFFFFFFFu;
+      } else {                                       // wins every tie, like slot 0
+        e = mine - (last - first);
+        key = sh.ek[e];
+        id = 0;
+        survivor = true;
+      }
+    }
+    uint32_t n_below = 0;
+    for (uint32_t tile = 0; tile < places; tile += kBucketLds) {
+      __syncthreads();
+      for (uint32_t q = tid; q < static_cast<uint32_t>(kBucketLds); q += kThreads) record(tile + q, sh.sk[q], sh.si[q]);
+      __syncthreads();
+      const uint32_t count = min(places - tile, static_cast<uint32_t>(kBucketLds));
+      if (offspring || survivor)
+        for (uint32_t q = part; q < count; q += parts) n_below += key_less(sh.sk[q], sh.si[q], key, id) ? 1u : 0u;
+    }
+    sh.below[tid] = 0;
+    __syncthreads();
+    if (n_below) atomicAdd(&sh.below[i], n_below);
+    __syncthreads();
+    uint32_t g = K, slot = 0;
+    if (part == 0 && (offspring || survivor)) {
+      g = off + sh.below[i];
+      slot = survivor ? e0 + e : id;
+      if (survivor) {
+        g += e;
+      } else {                                       // survivors with a score at or below its own come before it
+        uint32_t lo = 0, hi = ne;
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (sh.ek[mid] <= key) lo = mid + 1; else hi = mid;
+        }
+        g += lo;
+      }
+      if (g < K) {
+        sel[g] = static_cast<int32_t>(slot);
+        if (kElites) note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+      }
+    }
+    keep_rows(rp, g < K, g, slot);
+  }
 }
 
 // kElites: the quantile buckets above, each with its share of the survivors.  Without: the last
 // step of the sample sort of the general path below, a bucket holds candidates only (fit_row,
 // parent_row, count_next unused) and its first rank is the number of candidates before it.
 // kThreads: a bucket of at most that many offspring (nearly all) is ranked straight from registers.
+// A bucket is crowded, and left to all workgroups together, when it holds more than a workgroup
+// sorts in LDS, or more than it ranks by counting while only a few buckets do (the LDS sort of 2048
+// takes one workgroup 20 us; with many such buckets the workgroups are all busy anyway).
 template <bool kElites, int kThreads>
 __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *fit_row,
                                                                        const uint32_t *parent_row, BucketArgs bk,
                                                                        RowPlan rp, uint32_t K, uint32_t *count_next,
                                                                        int32_t *sel) {
-  __shared__ uint64_t sk[kBucketLds];
-  __shared__ uint32_t si[kBucketLds];
-  __shared__ uint64_t ek[kBucketElites];
-  __shared__ uint32_t red[kThreads / kLanes];
-  __shared__ uint32_t spill_cursor, pool_base;
+  __shared__ BucketShared<kThreads> sh;
   const uint32_t b = blockIdx.x, nb = bk.nb, tid = threadIdx.x;
   // offset of this bucket = its first survivor rank + all offspring of the buckets before it
   uint32_t before = 0;
   for (uint32_t c = tid; c < b; c += kThreads) before += bk.count[c];
   before = wave_sum_u32(before);
-  if ((tid & (kLanes - 1)) == 0) red[tid / kLanes] = before;
+  if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
+  const bool any_many = bk.count[kManyFlag] != 0;    // a bucket holds more than kBucketCount
   const uint32_t e0 = kElites ? bucket_bound(b, K, nb) : 0u, ne = kElites ? bucket_bound(b + 1, K, nb) - e0 : 0u;
   const uint32_t n = bk.count[b];
   // Every global load a small bucket needs is issued here, before anything waits for one: an
@@ -280,27 +385,31 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
   const bool small = n <= static_cast<uint32_t>(kThreads) && n <= seg && ne <= static_cast<uint32_t>(kThreads);
   // counting loops run in steps of 8 over padding; the sorting network needs a power of two
   const bool sorted = n > static_cast<uint32_t>(kBucketCount);
-  const uint32_t npad = sorted ? pow2_at_least(n) : (n < 8 ? 8u : (n + 7) & ~7u);
-  const bool in_lds = npad <= static_cast<uint32_t>(kBucketLds);
+  const bool in_lds = n <= static_cast<uint32_t>(kBucketLds);
+  const uint32_t npad = !in_lds ? 0u : sorted ? pow2_at_least(n) : (n < 8 ? 8u : (n + 7) & ~7u);
   if (small) {
     if (tid < npad) {                                // never sorted: npad <= the threads
-      sk[tid] = tid < n ? my_key : ~0ull;
-      si[tid] = tid < n ? my_idx : 0xFFFFFFFFu;
+      sh.sk[tid] = tid < n ? my_key : ~0ull;
+      sh.si[tid] = tid < n ? my_idx : 0xFFFFFFFFu;
     }
-    if (se < ne) ek[se] = elite_key;
+    if (se < ne) sh.ek[se] = elite_key;
   } else {
     for (uint32_t e = tid; e < ne; e += kThreads)
-      ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[parent_row[e0 + e]]));
+      sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[parent_row[e0 + e]]));
   }
-  if (tid == 0) {
-    spill_cursor = 0;
-    pool_base = in_lds ? 0u : atomicAdd(&bk.count[kPoolCounter], npad);   // a slice of the scratch pool
-  }
+  if (tid == 0) sh.spill_cursor = sh.n_crowded = 0;
   __syncthreads();
   uint32_t off = e0;
 #pragma unroll
-  for (int w = 0; w < kThreads / kLanes; ++w) off += red[w];
-  if (off < K && n + ne != 0) {                      // otherwise nothing of this bucket survives
+  for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
+  bool crowded = false;                              // this workgroup's own bucket
+  if (any_many) {                               // list the buckets that hold many, in any order
+    for (uint32_t c = tid; c < nb; c += kThreads)
+      if (bk.count[c] > static_cast<uint32_t>(kBucketCount)) sh.crowded[atomicAdd(&sh.n_crowded, 1u)] = c;
+    __syncthreads();
+    crowded = n > static_cast<uint32_t>(kBucketLds) || (sorted && sh.n_crowded <= kFewCrowded);
+  }
+  if (!crowded && off < K && n + ne != 0) {          // otherwise nothing of this bucket survives
     if (small) {
       // offspring tid: rank = offspring below it + survivors with score <= its score (a survivor
       // wins a tie: smaller slot)
@@ -311,17 +420,17 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
           for (uint32_t q = 0; q < npad; q += 8) {
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
-              const uint64_t other = sk[q + v];
+              const uint64_t other = sh.sk[q + v];
               below += other < my_key ? 1u : 0u;
               equal += other == my_key ? 1u : 0u;
             }
           }
           if (equal > 1)                             // shares its score: the slots decide
-            for (uint32_t q = 0; q < n; ++q) below += (sk[q] == my_key && si[q] < my_idx) ? 1u : 0u;
+            for (uint32_t q = 0; q < n; ++q) below += (sh.sk[q] == my_key && sh.si[q] < my_idx) ? 1u : 0u;
           uint32_t lo = 0, hi = ne;
           while (lo < hi) {
             const uint32_t mid = (lo + hi) >> 1;
-            if (ek[mid] <= my_key) lo = mid + 1; else hi = mid;
+            if (sh.ek[mid] <= my_key) lo = mid + 1; else hi = mid;
           }
           g = off + below + lo;
           if (g < K) {
@@ -338,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
           uint32_t lo = 0;
           for (uint32_t q = 0; q < npad; q += 8) {
 #pragma unroll
-            for (int v = 0; v < 8; ++v) lo += sk[q + v] < elite_key ? 1u : 0u;
+            for (int v = 0; v < 8; ++v) lo += sh.sk[q + v] < elite_key ? 1u : 0u;
           }
           g = off + se + lo;
           if (g < K) {
@@ -348,21 +457,23 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
         }
         keep_rows_at(rp, g < K, g, elite_row);
       }
-    } else if (in_lds) {
-      gather_bucket(sk, si, bk, b, n, npad, &spill_cursor);
-      if (sorted) bitonic_sort(sk, si, npad);
-      rank_bucket<kElites, kThreads>(sk, si, ek, n, npad, ne, e0, off, sorted, K, bk, rp, sel);
-    } else {                                         // oversized bucket: same network in global memory
-      uint64_t *pk = bk.pool_keys + pool_base;
-      uint32_t *pi = bk.pool_idx + pool_base;
-      gather_bucket(pk, pi, bk, b, n, npad, &spill_cursor);
-      bitonic_sort(pk, pi, npad);
-      rank_bucket<kElites, kThreads>(pk, pi, ek, n, npad, ne, e0, off, true, K, bk, rp, sel);
+    } else {
+      gather_bucket(sh.sk, sh.si, bk, b, n, npad, &sh.spill_cursor);
+      if (sorted) bitonic_sort(sh.sk, sh.si, npad);
+      rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek, n, npad, ne, e0, off, sorted, K, bk, rp, sel);
+    }
+  }
+  if (any_many) {
+    const uint32_t listed = sh.n_crowded;
+    for (uint32_t k = 0; k < listed; ++k) {
+      const uint32_t o = sh.crowded[k];
+      if (listed <= kFewCrowded || bk.count[o] > static_cast<uint32_t>(kBucketLds))
+        rank_crowded<kElites, kThreads>(sh, fit_row, parent_row, bk, rp, K, o, sel);
     }
   }
   if (kElites) {                                     // the other counter set, for the next generation
     if (tid == 0) count_next[b] = 0;
-    if (b == 0 && tid < 2) count_next[kMaxBuckets + tid] = 0;
+    if (b == 0 && tid == 0) count_next[kSpillCounter] = count_next[kManyFlag] = 0;
   }
 }
 
@@ -373,91 +484,93 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
 // only those that reach below rank K do any work.  The sample only decides how even the buckets
 // are, never the result.
 
-// Splitters: `sample` = per * nb scores taken at a fixed stride from the pool; those of rank
-// per * (c + 1) - 1 among them become splitter c (per = kOversample sample points per bucket, two
-// where that would take more than kSampleMax; a bucket of 64 to 127 candidates on average then
-// hardly ever grows beyond the 512 that are ranked straight from registers).  A splitter may be any value, so the low bits of a sample score
-// give way to its position in the sample: all sample values differ and one 64-bit comparison
-// orders them.  Ranks by counting: every workgroup loads the whole sample into LDS and each of
-// its waves ranks four elements, the lanes striding over the sample.
+// Splitters: `sample` = per * nb candidates taken at a fixed stride from the pool; those of rank
+// per * (c + 1) - 1 among them, in (score, slot) order like everything else, become splitter c (per =
+// kOversample sample points per bucket, two where that would take more than kSampleMax; a bucket of
+// 64 to 127 candidates on average then hardly ever grows beyond the 512 that are ranked straight from
+// registers).  A splitter is a (score, slot) pair, not a score: a pool that has been searched for a
+// while is full of copies of one genome, and splitters that only knew the scores put all of them into
+// one bucket, which one workgroup then ranked alone (16384 candidates of 512 jobs: 544 us for the
+// bucket kernel where a pool of distinct scores takes 9).  Ranks by counting: every workgroup loads the
+// whole sample into LDS and each of its waves ranks one element, the lanes striding over the sample.
 constexpr int kSampleThreads = 1024;
 constexpr int kOversample = 4;
 constexpr int kSampleMax = 2048;
-constexpr int kSamplePerWave = 1;
-constexpr int kSamplePer = kSamplePerWave * kSampleThreads / kLanes;    // elements ranked by one workgroup
+constexpr int kSamplePer = kSampleThreads / kLanes;    // elements ranked by one workgroup
 __global__ __launch_bounds__(kSampleThreads) void sample_splitters_kernel(const double *fit_row, const double *slot_score,
                                                                          const uint32_t *row_of, uint32_t P,
                                                                          uint32_t sample, uint32_t nb,
-                                                                         uint64_t *split, uint32_t *count) {
+                                                                         uint64_t *split, uint32_t *split_slot,
+                                                                         uint32_t *count) {
   __shared__ uint64_t sk[kSampleMax];
-  static_assert(kSampleMax <= 4096, "the position in the sample takes the low 12 bits of a score");
   const uint32_t per = sample / nb;                   // sample points per bucket: kOversample, or fewer with kMaxBuckets buckets
   const uint32_t t = threadIdx.x;
   const uint32_t sample_log2 = 31 - __clz(static_cast<int>(sample));
+  // sample point e: slot floor(e P / sample); sample is a power of two
+  auto slot_of = [&](uint32_t e) { return static_cast<uint32_t>((static_cast<uint64_t>(e) * P) >> sample_log2); };
   if (blockIdx.x == 0)
     for (uint32_t c = t; c < static_cast<uint32_t>(kBucketCounters); c += kSampleThreads) count[c] = 0;
   uint64_t mine_of[kSampleMax / kSampleThreads];
 #pragma unroll
   for (int u = 0; u < kSampleMax / kSampleThreads; ++u) {          // all loads first, then the stores
-    const uint32_t e = t + u * kSampleThreads;
-    // slot floor(e P / sample); sample is a power of two
-    const uint32_t p = static_cast<uint32_t>((static_cast<uint64_t>(e) * P) >> sample_log2);
-    mine_of[u] = e < sample ? static_cast<uint64_t>(__double_as_longlong(slot_score ? slot_score[p] : fit_row[row_of[p]])) : 0ull;
+    const uint32_t e = t + u * kSampleThreads, p = slot_of(e);
+    mine_of[u] = e < sample ? static_cast<uint64_t>(__double_as_longlong(slot_score ? slot_score[p] : fit_row[row_of[p]])) : ~0ull;
   }
 #pragma unroll
-  for (int u = 0; u < kSampleMax / kSampleThreads; ++u) {
-    const uint32_t e = t + u * kSampleThreads;
-    sk[e] = e < sample ? (mine_of[u] & ~0xFFFull) | e : ~0ull;     // the padding is never below an element
-  }
+  for (int u = 0; u < kSampleMax / kSampleThreads; ++u) sk[t + u * kSampleThreads] = mine_of[u];
   __syncthreads();
   const uint32_t lane = t % kLanes;
-  const uint32_t first = blockIdx.x * kSamplePer + (t / kLanes) * kSamplePerWave;   // sample = kSamplePer * the workgroups
-  uint64_t key[kSamplePerWave];
-  uint32_t below[kSamplePerWave];
-#pragma unroll
-  for (int m = 0; m < kSamplePerWave; ++m) { key[m] = sk[first + m]; below[m] = 0; }
+  const uint32_t mine = blockIdx.x * kSamplePer + t / kLanes;      // sample = kSamplePer * the workgroups
+  const uint64_t key = sk[mine];
+  uint32_t below = 0;
   for (uint32_t q = lane; q < sample; q += 2 * kLanes) {           // sample is a multiple of 128
     const uint64_t a = sk[q], b = sk[q + kLanes];
-#pragma unroll
-    for (int m = 0; m < kSamplePerWave; ++m) below[m] += (a < key[m] ? 1u : 0u) + (b < key[m] ? 1u : 0u);
+    // sample points in ascending order are slots in ascending order
+    below += (a < key || (a == key && q < mine) ? 1u : 0u) + (b < key || (b == key && q + kLanes < mine) ? 1u : 0u);
   }
-#pragma unroll
-  for (int m = 0; m < kSamplePerWave; ++m) {
-    const uint32_t r = wave_sum_u32(below[m]);
-    // rank per * (c + 1) - 1 makes splitter c; the last bucket has none
-    if (lane == 0 && r % per == per - 1 && r / per + 1 < nb) split[r / per] = key[m];
+  const uint32_t r = wave_sum_u32(below);
+  // rank per * (c + 1) - 1 makes splitter c; the last bucket has none
+  if (lane == 0 && r % per == per - 1 && r / per + 1 < nb) {
+    split[r / per] = key;
+    split_slot[r / per] = slot_of(mine);
   }
-  // the splitters beyond are +inf: nothing lands in those buckets
-  if (blockIdx.x == 0)
-    for (uint32_t c = nb - 1 + t; c < static_cast<uint32_t>(kMaxBuckets); c += kSampleThreads) split[c] = ~0ull;
 }
 
-// Bucket of a score = number of splitters <= it (equal scores share a bucket).  A workgroup
-// first counts its candidates per bucket in LDS and reserves their places with one global
-// atomic per bucket, instead of one per candidate.
+// Bucket of a candidate = number of splitters at or below it.  A workgroup first counts its
+// candidates per bucket in LDS and reserves their places with one global atomic per bucket,
+// instead of one per candidate.
 constexpr int kDropThreads = 1024;
 __global__ __launch_bounds__(kDropThreads) void drop_all_kernel(const double *fit_row, const double *slot_score,
-                                                               const uint32_t *row_of, uint32_t P, BucketArgs bk) {
+                                                               const uint32_t *row_of, uint32_t P, BucketArgs bk,
+                                                               const uint32_t *split_slot) {
   __shared__ uint64_t split[kMaxBuckets];
+  __shared__ uint32_t slot_at[kMaxBuckets];
   __shared__ uint32_t here[kMaxBuckets], base[kMaxBuckets];
   const uint32_t t = threadIdx.x, nb = bk.nb;
-  for (uint32_t c = t; c < nb; c += kDropThreads) { split[c] = bk.split[c]; here[c] = 0; }
-  __syncthreads();
+  for (uint32_t c = t; c < nb; c += kDropThreads) {
+    split[c] = c + 1 < nb ? bk.split[c] : ~0ull;
+    slot_at[c] = c + 1 < nb ? split_slot[c] : ~0u;
+    here[c] = 0;
+  }
   const uint32_t p = blockIdx.x * kDropThreads + t;
   uint64_t key = 0;
+  if (p < P) key = static_cast<uint64_t>(__double_as_longlong(slot_score ? slot_score[p] : fit_row[row_of[p]]));
+  __syncthreads();
   uint32_t b = 0, r = 0;
   if (p < P) {
-    key = static_cast<uint64_t>(__double_as_longlong(slot_score ? slot_score[p] : fit_row[row_of[p]]));
     uint32_t lo = 0, hi = nb - 1;                    // splitters 0 .. nb-2
     while (lo < hi) {
       const uint32_t mid = (lo + hi) >> 1;
-      if (split[mid] <= key) lo = mid + 1; else hi = mid;
+      if (!key_less(key, p, split[mid], slot_at[mid])) lo = mid + 1; else hi = mid;
     }
     b = lo;
     r = atomicAdd(&here[b], 1u);
   }
   __syncthreads();
-  for (uint32_t c = t; c < nb; c += kDropThreads) base[c] = here[c] ? atomicAdd(&bk.count[c], here[c]) : 0u;
+  for (uint32_t c = t; c < nb; c += kDropThreads) {
+    base[c] = here[c] ? atomicAdd(&bk.count[c], here[c]) : 0u;
+    if (base[c] + here[c] > static_cast<uint32_t>(kBucketCount)) bk.count[kManyFlag] = 1;
+  }
   __syncthreads();
   if (p < P) {
     const uint32_t slot = base[b] + r;
@@ -672,11 +785,11 @@ hipError_t launch_select(const double *fit, const double *slot_score, const RowP
   bk.seg = static_cast<uint32_t>(static_cast<size_t>(store.nb) * store.seg / nb);   // the same storage, re-divided
   bk.nb = nb;
   hipLaunchKernelGGL(sample_splitters_kernel, dim3(sample / kSamplePer), dim3(kSampleThreads), 0, s, fit, slot_score,
-                     rp.row_of_cur, P, sample, nb, const_cast<uint64_t *>(bk.split), bk.count);
+                     rp.row_of_cur, P, sample, nb, const_cast<uint64_t *>(bk.split), bk.split_slot, bk.count);
   hipError_t rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(drop_all_kernel, dim3((P + kDropThreads - 1) / kDropThreads), dim3(kDropThreads), 0, s, fit,
-                     slot_score, rp.row_of_cur, P, bk);
+                     slot_score, rp.row_of_cur, P, bk, bk.split_slot);
   rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL((bucket_select_kernel<false, kBucketCount>), dim3(nb), dim3(kBucketCount), 0, s, nullptr, nullptr,

@@ -13,9 +13,8 @@ __device__ __forceinline__ bool key_less(uint64_t ka, uint32_t ia, uint64_t kb, 
 }
 
 // Bitonic sorting network over n (a power of two) keys by one workgroup, ascending
-// (score bits, slot).  Works on LDS or, for oversized inputs, on global memory.
-template <typename K64, typename I32>
-__device__ __forceinline__ void bitonic_sort(K64 *sk, I32 *si, uint32_t n) {
+// (score bits, slot), in LDS.
+__device__ __forceinline__ void bitonic_sort(uint64_t *sk, uint32_t *si, uint32_t n) {
   for (uint32_t k = 2; k <= n; k <<= 1) {
     for (uint32_t j = k >> 1; j > 0; j >>= 1) {
       for (uint32_t e = threadIdx.x; e < n / 2; e += blockDim.x) {
@@ -29,7 +28,6 @@ __device__ __forceinline__ void bitonic_sort(K64 *sk, I32 *si, uint32_t n) {
           sk[hi] = ka; si[hi] = ia;
         }
       }
-      __threadfence_block();
       __syncthreads();
     }
   }

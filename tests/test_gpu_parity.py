@@ -109,10 +109,33 @@ def test_stress_reduced_population(ones, ref):
                                                (20000, 5, 4)])
 def test_selection_with_massive_ties(ones, ref, pop, n_jobs, n_gpus):
     """Pools larger than one LDS sort chunk with few distinct genomes, hence few distinct scores:
-    single buckets overflow into the spill list and the scratch pool."""
+    single buckets overflow into the spill list."""
     rng = np.random.default_rng(pop)
     jobs = make_jobs(n_jobs, bmin=256, bmax=512, remaining=rng.uniform(1e5, 1e7, n_jobs))
     run_pair(ones, ref, cluster(n_gpus, n_jobs, pop, seed=12), jobs, 4, 1, f"ties/P={pop}")
+
+
+@pytest.mark.parametrize("pop,n_slots,n_gpus", [(260, 70, 8), (4100, 5, 4), (8192, 66, 9), (16388, 70, 12), (65536, 5, 6)])
+def test_selection_of_a_pool_of_copies(ones, ref, pop, n_slots, n_gpus):
+    """A search that has nearly converged, under a new table and again: thousands of copies of one
+    genome share a score.  The splitters of the sample sort tell them apart by their slots, and the
+    children that crowd into one quantile bucket (513 and more) are ranked by all workgroups together."""
+    ref.set_threads(8)
+    rng = np.random.default_rng(pop + n_slots)
+    jobs = make_jobs(n_slots, bmin=256, bmax=512, remaining=rng.uniform(1e5, 1e7, n_slots))
+    gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=5), jobs) for make in (ones.Search, ref.RefSearch))
+    try:
+        for step, gens in enumerate((12, 2, 5)):
+            say(f"[parity] copies: P={pop} slots={n_slots} G={n_gpus} step={step}")
+            for s in (gpu, cpu):
+                s.generation(gens)
+            assert_same_state(gpu, cpu, f"copies P={pop} step {step}")
+            jobs.remaining = jobs.remaining * rng.uniform(0.8, 1.0, n_slots)
+            for s in (gpu, cpu):
+                s.set_jobs(jobs)
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
 
 
 @pytest.mark.parametrize("pop", [4100, 8192, 20000, 40004])
