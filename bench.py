@@ -187,7 +187,7 @@ def online(args, torch, ones, W) -> int:
     out = {"metric": "candidate-job fitness evals/sec", "value": res["evals"] / dt, "unit": "evals/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": dt * 1e3 / args.steps,
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-           "dtype": "i32 genes, f64 fitness", "data": "synthetic",
+           "dtype": "i32 genes (stored as u8 codes), f64 fitness", "data": "synthetic",
            "config": {"workload": "online", "n_gpus_cluster": cl.n_gpus, "slots": cl.n_slots,
                       "population": cl.population, "generations_per_epoch": gens, "seed": cl.seed,
                       "limit_policies": bool(args.policies), "crossover": "over " + args.crossover,
@@ -305,13 +305,13 @@ def main() -> int:
     if single_launch:
         evolve_ms, select_ms = evolve_ms / args.steps, 0.0    # the launch runs all timed generations
     # Bytes one evolve launch has to move for what it computes: it composes the 3P/4 children and
-    # mutants (the P/4 survivors stay where they are), each gene of them read once from a parent
-    # row and written once (int32), plus one fp64 score per candidate composed.
+    # mutants (the P/4 survivors stay where they are), each gene of them, a byte, read once from a
+    # parent row and written once, plus one fp64 score per candidate composed.
     composed = cl.population * 3 // 4
-    alg_bytes = composed * cl.n_slots * 8 + composed * 8
+    alg_bytes = composed * cl.n_slots * 2 + composed * 8
     if args.sampled:      # the survivors are read once more to be scored again
-        alg_bytes += (cl.population // 4) * (cl.n_slots * 4 + 8)
-    pool_bytes = cl.population * cl.n_slots * 8 + cl.population * 8   # every candidate of the pool counted as read and written
+        alg_bytes += (cl.population // 4) * (cl.n_slots + 8)
+    pool_bytes = cl.population * cl.n_slots * 2 + cl.population * 8   # every candidate of the pool counted as read and written
     achieved = alg_bytes / (evolve_ms * 1e-3) / 1e9
     traffic = None
     if MEASURED_TRAFFIC["source_sha256"] == evolve_source_hash() and args.workload == "stress" and not args.sampled \
@@ -326,7 +326,7 @@ def main() -> int:
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": dt * 1e3 / args.steps,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "i32 genes, f64 fitness", "data": "synthetic",
+        "dtype": "i32 genes (stored as u8 codes), f64 fitness", "data": "synthetic",
         "config": {"workload": args.workload, "n_gpus_cluster": cl.n_gpus, "jobs": active,
                    "slots_padded": jp, "population": cl.population, "survivors": cl.population // 4,
                    "mutation_rate": cl.mutation_rate, "crossover_rate": cl.crossover_rate,
@@ -343,7 +343,7 @@ def main() -> int:
                      "achieved": achieved, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic,
                      "algorithmic_bytes_per_launch": alg_bytes,
-                     "units_per_launch": f"{composed} candidates composed x {cl.n_slots} job slots, 8 B each, + 8 B per candidate",
+                     "units_per_launch": f"{composed} candidates composed x {cl.n_slots} job slots, 2 B each, + 8 B per candidate",
                      # measured traffic over the same duration (None once the kernel has changed since the counters were read)
                      "physical_gbps": None if traffic is None else traffic / (evolve_ms * 1e-3) / 1e9,
                      "physical_frac": None if traffic is None else traffic / (evolve_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,

@@ -76,8 +76,8 @@ struct ScratchLayout {
 };
 
 struct Layout {
-  size_t genes, fit_row, slot_score, row_of[2], parent_row[2], occupied[2], sel, fsync, xkeys, scratch, cstart, cmax, info, abl, cc, d, Y[kDrawRing], terms[kDrawRing];
-  size_t rawinfo, changed, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
+  size_t genes, fit_row, slot_score, row_of[2], parent_row[2], occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
+  size_t unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
 
@@ -124,12 +124,16 @@ ScratchLayout make_scratch_layout(uint32_t P) {
   return S;
 }
 
+// Pool slots that ones_export unpacks at a time (16 MiB of batch sizes).
+uint32_t unpack_slots(uint32_t P, uint32_t Jp) { return std::min<uint32_t>(P, (16u << 20) / (Jp * 4)); }
+
 Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   Layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes); return at; };
   const size_t rows = static_cast<size_t>(P) + P / 4;      // a pool of P slots lives in P + K physical rows
-  L.genes = take(rows * Jp * 4);
+  const size_t row_bytes = static_cast<size_t>(words_of(Jp / kLanes)) * kLanes * 4;
+  L.genes = take(rows * row_bytes);
   L.fit_row = take(rows * 8);
   L.slot_score = take(static_cast<size_t>(P) * 8);
   L.row_of[0] = take(static_cast<size_t>(P) * 4);
@@ -145,13 +149,16 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   // the selection's scratch: splitters, counters, bucket storage, spill list
   L.S = make_scratch_layout(P);
   L.scratch = take(L.S.total);
-  L.cstart = take(Jp * 4); L.cmax = take(Jp * 4); L.info = take(Jp * 4);
+  L.start = take(row_bytes); L.most = take(row_bytes); L.draws = take(row_bytes); L.base = take(row_bytes);
+  L.info[0] = take(Jp * 4); L.info[1] = take(Jp * 4);
   L.abl = take(Jp * 8); L.cc = take(Jp * 8); L.d = take(Jp * 8);
   // remaining work and the term table built from it, a ring of kDrawRing pairs at equal distances:
   // under probability sampling the draws of that many generations are made in one launch, and
   // generation g is scored with pair g mod kDrawRing
   for (int k = 0; k < kDrawRing; ++k) { L.Y[k] = take(Jp * 8); L.terms[k] = take(static_cast<size_t>(Jp) * kMaxTermEntries * 8); }
-  L.rawinfo = take(Jp * 4); L.changed = take(Jp * 4);
+  // ones_export: batch sizes of a run of pool slots on their way to the host
+  L.unpacked = take(static_cast<size_t>(unpack_slots(P, Jp)) * Jp * 4);
+  L.rawinfo = take(Jp * 4);
   L.ra = take(Jp * 8); L.rc = take(Jp * 8); L.rd = take(Jp * 8); L.rY = take(Jp * 8);
   L.alpha = take(Jp * 8); L.beta = take(Jp * 8); L.processed = take(Jp * 8);
   L.time_rank = take(Jp * 4);
@@ -165,7 +172,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
 // travel together lie next to each other in the workspace (every size below is a multiple of the
 // 256-byte alignment except the last of a group).
 size_t stage_bytes(const Layout &L, uint32_t Jp, uint32_t G) {
-  const size_t table = L.rY + static_cast<size_t>(Jp) * 8 - L.rawinfo;        // rawinfo, changed, a, c, d, Y
+  const size_t table = L.rY + static_cast<size_t>(Jp) * 8 - L.rawinfo;        // rawinfo, a, c, d, Y
   const size_t progress = L.processed + static_cast<size_t>(Jp) * 8 - L.alpha; // alpha, beta, processed
   const size_t best = L.best_err + 8 - L.best_batch;                           // batch, gpus, fitness, error words
   const size_t place = L.place_batch + static_cast<size_t>(G) * 4 - L.place_slot;
@@ -249,6 +256,7 @@ struct ones_ctx {
   char *stage_dev;            // the same buffer as the device addresses it (ones_best's kernel writes the winner there)
   Layout L;
   int cur;                    // which row_of array describes the current generation
+  int info_now, info_stored;  // which info array belongs to the job table, and to the one the genomes are stored under
   bool table_changed;         // job table replaced since the current generation was computed
   bool no_schedule;           // ... by ones_set_jobs: the winner is not a schedule under the new table
   bool new_jobs_first;        // option: the generation after ones_set_jobs serves the arrived jobs first
@@ -282,8 +290,8 @@ struct ones_ctx {
 
   template <typename T> T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
   JobTable table(int which) const {     // with the remaining work and term table number `which`
-    return JobTable{at<uint32_t>(L.cstart), at<uint32_t>(L.cmax), at<uint32_t>(L.info),
-                    at<double>(L.abl), at<double>(L.cc), at<double>(L.d), at<double>(L.Y[which]),
+    return JobTable{at<uint32_t>(L.start), at<uint32_t>(L.most), at<uint32_t>(L.draws), at<uint32_t>(L.base),
+                    at<uint32_t>(L.info[info_now]), at<uint32_t>(L.info[info_stored]), at<double>(L.abl), at<double>(L.cc), at<double>(L.d), at<double>(L.Y[which]),
                     at<double>(L.terms[which]), term_E};
   }
   JobTable table() const { return table(y_cur); }
@@ -291,14 +299,11 @@ struct ones_ctx {
 
 namespace {
 
-int upload_table(ones_ctx *c, const HostJobs &h, const std::vector<uint32_t> *changed) {
+int upload_table(ones_ctx *c, const HostJobs &h) {
   const size_t n4 = static_cast<size_t>(c->Jp) * 4, n8 = static_cast<size_t>(c->Jp) * 8;
   const Layout &L = c->L;
   auto staged = [&](size_t off) { return c->stage + (off - L.rawinfo); };   // laid out as in the workspace
   memcpy(staged(L.rawinfo), h.rawinfo.data(), n4);
-  const size_t n_changed = changed ? changed->size() : 0;          // the slots that changed hands, as a list
-  if (n_changed) memcpy(staged(L.changed), changed->data(), n_changed * 4);
-  memset(staged(L.changed) + n_changed * 4, 0, n4 - n_changed * 4);
   memcpy(staged(L.ra), h.a.data(), n8);
   memcpy(staged(L.rc), h.c.data(), n8);
   memcpy(staged(L.rd), h.d.data(), n8);
@@ -307,9 +312,7 @@ int upload_table(ones_ctx *c, const HostJobs &h, const std::vector<uint32_t> *ch
   RawJobs raw{c->at<uint32_t>(c->L.rawinfo), c->at<double>(c->L.ra), c->at<double>(c->L.rc),
               c->at<double>(c->L.rd), c->at<double>(c->L.rY)};
   c->term_E = h.term_E;
-  // every physical row, whether a candidate lives in it or not
-  HIP_TRY(launch_table_change(raw, c->table(), c->Jp, c->at<int32_t>(c->L.genes), c->at<uint32_t>(c->L.changed),
-                              static_cast<uint32_t>(n_changed), c->P + c->K, c->stream));
+  HIP_TRY(launch_table_change(raw, c->table(), c->Jp, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));     // the staging buffer is free again
   return ONES_OK;
 }
@@ -340,7 +343,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   // generation 0 fills row_of[cur]; later generations complete the array whose first K entries
   // the last selection wrote
   const int next = t == 0 ? c->cur : c->cur ^ 1;
-  a.genes = c->at<int32_t>(c->L.genes);
+  a.genes = c->at<uint32_t>(c->L.genes);
   a.fit_row = c->at<double>(c->L.fit_row);
   a.parent_row = c->at<uint32_t>(c->L.parent_row[next]);
   a.row_of = c->at<uint32_t>(c->L.row_of[next]);
@@ -362,7 +365,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.rescore = same_table && sampled ? 1u : 0u;
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;   // the table's "arrived" marks are fresh
   a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.stash_stride = 0;                                            // the launcher sets it
+  a.coin_stride = 0;                                             // the launcher sets it
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   a.slot_score = c->at<double>(c->L.slot_score);
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
@@ -431,6 +434,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   if (events && (rc = timed(c, c->select_ev, c->select_used, false))) return rc;
   c->cur = next;
   c->y_cur = y_this;
+  c->info_stored = c->info_now;     // every genome of the new pool was made under the current table
   c->table_changed = false;
   c->no_schedule = false;
   c->profile_tick += 1;
@@ -488,6 +492,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     c->stage_dev = static_cast<char *>(mapped);
   }
   c->cur = 0; c->t = 0;
+  c->info_now = c->info_stored = 0;
   c->table_changed = false;
   c->no_schedule = false;
   c->new_jobs_first = false;
@@ -530,7 +535,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
       e = launch_zero_words(c->at<uint32_t>(c->L.xkeys), static_cast<uint32_t>(fused_exchange_bytes(c->P) / 4), c->stream);
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
-  if ((rc = upload_table(c, h, nullptr)) ||
+  if ((rc = upload_table(c, h)) ||
       (rc = run_generation(c, 0, c->ws + c->L.scratch, c->splitters_valid, false)))
     return rc;
   hipError_t e = hipStreamSynchronize(c->stream);
@@ -544,13 +549,14 @@ static int set_jobs_impl(ones_ctx *c, const ones_jobs *jobs) {
   HostJobs h;
   int rc = stage_jobs(static_cast<int>(c->Jn), static_cast<int>(c->Jp), jobs, h);
   if (rc) return rc;
-  std::vector<uint32_t> changed;                                  // the slots that changed hands
   for (uint32_t j = 0; j < c->Jn; ++j)
-    if (h.id[j] != c->ids[j]) {
-      changed.push_back(j);
-      if ((h.rawinfo[j] >> 15) & 1u) h.rawinfo[j] |= 1u << 16;   // an active job arrived in this slot
+    if (h.id[j] != c->ids[j]) {                                  // the slot changed hands
+      h.rawinfo[j] |= 1u << 17;
+      if ((h.rawinfo[j] >> 15) & 1u) h.rawinfo[j] |= 1u << 16;   // an active job arrived in it
     }
-  if ((rc = upload_table(c, h, changed.empty() ? nullptr : &changed))) return rc;
+  // the genomes stay as they are stored; info_stored says how to read them until the next generation
+  c->info_now = c->info_stored ^ 1;
+  if ((rc = upload_table(c, h))) return rc;
   c->ids = h.id;
   c->table_changed = true;
   c->no_schedule = true;
@@ -639,7 +645,7 @@ static int export_remaining_impl(ones_ctx *c, double *remaining_out) {
 static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   FusedArgs fa;
   EvolveArgs &a = fa.ev;
-  a.genes = c->at<int32_t>(c->L.genes);
+  a.genes = c->at<uint32_t>(c->L.genes);
   a.fit_row = c->at<double>(c->L.fit_row);
   a.parent_row = nullptr; a.row_of = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
   a.slot_score = nullptr;                              // no selection kernel follows
@@ -653,7 +659,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
   a.rescore = 0;
   a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.stash_stride = 0; a.term_lds = 0;
+  a.coin_stride = 0; a.term_lds = 0;
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   a.bk = BucketArgs{};
   const int next = c->cur ^ 1;
@@ -687,6 +693,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
     c->fused_draws += n;
     c->drawn_from = c->drawn_to = 0;   // the ring may hold tables this launch wrote over (y_out); the two-launch path draws again
   }
+  c->info_stored = c->info_now;
   c->table_changed = false;
   c->no_schedule = false;
   c->splitters_valid = false;       // the two-launch path ranks the pool in full before it uses buckets again
@@ -764,9 +771,10 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
   // one launch and one wait, no copy.
   const Layout &L = c->L;
   auto mapped = [&](size_t off) { return c->stage_dev + (off - L.best_batch); };
-  HIP_TRY(launch_best(c->at<int32_t>(c->L.genes), c->at<double>(c->L.fit_row), c->at<uint32_t>(c->L.row_of[c->cur]),
-                      c->at<int32_t>(c->L.sel), c->at<uint32_t>(c->L.info), c->Jn, c->Jp,
-                      reinterpret_cast<int32_t *>(mapped(L.best_batch)), reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
+  HIP_TRY(launch_best(c->at<uint32_t>(c->L.genes), c->at<double>(c->L.fit_row), c->at<uint32_t>(c->L.row_of[c->cur]),
+                      c->at<int32_t>(c->L.sel), c->at<uint32_t>(L.info[c->info_stored]),
+                      c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, reinterpret_cast<int32_t *>(mapped(L.best_batch)),
+                      reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
                       reinterpret_cast<double *>(mapped(L.best_fit)), c->at<uint32_t>(c->L.fsync) + 1,
                       reinterpret_cast<uint32_t *>(mapped(L.best_err)), c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -785,8 +793,8 @@ static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_g
   if (!c || c->no_schedule) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
   const size_t n4 = static_cast<size_t>(c->G) * 4;
-  HIP_TRY(launch_placement(c->at<int32_t>(c->L.genes), c->at<uint32_t>(c->L.row_of[c->cur]), c->at<int32_t>(c->L.sel),
-                           c->at<uint32_t>(c->L.info), c->Jn, c->Jp, c->G, c->at<int32_t>(c->L.place_slot),
+  HIP_TRY(launch_placement(c->at<uint32_t>(c->L.genes), c->at<uint32_t>(c->L.row_of[c->cur]), c->at<int32_t>(c->L.sel),
+                           c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->G, c->at<int32_t>(c->L.place_slot),
                            c->at<int32_t>(c->L.place_batch), c->stream));
   const Layout &L = c->L;
   if (c->G)
@@ -804,25 +812,29 @@ static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, i
   if (!c) return ONES_E_INVALID_ARG;
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (int rc = check_waits(c)) return rc;
-  // candidates live in physical rows: fetch the rows and put them in slot order on the host
-  const size_t rows = static_cast<size_t>(c->P) + c->K, Jp = c->Jp;
-  std::vector<uint32_t> row_of(c->P);
-  std::vector<int32_t> g;
-  std::vector<double> f;
-  HIP_TRY(hipMemcpy(row_of.data(), c->ws + c->L.row_of[c->cur], static_cast<size_t>(c->P) * 4, hipMemcpyDeviceToHost));
+  // candidates live in physical rows, their genes as codes: the genomes are unpacked on the device,
+  // a run of pool slots at a time, the scores put in slot order on the host
+  const size_t rows = static_cast<size_t>(c->P) + c->K;
+  const uint32_t *row_of = c->at<uint32_t>(c->L.row_of[c->cur]);
   if (genes) {
-    g.resize(rows * Jp);
-    HIP_TRY(hipMemcpy(g.data(), c->ws + c->L.genes, rows * Jp * 4, hipMemcpyDeviceToHost));
+    const uint32_t most = unpack_slots(c->P, c->Jp);
+    for (uint32_t first = 0; first < c->P; first += most) {
+      const uint32_t count = std::min(most, c->P - first);
+      HIP_TRY(launch_unpack(c->at<uint32_t>(c->L.genes), row_of, c->at<uint32_t>(c->L.info[c->info_stored]), c->Jp, first,
+                            count, c->at<int32_t>(c->L.unpacked), c->stream));
+      HIP_TRY(hipMemcpyAsync(genes + static_cast<size_t>(first) * c->Jp, c->ws + c->L.unpacked,
+                             static_cast<size_t>(count) * c->Jp * 4, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+    }
   }
   if (fit) {
-    f.resize(rows);
+    std::vector<uint32_t> row(c->P);
+    std::vector<double> f(rows);
+    HIP_TRY(hipMemcpy(row.data(), row_of, static_cast<size_t>(c->P) * 4, hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(f.data(), c->ws + c->L.fit_row, rows * 8, hipMemcpyDeviceToHost));
+    for (uint32_t p = 0; p < c->P; ++p) fit[p] = f[row[p]];
   }
   if (sel) HIP_TRY(hipMemcpy(sel, c->ws + c->L.sel, static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
-  for (uint32_t p = 0; p < c->P; ++p) {
-    if (genes) memcpy(genes + static_cast<size_t>(p) * Jp, g.data() + static_cast<size_t>(row_of[p]) * Jp, Jp * 4);
-    if (fit) fit[p] = f[row_of[p]];
-  }
   if (generation) *generation = c->t;
   return ONES_OK;
 }

@@ -1,13 +1,20 @@
 // Device code that composes, repairs and scores one candidate schedule of the ONES search
 // (arXiv 2108.03645, Section 3.2.2) on gfx950: one wave64 per candidate, the job columns across
-// the 64 lanes, the rows of a column in the lane's registers.  Shared by the kernels of
-// ones_evolve.hip (a generation of a large pool) and ones_fused.hip (all generations of a small
-// pool in one launch).
+// the 64 lanes, the rows of a column in the lane's registers, four to a register.  Shared by the
+// kernels of ones_evolve.hip (a generation of a large pool) and ones_fused.hip (all generations of
+// a small pool in one launch).
+//
+// A gene is a byte, the code of the job's GPU count: 0 = the job waits, e + 1 = 2^e GPUs (at most
+// 2^20).  Compose and repair work on four genes per instruction.  What this is bound by is the issue
+// of vector instructions: with one gene per 32-bit register the kernel of a generation issued for
+// 80 % of its cycles while it moved its bytes at the rate of a plain copy, so fewer bytes alone would
+// have gained little.
 #pragma once
 
 #include "ones_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #pragma clang fp contract(off)   // every fp64 product and sum is rounded on its own
 
@@ -36,28 +43,55 @@ __device__ __forceinline__ uint32_t bounded(uint32_t w, uint32_t n) { return __u
 // the repair order.  Counter block 0xFFFFFFFF is reserved for it.
 struct Draw { uint32_t ra, rb, r; };
 
-// t: the generation the draw is for.
+// t: the generation the draw is for.  One draw per lane (p may differ from lane to lane).
 __device__ __forceinline__ Draw candidate_draw(const EvolveArgs &a, uint32_t t, uint32_t p) {
   const Words w = philox4x32_10(0xFFFFFFFFu, p, t, 0u, a.key0, a.key1);
-  Draw d;
-  d.ra = __builtin_amdgcn_readfirstlane(bounded(w.w[0], a.K));
-  d.rb = __builtin_amdgcn_readfirstlane(bounded(w.w[1], a.K));
-  d.r  = __builtin_amdgcn_readfirstlane(bounded(w.w[2], a.Jp));
-  return d;
+  return Draw{bounded(w.w[0], a.K), bounded(w.w[1], a.K), bounded(w.w[2], a.Jp)};
 }
 
-// One 32-bit word per gene: the lane's rows 4q..4q+3 share Philox block q*64 + lane.
-template <int R>
-__device__ __forceinline__ void gene_words(const EvolveArgs &a, uint32_t t, uint32_t p, int lane, uint32_t (&w)[R]) {
-#pragma unroll
-  for (int q = 0; q < (R + 3) / 4; ++q) {
-    const Words x = philox4x32_10(static_cast<uint32_t>(q * kLanes + lane), p, t, 0u, a.key0, a.key1);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (4 * q + k < R) w[4 * q + k] = x.w[k];
-    fence_every(q, 2);
-  }
+// One 32-bit word per gene: the lane's rows 4q..4q+3, which share a register, share Philox block
+// q*64 + lane, counter (q*64 + lane, p, t, 0).
+// The first two of the ten rounds hardly depend on the candidate: in round 0 the product of the
+// block number and, in round 1, the product of what comes of it are the same for every candidate,
+// and the other products are the same in all lanes.  The former are kept in LDS (prefix), the latter
+// are scalar, so a block costs 16 vector multiplications instead of 20.
+constexpr uint32_t kPhiloxA = 0xD2511F53u, kPhiloxB = 0xCD9E8D57u;
+
+// prefix of block number `block`: low and high half of round 1's product
+__device__ __forceinline__ uint2 philox_prefix(uint32_t block, uint32_t key1) {
+  const uint32_t x2 = __umulhi(block, kPhiloxA) ^ key1;
+  return make_uint2(x2 * kPhiloxB, __umulhi(x2, kPhiloxB));
 }
+
+struct WordSource {                                  // what the blocks of one candidate share (wave-uniform)
+  uint32_t u0, u2, u3, k0, k1;
+  __device__ __forceinline__ WordSource(const EvolveArgs &a, uint32_t t, uint32_t p) {
+    const uint64_t pb = static_cast<uint64_t>(t) * kPhiloxB;
+    const uint64_t pa = static_cast<uint64_t>(static_cast<uint32_t>(pb >> 32) ^ p ^ a.key0) * kPhiloxA;
+    k0 = a.key0 + 0x9E3779B9u;
+    k1 = a.key1 + 0xBB67AE85u;
+    u0 = static_cast<uint32_t>(pb) ^ k0;
+    u2 = static_cast<uint32_t>(pa >> 32) ^ k1;
+    u3 = static_cast<uint32_t>(pa);
+  }
+  // the words of the lane's rows 4q .. 4q + 3
+  __device__ __forceinline__ Words block(const uint2 *prefix, int q, int lane) const {
+    const uint2 e = prefix[q * kLanes + lane];
+    uint32_t x0 = e.y ^ u0, x1 = e.x, x2 = (static_cast<uint32_t>(q * kLanes + lane) * kPhiloxA) ^ u2, x3 = u3;
+    uint32_t ka = k0, kb = k1;
+#pragma unroll
+    for (int round = 2; round < 10; ++round) {
+      ka += 0x9E3779B9u;
+      kb += 0xBB67AE85u;
+      const uint64_t pa = static_cast<uint64_t>(x0) * kPhiloxA, pb = static_cast<uint64_t>(x2) * kPhiloxB;
+      x0 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pb >> 32), x1, ka, 0x96);   // three-input xor
+      x2 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pa >> 32), x3, kb, 0x96);
+      x1 = static_cast<uint32_t>(pb);
+      x3 = static_cast<uint32_t>(pa);
+    }
+    return Words{{x0, x1, x2, x3}};
+  }
+};
 
 // --------------------------------------------------------- wave primitives ---------
 // DPP controls (gfx9): row_shr:n shifts within a row of 16 lanes, row_bcast:15 / :31 copy the
@@ -83,93 +117,207 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kLanes - 1);
 }
 
+// The sum that a xor butterfly 32, 16, .., 1 over the lanes leaves in every lane (each step adds the
+// partner's value, so the order of the additions is that of the butterfly), without LDS: gfx950 swaps
+// halves and rows of 16 lanes between two registers; below that, what a lane holds only depends
+// on its place among the last 2^k lanes, so a rotation of the row stands for the xor.
+__device__ __forceinline__ double butterfly_sum(double v) {
+  auto halves = [](double x, auto swap) {             // x of this lane's half (row) of a pair, x of the other's
+    const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(x));
+    const auto lo = swap(static_cast<uint32_t>(bits)), hi = swap(static_cast<uint32_t>(bits >> 32));
+    return __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0])) +
+           __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
+  };
+  v = halves(v, [](uint32_t w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
+  v = halves(v, [](uint32_t w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
+  auto add_from = [](double x, auto ctrl) {
+    constexpr int kCtrl = decltype(ctrl)::value;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, 0xF, 0xF, true);
+    return x + __hiloint2double(hi, lo);
+  };
+  v = add_from(v, std::integral_constant<int, 0x128>{});    // row_ror:8
+  v = add_from(v, std::integral_constant<int, 0x124>{});    // row_ror:4
+  v = add_from(v, std::integral_constant<int, 0x4E>{});     // quad_perm 2,3,0,1
+  return add_from(v, std::integral_constant<int, 0xB1>{});  // quad_perm 1,0,3,2
+}
+
+// ------------------------------------------------------------- four genes at once --
+// All byte values below are under 128, so that sums and differences with the top bits set do not
+// run over into the neighbouring byte.
+constexpr uint32_t kTops = 0x80808080u, kOnes = 0x01010101u, kSevens = 0x7F7F7F7Fu;
+
+// 0x7F in the bytes whose top bit is set in t, 0 elsewhere
+__device__ __forceinline__ uint32_t spread_tops(uint32_t t) {
+  const uint32_t f = t & kTops;
+  return f - (f >> 7);
+}
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) { return spread_tops(v + kSevens); }
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t yes, uint32_t no) { return (yes & mask) | (no & ~mask); }
+__device__ __forceinline__ uint32_t max_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), x, y); }
+__device__ __forceinline__ uint32_t min_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), y, x); }
+
+// acc + the GPUs of the four codes.  Codes up to 7 (at most 64 GPUs per job, the usual case) become
+// counts by one byte look-up; a table with larger jobs (kWide) shifts them one by one.
+template <bool kWide>
+__device__ __forceinline__ uint32_t add_gpus(uint32_t codes, uint32_t acc) {
+  if (!kWide) return __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x40201008u, 0x04020100u, codes), 0u, acc);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) acc += (1u << ((codes >> (8 * k)) & 31u)) >> 1;
+  return acc;
+}
+
 // ------------------------------------------------------------- job table in LDS ----
 struct Smem {
-  uint2    *cc2;     // [Jp] {cstart, cmax}: GPUs a waiting job resumes with / at the limit R_j
-  uint32_t *info;    // [Jp]
-  double   *abl, *cc, *d, *Y;   // [Jp] model parameters (when the term table does not fit)
-  double   *terms;   // [E][R][64] T_j c_j of job (row, lane) at GPU-count code E-1-e, or null
+  // a byte per gene, four rows to a word, word q*64 + lane (like the genomes): codes of the GPU count
+  // a waiting job resumes with and of the one at its limit R_j, number of outcomes of a redraw
+  // (0: empty slot), code of the outcome k less k (biased); after a table change also the distance
+  // from a stored code to the new one (biased; 0: the slot changed hands) and the arrived jobs (0x7F)
+  uint32_t *start, *most, *draws, *base, *shift, *fresh;
+  uint32_t *bl;      // log2 of the local batch (when the term table does not fit)
+  uint2    *prefix;  // [Q][64] Philox prefixes
+  double   *abl, *cc, *d, *Y;   // [Q*256] model parameters (when the term table does not fit)
+  double   *terms;   // [E][4Q][64] T_j c_j of job (row, lane) at GPU-count code e, or null
   uint64_t *split;   // [kMaxBuckets] bucket splitters, then [1] the K-th survivor's score bits
-  uint8_t  *stash;   // [waves][stash_stride] second crossover child while the first is repaired; before
-                     //                       that, the coins of a crossover over the GPUs
+  uint8_t  *coins;   // [waves][coin_stride] the coins of a crossover over the GPUs
   uint32_t *free_in_group; // [groups] free rows in each group of kRowGroupWords bitmap words
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
+  uint64_t *drawn;         // [4 * kRound] the draws of those slots (PackedDraw)
   uint32_t *next_item;     // [1] the next work item of the round that no wave has taken yet
 };
 
-// E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
 constexpr uint32_t kRound = 256;                     // survivors' ranks a workgroup covers between two barriers
+constexpr uint32_t kCoinStride = kMaxCoinGpus / 32 * 8;   // the 256 coin words with their running counts
 
 inline uint32_t row_groups(uint32_t rows) {
   return ((rows + 31) / 32 + kRowGroupWords - 1) / kRowGroupWords;
 }
 
-// LDS scratch per wave: a byte per job, or the 256 coin words with their running counts
-inline uint32_t stash_stride(uint32_t Jp, bool per_gpu) {
-  return per_gpu ? std::max<uint32_t>(Jp, kMaxCoinGpus / 32 * 8) : Jp;
-}
+// LDS scratch per wave: only the crossover over the GPUs needs any
+inline uint32_t coin_stride(bool per_gpu) { return per_gpu ? kCoinStride : 0u; }
 
-inline size_t smem_bytes(uint32_t Jp, int waves, uint32_t E, uint32_t rows, uint32_t stride) {
-  return static_cast<size_t>(Jp) * (8 + 4 + (E ? 8 * E : 32)) + (kMaxBuckets + 1) * 8 +
+// E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
+inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride) {
+  const size_t words = static_cast<size_t>(Q) * kLanes;
+  return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 +
          static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16;
 }
 
-__device__ __forceinline__ Smem carve(unsigned char *base, uint32_t Jp, uint32_t E, uint32_t waves, uint32_t stride) {
+template <int Q>
+__device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t waves, uint32_t stride) {
+  constexpr uint32_t kWords = Q * kLanes;
   Smem s;
-  s.abl = reinterpret_cast<double *>(base);
-  s.cc = s.abl + Jp;
-  s.d = s.cc + Jp;
-  s.Y = s.d + Jp;
+  s.abl = reinterpret_cast<double *>(at);
+  s.cc = s.abl + 4 * kWords;
+  s.d = s.cc + 4 * kWords;
+  s.Y = s.d + 4 * kWords;
   s.terms = E ? s.abl : nullptr;
-  s.split = reinterpret_cast<uint64_t *>(s.abl + static_cast<size_t>(Jp) * (E ? E : 4));
-  s.cc2 = reinterpret_cast<uint2 *>(s.split + kMaxBuckets + 1);
-  s.info = reinterpret_cast<uint32_t *>(s.cc2 + Jp);
-  s.stash = reinterpret_cast<uint8_t *>(s.info + Jp);
-  s.rows = reinterpret_cast<uint32_t *>(s.stash + static_cast<size_t>(waves) * stride);   // a multiple of 64
+  s.split = reinterpret_cast<uint64_t *>(s.abl + static_cast<size_t>(4 * kWords) * (E ? E : 4));
+  s.drawn = s.split + kMaxBuckets + 1;
+  s.prefix = reinterpret_cast<uint2 *>(s.drawn + 4 * kRound);
+  s.start = reinterpret_cast<uint32_t *>(s.prefix + kWords);
+  s.most = s.start + kWords;
+  s.draws = s.most + kWords;
+  s.base = s.draws + kWords;
+  s.shift = s.base + kWords;
+  s.fresh = s.shift + kWords;
+  s.bl = s.fresh + kWords;
+  s.coins = reinterpret_cast<uint8_t *>(s.bl + kWords);
+  s.rows = reinterpret_cast<uint32_t *>(s.coins + static_cast<size_t>(waves) * stride);
   s.next_item = s.rows + 4 * kRound;
   s.free_in_group = s.next_item + 4;
   return s;
 }
 
+// Distances between codes are kept above 0: the code of 2^(x - mu) GPUs is x - mu + 1, and every log2
+// of a batch or a local batch lies in 0 .. 30.
+constexpr uint32_t kBias = 31;
+
 // Stages the job table into LDS, the work dealt to the `threads` threads (whole waves) that call it
-// with tid = 0 .. threads - 1.  No barrier at the end: the caller places one before the first use.
+// with tid = 0 .. threads - 1.  R: rows of job slots (at most 4Q).  changed: genes are stored under
+// another table (tab.stored).  No barrier at the end: the caller places one before the first use.
 constexpr int kStageBatch = 3;
-template <int R>
-__device__ __forceinline__ void stage_table(const JobTable &tab, const BucketArgs &bk, const Smem &s, uint32_t Jp,
-                                            uint32_t E, uint32_t tid, uint32_t threads) {
-  if (bk.nb != 0) {
+template <int Q>
+__device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, uint32_t E, bool changed, uint32_t tid,
+                                            uint32_t threads) {
+  const JobTable &tab = a.tab;
+  const uint32_t R = a.Jp / kLanes;
+  constexpr uint32_t kWords = Q * kLanes;
+  if (a.bk.nb != 0) {
     for (uint32_t q = tid; q <= kMaxBuckets; q += threads)
-      s.split[q] = q < kMaxBuckets ? bk.split[q] : *bk.thresh;
+      s.split[q] = q < kMaxBuckets ? a.bk.split[q] : *a.bk.thresh;
   }
-  for (uint32_t j = tid; j < Jp; j += threads) {
-    s.cc2[j] = make_uint2(tab.cstart[j], tab.cmax[j]);
-    s.info[j] = tab.info[j];
-    if (E == 0) {
-      s.abl[j] = tab.abl[j];
-      s.cc[j] = tab.cc[j];
-      s.d[j] = tab.d[j];
-      s.Y[j] = tab.Y[j];
+  for (uint32_t w = tid; w < kWords; w += threads) {
+    s.start[w] = tab.start[w];
+    s.most[w] = tab.most[w];
+    s.draws[w] = tab.draws[w];
+    s.base[w] = tab.base[w];
+    s.prefix[w] = philox_prefix(w, a.key1);
+    if (changed || E == 0) {
+      uint32_t shift = 0, fresh = 0, bl = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t row = w / kLanes * 4 + k, j = row * kLanes + w % kLanes;
+        if (row < R) {
+          const uint32_t now = tab.info[j], then = tab.stored[j];
+          shift |= (info_reset(then) ? 0u : info_blexp(then) - info_mu(now) + kBias) << (8 * k);
+          fresh |= (info_new(now) ? 0x7Fu : 0u) << (8 * k);
+          bl |= info_blexp(now) << (8 * k);
+        }
+      }
+      s.shift[w] = shift;
+      s.fresh[w] = fresh;
+      s.bl[w] = bl;
     }
   }
-  if (E != 0)
+  if (E == 0) {
+    for (uint32_t j = tid; j < 4 * kWords; j += threads) {
+      const bool real = j < a.Jp;
+      s.abl[j] = real ? tab.abl[j] : 0.0;
+      s.cc[j] = real ? tab.cc[j] : 0.0;
+      s.d[j] = real ? tab.d[j] : 0.0;
+      s.Y[j] = real ? tab.Y[j] : 0.0;
+    }
+  } else {
     // global memory holds the table row-major ([row][code][lane]); here the code is the slowest
-    // index, so that a row's part of the LDS address is a compile-time offset, and the codes
-    // run backwards, so that the index follows the count of leading zeros of the GPU count
-    // (tiles of 64 entries; a batch of loads in flight per wave before the first LDS store waits for one)
-    for (uint32_t first = tid / kLanes; first < E * R; first += kStageBatch * (threads / kLanes)) {
+    // index, so that a row's part of the LDS address is a compile-time offset (tiles of 64 entries;
+    // a batch of loads in flight per wave before the first LDS store waits for one)
+    for (uint32_t first = tid / kLanes; first < E * 4 * Q; first += kStageBatch * (threads / kLanes)) {
       const uint32_t l = tid % kLanes;
       double v[kStageBatch];
 #pragma unroll
       for (int u = 0; u < kStageBatch; ++u) {
-        const uint32_t tile = first + u * (threads / kLanes), e = tile / R, row = tile % R;
-        if (tile < E * R) v[u] = tab.terms[(row * E + e) * kLanes + l];
+        const uint32_t tile = first + u * (threads / kLanes), e = tile / (4 * Q), row = tile % (4 * Q);
+        v[u] = 0.0;
+        if (tile < E * 4 * Q && row < R) v[u] = tab.terms[(row * E + e) * kLanes + l];
       }
 #pragma unroll
       for (int u = 0; u < kStageBatch; ++u) {
-        const uint32_t tile = first + u * (threads / kLanes), e = tile / R, row = tile % R;
-        if (tile < E * R) s.terms[((E - 1 - e) * R + row) * kLanes + l] = v[u];
+        const uint32_t tile = first + u * (threads / kLanes);
+        if (tile < E * 4 * Q) s.terms[tile * kLanes + l] = v[u];
       }
     }
+  }
+}
+
+// ------------------------------------------------------------------ draws ----------
+// A slot's draw as the waves find it in LDS: genome rows of the two parents (21 bits each; a pool has at
+// most 1.25 * 2^20 rows), lane and row of the job the repair starts from.
+struct PackedDraw {
+  uint32_t lo, hi;
+  __device__ __forceinline__ uint32_t row_a() const { return lo & 0x1FFFFFu; }
+  __device__ __forceinline__ uint32_t row_b() const { return (lo >> 21) | ((hi & 0x3FFu) << 11); }
+  __device__ __forceinline__ uint32_t lane() const { return (hi >> 10) & 63u; }
+  __device__ __forceinline__ uint32_t row() const { return hi >> 16; }
+};
+__device__ __forceinline__ uint64_t pack_draw(uint32_t row_a, uint32_t row_b, uint32_t r, uint32_t R) {
+  return static_cast<uint64_t>(row_a) | (static_cast<uint64_t>(row_b) << 21) |
+         (static_cast<uint64_t>(r / R) << 42) | (static_cast<uint64_t>(r % R) << 48);
+}
+__device__ __forceinline__ PackedDraw draw_at(const uint64_t *drawn, uint32_t i) {
+  const uint64_t v = drawn[i];
+  return PackedDraw{static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))),
+                    static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)))};
 }
 
 // ------------------------------------------------------------------ free rows ----
@@ -275,193 +423,259 @@ __device__ __forceinline__ uint32_t checked_row(const Smem &s, uint32_t row, uin
 }
 
 // Row listed at position i of the current round (wave-uniform); never outside the genome array.
-// (No note here: this sits in the work-item loop, whose register allocation has no room to spare,
-// and reads the entries that checked_row has seen.)
+// (No note here: it reads the entries that checked_row has seen.)
 __device__ __forceinline__ uint32_t row_at(const Smem &s, uint32_t i, const EvolveArgs &a) {
   return min(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(s.rows[i])), a.P + a.K - 1);
 }
 
-// Global batch -> GPU count.  In general: clamp to the window and lift for free to the
-// per-GPU max batch, i.e. clamp(B >> mu, cstart, cmax) for a running job.  A gene written by
-// this kernel under the same job table is already of the form c << bl_exp.
-template <int R, bool kSameTable>
-__device__ __forceinline__ void gpus_from_batches(const Smem &s, int lane, uint32_t (&c)[R]) {
+// ------------------------------------------------------------------ genes ----------
+// Biased codes pulled inside the job's window (an empty slot's window is 0), the bias taken off.
+__device__ __forceinline__ uint32_t into_window(uint32_t biased, uint32_t start, uint32_t most) {
+  return min_bytes(max_bytes(biased, start + kBias * kOnes), most + kBias * kOnes) - kBias * kOnes;
+}
+
+// Redraw of four genes from k in [0, n) each: 0 = the job is pre-empted, else the batch 2^(lo + k - 1)
+// on the GPUs it takes, with the free lift to the per-GPU max batch.
+__device__ __forceinline__ uint32_t codes_of_draws(const Smem &s, int w, uint32_t k) {
+  return into_window(s.base[w] + k, s.start[w], s.most[w]) & nonzero_bytes(k);
+}
+
+// Genes stored under another job table: the batch they stood for, pulled inside the new window and
+// lifted for free to the per-GPU max batch; slots that changed hands wait.
+template <int Q>
+__device__ __forceinline__ void to_new_table(const Smem &s, int lane, uint32_t (&c)[Q]) {
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const int j = lane + kLanes * i;
-    const uint32_t w = s.info[j];
-    if (kSameTable) {
-      c[i] = c[i] >> info_blexp(w);
-    } else {
-      const uint2 k = s.cc2[j];
-      const uint32_t g = min(max(c[i] >> info_mu(w), k.x), k.y);
-      c[i] = c[i] ? g : 0u;
-    }
-    fence_every(i, 8);
+  for (int q = 0; q < Q; ++q) {
+    const int w = q * kLanes + lane;
+    c[q] = into_window(c[q] + s.shift[w], s.start[w], s.most[w]) & nonzero_bytes(c[q]) & nonzero_bytes(s.shift[w]);
   }
 }
 
-// Accept the longest prefix, in the rotated visiting order, of the asks v whose running sum
-// stays within limit.  Visiting order: column-major (a lane's rows are consecutive), starting
-// at lane lr, row ir, wrapping.  On return v[i] is unchanged if accepted, else 0; returns the
-// accepted sum (wave-uniform).
-template <int R>
-__device__ __forceinline__ uint32_t accept_prefix(uint32_t (&v)[R], uint32_t limit, uint32_t lr, uint32_t ir,
-                                                  int lane) {
-  // first pass: lane totals, with the running sum noted after every eighth row
-  constexpr int kBlocks = (R + 7) / 8;
-  uint32_t run = 0, snap[kBlocks];
+template <int Q>
+__device__ __forceinline__ void load_genes(const uint32_t *genes, uint32_t row, int lane, uint32_t (&c)[Q]) {
+  const uint32_t *at = genes + static_cast<size_t>(row) * (Q * kLanes);
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    run += v[i];
-    if (i % 8 == 7 || i == R - 1) snap[i / 8] = run;
+  for (int q = 0; q < Q; ++q) c[q] = at[q * kLanes + lane];
+}
+
+// 0xFF in byte k where words.w[k] < limit
+__device__ __forceinline__ uint32_t words_below(const Words &w, uint32_t limit) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) m |= w.w[k] < limit ? 0xFFu << (8 * k) : 0u;
+  return m;
+}
+
+// ------------------------------------------------------------------ repair ---------
+// The bytes of word q that belong to rows before ir, ir > 4q.
+__device__ __forceinline__ uint32_t rows_before(uint32_t ir, int q) {
+  return ir >= 4u * q + 4u ? 0xFFFFFFFFu : (1u << (8 * (ir & 3u))) - 1u;
+}
+
+// Accept the longest prefix, in the rotated visiting order, of the asks (codes v, 0 = none) whose
+// running sum of GPUs stays within limit.  Visiting order: column-major (a lane's rows are
+// consecutive), starting at lane lr, row ir, wrapping.  On return the bytes of m are cleared where
+// the ask was not accepted (elsewhere they stay); returns the accepted sum (wave-uniform).
+// A lane's asks lie in one stretch of that order (lane lr's in two), so with the lanes' sums scanned
+// every lane knows whether its stretch fits as a whole, and at most one stretch is cut: its rows
+// are laid out over the lanes, a row each, scanned, and the outcome is written back to the lane.
+// kOneRow: a single row of job slots, so a stretch is a single ask and nothing is cut.
+template <int Q, bool kWide, bool kOneRow>
+__device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32_t (&m)[Q], uint32_t limit, uint32_t lr,
+                                                  uint32_t ir, int lane) {
+  uint32_t run = 0;
+  if (kOneRow) {
+    run = (1u << v[0]) >> 1;
+  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) run = add_gpus<kWide>(v[q], run);
   }
   const uint32_t incl = wave_inclusive_scan(run);
   const uint32_t total = __builtin_amdgcn_readlane(incl, kLanes - 1);
-  if (total <= limit) return total;                // everything fits: no second pass
-  const uint32_t excl = incl - run;
-  // pre = sum of the lane's rows above ir (only lane lr's value is used): the snapshot of the
-  // blocks before ir's block plus the rows of that block above ir.  ir is wave-uniform.
+  if (total <= limit) return total;                // everything fits
+  if (kOneRow) {
+    const uint32_t base = __builtin_amdgcn_readlane(incl - run, lr);             // asks visited after the wrap
+    const uint32_t end = incl - base + (static_cast<uint32_t>(lane) < lr ? total : 0u);
+    const bool fits = end <= limit;
+    m[0] = fits ? m[0] : 0u;
+    // what fits is what comes before the first lane, in visiting order, whose ask does not
+    const uint64_t beyond = __ballot(!fits), after = beyond >> lr << lr;
+    return __builtin_amdgcn_readlane(end - run, __ffsll(static_cast<long long>(after ? after : beyond)) - 1);
+  }
+  // lane lr's rows before ir (only that lane's value is used); ir is wave-uniform
   uint32_t pre = 0;
 #pragma unroll
-  for (int k = 0; k < kBlocks; ++k) {
-    if (ir / 8 == static_cast<uint32_t>(k)) {
-      if (k > 0) pre = snap[k - 1];
-#pragma unroll
-      for (int t = 0; t < 7; ++t)
-        if (8 * k + t < R && static_cast<uint32_t>(t) < ir % 8) pre += v[8 * k + t];
-    }
+  for (int q = 0; q < Q; ++q)
+    if (ir > 4u * q) pre = add_gpus<kWide>(v[q] & rows_before(ir, q), pre);
+  const uint32_t skipped = __builtin_amdgcn_readlane(pre, lr);                   // visited last, after the wrap
+  const uint32_t base = __builtin_amdgcn_readlane(incl - run, lr) + skipped;     // asks visited after the wrap
+  const uint32_t end = incl - base + (static_cast<uint32_t>(lane) < lr ? total : 0u);
+  const uint32_t begin = end - (run - (static_cast<uint32_t>(lane) == lr ? skipped : 0u));
+  const bool fits = end <= limit;
+  uint32_t got = limit;                              // a cut between two stretches uses the limit up
+  // the stretch that is cut: its lane, its rows [from, to), what is left for it
+  const uint64_t cut = __ballot(begin < limit && !fits);
+  const bool wrapped = total - skipped < limit;      // lane lr's second stretch; then every other one fits
+  uint32_t b = lr, from = 0, to = ir, room = limit - (total - skipped);
+  if (!wrapped) {
+    b = cut ? static_cast<uint32_t>(__ffsll(static_cast<long long>(cut)) - 1) : 0u;
+    from = b == lr ? ir : 0u;
+    to = 4 * Q;
+    room = limit - __builtin_amdgcn_readlane(begin, b);
   }
-  const uint32_t base = __builtin_amdgcn_readlane(excl + pre, lr);   // asks visited after the wrap
-  // A row's prefix is run_i + off; it fits iff run_i <= limit - off (0 when off exceeds the
-  // limit: then only rows without an ask "fit", which changes nothing).
-  const uint32_t off_hi = excl - base;             // rows at or after the start
-  const uint32_t off_lo = excl + (total - base);   // rows before the start, visited after the wrap
-  const bool at = static_cast<uint32_t>(lane) == lr;
-  // off_hi of lane lr is -pre (mod 2^32): add pre to the threshold instead
-  const uint32_t thr_hi = at ? limit + pre : (off_hi <= limit ? limit - off_hi : 0u);
-  const uint32_t thr_lo = off_lo <= limit ? limit - off_lo : 0u;
-  // first row of the lane that is visited before the wrap (a per-lane value on purpose, so
-  // that the row test below is one vector compare instead of a scalar mask per row)
-  const uint32_t first_hi = static_cast<uint32_t>(lane) > lr ? 0u : (at ? ir : static_cast<uint32_t>(R));
-  uint32_t acc = 0;
-  run = 0;
+  if (!wrapped) {                                    // lane lr's second stretch lies beyond the limit
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    run += v[i];
-    const uint32_t thr = static_cast<uint32_t>(i) >= first_hi ? thr_hi : thr_lo;
-    v[i] = run <= thr ? v[i] : 0u;
-    acc += v[i];
+    for (int q = 0; q < Q; ++q)
+      if (ir > 4u * q) m[q] &= static_cast<uint32_t>(lane) == lr ? ~rows_before(ir, q) : 0xFFFFFFFFu;
   }
-  return wave_sum(acc);
+  const uint32_t whole = fits ? 0xFFFFFFFFu : 0u;
+  if (!wrapped && cut == 0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) m[q] &= whole;
+    return got;
+  }
+  uint32_t x = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t u = __builtin_amdgcn_readlane(v[q], b);
+    x = (lane >> 2) == q ? u : x;
+  }
+  x = (x >> ((lane & 3) * 8)) & 31u;
+  const bool inside = static_cast<uint32_t>(lane) >= from && static_cast<uint32_t>(lane) < to;
+  const uint32_t sum = wave_inclusive_scan(inside ? (1u << x) >> 1 : 0u);
+  const uint64_t within = __ballot(inside && sum <= room);                       // rows from .. of the accepted prefix
+  const uint32_t count = static_cast<uint32_t>(__popcll(within));
+  got = limit - room + (count ? __builtin_amdgcn_readlane(sum, from + count - 1) : 0u);
+  uint32_t rows = static_cast<uint32_t>(within);
+  if (wrapped) rows |= ~((1u << ir) - 1u);           // its first stretch fits
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t bits = (((rows >> (4 * q)) & 15u) * 0x00204081u) & kOnes;     // bit k to byte k
+    m[q] &= static_cast<uint32_t>(lane) == b ? bits * 0xFFu : whole;
+  }
+  return got;
 }
 
-// Refresh + fill (Section 3.2.2) on GPU counts c[]; clamp and lift already applied.
-// new_first (only in the generation after a table change): the jobs that arrived with the table
-// are served first (refresh (3)): each starts on cstart GPUs while the capacity lasts, in
-// visiting order, and the others are admitted to what is left: in visiting order too, or, with
-// time_rank (position of every job in ascending order of executed time), least executed time
-// first, so that the room is taken from the jobs with the largest T_processed.
-template <int R>
-__device__ __forceinline__ void repair(uint32_t (&c)[R], const Smem &s, uint32_t G, uint32_t r, int lane,
-                                       bool new_first, const uint32_t *time_rank = nullptr) {
-  const uint32_t lr = r / R, ir = r % R;
+// Refresh + fill (Section 3.2.2) on codes c[]; window and lift already applied.
+// kArrivals (only in the generation after a table change): the jobs that arrived with the table
+// are served first (refresh (3)): each starts on the GPUs a waiting job resumes with while the
+// capacity lasts, in visiting order, and the others are admitted to what is left: in visiting order
+// too, or, with time_rank (position of every job in ascending order of executed time), least executed
+// time first, so that the room is taken from the jobs with the largest T_processed.
+template <int Q, bool kWide, bool kArrivals, bool kOneRow = false>
+__device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t G, uint32_t lr, uint32_t ir, int lane,
+                                       uint32_t Jp, const uint32_t *time_rank) {
   uint32_t used;
-  if (new_first) {
-    uint32_t v[R];
+  if (kArrivals) {
+    uint32_t v[Q], fresh[Q];
 #pragma unroll
-    for (int i = 0; i < R; ++i) v[i] = info_new(s.info[lane + kLanes * i]) ? s.cc2[lane + kLanes * i].x : 0u;
-    const uint32_t taken = accept_prefix<R>(v, G, lr, ir, lane);
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const bool is_new = info_new(s.info[lane + kLanes * i]) != 0;
-      c[i] = is_new ? v[i] : c[i];
-      v[i] = is_new ? 0u : c[i];
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t arrived = s.fresh[q * kLanes + lane];
+      v[q] = fresh[q] = s.start[q * kLanes + lane] & arrived;
+      c[q] &= ~arrived;
     }
-    phase_fence();
+    const uint32_t taken = accept_prefix<Q, kWide, kOneRow>(v, fresh, G, lr, ir, lane);
     if (time_rank) {
       // The running sum over the ranks never decreases, so the admitted jobs are the ranks below
       // some bound: the largest n whose first n ranks ask for no more than what is left.
       const uint32_t cap = G - taken;
-      uint32_t rk[R];
+      // 0xFF for the jobs of word q with a rank below n
+      auto ranked_below = [&](int q, uint32_t n) {
+        uint32_t mask = 0;
 #pragma unroll
-      for (int i = 0; i < R; ++i) rk[i] = time_rank[lane + kLanes * i];
-      uint32_t lo = 0, hi = static_cast<uint32_t>(R * kLanes), fits = 0;   // the first lo ranks fit (sum fits)
-      while (lo < hi) {                                                    // at most log2(R * 64) + 1 steps
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t j = (4 * q + k) * kLanes + lane;
+          mask |= j < Jp && time_rank[j] < n ? 0xFFu << (8 * k) : 0u;
+        }
+        return mask;
+      };
+      uint32_t lo = 0, hi = Jp, fit = 0;                                   // the first lo ranks fit (sum fit)
+      while (lo < hi) {                                                    // at most log2(Jp) + 1 steps
         const uint32_t mid = (lo + hi + 1) / 2;
         uint32_t sum = 0;
+        phase_fence();                                                     // the ranks are not kept in registers
 #pragma unroll
-        for (int i = 0; i < R; ++i) sum += rk[i] < mid ? v[i] : 0u;
+        for (int q = 0; q < Q; ++q) sum = add_gpus<kWide>(c[q] & ranked_below(q, mid), sum);
         sum = wave_sum(sum);
-        if (sum <= cap) { lo = mid; fits = sum; } else { hi = mid - 1; }
+        if (sum <= cap) { lo = mid; fit = sum; } else { hi = mid - 1; }
       }
 #pragma unroll
-      for (int i = 0; i < R; ++i) v[i] = rk[i] < lo ? v[i] : 0u;
-      used = taken + fits;
+      for (int q = 0; q < Q; ++q) c[q] &= ranked_below(q, lo);
+      used = taken + fit;
     } else {
-      used = taken + accept_prefix<R>(v, G - taken, lr, ir, lane);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = c[q];
+      used = taken + accept_prefix<Q, kWide, kOneRow>(v, c, G - taken, lr, ir, lane);
     }
 #pragma unroll
-    for (int i = 0; i < R; ++i) c[i] = info_new(s.info[lane + kLanes * i]) ? c[i] : v[i];
+    for (int q = 0; q < Q; ++q) c[q] |= fresh[q];
   } else {
     // admit: jobs beyond the capacity in visiting order wait (Eq. 4)
-    used = accept_prefix<R>(c, G, lr, ir, lane);
+    uint32_t v[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = c[q];
+    used = accept_prefix<Q, kWide, kOneRow>(v, c, G, lr, ir, lane);
   }
-  // fill: a waiting job asks for cstart GPUs, a running one below its limit asks to double.
-  // Every round accepts at least its first ask (got == 0: nobody could ask), and a job doubles
-  // at most 20 times, so kMaxRows * 64 * 21 rounds always suffice; the bound only makes the
-  // loop end whatever happens.
+  // fill: a waiting job asks for its starting GPUs, a running one below its limit asks to double,
+  // both only if the GPUs are there (a power of two fits when its code is not above that of the idle
+  // GPUs).  Every round that accepts anything uses up idle GPUs, and a round that accepts nothing ends it.
   uint32_t idle = G - used;
-  for (int round = 0; round < kMaxRows * kLanes * 21 && idle > 0; ++round) {
-    uint32_t v[R];
+  if (idle == 0) return;
+  uint32_t waits[Q];                                 // 0x7F for the jobs that wait
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const uint2 k = s.cc2[lane + kLanes * i];
-      const uint32_t cost = max(c[i], k.x);
-      v[i] = (c[i] < k.y && cost <= idle) ? cost : 0u;
-      if (i % 8 == 7) { pin(v[i]); phase_fence(); }
+  for (int q = 0; q < Q; ++q) waits[q] = ~nonzero_bytes(c[q]) & kSevens;
+  while (idle > 0) {
+    const uint32_t fitting = kTops | (static_cast<uint32_t>(32 - __clz(static_cast<int>(idle))) * kOnes);
+    uint32_t v[Q], m[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int w = q * kLanes + lane;
+      const uint32_t cost = c[q] | (s.start[w] & waits[q]);
+      m[q] = spread_tops(((c[q] ^ s.most[w]) + kSevens) & (fitting - cost));   // below its limit, and the GPUs are there
+      v[q] = cost & m[q];
     }
-    const uint32_t got = accept_prefix<R>(v, idle, lr, ir, lane);
+    const uint32_t got = accept_prefix<Q, kWide, kOneRow>(v, m, idle, lr, ir, lane);
+    if (got == 0 || got > idle) break;
 #pragma unroll
-    for (int i = 0; i < R; ++i) c[i] += v[i];
-    if (got == 0) break;
+    for (int q = 0; q < Q; ++q) {
+      const int w = q * kLanes + lane;
+      c[q] += pick(waits[q], s.start[w], kOnes) & m[q];          // a running job's code goes up by one
+      waits[q] &= ~m[q];
+    }
     idle -= got;
   }
 }
 
 // Eq. 3: sum over running jobs of T_j c_j = Y_j t_j / (local batch), t = a b + c log2(g) + d.
 // Summation order: a lane's rows top to bottom, then a xor butterfly 32,16,..,1 over lanes.
-template <int R>
-__device__ __forceinline__ double score(const uint32_t (&c)[R], const Smem &s, uint32_t E, int lane) {
+// kRows: rows that can hold job slots (the terms of rows beyond the slots are 0).
+template <int Q, int kRows = 4 * Q>
+__device__ __forceinline__ double score(const uint32_t (&c)[Q], const Smem &s, uint32_t E, int lane) {
   double acc = 0.0;
   if (E != 0) {
-    // the job's term only depends on its GPU count c = 2^(code-1) (code 0: waiting), and the
-    // table holds exactly the value the formula below produces
-    // code = 32 - z with z the leading zeros of c (32 for a waiting job); the table is stored
-    // with the codes backwards, entry E-1-code = z - (33 - E)
-    // (column itself lies before the table; every address formed from it lies inside: z >= 33 - E)
-    const double *column = s.terms + lane + (static_cast<int>(E) - 33) * (R * kLanes);
+    // the job's term only depends on the code of its GPU count, and the table holds exactly the
+    // value the formula below produces
+    const double *column = s.terms + lane;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int z = __clz(static_cast<int>(c[i]));
-      acc = acc + (column + z * (R * kLanes))[i * kLanes];
+    for (int i = 0; i < kRows; ++i) {
+      const uint32_t code = (c[i / 4] >> (8 * (i % 4))) & 0xFFu;
+      acc = acc + (column + code * (4 * Q * kLanes))[i * kLanes];
       if (i % 8 == 7) { pin(acc); phase_fence(); }
     }
   } else
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
+  for (int i = 0; i < kRows; ++i) {
     const int j = lane + kLanes * i;
-    const uint32_t ci = c[i];
-    const double lg = static_cast<double>(31 - __clz(static_cast<int>(ci | 1u)));
-    const double inv_bl = __hiloint2double(static_cast<int>((1023u - info_blexp(s.info[j])) << 20), 0);
+    const uint32_t code = (c[i / 4] >> (8 * (i % 4))) & 0xFFu;
+    const uint32_t bl = (s.bl[(i / 4) * kLanes + lane] >> (8 * (i % 4))) & 0xFFu;
+    const double lg = static_cast<double>(static_cast<int>(code) - 1);
+    const double inv_bl = __hiloint2double(static_cast<int>((1023u - bl) << 20), 0);
     const double t = (s.abl[j] + s.cc[j] * lg) + s.d[j];
     const double term = (s.Y[j] * t) * inv_bl;
-    acc = acc + (ci ? term : 0.0);
+    acc = acc + (code ? term : 0.0);
     if (i % 4 == 3) { pin(acc); phase_fence(); }
   }
-#pragma unroll
-  for (int sft = 32; sft >= 1; sft >>= 1) acc = acc + __shfl_xor(acc, sft, kLanes);
-  return acc;
+  return butterfly_sum(acc);
 }
 
 // The score of pool slot p, for a general selection that follows (the pointer is read from the
@@ -473,7 +687,7 @@ __device__ __forceinline__ void note_slot_score(uint32_t p, double f, int lane) 
 // A child or mutant that beats the K-th survivor joins the bucket of the survivors it falls
 // between: bucket = number of splitters <= its score.  Scores at or above the threshold
 // cannot be among the best K (the K survivors themselves are in the pool, in smaller slots).
-__device__ __forceinline__ void drop_in_bucket(const EvolveArgs &a, const Smem &s, uint32_t p, double f, int lane) {
+__device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double f, int lane) {
   const uint64_t raw = static_cast<uint64_t>(__double_as_longlong(f));
   // the butterfly leaves the same sum in every lane; make that visible to the compiler
   // (the builtin returns a signed int: widen through uint32_t, not by sign extension)
@@ -481,9 +695,13 @@ __device__ __forceinline__ void drop_in_bucket(const EvolveArgs &a, const Smem &
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(raw)));
   const uint64_t bits = (static_cast<uint64_t>(hi) << 32) | lo;
   if (bits >= s.split[kMaxBuckets]) return;
-  uint32_t b = 0;
-  for (uint32_t q = 0; q * kLanes + 1 < a.bk.nb; ++q)      // splitters 0 .. nb-2, the rest is +inf
-    b += static_cast<uint32_t>(__popcll(__ballot(s.split[q * kLanes + lane] <= bits)));
+  // two steps over the ascending splitters (the last ones are +inf): the sixteenth ones, then the
+  // sixteen in front of the first of those that is above
+  constexpr int kStep = kMaxBuckets / kLanes;
+  static_assert(kStep <= kLanes, "one splitter per lane");
+  const uint32_t block = kStep * static_cast<uint32_t>(__popcll(__ballot(s.split[lane * kStep + kStep - 1] <= bits)));
+  const uint32_t b = block + static_cast<uint32_t>(__popcll(
+                                 __ballot(lane < kStep && s.split[min(block + lane, kMaxBuckets - 1u)] <= bits)));
   if (lane == 0) {
     // The pointers of the bucket storage are read from the kernel's argument block here, where
     // the few candidates that get this far need them, instead of being carried (and spilled)
@@ -506,28 +724,6 @@ __device__ __forceinline__ void drop_in_bucket(const EvolveArgs &a, const Smem &
   }
 }
 
-template <int R>
-__device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t r,
-                                         uint32_t (&c)[R], int lane, bool new_first = false) {
-  repair<R>(c, s, a.G, r, lane, new_first, a.time_rank);
-  phase_fence();
-  const double f = score<R>(c, s, a.term_lds, lane);
-  phase_fence();
-  int32_t *row = a.genes + static_cast<size_t>(dst_row) * a.Jp;
-#pragma unroll
-  for (int i = 0; i < R; ++i)
-    __builtin_nontemporal_store(static_cast<int32_t>(c[i] << info_blexp(s.info[lane + kLanes * i])),
-                                &row[lane + kLanes * i]);
-  if (lane == 0) a.fit_row[dst_row] = f;
-  return f;
-}
-
-template <int R>
-__device__ __forceinline__ void load_genes(const int32_t *row, int lane, uint32_t (&B)[R]) {
-#pragma unroll
-  for (int i = 0; i < R; ++i) B[i] = static_cast<uint32_t>(row[lane + kLanes * i]);
-}
-
 // Uniform crossover over the GPUs (Section 3.2.2 on the encoding of Eq. 1).  Both parents are
 // laid out as the reorder operator leaves them: the jobs in slot order on consecutive GPUs, cA
 // resp. cB GPUs each, GPUs beyond the cluster do not exist.  Every GPU has a fair coin: heads,
@@ -540,9 +736,10 @@ __device__ __forceinline__ void load_genes(const int32_t *row, int lane, uint32_
 // entries of LDS, each a coin word and, above it, the number of heads on the GPUs before it.
 // kFeasible: both parents are known to fit the cluster (they were repaired under the current
 // job table), so no GPU position needs to be cut off at the cluster's size.
-template <int R, bool kFeasible>
+template <int Q, bool kFeasible>
 __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_t t, const Smem &s, uint64_t *coins, uint32_t p0,
-                                                    int lane, uint32_t (&cA)[R], uint32_t (&cB)[R]) {
+                                                    int lane, uint32_t (&cA)[Q], uint32_t (&cB)[Q]) {
+  const uint32_t R = a.Jp / kLanes;
   {
     const Words w = philox4x32_10(static_cast<uint32_t>(lane), p0, t, 3u, a.key0, a.key1);
     const uint32_t heads = __popc(w.w[0]) + __popc(w.w[1]) + __popc(w.w[2]) + __popc(w.w[3]);
@@ -570,35 +767,38 @@ __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_
   uint32_t carry_a = 0, carry_b = 0;                             // GPUs of the rows above (wave-uniform)
   uint32_t above_a = 0, above_b = 0;                             // heads below the first GPU of the row (wave-uniform)
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const uint32_t incl_a = wave_inclusive_scan(cA[i]), incl_b = wave_inclusive_scan(cB[i]);
-    uint32_t end_a = carry_a + incl_a, start_a = end_a - cA[i];
-    uint32_t end_b = carry_b + incl_b, start_b = end_b - cB[i];
-    if (!kFeasible) {
-      end_a = min(end_a, a.G); start_a = min(start_a, a.G);
-      end_b = min(end_b, a.G); start_b = min(start_b, a.G);
+  for (int q = 0; q < Q; ++q) {
+    uint32_t first = 0, second = 0;                              // the children's codes before the window
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (static_cast<uint32_t>(4 * q + k) >= R) continue;       // no job slots (wave-uniform)
+      const uint32_t ga = (1u << ((cA[q] >> (8 * k)) & 31u)) >> 1, gb = (1u << ((cB[q] >> (8 * k)) & 31u)) >> 1;
+      const uint32_t incl_a = wave_inclusive_scan(ga), incl_b = wave_inclusive_scan(gb);
+      uint32_t end_a = carry_a + incl_a, start_a = end_a - ga;
+      uint32_t end_b = carry_b + incl_b, start_b = end_b - gb;
+      if (!kFeasible) {
+        end_a = min(end_a, a.G); start_a = min(start_a, a.G);
+        end_b = min(end_b, a.G); start_b = min(start_b, a.G);
+      }
+      carry_a += __builtin_amdgcn_readlane(incl_a, kLanes - 1);
+      carry_b += __builtin_amdgcn_readlane(incl_b, kLanes - 1);
+      const uint32_t at_end_a = heads_below(end_a), at_end_b = heads_below(end_b);
+      const uint32_t left_a = __shfl_up(at_end_a, 1, kLanes), left_b = __shfl_up(at_end_b, 1, kLanes);
+      const uint32_t heads_a = at_end_a - (lane == 0 ? above_a : left_a);
+      const uint32_t heads_b = at_end_b - (lane == 0 ? above_b : left_b);
+      above_a = __builtin_amdgcn_readlane(at_end_a, kLanes - 1);
+      above_b = __builtin_amdgcn_readlane(at_end_b, kLanes - 1);
+      const uint32_t n1 = heads_a + ((end_b - start_b) - heads_b);
+      const uint32_t n2 = ((end_a - start_a) - heads_a) + heads_b;
+      first |= static_cast<uint32_t>(32 - __clz(static_cast<int>(n1))) << (8 * k);     // 0 GPUs: 0
+      second |= static_cast<uint32_t>(32 - __clz(static_cast<int>(n2))) << (8 * k);
     }
-    carry_a += __builtin_amdgcn_readlane(incl_a, kLanes - 1);
-    carry_b += __builtin_amdgcn_readlane(incl_b, kLanes - 1);
-    const uint32_t at_end_a = heads_below(end_a), at_end_b = heads_below(end_b);
-    const uint32_t left_a = __shfl_up(at_end_a, 1, kLanes), left_b = __shfl_up(at_end_b, 1, kLanes);
-    const uint32_t heads_a = at_end_a - (lane == 0 ? above_a : left_a);
-    const uint32_t heads_b = at_end_b - (lane == 0 ? above_b : left_b);
-    above_a = __builtin_amdgcn_readlane(at_end_a, kLanes - 1);
-    above_b = __builtin_amdgcn_readlane(at_end_b, kLanes - 1);
-    const uint32_t n1 = heads_a + ((end_b - start_b) - heads_b);
-    const uint32_t n2 = ((end_a - start_a) - heads_a) + heads_b;
-    const uint2 k = s.cc2[lane + kLanes * i];
-    cA[i] = n1 ? min(max(0x80000000u >> __clz(static_cast<int>(n1)), k.x), k.y) : 0u;
-    cB[i] = n2 ? min(max(0x80000000u >> __clz(static_cast<int>(n2)), k.x), k.y) : 0u;
-    fence_every(i, 4);
+    const int w = q * kLanes + lane;
+    const uint32_t start = s.start[w], most = s.most[w];
+    cA[q] = min_bytes(max_bytes(first, start), most) & nonzero_bytes(first);
+    cB[q] = min_bytes(max_bytes(second, start), most) & nonzero_bytes(second);
+    phase_fence();
   }
-}
-
-// Redraw of a gene from k in [0, n): 0 = the job is pre-empted, else 2^(lo + k - 1).
-__device__ __forceinline__ uint32_t batch_from_draw(uint32_t k, uint32_t info) {
-  const uint32_t b = (info_active(info) << (info_lo(info) + k)) >> 1;   // k = 0 or empty slot -> 0
-  return k ? b : 0u;
 }
 
 }  // namespace

@@ -38,14 +38,26 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t x0, uint32_t x1, uint32_
   return Words{{x0, x1, x2, x3}};
 }
 
-// Per-slot constants derived from the job table, structure of arrays over the padded
-// slots (column = slot mod 64, row = slot div 64).  A gene is handled on the device as
-// the job's GPU count c (0 = waiting): after the free lift to the per-GPU max batch the
-// global batch is B = c << bl_exp, so c in {0} U {cstart, 2 cstart, .., cmax} says it all.
+// Genomes.  A gene is a byte: the code of the job's GPU count, 0 = the job waits, e + 1 = it runs on
+// 2^e GPUs (at most 2^20).  After the free lift to the per-GPU max batch a running job's global batch
+// is B = GPUs << bl_exp with bl_exp a property of its slot in the job table, so the code says it
+// all, for the table the genome was made under.  A genome row is Q * 64 words, Q = ceil(rows / 4):
+// job slot j lies in column (lane) j mod 64 and row i = j div 64, at byte i mod 4 of word
+// (i div 4) * 64 + lane; the bytes of rows beyond the job slots are 0.
+constexpr int words_of(int rows) { return (rows + 3) / 4; }          // Q
+__host__ __device__ inline uint32_t gene_byte(uint32_t j) { return ((j / 64 / 4) * 64 + j % 64) * 4 + j / 64 % 4; }
+__host__ __device__ inline uint32_t batch_of_code(uint32_t code, uint32_t bl_exp) { return ((1u << code) >> 1) << bl_exp; }
+
+// Per-slot constants derived from the job table, over the padded slots.
 struct JobTable {
-  uint32_t *cstart;   // GPU count a waiting job resumes with; 0 for an empty slot
-  uint32_t *cmax;     // GPU count at the batch-size limit R_j;  0 for an empty slot
+  // laid out like a genome row, a byte per slot: code a waiting job resumes with and code at the
+  // batch-size limit R_j (0 for an empty slot), number of outcomes of a redraw (hi - lo + 2; 0 for an
+  // empty slot), lo - mu + 31
+  uint32_t *start, *most, *draws, *base;
   uint32_t *info;     // bits 0-4 lo, 5-10 (hi-lo+2), 11-15 mu, 16-20 bl_exp, 21 active, 22 arrived with this table
+  // info of the table the genomes are stored under: this one, or, between ones_set_jobs and the next
+  // generation, an earlier one, where bit 23 marks the slots that have changed hands since (they wait)
+  uint32_t *stored;
   double   *abl;      // a * 2^bl_exp: compute time of one iteration at the local batch
   double   *cc;       // synchronisation cost per doubling of the GPU count
   double   *d;        // fixed cost per iteration
@@ -62,6 +74,8 @@ __host__ __device__ inline uint32_t info_mu(uint32_t w)     { return (w >> 11) &
 __host__ __device__ inline uint32_t info_blexp(uint32_t w)  { return (w >> 16) & 31u; }
 __host__ __device__ inline uint32_t info_active(uint32_t w) { return (w >> 21) & 1u; }
 __host__ __device__ inline uint32_t info_new(uint32_t w)    { return (w >> 22) & 1u; }
+__host__ __device__ inline uint32_t info_reset(uint32_t w)  { return (w >> 23) & 1u; }
+constexpr uint32_t kInfoReset = 1u << 23;
 
 // Quantile buckets of the selection (valid while the job table stays the same): children and
 // mutants that beat the K-th survivor are dropped into the bucket of the survivors they fall
@@ -105,7 +119,7 @@ constexpr int kDrawRing = 8;
 // slot K + q of the new pool takes the q-th; a survivor that must be refreshed after a table
 // change (rank p) takes the (3K + p)-th.  The evolve kernel looks its rows up in the bitmap.
 struct EvolveArgs {
-  int32_t        *genes;      // [P + K][Jp] genome rows (global batch sizes)
+  uint32_t       *genes;      // [P + K][Q * 64] genome rows
   double         *fit_row;    // [P + K] score of the genome in each row
   const uint32_t *parent_row; // [K] rows of the survivors, best first
   uint32_t       *row_of;     // [P] row of every slot of the new pool: entries [0,K) prefilled
@@ -122,7 +136,7 @@ struct EvolveArgs {
                               //      time, the order the other jobs are admitted in; null = visiting order
   uint32_t       rescore;     // the survivors' scores are stale (remaining work redrawn): score them again
   uint32_t       per_gpu;     // the uniform crossover scans the GPUs (Eq. 1) instead of the jobs; needs G <= kMaxCoinGpus
-  uint32_t       stash_stride; // set by the launcher: bytes of LDS scratch per wave
+  uint32_t       coin_stride; // set by the launcher: bytes of LDS scratch per wave
   uint32_t       term_lds;    // set by the launcher: entries per job of the term table in LDS, 0 = none
   uint32_t       *fault;      // [1] raised when a row index had to be pulled back into the genome array
   double         *slot_score; // [P] the score of every candidate this launch scores, by pool slot (written when
@@ -189,15 +203,14 @@ __device__ __forceinline__ double term_of(double abl, double cc, double d, doubl
 }
 
 struct RawJobs {              // uploaded by the host after validation, [Jp] each
-  const uint32_t *rawinfo;    // bits 0-4 lo, 5-9 hi, 10-14 mu, 15 active, 16 arrived with this table
+  const uint32_t *rawinfo;    // bits 0-4 lo, 5-9 hi, 10-14 mu, 15 active, 16 arrived with this table, 17 changed hands
   const double   *a, *c, *d, *Y;
 };
 
 // launchers (each returns the hipGetLastError of its launch)
-// The per-slot values and the term table from the raw table, and the n_changed slots (may be 0)
-// that changed hands set to "waiting" in every one of the genome rows; one launch.
-hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, int32_t *genes, const uint32_t *slots,
-                               uint32_t n_changed, uint32_t rows, hipStream_t s);
+// The per-slot values and the term table from the raw table, and the slots that changed hands marked
+// in tab.stored (unless the genomes are, or will be, stored under this table); one launch.
+hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, hipStream_t s);
 hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s);
 // ring: the job table with Y and terms pointing at place 0 of the ring, whose places lie
 // ring_stride doubles apart; draws generations t .. t + count - 1 (count <= kDrawRing).
@@ -205,19 +218,22 @@ hipError_t launch_sample_remaining(const Progress &pr, const JobTable &ring, uin
                                    uint32_t Jp, uint32_t key0, uint32_t key1, uint32_t t, uint32_t count,
                                    hipStream_t s);
 // same_table: the job table is the one the previous generation was repaired and scored with
-hipError_t launch_evolve_group0(const EvolveArgs &a, int rows, bool same_table, int n_cus, hipStream_t s);
-hipError_t launch_evolve_group1(const EvolveArgs &a, int rows, bool same_table, int n_cus, hipStream_t s);
-hipError_t launch_evolve_group2(const EvolveArgs &a, int rows, bool same_table, int n_cus, hipStream_t s);
-hipError_t launch_evolve_group3(const EvolveArgs &a, int rows, bool same_table, int n_cus, hipStream_t s);
+hipError_t launch_evolve_group0(const EvolveArgs &a, int words, bool same_table, int n_cus, hipStream_t s);
+hipError_t launch_evolve_group1(const EvolveArgs &a, int words, bool same_table, int n_cus, hipStream_t s);
+hipError_t launch_evolve_group2(const EvolveArgs &a, int words, bool same_table, int n_cus, hipStream_t s);
+hipError_t launch_evolve_group3(const EvolveArgs &a, int words, bool same_table, int n_cus, hipStream_t s);
 inline hipError_t launch_evolve(const EvolveArgs &a, int rows, bool same_table, int n_cus, hipStream_t s) {
-  switch ((rows - 1) / 8) {
-    case 0: return launch_evolve_group0(a, rows, same_table, n_cus, s);
-    case 1: return launch_evolve_group1(a, rows, same_table, n_cus, s);
-    case 2: return launch_evolve_group2(a, rows, same_table, n_cus, s);
-    case 3: return launch_evolve_group3(a, rows, same_table, n_cus, s);
+  const int words = words_of(rows);
+  switch ((words - 1) / 2) {
+    case 0: return launch_evolve_group0(a, words, same_table, n_cus, s);
+    case 1: return launch_evolve_group1(a, words, same_table, n_cus, s);
+    case 2: return launch_evolve_group2(a, words, same_table, n_cus, s);
+    case 3: return launch_evolve_group3(a, words, same_table, n_cus, s);
     default: return hipErrorInvalidValue;
   }
 }
+// A table whose largest job takes more than 64 GPUs: codes above 7 (see add_gpus).
+inline bool wide_table(const JobTable &tab) { return tab.term_E > 8; }
 // General selection (any scores).  store: the bucket storage (count, keys, idx and spill arrays,
 // split and split_slot as scratch for the splitters, nb * seg entries of bucket space); used by pools
 // too large for the single launch that ranks a whole pool.  slot_score: the pool's scores by slot
@@ -232,12 +248,16 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
                             hipStream_t s);
 // Eq. 1 for the winner: GPU i runs slot slot_of_gpu[i] (-1 = idle) with batch_of_gpu[i] samples;
 // jobs in slot order on consecutive GPUs.  G entries each.
-hipError_t launch_placement(const int32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
+hipError_t launch_placement(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
                             uint32_t Jn, uint32_t Jp, uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu,
                             hipStream_t s);
-hipError_t launch_best(const int32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                       const uint32_t *info,
+// stored: info of the table the genomes are stored under, info: of the table in force.
+hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
+                       const uint32_t *stored, const uint32_t *info,
                        uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out, double *fit_out,
                        const uint32_t *err_in, uint32_t *err_out, hipStream_t s);
+// Batch sizes of the pool slots [first, first + count), in slot order: out[count][Jp].
+hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const uint32_t *stored, uint32_t Jp, uint32_t first,
+                         uint32_t count, int32_t *out, hipStream_t s);
 
 }  // namespace ones

@@ -96,12 +96,13 @@ struct Ranks {
   uint64_t *ukeys;     // [waves][kFusedUnits] per unit: the score, until the wave publishes it
   double   *ydraw;     // [64] remaining work of every slot as drawn for the generation being computed (Alg. 1)
   double   *model;     // [3][64] the slots' a * local batch, c and d, from which a draw gives the term table
+  uint32_t *blexp;     // [64] ... and log2 of their local batch
 };
 
 inline size_t ranks_bytes(uint32_t P) {
   const size_t K = P / 4;
   return 2 * K * 8 + 2 * K * 2 + K * 2 + P * 2 + P * 8 + 3 * K * 8 + 3 * K * 4 + kMergeMax * (8 + 4 + 4) +
-         ((P + K + 31) / 32) * 8 + 16 + kFusedWaves * kFusedUnits * ((4 + kLanes) * 4 + 8) + 4 * kLanes * 8 + 64;
+         ((P + K + 31) / 32) * 8 + 16 + kFusedWaves * kFusedUnits * ((4 + kLanes) * 4 + 8) + 4 * kLanes * 8 + kLanes * 4 + 64;
 }
 
 __device__ __forceinline__ Ranks carve_ranks(unsigned char *base, uint32_t P) {
@@ -123,7 +124,8 @@ __device__ __forceinline__ Ranks carve_ranks(unsigned char *base, uint32_t P) {
   r.misc = r.wfree + (P + K + 31) / 32;
   r.draws = r.misc + 4;
   r.words = r.draws + kFusedWaves * kFusedUnits * 4;
-  r.srows = reinterpret_cast<uint16_t *>(r.words + kFusedWaves * kFusedUnits * kLanes);
+  r.blexp = r.words + kFusedWaves * kFusedUnits * kLanes;
+  r.srows = reinterpret_cast<uint16_t *>(r.blexp + kLanes);
   r.nsel = r.srows + 2 * K;
   r.frow = r.nsel + K;
   return r;
@@ -227,27 +229,27 @@ __device__ __forceinline__ void draw_parents(const EvolveArgs &a, uint32_t t, ui
   if (lane == 0) { draws[0] = d.ra; draws[1] = d.rb; draws[2] = d.r; }
 }
 
+// The one row of job slots takes the first word of a Philox block.
 template <bool kOverGpus>
-__device__ __forceinline__ void draw_words(const EvolveArgs &a, uint32_t t, uint32_t u, int lane, uint32_t *words) {
+__device__ __forceinline__ void draw_words(const EvolveArgs &a, uint32_t t, uint32_t u, int lane, const uint2 *prefix,
+                                           uint32_t *words) {
   const uint32_t K = a.K;
-  uint32_t w[1] = {0u};
-  if (u >= 2 * K) gene_words<1>(a, t, K + u, lane, w);
-  else if (!kOverGpus) gene_words<1>(a, t, K + (u & ~1u), lane, w);   // both children share the pair's words
-  words[lane] = w[0];
+  uint32_t w = 0;
+  if (u >= 2 * K) w = WordSource(a, t, K + u).block(prefix, 0, lane).w[0];
+  else if (!kOverGpus) w = WordSource(a, t, K + (u & ~1u)).block(prefix, 0, lane).w[0];   // both children share the pair's words
+  words[lane] = w;
 }
 
 // One candidate of generation t: unit u < 2K is a child of pair u / 2, u < 3K a mutant, u >= 3K
 // (only after a table change) the survivor of rank u - 3K to refresh.  srow: rows of the
-// survivors by rank.  Returns the score; the repaired GPU counts are left in c.
+// survivors by rank.  Returns the score; the repaired genes are left in c.
 template <bool kSameTable, bool kOverGpus>
 __device__ __forceinline__ double compose_unit(const EvolveArgs &a, uint32_t t, const Smem &s, const uint16_t *srow,
-                                               uint32_t u, bool new_first, uint8_t *stash, const uint32_t *draws,
+                                               uint32_t u, bool new_first, uint64_t *coins, const uint32_t *draws,
                                                const uint32_t *words, int lane, uint32_t (&c)[1]) {
   const uint32_t K = a.K;
   uint32_t r;
-  auto gene_of = [&](uint32_t row) {
-    return static_cast<uint32_t>(shared_load(a.genes + static_cast<size_t>(row) * kLanes + lane));
-  };
+  auto gene_of = [&](uint32_t row) { return shared_load(a.genes + static_cast<size_t>(row) * kLanes + lane); };
   if (u < 3 * K) {
     const uint32_t ra = __builtin_amdgcn_readfirstlane(draws[0]), rb = __builtin_amdgcn_readfirstlane(draws[1]);
     r = __builtin_amdgcn_readfirstlane(draws[2]);
@@ -257,30 +259,30 @@ __device__ __forceinline__ double compose_unit(const EvolveArgs &a, uint32_t t, 
       uint32_t B[1];
       c[0] = gene_of(srow[ra]);
       B[0] = gene_of(srow[rb]);
-      gpus_from_batches<1, kSameTable>(s, lane, c);
-      gpus_from_batches<1, kSameTable>(s, lane, B);
       if (kOverGpus) {
-        crossover_over_gpus<1, kSameTable>(a, t, s, reinterpret_cast<uint64_t *>(stash), K + (u & ~1u), lane, c, B);
+        if (!kSameTable) { to_new_table<1>(s, lane, c); to_new_table<1>(s, lane, B); }
+        crossover_over_gpus<1, kSameTable>(a, t, s, coins, K + (u & ~1u), lane, c, B);
         c[0] = side ? B[0] : c[0];
       } else {
         const bool swap = w < a.T_x;                 // the first child takes the second parent's gene
         c[0] = (swap != (side != 0)) ? B[0] : c[0];
+        if (!kSameTable) to_new_table<1>(s, lane, c);
       }
     } else {
       c[0] = gene_of(srow[ra]);
-      const uint32_t word = s.info[lane];
-      const uint32_t k = ((w & 0xFFFFu) * info_n(word)) >> 16;
-      c[0] = w < a.T_mut ? batch_from_draw(k, word) : c[0];
-      gpus_from_batches<1, false>(s, lane, c);
+      if (!kSameTable) to_new_table<1>(s, lane, c);
+      const uint32_t k = ((w & 0xFFFFu) * (s.draws[lane] & 0xFFu)) >> 16;
+      c[0] = w < a.T_mut ? codes_of_draws(s, lane, k) : c[0];
     }
   } else {
     const uint32_t p = u - 3 * K;
-    r = candidate_draw(a, t, p).r;
+    r = __builtin_amdgcn_readfirstlane(candidate_draw(a, t, p).r);
     c[0] = gene_of(srow[p]);
-    gpus_from_batches<1, false>(s, lane, c);
+    to_new_table<1>(s, lane, c);
   }
-  repair<1>(c, s, a.G, r, lane, new_first, a.time_rank);
-  return score<1>(c, s, a.term_lds, lane);
+  if (!kSameTable && new_first) repair<1, false, true, true>(c, s, a.G, r, 0, lane, kLanes, a.time_rank);
+  else repair<1, false, false, true>(c, s, a.G, r, 0, lane, kLanes, nullptr);
+  return score<1, 1>(c, s, a.term_lds, lane);
 }
 
 // (Argument block: FusedArgs by value, which starts with its EvolveArgs, see kernel_args.)
@@ -292,14 +294,14 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const EvolveArgs &a = fa.ev;
   const uint32_t P = a.P, K = a.K, tid = threadIdx.x;
-  const Smem s = carve(smem_raw, kLanes, a.term_lds, kFusedWaves, a.stash_stride);
+  const Smem s = carve<1>(smem_raw, a.term_lds, kFusedWaves, a.coin_stride);
   const Ranks rk = carve_ranks(smem_raw + fa.table_lds, P);
   const int lane0 = tid & (kLanes - 1);
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the first work_groups workgroups compute candidates; under probability sampling kDrawGroups more only draw
   const uint32_t n_groups = fa.work_groups;
   const uint32_t wave = blockIdx.x * kFusedWaves + wave_in_block, n_waves = n_groups * kFusedWaves;
-  uint8_t *stash = s.stash + static_cast<size_t>(wave_in_block) * a.stash_stride;
+  uint64_t *coins = reinterpret_cast<uint64_t *>(s.coins + static_cast<size_t>(wave_in_block) * a.coin_stride);
   uint32_t *my_draws = rk.draws + wave_in_block * kFusedUnits * 4;
   uint32_t *my_words = rk.words + wave_in_block * kFusedUnits * kLanes;
   uint64_t *my_keys = rk.ukeys + wave_in_block * kFusedUnits;
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   };
   auto draw_unit_words = [&](uint32_t t) {
     for (uint32_t k = 0, u = wave; k < kFusedUnits && u < 3 * K; ++k, u += n_waves)
-      draw_words<kOverGpus>(a, t, u, opaque(lane0), my_words + kLanes * k);
+      draw_words<kOverGpus>(a, t, u, opaque(lane0), s.prefix, my_words + kLanes * k);
   };
   // Probability sampling.  The draw of a generation takes a long chain of fp64 operations (about
   // 5 us), so it is made two generations ahead, by workgroups that do nothing else (sixteen lanes
@@ -330,8 +332,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     const uint32_t E = a.term_lds;
     for (uint32_t q = tid; q < E * kLanes; q += kFusedThreads) {
       const uint32_t e = q / kLanes, j = q % kLanes;
-      s.terms[(E - 1 - e) * kLanes + j] =
-          term_of(rk.model[j], rk.model[kLanes + j], rk.model[2 * kLanes + j], rk.ydraw[j], info_blexp(s.info[j]), e);
+      s.terms[e * (4 * kLanes) + j] =
+          term_of(rk.model[j], rk.model[kLanes + j], rk.model[2 * kLanes + j], rk.ydraw[j], rk.blexp[j], e);
     }
     __syncthreads();
     return true;
@@ -355,8 +357,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     return;
   }
   draw_unit_parents(a.t + 1);
-  draw_unit_words(a.t + 1);
-  stage_table<1>(a.tab, a.bk, s, kLanes, a.term_lds, threadIdx.x, blockDim.x);
+  stage_table<1>(a, s, a.term_lds, fa.first_changed != 0, threadIdx.x, blockDim.x);
   // the state the last selection left: the survivors' rows and scores, the bitmap of their rows
   for (uint32_t e = tid; e < K; e += kFusedThreads) {
     const uint32_t row = fa.parent_rows[e];
@@ -369,8 +370,10 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     rk.model[tid] = a.tab.abl[tid];
     rk.model[kLanes + tid] = a.tab.cc[tid];
     rk.model[2 * kLanes + tid] = a.tab.d[tid];
+    rk.blexp[tid] = info_blexp(a.tab.info[tid]);
   }
   __syncthreads();
+  draw_unit_words(a.t + 1);
   list_free_rows(rk, nullptr, P, true);
   if (kSampled && !build_terms(fa.draws_before)) {
     if (tid == 0) shared_store(fa.sync + 1, 1u);
@@ -396,22 +399,20 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       if (kSampled && !changed && u >= 3 * K) {
         // the survivor of rank u - 3K keeps genome and row; only its score changes with the draw
         const uint32_t row = rk.srow(cur)[u - 3 * K];
-        c[0] = static_cast<uint32_t>(shared_load(a.genes + static_cast<size_t>(row) * kLanes + lane));
-        gpus_from_batches<1, true>(s, lane, c);
-        const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(score<1>(c, s, a.term_lds, lane)));
+        c[0] = shared_load(a.genes + static_cast<size_t>(row) * kLanes + lane);
+        const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(score<1, 1>(c, s, a.term_lds, lane)));
         if (lane == 0) {
           shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + row, bits);
           my_keys[k] = bits;
         }
         continue;
       }
-      const double f = changed ? compose_unit<false, kOverGpus>(a, t, s, rk.srow(cur), u, new_first, stash,
-                                                                my_draws + 4 * k, my_words + kLanes * k, lane, c)
-                               : compose_unit<true, kOverGpus>(a, t, s, rk.srow(cur), u, false, stash,
-                                                               my_draws + 4 * k, my_words + kLanes * k, lane, c);
+      const double f = changed ? compose_unit<false, kOverGpus>(a, t, s, rk.srow(cur), u, new_first, coins,
+                                                                       my_draws + 4 * k, my_words + kLanes * k, lane, c)
+                               : compose_unit<true, kOverGpus>(a, t, s, rk.srow(cur), u, false, coins,
+                                                                      my_draws + 4 * k, my_words + kLanes * k, lane, c);
       const uint32_t row = rk.frow[u];
-      shared_store(a.genes + static_cast<size_t>(row) * kLanes + lane,
-                   static_cast<int32_t>(c[0] << info_blexp(s.info[lane])));
+      shared_store(a.genes + static_cast<size_t>(row) * kLanes + lane, c[0]);
       if (lane == 0) {
         // (the score kept with the row goes to the point of coherence too: a row is written by
         // different workgroups in different generations, and a plain store could linger in one
@@ -606,7 +607,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
 }
 
 size_t table_lds_bytes(const EvolveArgs &ev) {
-  return (smem_bytes(kLanes, kFusedWaves, ev.term_lds, ev.P + ev.K, ev.stash_stride) + 15) & ~size_t(15);
+  return (smem_bytes(1, kFusedWaves, ev.term_lds, ev.P + ev.K, ev.coin_stride) + 15) & ~size_t(15);
 }
 
 }  // namespace
@@ -634,7 +635,7 @@ hipError_t launch_fused(const FusedArgs &args, hipStream_t stream) {
   if ((fa.ev.P + n_wg * kFusedWaves - 1) / (n_wg * kFusedWaves) > kFusedUnits || (fa.ev.P + n_wg - 1) / n_wg > kMergeMax)
     return hipErrorInvalidValue;
   fa.ev.bk.nb = 0;
-  fa.ev.stash_stride = stash_stride(kLanes, fa.ev.per_gpu != 0);
+  fa.ev.coin_stride = coin_stride(fa.ev.per_gpu != 0);
   fa.ev.term_lds = fa.ev.tab.term_E;                  // 64 job columns: the term table always fits
   fa.table_lds = static_cast<uint32_t>(table_lds_bytes(fa.ev));
   const size_t lds = fa.table_lds + ranks_bytes(fa.ev.P);

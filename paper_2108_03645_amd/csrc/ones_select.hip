@@ -605,17 +605,19 @@ __global__ void splitters_kernel(const double *fit_row, const uint32_t *row_of, 
 }
 
 // What the kernels need of one job slot, derived from the validated raw table.
-struct SlotValues { uint32_t cstart, cmax, info; double abl, cc, d, Y; };
+struct SlotValues { uint32_t start, most, draws, base, info; double abl, cc, d, Y; };
 
 __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j) {
   const uint32_t w = raw.rawinfo[j];
   const int lo = w & 31, hi = (w >> 5) & 31, mu = (w >> 10) & 31;
-  if (!((w >> 15) & 1u)) return SlotValues{0u, 0u, 0u, 0.0, 0.0, 0.0, 0.0};
+  if (!((w >> 15) & 1u)) return SlotValues{0u, 0u, 0u, 0u, 0u, 0.0, 0.0, 0.0, 0.0};
   const int bl = min(mu, hi);                       // log2 of the local batch of a running job
   const int gstart = max(lo, bl);                   // batch a waiting job resumes with
   SlotValues v;
-  v.cstart = 1u << max(0, gstart - mu);
-  v.cmax = 1u << max(0, hi - mu);
+  v.start = static_cast<uint32_t>(max(0, gstart - mu) + 1);
+  v.most = static_cast<uint32_t>(max(0, hi - mu) + 1);
+  v.draws = static_cast<uint32_t>(hi - lo + 2);
+  v.base = static_cast<uint32_t>(lo - mu + 31);     // code of the batch 2^(lo + k - 1): lo + k - mu, kept above 0
   v.info = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo + 2) << 5) | (static_cast<uint32_t>(mu) << 11) |
            (static_cast<uint32_t>(bl) << 16) | (1u << 21) | (((w >> 16) & 1u) << 22);
   v.abl = raw.a[j] * static_cast<double>(1u << bl);
@@ -625,36 +627,34 @@ __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j
   return v;
 }
 
-// A new job table in one launch.  The first table_blocks workgroups derive the per-slot values
-// and the term table (thread q: entry q of the term table; the thread of a slot's code 0 also
-// writes the slot's values); the workgroups behind them set the n_changed slots that changed
-// hands to "waiting" in every genome row (one thread per (row, changed slot), the slots of a
-// row next to each other).
+// A new job table in one launch.  Thread q: entry q of the term table; the thread of a slot's code 0
+// also writes the slot's values, marks the slot in tab.stored if it changed hands (the genomes,
+// stored under another table, hold a gene of its former job: whoever reads one from then on takes
+// it as "waiting"; resetting the genes themselves was a scattered store per row and slot, 80 to 240 us
+// on the stress cluster) and clears the bytes of the rows beyond the job slots.
 constexpr int kTableThreads = 256;
-__global__ __launch_bounds__(kTableThreads) void table_change_kernel(RawJobs raw, JobTable tab, uint32_t Jp,
-                                                                     uint32_t table_blocks, int32_t *genes,
-                                                                     const uint32_t *slots, uint32_t n_changed,
-                                                                     uint32_t rows) {
-  if (blockIdx.x < table_blocks) {
-    const uint32_t q = blockIdx.x * kTableThreads + threadIdx.x;
-    const uint32_t E = tab.term_E;
-    if (q >= Jp * E) return;
-    const uint32_t lane = q % kLanes, e = (q / kLanes) % E, row = q / (kLanes * E);
-    const uint32_t j = row * kLanes + lane;
-    const SlotValues v = derive_slot(raw, j);
-    tab.terms[q] = term_of(v.abl, v.cc, v.d, v.Y, info_blexp(v.info), e);
-    if (e == 0) {
-      tab.cstart[j] = v.cstart; tab.cmax[j] = v.cmax; tab.info[j] = v.info;
-      tab.abl[j] = v.abl; tab.cc[j] = v.cc; tab.d[j] = v.d; tab.Y[j] = v.Y;
-    }
-    return;
-  }
-  const uint32_t n = rows * n_changed;               // at most 1.25 * 2^20 * 2048 < 2^32
-  const uint32_t reset_blocks = gridDim.x - table_blocks;
-  for (uint32_t e = (blockIdx.x - table_blocks) * kTableThreads + threadIdx.x; e < n; e += reset_blocks * kTableThreads) {
-    const uint32_t row = e / n_changed, k = e - row * n_changed;
-    genes[static_cast<size_t>(row) * Jp + slots[k]] = 0;
-  }
+__global__ __launch_bounds__(kTableThreads) void table_change_kernel(RawJobs raw, JobTable tab, uint32_t Jp) {
+  const uint32_t q = blockIdx.x * kTableThreads + threadIdx.x;
+  const uint32_t E = tab.term_E;
+  if (q >= Jp * E) return;
+  const uint32_t lane = q % kLanes, e = (q / kLanes) % E, row = q / (kLanes * E);
+  const uint32_t j = row * kLanes + lane;
+  const SlotValues v = derive_slot(raw, j);
+  tab.terms[q] = term_of(v.abl, v.cc, v.d, v.Y, info_blexp(v.info), e);
+  if (e != 0) return;
+  uint8_t *arrays[4] = {reinterpret_cast<uint8_t *>(tab.start), reinterpret_cast<uint8_t *>(tab.most),
+                        reinterpret_cast<uint8_t *>(tab.draws), reinterpret_cast<uint8_t *>(tab.base)};
+  const uint32_t values[4] = {v.start, v.most, v.draws, v.base};
+  const uint32_t at = gene_byte(j);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) arrays[k][at] = static_cast<uint8_t>(values[k]);
+  if (row == Jp / kLanes - 1)
+    for (uint32_t beyond = at % 4 + 1; beyond < 4; ++beyond)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) arrays[k][at - at % 4 + beyond] = 0;
+  tab.info[j] = v.info;
+  tab.abl[j] = v.abl; tab.cc[j] = v.cc; tab.d[j] = v.d; tab.Y[j] = v.Y;
+  if (tab.stored != tab.info && ((raw.rawinfo[j] >> 17) & 1u)) tab.stored[j] |= kInfoReset;
 }
 
 // Term table: the score formula evaluated once per (slot, GPU-count code), same operations in
@@ -668,13 +668,20 @@ __global__ void build_terms_kernel(JobTable tab, uint32_t Jp) {
   tab.terms[q] = term_of(tab.abl[j], tab.cc[j], tab.d[j], tab.Y[j], info_blexp(tab.info[j]), e);
 }
 
-__global__ void best_kernel(const int32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                            const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
-                            double *fit_out, const uint32_t *err_in, uint32_t *err_out) {
+// Batch size of job slot j in a genome row.
+__device__ __forceinline__ uint32_t stored_batch(const uint32_t *row, const uint32_t *stored, uint32_t j) {
+  const uint32_t w = stored[j];
+  return info_reset(w) ? 0u : batch_of_code(reinterpret_cast<const uint8_t *>(row)[gene_byte(j)], info_blexp(w));
+}
+
+__global__ void best_kernel(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
+                            const uint32_t *stored, const uint32_t *info, uint32_t Jn, uint32_t row_words,
+                            int32_t *batch_out, int32_t *gpus_out, double *fit_out, const uint32_t *err_in,
+                            uint32_t *err_out) {
   const uint32_t best = row_of[sel[0]];
-  const int32_t *row = genes + static_cast<size_t>(best) * Jp;
+  const uint32_t *row = genes + static_cast<size_t>(best) * row_words;
   for (uint32_t j = threadIdx.x; j < Jn; j += blockDim.x) {
-    const uint32_t B = static_cast<uint32_t>(row[j]);
+    const uint32_t B = stored_batch(row, stored, j);
     batch_out[j] = static_cast<int32_t>(B);
     gpus_out[j] = static_cast<int32_t>(B ? max(1u, B >> info_mu(info[j])) : 0u);
   }
@@ -685,25 +692,35 @@ __global__ void best_kernel(const int32_t *genes, const double *fit_row, const u
   }
 }
 
+// The genomes of a run of pool slots as batch sizes, in slot order; one workgroup per slot.
+constexpr int kUnpackThreads = 256;
+__global__ __launch_bounds__(kUnpackThreads) void unpack_kernel(const uint32_t *genes, const uint32_t *row_of,
+                                                                const uint32_t *stored, uint32_t Jp, uint32_t row_words,
+                                                                uint32_t first, int32_t *out) {
+  const uint32_t *row = genes + static_cast<size_t>(row_of[first + blockIdx.x]) * row_words;
+  for (uint32_t j = threadIdx.x; j < Jp; j += kUnpackThreads)
+    out[static_cast<size_t>(blockIdx.x) * Jp + j] = static_cast<int32_t>(stored_batch(row, stored, j));
+}
+
 // The winner unrolled over the GPUs (Eq. 1, reorder): every workgroup scans the jobs' GPU
 // counts in LDS (at most 2048 slots), then each thread finds the job of one GPU by binary
 // search over the prefix sums.
 constexpr int kPlaceThreads = 1024;
-__global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const int32_t *genes, const uint32_t *row_of,
+__global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const uint32_t *genes, const uint32_t *row_of,
                                                                  const int32_t *sel, const uint32_t *info, uint32_t Jn,
-                                                                 uint32_t Jp, uint32_t G, int32_t *slot_of_gpu,
+                                                                 uint32_t row_words, uint32_t G, int32_t *slot_of_gpu,
                                                                  int32_t *batch_of_gpu) {
   __shared__ uint32_t first[2 * kPlaceThreads + 1];    // first GPU of every slot, then the GPUs in use
   __shared__ uint32_t per_gpu[2 * kPlaceThreads];      // local batch of every slot's workers
   __shared__ uint32_t wave_total[kPlaceThreads / kLanes];
-  const int32_t *row = genes + static_cast<size_t>(row_of[sel[0]]) * Jp;
+  const uint32_t *row = genes + static_cast<size_t>(row_of[sel[0]]) * row_words;
   const uint32_t t = threadIdx.x;
   // thread t owns slots 2t and 2t + 1
   uint32_t c[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const uint32_t j = 2 * t + u;
-    const uint32_t B = j < Jn ? static_cast<uint32_t>(row[j]) : 0u;
+    const uint32_t B = j < Jn ? stored_batch(row, info, j) : 0u;
     c[u] = B ? max(1u, B >> info_mu(info[j < Jn ? j : 0])) : 0u;
     per_gpu[j] = B ? B / c[u] : 0u;
   }
@@ -748,14 +765,16 @@ hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, int32_t *genes, const uint32_t *slots,
-                               uint32_t n_changed, uint32_t rows, hipStream_t s) {
-  const uint32_t table_blocks = (Jp * tab.term_E + kTableThreads - 1) / kTableThreads;
-  const uint64_t n = static_cast<uint64_t>(rows) * n_changed;
-  if (n > 0xFFFFFFFFull) return hipErrorInvalidValue;
-  const uint32_t reset_blocks = static_cast<uint32_t>(std::min<uint64_t>((n + kTableThreads - 1) / kTableThreads, 16384));
-  hipLaunchKernelGGL(table_change_kernel, dim3(table_blocks + reset_blocks), dim3(kTableThreads), 0, s, raw, tab, Jp,
-                     table_blocks, genes, slots, n_changed, rows);
+hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, hipStream_t s) {
+  const uint32_t blocks = (Jp * tab.term_E + kTableThreads - 1) / kTableThreads;
+  hipLaunchKernelGGL(table_change_kernel, dim3(blocks), dim3(kTableThreads), 0, s, raw, tab, Jp);
+  return hipGetLastError();
+}
+
+hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const uint32_t *stored, uint32_t Jp, uint32_t first,
+                         uint32_t count, int32_t *out, hipStream_t s) {
+  hipLaunchKernelGGL(unpack_kernel, dim3(count), dim3(kUnpackThreads), 0, s, genes, row_of, stored, Jp,
+                     words_of(Jp / kLanes) * kLanes, first, out);
   return hipGetLastError();
 }
 
@@ -812,20 +831,20 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
   return hipGetLastError();
 }
 
-hipError_t launch_placement(const int32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
+hipError_t launch_placement(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
                             uint32_t Jn, uint32_t Jp, uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu,
                             hipStream_t s) {
   const uint32_t blocks = std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u));
-  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, row_of, sel, info, Jn, Jp, G,
-                     slot_of_gpu, batch_of_gpu);
+  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, row_of, sel, info, Jn,
+                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), G, slot_of_gpu, batch_of_gpu);
   return hipGetLastError();
 }
 
-hipError_t launch_best(const int32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                       const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
-                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s) {
-  hipLaunchKernelGGL(best_kernel, dim3(1), dim3(256), 0, s, genes, fit_row, row_of, sel, info, Jn, Jp, batch_out,
-                     gpus_out, fit_out, err_in, err_out);
+hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
+                       const uint32_t *stored, const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out,
+                       int32_t *gpus_out, double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s) {
+  hipLaunchKernelGGL(best_kernel, dim3(1), dim3(256), 0, s, genes, fit_row, row_of, sel, stored, info, Jn,
+                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), batch_out, gpus_out, fit_out, err_in, err_out);
   return hipGetLastError();
 }
 

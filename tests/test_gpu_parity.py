@@ -1004,3 +1004,47 @@ def test_random_selections_of_larger_pools(ones, ref, block):
             gpu.close(); cpu.close()
     finally:
         ref.set_threads(1)
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(1, 70, 64), (64, 3000, 256), (65, 100000, 64), (193, 20000, 128), (256, 1 << 20, 64),
+                                                (257, 9000, 300), (500, 8192, 64), (1025, 100000, 64), (2048, 1 << 20, 128)])
+def test_gpu_counts_and_tables_between_generations(ones, ref, n_slots, n_gpus, pop):
+    """Genes are stored as codes of the GPU count under the job table of their generation.  Jobs of at
+    most 64 GPUs (the largest that is counted by a byte look-up), of 128 (the smallest that is not) and
+    of up to 2^20, one table after the other, two or three tables between generations: slots change
+    hands once and twice, empty and fill again, batch limits move past the stored genes.  The state
+    is compared after every table and after every generation; every fourth row count at its edges."""
+    rng = np.random.default_rng(n_slots)
+
+    def table(widest, jobs=None):
+        new = random_jobs(rng, n_slots, inactive_frac=0.15)
+        wide = rng.integers(0, widest + 1, n_slots)                # log2 of the most GPUs of each job
+        mu = rng.integers(0, 31 - wide)
+        new.gpu_max_batch = (1 << mu).astype(np.int32)
+        new.bmax = (1 << (mu + wide)).astype(np.int32)
+        new.bmin = (1 << rng.integers(0, mu + wide + 1)).astype(np.int32)
+        if jobs is not None:
+            new.job_id = np.where(rng.random(n_slots) < 0.3, jobs.job_id + 1000, jobs.job_id)
+        return new
+
+    jobs = table(6)
+    gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=n_slots, theta=0.3), jobs) for make in (ones.Search, ref.RefSearch))
+    over_gpus = n_gpus <= 8192
+    for step, widest in enumerate((6, 7, 20, 6)):
+        tag = f"codes slots={n_slots} G={n_gpus} P={pop} step={step} widest=2^{widest}"
+        say(f"[parity] {tag}")
+        for _ in range(1 + step % 3):
+            jobs = table(widest, jobs)
+            for s in (gpu, cpu):
+                s.set_jobs(jobs)
+            assert_same_state(gpu, cpu, tag + " new table")
+            assert gpu.best()[0].tolist() == cpu.best()[0].tolist(), tag
+        for s in (gpu, cpu):
+            s.set_new_jobs_first(step % 2 == 1)
+            s.set_crossover(per_gpu=over_gpus and step == 3)
+        for gens in (1, 1, 3):
+            for s in (gpu, cpu):
+                s.generation(gens)
+            assert_same_state(gpu, cpu, tag)
+        assert all(np.array_equal(x, y) for x, y in zip(gpu.placement(), cpu.placement())), tag
+    gpu.close(); cpu.close()
