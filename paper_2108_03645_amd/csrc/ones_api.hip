@@ -76,7 +76,7 @@ struct ScratchLayout {
 };
 
 struct Layout {
-  size_t genes, fit_row, slot_score, row_of[2], parent_row[2], occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
+  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
   size_t unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
@@ -136,8 +136,8 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   L.genes = take(rows * row_bytes);
   L.fit_row = take(rows * 8);
   L.slot_score = take(static_cast<size_t>(P) * 8);
-  L.row_of[0] = take(static_cast<size_t>(P) * 4);
-  L.row_of[1] = take(static_cast<size_t>(P) * 4);
+  L.row_of = take(static_cast<size_t>(P) * 4);
+  L.spare = take(static_cast<size_t>(P / 4) * 4);
   L.parent_row[0] = take(static_cast<size_t>(P / 4) * 4);
   L.parent_row[1] = take(static_cast<size_t>(P / 4) * 4);
   L.occupied[0] = take((rows + 31) / 32 * 4);     // bitmaps of the rows the survivors keep
@@ -255,7 +255,9 @@ struct ones_ctx {
   char *stage;                // pinned host staging buffer (stage_bytes), free between calls
   char *stage_dev;            // the same buffer as the device addresses it (ones_best's kernel writes the winner there)
   Layout L;
-  int cur;                    // which row_of array describes the current generation
+  int cur;                    // the survivors of the current generation are in parent_row[cur ^ 1]
+  int occ;                    // which bitmap holds the survivors' rows, unless
+  bool rows_assigned;         // row_of and spare hold the rows of the next generation's slots
   int info_now, info_stored;  // which info array belongs to the job table, and to the one the genomes are stored under
   bool table_changed;         // job table replaced since the current generation was computed
   bool no_schedule;           // ... by ones_set_jobs: the winner is not a schedule under the new table
@@ -340,15 +342,14 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   EvolveArgs a;
   const ScratchLayout &S = c->L.S;
   auto sc = [&](size_t off) { return scratch + off; };
-  // generation 0 fills row_of[cur]; later generations complete the array whose first K entries
-  // the last selection wrote
   const int next = t == 0 ? c->cur : c->cur ^ 1;
   a.genes = c->at<uint32_t>(c->L.genes);
   a.fit_row = c->at<double>(c->L.fit_row);
   a.parent_row = c->at<uint32_t>(c->L.parent_row[next]);
-  a.row_of = c->at<uint32_t>(c->L.row_of[next]);
-  a.occupied = c->at<uint32_t>(c->L.occupied[c->cur]);          // set by the last selection
-  a.occupied_other = c->at<uint32_t>(c->L.occupied[c->cur ^ 1]);
+  a.row_of = c->at<uint32_t>(c->L.row_of);
+  a.spare = c->at<uint32_t>(c->L.spare);
+  a.occupied = c->at<uint32_t>(c->L.occupied[c->occ]);          // set by the last selection, unless it assigned the rows
+  a.assigned = c->rows_assigned ? 1u : 0u;
   // Under probability sampling this generation is scored with its own place of the ring of
   // remaining-work arrays and term tables: a launch of an earlier generation has filled it
   // already, or the draws of this and the next generations are made now.
@@ -371,6 +372,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
   // quantile buckets: only when the survivors reappear with the scores they had
   const bool buckets = same_table && !sampled && c->bp.nb != 0 && splitters_valid;
+  a.occupied_other = buckets ? nullptr : c->at<uint32_t>(c->L.occupied[c->occ ^ 1]);
   a.bk.nb = buckets ? c->bp.nb : 0;
   a.bk.seg = c->bp.seg;
   a.bk.split = a.bk.split_next = reinterpret_cast<uint64_t *>(sc(S.split));
@@ -382,12 +384,12 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.bk.spill_idx = reinterpret_cast<uint32_t *>(sc(S.sidx));
   a.bk.spill_bucket = reinterpret_cast<uint32_t *>(sc(S.sbucket));
   a.bk.split_slot = reinterpret_cast<uint32_t *>(sc(S.split_slot));
-  // the selection notes the rows the survivors keep: parents and first K slots of the next pool
+  // the selection notes the rows the survivors keep, the next generation's parents
   RowPlan rp;
-  rp.row_of_cur = a.row_of;
+  rp.row_of = a.row_of;
+  rp.parents = a.parent_row;
   rp.parent_next = c->at<uint32_t>(c->L.parent_row[next ^ 1]);
-  rp.row_of_next = c->at<uint32_t>(c->L.row_of[next ^ 1]);
-  rp.occupied = c->at<uint32_t>(c->L.occupied[next]);
+  rp.occupied = a.occupied_other;
   int rc;
   const Progress pr{c->at<double>(c->L.alpha), c->at<double>(c->L.beta), c->at<double>(c->L.processed)};
   if (sampled && !(c->drawn_from <= static_cast<int64_t>(t) && static_cast<int64_t>(t) < c->drawn_to)) {
@@ -403,7 +405,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
   if (events && (rc = timed(c, c->select_ev, c->select_used, true))) return rc;
   if (buckets) {
-    HIP_TRY(launch_bucket_select(a.fit_row, a.parent_row, a.bk, rp, c->K,
+    HIP_TRY(launch_bucket_select(a.fit_row, a.bk, rp, c->K,
                                  reinterpret_cast<uint32_t *>(sc(S.bcount[c->bucket_phase ^ 1])),
                                  c->at<int32_t>(c->L.sel), c->stream));
     c->bucket_phase ^= 1;
@@ -433,6 +435,8 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   }
   if (events && (rc = timed(c, c->select_ev, c->select_used, false))) return rc;
   c->cur = next;
+  c->rows_assigned = buckets;
+  if (!buckets) c->occ ^= 1;
   c->y_cur = y_this;
   c->info_stored = c->info_now;     // every genome of the new pool was made under the current table
   c->table_changed = false;
@@ -492,6 +496,8 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     c->stage_dev = static_cast<char *>(mapped);
   }
   c->cur = 0; c->t = 0;
+  c->occ = 0;
+  c->rows_assigned = false;
   c->info_now = c->info_stored = 0;
   c->table_changed = false;
   c->no_schedule = false;
@@ -647,7 +653,8 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   EvolveArgs &a = fa.ev;
   a.genes = c->at<uint32_t>(c->L.genes);
   a.fit_row = c->at<double>(c->L.fit_row);
-  a.parent_row = nullptr; a.row_of = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
+  a.parent_row = nullptr; a.row_of = nullptr; a.spare = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
+  a.assigned = 0;
   a.slot_score = nullptr;                              // no selection kernel follows
   a.tab = c->table();
   a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
@@ -664,9 +671,8 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   a.bk = BucketArgs{};
   const int next = c->cur ^ 1;
   fa.parent_rows = c->at<uint32_t>(c->L.parent_row[next]);
-  fa.row_of_next = c->at<uint32_t>(c->L.row_of[next]);
-  fa.row_of_cur = c->at<uint32_t>(c->L.row_of[c->cur]);
-  fa.occupied = c->at<uint32_t>(c->L.occupied[c->cur]);
+  fa.row_of = c->at<uint32_t>(c->L.row_of);
+  fa.occupied = c->at<uint32_t>(c->L.occupied[c->occ]);
   fa.sel = c->at<int32_t>(c->L.sel);
   fa.xkeys = c->at<uint64_t>(c->L.xkeys);
   fa.xsurv = fa.xkeys + static_cast<size_t>(2) * c->P;
@@ -693,6 +699,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
     c->fused_draws += n;
     c->drawn_from = c->drawn_to = 0;   // the ring may hold tables this launch wrote over (y_out); the two-launch path draws again
   }
+  c->rows_assigned = false;
   c->info_stored = c->info_now;
   c->table_changed = false;
   c->no_schedule = false;
@@ -763,6 +770,9 @@ static int check_waits(ones_ctx *c) {
   return words[1] ? row_fault(c) : ONES_OK;
 }
 
+// Rows of the current generation's survivors, best first.
+static const uint32_t *survivor_rows(const ones_ctx *c) { return c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]); }
+
 static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double *fitness_out) {
   if (!c) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
@@ -771,8 +781,8 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
   // one launch and one wait, no copy.
   const Layout &L = c->L;
   auto mapped = [&](size_t off) { return c->stage_dev + (off - L.best_batch); };
-  HIP_TRY(launch_best(c->at<uint32_t>(c->L.genes), c->at<double>(c->L.fit_row), c->at<uint32_t>(c->L.row_of[c->cur]),
-                      c->at<int32_t>(c->L.sel), c->at<uint32_t>(L.info[c->info_stored]),
+  HIP_TRY(launch_best(c->at<uint32_t>(c->L.genes), c->at<double>(c->L.fit_row), survivor_rows(c),
+                      c->at<uint32_t>(L.info[c->info_stored]),
                       c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, reinterpret_cast<int32_t *>(mapped(L.best_batch)),
                       reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
                       reinterpret_cast<double *>(mapped(L.best_fit)), c->at<uint32_t>(c->L.fsync) + 1,
@@ -793,8 +803,7 @@ static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_g
   if (!c || c->no_schedule) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
   const size_t n4 = static_cast<size_t>(c->G) * 4;
-  HIP_TRY(launch_placement(c->at<uint32_t>(c->L.genes), c->at<uint32_t>(c->L.row_of[c->cur]), c->at<int32_t>(c->L.sel),
-                           c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->G, c->at<int32_t>(c->L.place_slot),
+  HIP_TRY(launch_placement(c->at<uint32_t>(c->L.genes), survivor_rows(c), c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->G, c->at<int32_t>(c->L.place_slot),
                            c->at<int32_t>(c->L.place_batch), c->stream));
   const Layout &L = c->L;
   if (c->G)
@@ -815,26 +824,33 @@ static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, i
   // candidates live in physical rows, their genes as codes: the genomes are unpacked on the device,
   // a run of pool slots at a time, the scores put in slot order on the host
   const size_t rows = static_cast<size_t>(c->P) + c->K;
-  const uint32_t *row_of = c->at<uint32_t>(c->L.row_of[c->cur]);
+  const uint32_t *row_of = c->at<uint32_t>(c->L.row_of);
   if (genes) {
     const uint32_t most = unpack_slots(c->P, c->Jp);
     for (uint32_t first = 0; first < c->P; first += most) {
       const uint32_t count = std::min(most, c->P - first);
-      HIP_TRY(launch_unpack(c->at<uint32_t>(c->L.genes), row_of, c->at<uint32_t>(c->L.info[c->info_stored]), c->Jp, first,
-                            count, c->at<int32_t>(c->L.unpacked), c->stream));
+      HIP_TRY(launch_unpack(c->at<uint32_t>(c->L.genes), row_of, c->at<int32_t>(c->L.sel), survivor_rows(c), c->K,
+                            c->at<uint32_t>(c->L.info[c->info_stored]), c->Jp, first, count,
+                            c->at<int32_t>(c->L.unpacked), c->stream));
       HIP_TRY(hipMemcpyAsync(genes + static_cast<size_t>(first) * c->Jp, c->ws + c->L.unpacked,
                              static_cast<size_t>(count) * c->Jp * 4, hipMemcpyDeviceToHost, c->stream));
       HIP_TRY(hipStreamSynchronize(c->stream));
     }
   }
-  if (fit) {
-    std::vector<uint32_t> row(c->P);
-    std::vector<double> f(rows);
-    HIP_TRY(hipMemcpy(row.data(), row_of, static_cast<size_t>(c->P) * 4, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(f.data(), c->ws + c->L.fit_row, rows * 8, hipMemcpyDeviceToHost));
-    for (uint32_t p = 0; p < c->P; ++p) fit[p] = f[row[p]];
+  if (fit || sel) {
+    std::vector<int32_t> best(c->K);
+    HIP_TRY(hipMemcpy(best.data(), c->ws + c->L.sel, static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
+    if (fit) {
+      std::vector<uint32_t> row(c->P), parents(c->K);
+      std::vector<double> f(rows);
+      HIP_TRY(hipMemcpy(row.data(), row_of, static_cast<size_t>(c->P) * 4, hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(parents.data(), survivor_rows(c), static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(f.data(), c->ws + c->L.fit_row, rows * 8, hipMemcpyDeviceToHost));
+      for (uint32_t p = 0; p < c->P; ++p) fit[p] = f[row[p]];
+      for (uint32_t g = 0; g < c->K; ++g) fit[best[g]] = f[parents[g]];   // their slots may have been handed other rows
+    }
+    if (sel) memcpy(sel, best.data(), static_cast<size_t>(c->K) * 4);
   }
-  if (sel) HIP_TRY(hipMemcpy(sel, c->ws + c->L.sel, static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
   if (generation) *generation = c->t;
   return ONES_OK;
 }

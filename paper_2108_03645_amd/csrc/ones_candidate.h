@@ -236,22 +236,51 @@ constexpr uint32_t kBias = 31;
 // Stages the job table into LDS, the work dealt to the `threads` threads (whole waves) that call it
 // with tid = 0 .. threads - 1.  R: rows of job slots (at most 4Q).  changed: genes are stored under
 // another table (tab.stored).  No barrier at the end: the caller places one before the first use.
-constexpr int kStageBatch = 3;
+// What a workgroup stages comes from memory in one or two trips: every thread issues all its loads,
+// up to kStageBatch of a kind, before the first LDS store waits for one.  (In loops of one load and
+// one store each a pool of 8192 spent 4.5 of its workgroups' 9 us here.)
+constexpr int kStageBatch = 4;
 template <int Q>
 __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, uint32_t E, bool changed, uint32_t tid,
                                             uint32_t threads) {
   const JobTable &tab = a.tab;
   const uint32_t R = a.Jp / kLanes;
   constexpr uint32_t kWords = Q * kLanes;
-  if (a.bk.nb != 0) {
-    for (uint32_t q = tid; q <= kMaxBuckets; q += threads)
-      s.split[q] = q < kMaxBuckets ? a.bk.split[q] : *a.bk.thresh;
-  }
+  const uint32_t l = tid % kLanes, tiles = E * 4 * Q, tile_step = threads / kLanes;
+  const uint32_t splits = a.bk.nb != 0 ? kMaxBuckets + 1 : 0u;
+  uint64_t split[kStageBatch];
+  double term[kStageBatch];
+  // the term table: global memory holds it row-major ([row][code][lane]); here the code is the slowest
+  // index, so that a row's part of the LDS address is a compile-time offset (tiles of 64 entries)
+  auto load_splits = [&](uint32_t from) {
+#pragma unroll
+    for (int u = 0; u < kStageBatch; ++u) {
+      const uint32_t q = from + u * threads;
+      if (q < splits) split[u] = q < kMaxBuckets ? a.bk.split[q] : *a.bk.thresh;
+    }
+  };
+  auto load_terms = [&](uint32_t from) {
+#pragma unroll
+    for (int u = 0; u < kStageBatch; ++u) {
+      const uint32_t tile = from + u * tile_step, e = tile / (4 * Q), row = tile % (4 * Q);
+      term[u] = 0.0;
+      if (tile < tiles && row < R) term[u] = tab.terms[(row * E + e) * kLanes + l];
+    }
+  };
+  auto store_splits = [&](uint32_t from) {
+#pragma unroll
+    for (int u = 0; u < kStageBatch; ++u)
+      if (from + u * threads < splits) s.split[from + u * threads] = split[u];
+  };
+  auto store_terms = [&](uint32_t from) {
+#pragma unroll
+    for (int u = 0; u < kStageBatch; ++u)
+      if (from + u * tile_step < tiles) s.terms[(from + u * tile_step) * kLanes + l] = term[u];
+  };
+  load_splits(tid);
+  load_terms(tid / kLanes);
   for (uint32_t w = tid; w < kWords; w += threads) {
-    s.start[w] = tab.start[w];
-    s.most[w] = tab.most[w];
-    s.draws[w] = tab.draws[w];
-    s.base[w] = tab.base[w];
+    const uint32_t start = tab.start[w], most = tab.most[w], draws = tab.draws[w], base = tab.base[w];
     s.prefix[w] = philox_prefix(w, a.key1);
     if (changed || E == 0) {
       uint32_t shift = 0, fresh = 0, bl = 0;
@@ -269,7 +298,15 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
       s.fresh[w] = fresh;
       s.bl[w] = bl;
     }
+    s.start[w] = start;
+    s.most[w] = most;
+    s.draws[w] = draws;
+    s.base[w] = base;
   }
+  store_splits(tid);
+  store_terms(tid / kLanes);
+  for (uint32_t q = tid + kStageBatch * threads; q < splits; q += kStageBatch * threads) { load_splits(q); store_splits(q); }
+  for (uint32_t t = tid / kLanes + kStageBatch * tile_step; t < tiles; t += kStageBatch * tile_step) { load_terms(t); store_terms(t); }
   if (E == 0) {
     for (uint32_t j = tid; j < 4 * kWords; j += threads) {
       const bool real = j < a.Jp;
@@ -277,25 +314,6 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
       s.cc[j] = real ? tab.cc[j] : 0.0;
       s.d[j] = real ? tab.d[j] : 0.0;
       s.Y[j] = real ? tab.Y[j] : 0.0;
-    }
-  } else {
-    // global memory holds the table row-major ([row][code][lane]); here the code is the slowest
-    // index, so that a row's part of the LDS address is a compile-time offset (tiles of 64 entries;
-    // a batch of loads in flight per wave before the first LDS store waits for one)
-    for (uint32_t first = tid / kLanes; first < E * 4 * Q; first += kStageBatch * (threads / kLanes)) {
-      const uint32_t l = tid % kLanes;
-      double v[kStageBatch];
-#pragma unroll
-      for (int u = 0; u < kStageBatch; ++u) {
-        const uint32_t tile = first + u * (threads / kLanes), e = tile / (4 * Q), row = tile % (4 * Q);
-        v[u] = 0.0;
-        if (tile < E * 4 * Q && row < R) v[u] = tab.terms[(row * E + e) * kLanes + l];
-      }
-#pragma unroll
-      for (int u = 0; u < kStageBatch; ++u) {
-        const uint32_t tile = first + u * (threads / kLanes);
-        if (tile < E * 4 * Q) s.terms[tile * kLanes + l] = v[u];
-      }
     }
   }
 }
@@ -345,7 +363,7 @@ __device__ __forceinline__ IndexLoads index_free_rows_begin(const EvolveArgs &a,
   return ld;
 }
 
-// Also clears this workgroup's share of the other bitmap.  Ends with a barrier.
+// Ends with a barrier.
 __device__ __forceinline__ void index_free_rows_end(const EvolveArgs &a, const Smem &s, const IndexLoads &ld, int lane) {
   const uint32_t rows = a.P + a.K, words = (rows + 31) / 32;
   const uint32_t groups = (words + kRowGroupWords - 1) / kRowGroupWords;
@@ -359,8 +377,6 @@ __device__ __forceinline__ void index_free_rows_end(const EvolveArgs &a, const S
     const uint32_t n = wave_sum(__popc(free_bits(a.occupied, g * kRowGroupWords + lane, rows)));
     if (lane == 0) s.free_in_group[g] = n;
   }
-  for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < words; w += gridDim.x * blockDim.x)
-    a.occupied_other[w] = 0;
   __syncthreads();
 }
 
@@ -414,8 +430,8 @@ __device__ __forceinline__ KernelArgs *kernel_args() {
 
 // A row index is kept inside the genome array whatever the free-row list holds, so that a mistake
 // in it cannot turn into a stray access; but such a mistake must not pass unnoticed either.
-// Every entry of a round's list passes through checked_row once, when the kernel records the
-// rows of the round's slots: a clamp that changes a value is noted in LDS (s.next_item[1]) and
+// Every entry of a round's list passes through checked_row once, when the kernel takes or records
+// the rows of the round's slots: a clamp that changes a value is noted in LDS (s.next_item[1]) and
 // the workgroup raises the context's fault word, which ones_export reports, when it ends.
 __device__ __forceinline__ uint32_t checked_row(const Smem &s, uint32_t row, uint32_t n_rows) {
   if (row >= n_rows) s.next_item[1] = 1;

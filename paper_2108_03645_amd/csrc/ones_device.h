@@ -114,18 +114,26 @@ struct Progress {
 constexpr int kDrawRing = 8;
 
 // Genomes live in physical rows; a candidate keeps its row for as long as it survives, so a
-// survivor is never copied.  The pool of P slots uses P + K rows, K of them held by the
-// survivors (the selection marks them in a bitmap).  Of the P free rows in ascending order,
-// slot K + q of the new pool takes the q-th; a survivor that must be refreshed after a table
-// change (rank p) takes the (3K + p)-th.  The evolve kernel looks its rows up in the bitmap.
+// survivor is never copied.  The pool of P slots uses P + K rows.  While a generation is computed
+// the K survivors hold theirs (parent_row); 3K rows are for the new children and mutants, by slot
+// (row_of), and K are spare: a survivor that must be refreshed after a table change goes to the
+// spare row of its rank, and its old one is the next spare.
+// Which rows the 3K slots get:
+// - After a bucketed selection nearly all of them keep the row that their slot had, whose candidate
+//   dropped out.  A child that survived keeps it instead; as many survivors dropped out at the end
+//   of the ranking, and the selection hands the row of the last but i to the slot of the i-th best
+//   surviving child.  row_of and spare hold everything (assigned).
+// - After any other selection a bitmap holds the survivors' rows, and the evolve kernel looks the free
+//   ones up in ascending order: the slot K + q takes the q-th, the last K are spare.
 struct EvolveArgs {
   uint32_t       *genes;      // [P + K][Q * 64] genome rows
   double         *fit_row;    // [P + K] score of the genome in each row
   const uint32_t *parent_row; // [K] rows of the survivors, best first
-  uint32_t       *row_of;     // [P] row of every slot of the new pool: entries [0,K) prefilled
-                              //     (survivors keep their rows), the others written here
-  const uint32_t *occupied;   // bitmap over the P + K rows: the survivors' rows
-  uint32_t       *occupied_other;  // the other bitmap, cleared here for the coming selection
+  uint32_t       *row_of;     // [P] row of every slot of the new pool
+  uint32_t       *spare;      // [K] rows no slot uses
+  const uint32_t *occupied;   // bitmap over the P + K rows: the survivors' rows (unless assigned)
+  uint32_t       *occupied_other;  // the other bitmap, cleared here for the coming selection (null: it uses none)
+  uint32_t       assigned;    // row_of and spare hold the rows of the slots to fill
   JobTable       tab;
   uint32_t       G, P, K, Jp;
   uint32_t       key0, key1;  // seed
@@ -154,9 +162,8 @@ constexpr uint32_t kFusedMaxPool = 2048;
 struct FusedArgs {
   EvolveArgs ev;
   uint32_t *parent_rows;    // [K] in: rows of the survivors, best first; out: of the new survivors
-  uint32_t *row_of_next;    // [P] out, entries [0,K): the same rows (the next pool's first K slots)
-  uint32_t *row_of_cur;     // [P] out: row of every slot of the last generation's pool
-  uint32_t *occupied;       // bitmap over the P + K rows, in: the survivors' rows; out likewise
+  uint32_t *row_of;         // [P] out: row of every slot of the last generation's pool
+  uint32_t *occupied;       // out: bitmap over the P + K rows, the survivors' rows
   int32_t  *sel;            // [K] out: survivor slots of the last generation's pool, best first
   // exchange between the workgroups, zeroed when the context is created, then only written by these launches:
   uint64_t *xkeys;          // [2][P] tagged score bits of the children by pool slot, a buffer per generation parity
@@ -185,10 +192,10 @@ hipError_t launch_fused(const FusedArgs &fa, hipStream_t s);
 
 // What a selection records besides the survivor list: the survivors keep their rows.
 struct RowPlan {
-  const uint32_t *row_of_cur;   // [P] row of every slot of the pool being ranked
+  uint32_t       *row_of;       // [P] row of every slot of the pool being ranked
+  const uint32_t *parents;      // [K] rows of the survivors of the selection before (bucketed selection)
   uint32_t       *parent_next;  // [K] rows of the new survivors, best first
-  uint32_t       *row_of_next;  // [P] rows of the next pool; entries [0,K) are written here
-  uint32_t       *occupied;     // bitmap over the P + K rows, zero on entry; survivors' rows get set
+  uint32_t       *occupied;     // bitmap over the P + K rows, zero on entry; survivors' rows get set (general selection)
 };
 
 // T_j c_j of a job at GPU-count code e (0 = waiting, e = 1 + log2 of the GPU count): Eq. 3
@@ -241,23 +248,22 @@ inline bool wide_table(const JobTable &tab) { return tab.term_E > 8; }
 hipError_t launch_select(const double *fit_row, const double *slot_score, const RowPlan &rp, uint32_t P, uint32_t K,
                          const BucketArgs &store, int32_t *sel, hipStream_t s);
 hipError_t launch_zero_words(uint32_t *words, uint32_t n, hipStream_t s);
-hipError_t launch_bucket_select(const double *fit_row, const uint32_t *parent_row, const BucketArgs &bk,
-                                const RowPlan &rp, uint32_t K, uint32_t *count_next, int32_t *sel, hipStream_t s);
+hipError_t launch_bucket_select(const double *fit_row, const BucketArgs &bk, const RowPlan &rp, uint32_t K,
+                                uint32_t *count_next, int32_t *sel, hipStream_t s);
 hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const int32_t *sel, uint32_t K,
                             uint32_t nb, uint64_t *split, uint64_t *thresh, uint32_t *count0, uint32_t *count1,
                             hipStream_t s);
 // Eq. 1 for the winner: GPU i runs slot slot_of_gpu[i] (-1 = idle) with batch_of_gpu[i] samples;
-// jobs in slot order on consecutive GPUs.  G entries each.
-hipError_t launch_placement(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
-                            uint32_t Jn, uint32_t Jp, uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu,
-                            hipStream_t s);
+// jobs in slot order on consecutive GPUs.  G entries each.  best: row of the winner.
+hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
+                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, hipStream_t s);
 // stored: info of the table the genomes are stored under, info: of the table in force.
-hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                       const uint32_t *stored, const uint32_t *info,
-                       uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out, double *fit_out,
-                       const uint32_t *err_in, uint32_t *err_out, hipStream_t s);
-// Batch sizes of the pool slots [first, first + count), in slot order: out[count][Jp].
-hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const uint32_t *stored, uint32_t Jp, uint32_t first,
-                         uint32_t count, int32_t *out, hipStream_t s);
+hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *best, const uint32_t *stored,
+                       const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
+                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s);
+// Batch sizes of the pool slots [first, first + count), in slot order: out[count][Jp].  The rows of the
+// survivors, slot sel[g] in row parents[g], go by parents, those of the other slots by row_of.
+hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *parents, uint32_t K,
+                         const uint32_t *stored, uint32_t Jp, uint32_t first, uint32_t count, int32_t *out, hipStream_t s);
 
 }  // namespace ones

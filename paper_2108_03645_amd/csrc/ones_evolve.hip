@@ -6,9 +6,9 @@
 // uniform crossover, uniform mutation), repairs it to the cluster capacity (refresh + fill
 // under Eq. 4), scores it (Eq. 3 with T = Y/X, Eq. 5) and writes genome and score.
 //
-// Workgroups are persistent: each owns a contiguous share of the work; two or three of its waves
-// list the free genome rows the share will fill while the others stage the job table in LDS;
-// then all waves take the share's items one by one from an LDS counter and never wait for each other.
+// Workgroups are persistent: each owns a contiguous share of the work and stages the job table, the
+// draws and the rows of the slots it will fill in LDS; then its waves take the share's items one by
+// one from an LDS counter and never wait for each other.
 #include "ones_candidate.h"
 
 #ifndef ONES_ROW_GROUP
@@ -21,7 +21,7 @@ namespace {
 constexpr int kGroupFirst = 2 * ONES_ROW_GROUP + 1;   // words per lane kGroupFirst, kGroupFirst + 1
 
 // ----------------------------------------------------------------- kernels ---------
-template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : (Q > 1 ? 8 : 4); };
+template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : 8; };
 
 template <int Q, bool kWide, bool kArrivals>
 __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t lr, uint32_t ir,
@@ -91,53 +91,73 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride);
   const int lane0 = threadIdx.x & (kLanes - 1);
-  const IndexLoads index_loads = index_free_rows_begin(a, lane0);
   if (threadIdx.x == 0) s.next_item[1] = 0;          // no row index has been out of range (checked_row)
-  index_free_rows_end(a, s, index_loads, lane0);
+  const bool assigned = a.assigned != 0;
+  if (!assigned) {
+    const IndexLoads index_loads = index_free_rows_begin(a, lane0);
+    index_free_rows_end(a, s, index_loads, lane0);
+  }
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t K = a.K;
   uint64_t *coins = reinterpret_cast<uint64_t *>(s.coins + static_cast<size_t>(wave_in_block) * a.coin_stride);
   // This workgroup's share of the ranks 0..K-1: for each rank a pair, a mutant and, after a
-  // table change, a survivor.  Slot K + q of the new pool takes the q-th free row and the
-  // refreshed survivor of rank e the (3K + e)-th, so every share needs three runs of
-  // consecutive free rows, which one wave each lists into LDS, a round of kRound ranks at a time.
+  // table change, a survivor, a round of kRound ranks at a time.  The rows the round fills are read
+  // where the selection has assigned them; otherwise the slots K + 2 ra .., 3K + ra .. and the ranks
+  // ra .. take three runs of consecutive free rows, which one wave each lists into LDS while the
+  // others stage the job table and make the slots' draws, a lane per slot (a wave that drew for its
+  // own item spent a tenth of its time on a Philox block per slot with the same numbers in all lanes).
   const uint32_t first = static_cast<uint32_t>(static_cast<uint64_t>(K) * blockIdx.x / gridDim.x);
   const uint32_t last = static_cast<uint32_t>(static_cast<uint64_t>(K) * (blockIdx.x + 1) / gridDim.x);
-  // The first round's rows are listed while the other waves stage the job table and make the slots'
-  // draws, a lane per slot (a wave that drew for its own item spent a tenth of its time on a Philox
-  // block per slot with the same numbers in all lanes).
-  constexpr uint32_t kListing = (kSameTable ? 2 : 3) * kLanes;
-  constexpr uint32_t kKinds = kSameTable ? 3 : 4;               // slots filled per rank
-  auto slot_at = [&](uint32_t ra, uint32_t n, uint32_t i) {     // the i-th slot of a round
+  const uint32_t listing = assigned ? 0u : 3u * kLanes;          // threads that only list
+  constexpr uint32_t kDrawn = kSameTable ? 3 : 4;                // slots per rank that are drawn for
+  auto slot_at = [&](uint32_t ra, uint32_t n, uint32_t i) {      // the i-th slot of a round
     return i < 2 * n ? K + 2 * ra + i : i < 3 * n ? 3 * K + ra + (i - 2 * n) : ra + (i - 3 * n);
   };
-  auto list_round = [&](uint32_t ra, uint32_t n) {
-    if (wave_in_block == 0) list_free_rows(a, s, 2 * ra, 2 * n, s.rows, lane0);
-    if (wave_in_block == 1) list_free_rows(a, s, 2 * K + ra, n, s.rows + 2 * n, lane0);
-    if (!kSameTable && wave_in_block == 2) list_free_rows(a, s, 3 * K + ra, n, s.rows + 3 * n, lane0);
-    if (threadIdx.x >= kListing) {
-      const uint32_t R = a.Jp / kLanes;
-      for (uint32_t i = threadIdx.x - kListing; i < kKinds * n; i += blockDim.x - kListing) {
-        const uint32_t p = slot_at(ra, n, i);
+  auto prepare_round = [&](uint32_t ra, uint32_t n) {
+    if (threadIdx.x < listing) {
+      if (wave_in_block == 0) list_free_rows(a, s, 2 * ra, 2 * n, s.rows, lane0);
+      if (wave_in_block == 1) list_free_rows(a, s, 2 * K + ra, n, s.rows + 2 * n, lane0);
+      if (wave_in_block == 2) list_free_rows(a, s, 3 * K + ra, n, s.rows + 3 * n, lane0);
+      return;
+    }
+    const uint32_t R = a.Jp / kLanes;
+    for (uint32_t i = threadIdx.x - listing; i < 4 * n; i += blockDim.x - listing) {
+      const uint32_t p = slot_at(ra, n, i);
+      uint32_t row = 0;
+      if (assigned) row = i < 3 * n ? a.row_of[p] : a.spare[p];
+      if (i < kDrawn * n) {
         Draw d = candidate_draw(a, a.t, p);
         if (p < K) d.ra = d.rb = p;                              // a survivor is its own parent
         s.drawn[i] = pack_draw(min(a.parent_row[d.ra], a.P + K - 1), min(a.parent_row[d.rb], a.P + K - 1), d.r, R);
       }
+      if (assigned) s.rows[i] = checked_row(s, row, a.P + K);
     }
   };
-  if (first < last) list_round(first, min(kRound, last - first));
-  if (threadIdx.x >= kListing)
-    stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - kListing, blockDim.x - kListing);
+  if (first < last) prepare_round(first, min(kRound, last - first));
+  if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing);
+  if (a.occupied_other != nullptr)
+    for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < (a.P + K + 31) / 32; w += gridDim.x * blockDim.x)
+      a.occupied_other[w] = 0;
   for (uint32_t ra = first; ra < last; ra += kRound) {
   const uint32_t n = min(kRound, last - ra);
   if (ra != first) {
     __syncthreads();                                 // the previous round's rows have been used
-    list_round(ra, n);
+    prepare_round(ra, n);
   }
   if (threadIdx.x == blockDim.x - 1) *s.next_item = 0;
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kKinds * n; i += blockDim.x)
-    a.row_of[slot_at(ra, n, i)] = checked_row(s, s.rows[i], a.P + a.K);
+  // record what the slots and ranks got
+  for (uint32_t i = threadIdx.x; i < 4 * n; i += blockDim.x) {
+    const uint32_t p = slot_at(ra, n, i);
+    if (i < 3 * n) {
+      if (!assigned) a.row_of[p] = checked_row(s, s.rows[i], a.P + K);
+    } else {
+      const uint32_t row = checked_row(s, s.rows[i], a.P + K), old = a.parent_row[p];
+      a.row_of[p] = kSameTable ? old : row;
+      if (!kSameTable) a.spare[p] = old;
+      else if (!assigned) a.spare[p] = row;
+    }
+  }
   const uint32_t kinds = (!kSameTable || a.rescore) ? 3u : 2u;
   // The waves take the items one by one (the pairs first: they take twice as long), so that a
   // wave whose items needed many fill rounds does not hold the others up at the end.

@@ -132,15 +132,13 @@ __device__ __forceinline__ Ranks carve_ranks(unsigned char *base, uint32_t P) {
 }
 
 // The survivors' rows (rows[0..K)) as a bitmap, and from it the free rows in ascending order.
-// from_bitmap: the bitmap is there already.  Whole workgroup; ends with a barrier.
-__device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *rows, uint32_t P, bool from_bitmap) {
+// Whole workgroup; ends with a barrier.
+__device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *rows, uint32_t P) {
   const uint32_t K = P / 4, n_rows = P + K, words = (n_rows + 31) / 32;   // at most 80 words
-  if (!from_bitmap) {
-    for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) rk.occ[w] = 0;
-    __syncthreads();
-    for (uint32_t g = threadIdx.x; g < K; g += blockDim.x) atomicOr(&rk.occ[rows[g] >> 5], 1u << (rows[g] & 31u));
-    __syncthreads();
-  }
+  for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) rk.occ[w] = 0;
+  __syncthreads();
+  for (uint32_t g = threadIdx.x; g < K; g += blockDim.x) atomicOr(&rk.occ[rows[g] >> 5], 1u << (rows[g] & 31u));
+  __syncthreads();
   // free rows before each bitmap word (one wave scans the words' counts), ...
   if (threadIdx.x < kLanes) {
     uint32_t carry = 0;
@@ -358,13 +356,12 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   }
   draw_unit_parents(a.t + 1);
   stage_table<1>(a, s, a.term_lds, fa.first_changed != 0, threadIdx.x, blockDim.x);
-  // the state the last selection left: the survivors' rows and scores, the bitmap of their rows
+  // the state the last selection left: the survivors' rows and scores
   for (uint32_t e = tid; e < K; e += kFusedThreads) {
     const uint32_t row = fa.parent_rows[e];
     rk.srow(0)[e] = static_cast<uint16_t>(row);
     rk.skey(0)[e] = static_cast<uint64_t>(__double_as_longlong(a.fit_row[row]));
   }
-  for (uint32_t w = tid; w < (P + K + 31) / 32; w += kFusedThreads) rk.occ[w] = fa.occupied[w];
   if (tid == 0) rk.misc[0] = rk.misc[1] = 0;
   if (kSampled && tid < kLanes) {
     rk.model[tid] = a.tab.abl[tid];
@@ -374,7 +371,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   }
   __syncthreads();
   draw_unit_words(a.t + 1);
-  list_free_rows(rk, nullptr, P, true);
+  list_free_rows(rk, rk.srow(0), P);
   if (kSampled && !build_terms(fa.draws_before)) {
     if (tid == 0) shared_store(fa.sync + 1, 1u);
     return;
@@ -584,10 +581,9 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     const int nxt = moved ? cur ^ 1 : cur;
     if (last) {
       // the state the next call (of either kind) starts from
-      for (uint32_t p = tid; p < P; p += kFusedThreads) fa.row_of_cur[p] = row_of_slot(rk, cur, p, K, changed);
+      for (uint32_t p = tid; p < P; p += kFusedThreads) fa.row_of[p] = row_of_slot(rk, cur, p, K, changed);
       for (uint32_t e = tid; e < K; e += kFusedThreads) {
         fa.parent_rows[e] = rk.srow(nxt)[e];
-        fa.row_of_next[e] = rk.srow(nxt)[e];
         fa.sel[e] = rk.nsel[e];
       }
       const uint32_t words = (P + K + 31) / 32;
@@ -601,7 +597,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       if (kSampled && tid < kLanes) fa.y_out[tid] = rk.ydraw[tid];   // the remaining work the last generation was scored with
       return;
     }
-    if (moved) list_free_rows(rk, rk.srow(nxt), P, false);
+    if (moved) list_free_rows(rk, rk.srow(nxt), P);
     cur = nxt;
   }
 }

@@ -20,17 +20,15 @@ __device__ __forceinline__ uint32_t from_lane_above(uint32_t fallback, uint32_t 
                                                            0xF, 0xF, false));
 }
 
-// The candidate in genome row `row` takes rank g < K (lanes with valid set): it survives in its row.  Called by whole
+// The candidate in genome row `row` takes rank g < K (lanes with valid set): it survives in its
+// row, which the bitmap of the general selection notes.  Called by whole
 // waves.  Neighbouring lanes whose rows share a word of the bitmap hand their bits to the first
 // lane of their run (within a row of 16 lanes), which issues one atomic for all of them: the
 // rows of a pool that has stopped changing are neighbours, and one atomic per row would queue
 // up on the same few words.  Lanes that share a word without being neighbours simply issue
 // their own atomics.
-__device__ __forceinline__ void keep_rows_at(const RowPlan &rp, bool valid, uint32_t g, uint32_t row) {
-  if (valid) {
-    rp.parent_next[g] = row;
-    rp.row_of_next[g] = row;
-  }
+__device__ __forceinline__ void keep_and_mark(const RowPlan &rp, bool valid, uint32_t g, uint32_t row) {
+  if (valid) rp.parent_next[g] = row;
   const uint32_t word = valid ? row / 32 : 0xFFFFFFFFu;        // no bitmap has that many words
   uint32_t bits = valid ? 1u << (row % 32) : 0u;
   // after the steps 1, 2, 4, 8 a lane holds the bits of the lanes above it up to the end of its run
@@ -44,11 +42,12 @@ __device__ __forceinline__ void keep_rows_at(const RowPlan &rp, bool valid, uint
   if (valid && below != word) atomicOr(&rp.occupied[word], bits);
 }
 
-// The same, the row looked up from the slot.
-__device__ __forceinline__ void keep_rows(const RowPlan &rp, bool valid, uint32_t g, uint32_t id) {
-  uint32_t row = 0;
-  if (valid) row = rp.row_of_cur[id];
-  keep_rows_at(rp, valid, g, row);
+// The same for the i-th best child or mutant of a bucketed selection, in pool slot p: the slot is
+// handed the row of the last survivor of the selection before but i, which has dropped out (survivors
+// keep their order, so as many as there are surviving children drop out, and at the end).
+__device__ __forceinline__ void keep_child(const RowPlan &rp, uint32_t g, uint32_t row, uint32_t p, uint32_t i, uint32_t K) {
+  rp.parent_next[g] = row;
+  rp.row_of[p] = rp.parents[K - 1 - i];
 }
 
 // ---------------------------------------------------------------- general path -----
@@ -65,7 +64,7 @@ constexpr uint32_t kRankPoolMax = ONES_RANK_POOL_MAX;
 constexpr int kRankPoolPer = 64;
 __global__ __launch_bounds__(kSortThreads) void rank_pool_kernel(const double *fit_row, const double *slot_score,
                                                                 RowPlan rp, uint32_t P, uint32_t K, int32_t *sel) {
-  const uint32_t *row_of = rp.row_of_cur;
+  const uint32_t *row_of = rp.row_of;
   extern __shared__ __align__(16) uint64_t sk[];       // [padded] scores, then [kRankPoolPer] counters
   constexpr uint32_t kTeam = kSortThreads / kRankPoolPer;
   const uint32_t t = threadIdx.x;
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(kSortThreads) void rank_pool_kernel(const double *f
   if (t < kRankPoolPer) {                              // one whole wave
     const bool in = mine < P && below[t] < K;
     if (in) sel[below[t]] = static_cast<int32_t>(mine);
-    keep_rows(rp, in, below[t], mine);
+    keep_and_mark(rp, in, below[t], in ? row_of[mine] : 0u);
   }
 }
 
@@ -150,10 +149,11 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
   // wins a tie: smaller slot)
   for (uint32_t base = 0; base < n; base += kThreads) {   // whole waves go round together
     const uint32_t i = base + tid;
-    uint32_t g = K, id = 0;
+    uint32_t g = K, row = 0;
     if (i < n) {
       const uint64_t key = sk[i];
-      id = si[i];
+      const uint32_t id = si[i];
+      row = rp.row_of[id];
       uint32_t below = i;
       if (!sorted) {
         // scores alone decide nearly every comparison: count the smaller and the equal ones, and
@@ -179,17 +179,19 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
       g = off + below + lo;
       if (g < K) {
         sel[g] = static_cast<int32_t>(id);
-        if (kElites) note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+        if (kElites) {
+          note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+          keep_child(rp, g, row, id, off - e0 + below, K);
+        }
       }
     }
-    keep_rows(rp, g < K, g, id);
+    if (!kElites) keep_and_mark(rp, g < K, g, row);
   }
   if (!kElites) return;
   // survivor e: rank = e + offspring with a strictly smaller score.  The threads are taken from
   // the top, so that in a small bucket the survivors' waves are not the offspring's.
   for (uint32_t base = 0; base < ne; base += kThreads) {
     const uint32_t e = base + (kThreads - 1 - tid);
-    uint32_t g = K;
     if (e < ne) {
       const uint64_t key = ek[e];
       uint32_t lo = 0;
@@ -205,13 +207,13 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
           if (sk[mid] < key) lo = mid + 1; else hi = mid;
         }
       }
-      g = off + e + lo;
+      const uint32_t g = off + e + lo;
       if (g < K) {
         sel[g] = static_cast<int32_t>(e0 + e);
         note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+        rp.parent_next[g] = rp.parents[e0 + e];
       }
     }
-    keep_rows(rp, g < K, g, e0 + e);
   }
 }
 
@@ -257,8 +259,8 @@ struct BucketShared {
 // full of copies of one genome or because nearly all children beat its best members, one workgroup
 // alone took 0.2 to 1.8 ms (sorting network in global memory) for what takes all of them 10 to 50 us.
 template <bool kElites, int kThreads>
-__device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const double *fit_row, const uint32_t *parent_row,
-                                             const BucketArgs &bk, const RowPlan &rp, uint32_t K, uint32_t o, int32_t *sel) {
+__device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
+                                             const RowPlan &rp, uint32_t K, uint32_t o, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb, b = blockIdx.x;
   uint32_t before = 0;
   for (uint32_t c = tid; c < o; c += kThreads) before += bk.count[c];
@@ -267,7 +269,7 @@ __device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const d
   if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
   const uint32_t e0 = kElites ? bucket_bound(o, K, nb) : 0u, ne = kElites ? bucket_bound(o + 1, K, nb) - e0 : 0u;
   for (uint32_t e = tid; e < ne; e += kThreads)
-    sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[parent_row[e0 + e]]));
+    sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0 + e]]));
   __syncthreads();
   uint32_t off = e0;
 #pragma unroll
@@ -321,10 +323,10 @@ __device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const d
     __syncthreads();
     if (n_below) atomicAdd(&sh.below[i], n_below);
     __syncthreads();
-    uint32_t g = K, slot = 0;
+    uint32_t g = K, row = 0;
     if (part == 0 && (offspring || survivor)) {
-      g = off + sh.below[i];
-      slot = survivor ? e0 + e : id;
+      const uint32_t below = sh.below[i];
+      g = off + below;
       if (survivor) {
         g += e;
       } else {                                       // survivors with a score at or below its own come before it
@@ -336,26 +338,30 @@ __device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const d
         g += lo;
       }
       if (g < K) {
-        sel[g] = static_cast<int32_t>(slot);
+        sel[g] = static_cast<int32_t>(survivor ? e0 + e : id);
         if (kElites) note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+        if (survivor) {
+          rp.parent_next[g] = rp.parents[e0 + e];
+        } else {
+          row = rp.row_of[id];
+          if (kElites) keep_child(rp, g, row, id, off - e0 + below, K);
+        }
       }
     }
-    keep_rows(rp, g < K, g, slot);
+    if (!kElites) keep_and_mark(rp, g < K, g, row);
   }
 }
 
 // kElites: the quantile buckets above, each with its share of the survivors.  Without: the last
 // step of the sample sort of the general path below, a bucket holds candidates only (fit_row,
-// parent_row, count_next unused) and its first rank is the number of candidates before it.
+// rp.parents, count_next unused) and its first rank is the number of candidates before it.
 // kThreads: a bucket of at most that many offspring (nearly all) is ranked straight from registers.
 // A bucket is crowded, and left to all workgroups together, when it holds more than a workgroup
 // sorts in LDS, or more than it ranks by counting while only a few buckets do (the LDS sort of 2048
 // takes one workgroup 20 us; with many such buckets the workgroups are all busy anyway).
 template <bool kElites, int kThreads>
-__global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *fit_row,
-                                                                       const uint32_t *parent_row, BucketArgs bk,
-                                                                       RowPlan rp, uint32_t K, uint32_t *count_next,
-                                                                       int32_t *sel) {
+__global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *fit_row, BucketArgs bk, RowPlan rp,
+                                                                 uint32_t K, uint32_t *count_next, int32_t *sel) {
   __shared__ BucketShared<kThreads> sh;
   const uint32_t b = blockIdx.x, nb = bk.nb, tid = threadIdx.x;
   // offset of this bucket = its first survivor rank + all offspring of the buckets before it
@@ -378,9 +384,9 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     my_idx = bk.idx[static_cast<size_t>(b) * seg + tid];
   }
   const uint32_t se = kThreads - 1 - tid;
-  if (se < ne) elite_row = parent_row[e0 + se];
+  if (se < ne) elite_row = rp.parents[e0 + se];
   if (se < ne) elite_key = static_cast<uint64_t>(__double_as_longlong(fit_row[elite_row]));   // survivors stayed in their rows
-  if (my_idx < 4 * K) my_row = rp.row_of_cur[my_idx];
+  if (my_idx < 4 * K) my_row = rp.row_of[my_idx];
   static_assert(kThreads <= kBucketCount, "a small bucket is ranked by counting");
   const bool small = n <= static_cast<uint32_t>(kThreads) && n <= seg && ne <= static_cast<uint32_t>(kThreads);
   // counting loops run in steps of 8 over padding; the sorting network needs a power of two
@@ -395,7 +401,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     if (se < ne) sh.ek[se] = elite_key;
   } else {
     for (uint32_t e = tid; e < ne; e += kThreads)
-      sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[parent_row[e0 + e]]));
+      sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0 + e]]));
   }
   if (tid == 0) sh.spill_cursor = sh.n_crowded = 0;
   __syncthreads();
@@ -435,27 +441,29 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
           g = off + below + lo;
           if (g < K) {
             sel[g] = static_cast<int32_t>(my_idx);
-            if (kElites) note_rank(g, my_key, K, nb, bk.split_next, bk.thresh_next);
+            if (kElites) {
+              note_rank(g, my_key, K, nb, bk.split_next, bk.thresh_next);
+              keep_child(rp, g, my_row, my_idx, off - e0 + below, K);
+            }
           }
         }
-        keep_rows_at(rp, g < K, g, my_row);
+        if (!kElites) keep_and_mark(rp, g < K, g, my_row);
       }
       // survivor se: rank = se + offspring with a strictly smaller score
       if (kElites) {
-        uint32_t g = K;
         if (se < ne) {
           uint32_t lo = 0;
           for (uint32_t q = 0; q < npad; q += 8) {
 #pragma unroll
             for (int v = 0; v < 8; ++v) lo += sh.sk[q + v] < elite_key ? 1u : 0u;
           }
-          g = off + se + lo;
+          const uint32_t g = off + se + lo;
           if (g < K) {
             sel[g] = static_cast<int32_t>(e0 + se);
             note_rank(g, elite_key, K, nb, bk.split_next, bk.thresh_next);
+            rp.parent_next[g] = elite_row;
           }
         }
-        keep_rows_at(rp, g < K, g, elite_row);
       }
     } else {
       gather_bucket(sh.sk, sh.si, bk, b, n, npad, &sh.spill_cursor);
@@ -468,7 +476,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     for (uint32_t k = 0; k < listed; ++k) {
       const uint32_t o = sh.crowded[k];
       if (listed <= kFewCrowded || bk.count[o] > static_cast<uint32_t>(kBucketLds))
-        rank_crowded<kElites, kThreads>(sh, fit_row, parent_row, bk, rp, K, o, sel);
+        rank_crowded<kElites, kThreads>(sh, fit_row, bk, rp, K, o, sel);
     }
   }
   if (kElites) {                                     // the other counter set, for the next generation
@@ -674,11 +682,10 @@ __device__ __forceinline__ uint32_t stored_batch(const uint32_t *row, const uint
   return info_reset(w) ? 0u : batch_of_code(reinterpret_cast<const uint8_t *>(row)[gene_byte(j)], info_blexp(w));
 }
 
-__global__ void best_kernel(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                            const uint32_t *stored, const uint32_t *info, uint32_t Jn, uint32_t row_words,
-                            int32_t *batch_out, int32_t *gpus_out, double *fit_out, const uint32_t *err_in,
+__global__ void best_kernel(const uint32_t *genes, const double *fit_row, const uint32_t *best_row, const uint32_t *stored,
+                            const uint32_t *info, uint32_t Jn, uint32_t row_words, int32_t *batch_out, int32_t *gpus_out, double *fit_out, const uint32_t *err_in,
                             uint32_t *err_out) {
-  const uint32_t best = row_of[sel[0]];
+  const uint32_t best = *best_row;
   const uint32_t *row = genes + static_cast<size_t>(best) * row_words;
   for (uint32_t j = threadIdx.x; j < Jn; j += blockDim.x) {
     const uint32_t B = stored_batch(row, stored, j);
@@ -692,28 +699,40 @@ __global__ void best_kernel(const uint32_t *genes, const double *fit_row, const 
   }
 }
 
-// The genomes of a run of pool slots as batch sizes, in slot order; one workgroup per slot.
+// The genomes of a run of pool slots as batch sizes, in slot order; one workgroup per slot (the first
+// `count` workgroups, rows by row_of) and then per survivor (a survivor's slot may have been
+// handed another row already).
 constexpr int kUnpackThreads = 256;
-__global__ __launch_bounds__(kUnpackThreads) void unpack_kernel(const uint32_t *genes, const uint32_t *row_of,
-                                                                const uint32_t *stored, uint32_t Jp, uint32_t row_words,
-                                                                uint32_t first, int32_t *out) {
-  const uint32_t *row = genes + static_cast<size_t>(row_of[first + blockIdx.x]) * row_words;
-  for (uint32_t j = threadIdx.x; j < Jp; j += kUnpackThreads)
-    out[static_cast<size_t>(blockIdx.x) * Jp + j] = static_cast<int32_t>(stored_batch(row, stored, j));
+__device__ __forceinline__ void unpack_row(const uint32_t *row, const uint32_t *stored, uint32_t Jp, int32_t *out) {
+  for (uint32_t j = threadIdx.x; j < Jp; j += kUnpackThreads) out[j] = static_cast<int32_t>(stored_batch(row, stored, j));
+}
+__global__ __launch_bounds__(kUnpackThreads) void unpack_slots_kernel(const uint32_t *genes, const uint32_t *row_of,
+                                                                      const uint32_t *stored, uint32_t Jp,
+                                                                      uint32_t row_words, uint32_t first, int32_t *out) {
+  unpack_row(genes + static_cast<size_t>(row_of[first + blockIdx.x]) * row_words, stored, Jp,
+             out + static_cast<size_t>(blockIdx.x) * Jp);
+}
+__global__ __launch_bounds__(kUnpackThreads) void unpack_survivors_kernel(const uint32_t *genes, const int32_t *sel,
+                                                                          const uint32_t *parents, const uint32_t *stored,
+                                                                          uint32_t Jp, uint32_t row_words, uint32_t first,
+                                                                          uint32_t count, int32_t *out) {
+  const uint32_t at = static_cast<uint32_t>(sel[blockIdx.x]) - first;
+  if (at < count)
+    unpack_row(genes + static_cast<size_t>(parents[blockIdx.x]) * row_words, stored, Jp, out + static_cast<size_t>(at) * Jp);
 }
 
 // The winner unrolled over the GPUs (Eq. 1, reorder): every workgroup scans the jobs' GPU
 // counts in LDS (at most 2048 slots), then each thread finds the job of one GPU by binary
 // search over the prefix sums.
 constexpr int kPlaceThreads = 1024;
-__global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const uint32_t *genes, const uint32_t *row_of,
-                                                                 const int32_t *sel, const uint32_t *info, uint32_t Jn,
+__global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const uint32_t *genes, const uint32_t *best_row,
+                                                                 const uint32_t *info, uint32_t Jn,
                                                                  uint32_t row_words, uint32_t G, int32_t *slot_of_gpu,
                                                                  int32_t *batch_of_gpu) {
   __shared__ uint32_t first[2 * kPlaceThreads + 1];    // first GPU of every slot, then the GPUs in use
   __shared__ uint32_t per_gpu[2 * kPlaceThreads];      // local batch of every slot's workers
   __shared__ uint32_t wave_total[kPlaceThreads / kLanes];
-  const uint32_t *row = genes + static_cast<size_t>(row_of[sel[0]]) * row_words;
+  const uint32_t *row = genes + static_cast<size_t>(*best_row) * row_words;
   const uint32_t t = threadIdx.x;
   // thread t owns slots 2t and 2t + 1
   uint32_t c[2];
@@ -771,10 +790,15 @@ hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const uint32_t *stored, uint32_t Jp, uint32_t first,
-                         uint32_t count, int32_t *out, hipStream_t s) {
-  hipLaunchKernelGGL(unpack_kernel, dim3(count), dim3(kUnpackThreads), 0, s, genes, row_of, stored, Jp,
-                     words_of(Jp / kLanes) * kLanes, first, out);
+hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *parents, uint32_t K,
+                         const uint32_t *stored, uint32_t Jp, uint32_t first, uint32_t count, int32_t *out, hipStream_t s) {
+  const uint32_t row_words = static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes);
+  hipLaunchKernelGGL(unpack_slots_kernel, dim3(count), dim3(kUnpackThreads), 0, s, genes, row_of, stored, Jp, row_words,
+                     first, out);
+  const hipError_t rc = hipGetLastError();
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(unpack_survivors_kernel, dim3(K), dim3(kUnpackThreads), 0, s, genes, sel, parents, stored, Jp,
+                     row_words, first, count, out);
   return hipGetLastError();
 }
 
@@ -804,22 +828,22 @@ hipError_t launch_select(const double *fit, const double *slot_score, const RowP
   bk.seg = static_cast<uint32_t>(static_cast<size_t>(store.nb) * store.seg / nb);   // the same storage, re-divided
   bk.nb = nb;
   hipLaunchKernelGGL(sample_splitters_kernel, dim3(sample / kSamplePer), dim3(kSampleThreads), 0, s, fit, slot_score,
-                     rp.row_of_cur, P, sample, nb, const_cast<uint64_t *>(bk.split), bk.split_slot, bk.count);
+                     rp.row_of, P, sample, nb, const_cast<uint64_t *>(bk.split), bk.split_slot, bk.count);
   hipError_t rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(drop_all_kernel, dim3((P + kDropThreads - 1) / kDropThreads), dim3(kDropThreads), 0, s, fit,
-                     slot_score, rp.row_of_cur, P, bk, bk.split_slot);
+                     slot_score, rp.row_of, P, bk, bk.split_slot);
   rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
-  hipLaunchKernelGGL((bucket_select_kernel<false, kBucketCount>), dim3(nb), dim3(kBucketCount), 0, s, nullptr, nullptr,
+  hipLaunchKernelGGL((bucket_select_kernel<false, kBucketCount>), dim3(nb), dim3(kBucketCount), 0, s, nullptr,
                      bk, rp, K, nullptr, sel);
   return hipGetLastError();
 }
 
-hipError_t launch_bucket_select(const double *fit_row, const uint32_t *parent_row, const BucketArgs &bk,
-                                const RowPlan &rp, uint32_t K, uint32_t *count_next, int32_t *sel, hipStream_t s) {
-  hipLaunchKernelGGL((bucket_select_kernel<true, kBucketThreads>), dim3(bk.nb), dim3(kBucketThreads), 0, s, fit_row,
-                     parent_row, bk, rp, K, count_next, sel);
+hipError_t launch_bucket_select(const double *fit_row, const BucketArgs &bk, const RowPlan &rp, uint32_t K,
+                                uint32_t *count_next, int32_t *sel, hipStream_t s) {
+  hipLaunchKernelGGL((bucket_select_kernel<true, kBucketThreads>), dim3(bk.nb), dim3(kBucketThreads), 0, s, fit_row, bk,
+                     rp, K, count_next, sel);
   return hipGetLastError();
 }
 
@@ -831,19 +855,18 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
   return hipGetLastError();
 }
 
-hipError_t launch_placement(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *info,
-                            uint32_t Jn, uint32_t Jp, uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu,
-                            hipStream_t s) {
+hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
+                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, hipStream_t s) {
   const uint32_t blocks = std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u));
-  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, row_of, sel, info, Jn,
+  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, best, info, Jn,
                      static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), G, slot_of_gpu, batch_of_gpu);
   return hipGetLastError();
 }
 
-hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *row_of, const int32_t *sel,
-                       const uint32_t *stored, const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out,
-                       int32_t *gpus_out, double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s) {
-  hipLaunchKernelGGL(best_kernel, dim3(1), dim3(256), 0, s, genes, fit_row, row_of, sel, stored, info, Jn,
+hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *best, const uint32_t *stored,
+                       const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
+                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s) {
+  hipLaunchKernelGGL(best_kernel, dim3(1), dim3(256), 0, s, genes, fit_row, best, stored, info, Jn,
                      static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), batch_out, gpus_out, fit_out, err_in, err_out);
   return hipGetLastError();
 }
