@@ -143,7 +143,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   L.occupied[0] = take((rows + 31) / 32 * 4);     // bitmaps of the rows the survivors keep
   L.occupied[1] = take((rows + 31) / 32 * 4);
   L.sel = take(static_cast<size_t>(P / 4) * 4);
-  // single-launch generations of small pools: arrival counter + error word, scores exchanged by slot
+  // single-launch generations of small pools: error words, scores, ranks and draws exchanged
   L.fsync = take(256);
   L.xkeys = take(fused_pool(P, Jp) ? fused_exchange_bytes(P) : 0);
   // the selection's scratch: splitters, counters, bucket storage, spill list
@@ -653,8 +653,10 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   EvolveArgs &a = fa.ev;
   a.genes = c->at<uint32_t>(c->L.genes);
   a.fit_row = c->at<double>(c->L.fit_row);
-  a.parent_row = nullptr; a.row_of = nullptr; a.spare = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
-  a.assigned = 0;
+  a.parent_row = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
+  a.row_of = c->at<uint32_t>(c->L.row_of);
+  a.spare = c->at<uint32_t>(c->L.spare);
+  a.assigned = c->rows_assigned ? 1u : 0u;
   a.slot_score = nullptr;                              // no selection kernel follows
   a.tab = c->table();
   a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
@@ -671,13 +673,9 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   a.bk = BucketArgs{};
   const int next = c->cur ^ 1;
   fa.parent_rows = c->at<uint32_t>(c->L.parent_row[next]);
-  fa.row_of = c->at<uint32_t>(c->L.row_of);
-  fa.occupied = c->at<uint32_t>(c->L.occupied[c->occ]);
   fa.sel = c->at<int32_t>(c->L.sel);
-  fa.xkeys = c->at<uint64_t>(c->L.xkeys);
-  fa.xsurv = fa.xkeys + static_cast<size_t>(2) * c->P;
-  fa.xrank = fa.xsurv + static_cast<size_t>(2) * c->K;
-  fa.xdraw = fa.xrank + c->P;
+  fused_exchange(c->at<uint64_t>(c->L.xkeys), c->P, fa);
+  fa.changes_before = c->fused_changes;
   fa.draws_before = c->fused_draws;
   fa.sampled = c->sampling ? 1u : 0u;
   fa.pr = Progress{c->at<double>(c->L.alpha), c->at<double>(c->L.beta), c->at<double>(c->L.processed)};
@@ -685,7 +683,6 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   fa.y_out = c->at<double>(c->L.Y[c->y_cur]);      // what ones_export_remaining reads
   fa.sync = c->at<uint32_t>(c->L.fsync);
   fa.generations_before = c->fused_generations;
-  fa.changes_before = c->fused_changes;
   fa.n_generations = n;
   fa.first_changed = c->table_changed ? 1u : 0u;
   fa.spin_limit = c->spin_limit;
@@ -699,7 +696,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
     c->fused_draws += n;
     c->drawn_from = c->drawn_to = 0;   // the ring may hold tables this launch wrote over (y_out); the two-launch path draws again
   }
-  c->rows_assigned = false;
+  c->rows_assigned = true;
   c->info_stored = c->info_now;
   c->table_changed = false;
   c->no_schedule = false;

@@ -155,19 +155,17 @@ struct EvolveArgs {
 
 // All generations of one ones_generation call in a single launch, for pools that are small
 // enough to be ranked inside every workgroup's LDS (one row of 64 job columns, at most
-// kFusedMaxPool candidates).  ev describes the problem as for the evolve kernel; of its row
-// bookkeeping only genes, fit_row and tab are used, and ev.t is the generation counter BEFORE
-// the call (the launch runs generations ev.t + 1 .. ev.t + n_generations).
+// kFusedMaxPool candidates).  ev describes the problem as for the evolve kernel (row_of and spare
+// are written when the launch ends, and read when assigned is set); ev.t is the generation counter
+// BEFORE the call (the launch runs generations ev.t + 1 .. ev.t + n_generations).
 constexpr uint32_t kFusedMaxPool = 2048;
 struct FusedArgs {
   EvolveArgs ev;
   uint32_t *parent_rows;    // [K] in: rows of the survivors, best first; out: of the new survivors
-  uint32_t *row_of;         // [P] out: row of every slot of the last generation's pool
-  uint32_t *occupied;       // out: bitmap over the P + K rows, the survivors' rows
   int32_t  *sel;            // [K] out: survivor slots of the last generation's pool, best first
   // exchange between the workgroups, zeroed when the context is created, then only written by these launches:
   uint64_t *xkeys;          // [2][P] tagged score bits of the children by pool slot, a buffer per generation parity
-  uint64_t *xsurv;          // [2][K] the same for survivors refreshed after a table change
+  uint64_t *xsurv;          // [2][K] the same for survivors with a new score
   uint64_t *xrank;          // [P] ranks from a ranking by counting, stamped with the generation
   uint64_t *xdraw;          // [4][64] tagged draws of the remaining work (probability sampling), four generations rotating
   uint32_t *sync;           // [1] set when a poll ran out
@@ -178,7 +176,7 @@ struct FusedArgs {
   Progress pr;                  // its inputs
   uint32_t n_slots;             // Jn: slots at or beyond it have no remaining work
   double  *y_out;               // [64] out: the remaining work the last generation was scored with
-  uint32_t n_generations;   // > 0
+  uint32_t n_generations;   // > 1
   uint32_t first_changed;   // the job table changed since the survivors were scored: the first generation refreshes them
   uint32_t spin_limit;      // polls before a wait gives up (0: gives up at once; for tests of that path)
   uint32_t table_lds;       // set by the launcher: bytes of LDS the staged job table takes
@@ -187,7 +185,8 @@ struct FusedArgs {
 // Workgroups to launch for a pool of P (the launch must be co-resident: cooperative).
 uint32_t fused_workgroups(uint32_t P, bool sampled);
 uint32_t fused_grid_limit(uint32_t P);      // the largest grid a launch for a pool of P uses
-size_t fused_exchange_bytes(uint32_t P);    // xkeys, xsurv and xrank, consecutive
+size_t fused_exchange_bytes(uint32_t P);    // xkeys, xsurv, xrank and xdraw, consecutive
+void fused_exchange(uint64_t *base, uint32_t P, FusedArgs &fa);   // their addresses
 hipError_t launch_fused(const FusedArgs &fa, hipStream_t s);
 
 // What a selection records besides the survivor list: the survivors keep their rows.

@@ -5,13 +5,13 @@
 //
 // Two launches per generation cost more than the generation itself at this size, so here a
 // co-resident grid stays on the chip for the whole call.  Per generation every wave composes,
-// repairs and scores its share of the 3K children (4K candidates after a table change) and
-// publishes genome and score; every workgroup then collects all scores and ranks the pool by
-// itself in its LDS: the survivors' scores, rows and the list of free rows are kept there
-// redundantly, so the only data that cross workgroups are the genomes and one score per
-// candidate.  While the job table stays the same the K survivors reappear with the scores they
-// had, already in order, so the ranking is a merge of the few children that beat the K-th
-// survivor into that order; when there are many of them, or after a table change, every
+// repairs and scores its share of the 3K children (4K candidates when every score is new: after a
+// table change and under probability sampling) and publishes genome and score; every workgroup then
+// collects all scores and ranks the pool by itself in its LDS: the survivors' scores and rows and the
+// rows of the slots to fill are kept there redundantly, so the only data that cross workgroups are
+// the genomes and one score per candidate.  While the scores stay the same the K survivors
+// reappear with theirs, already in order, so the ranking is a merge of the few children that beat
+// the K-th survivor into that order; when there are many of them, or every score is new, every
 // workgroup ranks a share of the pool by counting and the ranks are exchanged like the scores.
 //
 // Exchange.  Data written by one workgroup and read by another inside the launch (genomes,
@@ -24,6 +24,12 @@
 // means that every wave has finished reading that generation's parents and writing its
 // children, which is all the ordering the rows need.  Every poll is bounded: a workgroup that
 // gives up sets an error word and leaves, and so, in time, do all others.
+// What bounds a generation is this exchange: all workgroups read the same few kilobytes of the memory
+// side at once, so a poll that comes too early delays those that matter.  (A generation of 1024
+// candidates, 96 workgroups: 4.5 us with one poll after the other, no branch around a load and a
+// pause before the first poll; 4.8 without the pause; 5.1 with a branch per load; two polls in
+// flight 4.8, four 5.4.  A flag per workgroup, polled in place of the scores, reads an eighth of the
+// bytes but waits for the workgroup's slowest wave first: 5.5.)
 #include "ones_candidate.h"
 #include "ones_sample.h"
 #include "ones_sort.h"
@@ -34,22 +40,18 @@
 namespace ones {
 namespace {
 
-#ifndef ONES_FUSED_WAVES
-#define ONES_FUSED_WAVES 8
-#endif
-#ifndef ONES_FUSED_WORKGROUPS
-#define ONES_FUSED_WORKGROUPS 192
-#endif
-constexpr int kFusedWaves = ONES_FUSED_WAVES;          // waves per workgroup
+constexpr int kFusedWaves = 8;                         // waves per workgroup
 constexpr int kFusedThreads = kFusedWaves * kLanes;
-constexpr uint32_t kFusedMaxWorkgroups = ONES_FUSED_WORKGROUPS;
-#ifndef ONES_FUSED_SAMPLED_WORKGROUPS
-#define ONES_FUSED_SAMPLED_WORKGROUPS 248
-#endif
-constexpr uint32_t kFusedMaxSampledWorkgroups = ONES_FUSED_SAMPLED_WORKGROUPS;   // plus the drawing ones: one per compute unit at most
+constexpr uint32_t kFusedMaxWorkgroups = 192;
+constexpr uint32_t kFusedMaxSampledWorkgroups = 248;   // plus the drawing ones: one per compute unit at most
 constexpr uint32_t kFusedUnits = 4;          // most units (candidates) one wave computes per generation
-constexpr uint32_t kMergeMax = 128;          // children beating the K-th survivor that are still merged locally
+constexpr uint32_t kMergeMax = 128;          // children beating the K-th survivor that are merged into the survivors' order
+// With so many workgroups a wave waits a little before its first poll, until the others' entries are
+// nearly there: 0.2 us for the scores of the children, 1.3 us where the survivors are scored too, 0.4 us
+// for ranks (1024 candidates: a generation 4.8 -> 4.5 us; 2048 sampled, over the GPUs: 14.4 -> 12.3).
+constexpr uint32_t kCrowd = 32;
 constexpr int kGatherPer = (kFusedMaxPool + kFusedThreads - 1) / kFusedThreads;   // entries per thread when a workgroup collects P values
+static_assert(kFusedMaxPool / 4 <= kFusedThreads, "a thread per survivor");
 
 template <typename T>
 __device__ __forceinline__ T shared_load(const T *p) {
@@ -81,16 +83,18 @@ struct Ranks {
   __device__ __forceinline__ uint64_t *skey(int which) const { return skeys + static_cast<uint32_t>(which) * K; }
   __device__ __forceinline__ uint16_t *srow(int which) const { return srows + static_cast<uint32_t>(which) * K; }
   uint16_t *nsel;      // [K] pool slot each new survivor had in the generation just ranked
-  uint16_t *frow;      // [P] the free rows in ascending order: unit u of a generation writes row frow[u]
+  uint16_t *frow;      // [P] the row unit u of a generation writes; the last K are spare between table changes
   uint64_t *ckey;      // [P] score bits by pool slot
-  uint64_t *mkey;      // [3K] children that beat the K-th survivor
-  uint32_t *mslot;     // [3K]
+  uint64_t *lkey;      // [3K] children that beat the K-th survivor
+  uint16_t *lslot;     // [3K] ... their slots
   uint64_t *okey;      // [kMergeMax] ... in order
-  uint32_t *oslot;     // [kMergeMax]
+  uint16_t *oslot;     // [kMergeMax]
   uint32_t *below;     // [kMergeMax] counters of the rankings by counting
-  uint32_t *occ;       // bitmap over the P + K rows: the survivors' rows
+  uint32_t *bits;      // bitmap: over the P + K rows when rows are listed, over the survivors of the generation before
   uint32_t *wfree;     // free rows before each word of the bitmap
-  uint32_t *misc;      // [0] number of children that beat the K-th survivor, [1] whether there is one
+  uint16_t *drow;      // [K] rows of survivors that dropped out
+  uint32_t *wcount;    // [2][kFusedWaves] counts of the waves, for prefix sums
+  uint32_t *misc;      // [0] number of children that beat the K-th survivor, [1 + generation mod 3] whether there is one
   uint32_t *draws;     // [waves][kFusedUnits][4] per unit: ranks of the parents, rotation (drawn ahead)
   uint32_t *words;     // [waves][kFusedUnits][64] per unit: the gene words (drawn ahead)
   uint64_t *ukeys;     // [waves][kFusedUnits] per unit: the score, until the wave publishes it
@@ -100,13 +104,14 @@ struct Ranks {
 };
 
 inline size_t ranks_bytes(uint32_t P) {
-  const size_t K = P / 4;
-  return 2 * K * 8 + 2 * K * 2 + K * 2 + P * 2 + P * 8 + 3 * K * 8 + 3 * K * 4 + kMergeMax * (8 + 4 + 4) +
-         ((P + K + 31) / 32) * 8 + 16 + kFusedWaves * kFusedUnits * ((4 + kLanes) * 4 + 8) + 4 * kLanes * 8 + kLanes * 4 + 64;
+  const size_t K = P / 4, words = (P + K + 31) / 32;
+  return 4 * kLanes * 8 + kFusedWaves * kFusedUnits * 8 + 2 * K * 8 + static_cast<size_t>(P) * 8 + 3 * K * 8 + kMergeMax * 8 +
+         4 * (kMergeMax + 2 * words + 2 * kFusedWaves + 4 + kFusedWaves * kFusedUnits * (4 + kLanes) + kLanes) +
+         2 * (2 * K + K + P + 3 * K + kMergeMax + K) + 64;
 }
 
 __device__ __forceinline__ Ranks carve_ranks(unsigned char *base, uint32_t P) {
-  const uint32_t K = P / 4;
+  const uint32_t K = P / 4, words = (P + K + 31) / 32;
   Ranks r;
   r.K = K;
   r.ydraw = reinterpret_cast<double *>(base);
@@ -114,37 +119,39 @@ __device__ __forceinline__ Ranks carve_ranks(unsigned char *base, uint32_t P) {
   r.ukeys = reinterpret_cast<uint64_t *>(r.model + 3 * kLanes);
   r.skeys = r.ukeys + kFusedWaves * kFusedUnits;
   r.ckey = r.skeys + 2 * K;
-  r.mkey = r.ckey + P;
-  r.okey = r.mkey + 3 * K;
-  r.mslot = reinterpret_cast<uint32_t *>(r.okey + kMergeMax);
-  r.oslot = r.mslot + 3 * K;
-  r.below = r.oslot + kMergeMax;
-  r.occ = r.below + kMergeMax;
-  r.wfree = r.occ + (P + K + 31) / 32;
-  r.misc = r.wfree + (P + K + 31) / 32;
+  r.lkey = r.ckey + P;
+  r.okey = r.lkey + 3 * K;
+  r.below = reinterpret_cast<uint32_t *>(r.okey + kMergeMax);
+  r.bits = r.below + kMergeMax;
+  r.wfree = r.bits + words;
+  r.wcount = r.wfree + words;
+  r.misc = r.wcount + 2 * kFusedWaves;
   r.draws = r.misc + 4;
   r.words = r.draws + kFusedWaves * kFusedUnits * 4;
   r.blexp = r.words + kFusedWaves * kFusedUnits * kLanes;
   r.srows = reinterpret_cast<uint16_t *>(r.blexp + kLanes);
   r.nsel = r.srows + 2 * K;
   r.frow = r.nsel + K;
+  r.lslot = r.frow + P;
+  r.oslot = r.lslot + 3 * K;
+  r.drow = r.oslot + kMergeMax;
   return r;
 }
 
-// The survivors' rows (rows[0..K)) as a bitmap, and from it the free rows in ascending order.
-// Whole workgroup; ends with a barrier.
+// The rows that are not the survivors' (rows[0..K)), in ascending order, as rows of the units, when
+// no selection has assigned them.  Whole workgroup; ends with a barrier.
 __device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *rows, uint32_t P) {
   const uint32_t K = P / 4, n_rows = P + K, words = (n_rows + 31) / 32;   // at most 80 words
-  for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) rk.occ[w] = 0;
+  for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) rk.bits[w] = 0;
   __syncthreads();
-  for (uint32_t g = threadIdx.x; g < K; g += blockDim.x) atomicOr(&rk.occ[rows[g] >> 5], 1u << (rows[g] & 31u));
+  for (uint32_t g = threadIdx.x; g < K; g += blockDim.x) atomicOr(&rk.bits[rows[g] >> 5], 1u << (rows[g] & 31u));
   __syncthreads();
   // free rows before each bitmap word (one wave scans the words' counts), ...
   if (threadIdx.x < kLanes) {
     uint32_t carry = 0;
     for (uint32_t base = 0; base < words; base += kLanes) {
       const uint32_t w = base + threadIdx.x;
-      const uint32_t n = w < words ? __popc(~rk.occ[w]) : 0u;   // bits beyond the last row are never looked at
+      const uint32_t n = w < words ? __popc(~rk.bits[w]) : 0u;   // bits beyond the last row are never looked at
       const uint32_t incl = wave_inclusive_scan(n);
       if (w < words) rk.wfree[w] = carry + incl - n;
       carry += __builtin_amdgcn_readlane(incl, kLanes - 1);
@@ -153,7 +160,7 @@ __device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *
   __syncthreads();
   // ... then every row finds its own place in the list
   for (uint32_t row = threadIdx.x; row < n_rows; row += blockDim.x) {
-    const uint32_t free_bits = ~rk.occ[row >> 5], bit = row & 31u;
+    const uint32_t free_bits = ~rk.bits[row >> 5], bit = row & 31u;
     if ((free_bits >> bit) & 1u) {
       const uint32_t pos = rk.wfree[row >> 5] + __popc(free_bits & ((1u << bit) - 1u));
       if (pos < P) rk.frow[pos] = static_cast<uint16_t>(row);
@@ -162,52 +169,46 @@ __device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *
   __syncthreads();
 }
 
-// Row of pool slot p in the generation just computed.
-__device__ __forceinline__ uint32_t row_of_slot(const Ranks &rk, int cur, uint32_t p, uint32_t K, bool changed) {
-  if (p >= K) return rk.frow[p - K];
-  return changed ? rk.frow[3 * K + p] : rk.srow(cur)[p];
-}
-
-// Collects published 64-bit entries from two arrays at once (n2 may be 0): thread t takes entries
-// t, t + threads, ... of each, polls until every one is ready and hands it to the array's take.
-// False when the polls ran out.
-template <typename Ready1, typename Take1, typename Ready2, typename Take2>
-__device__ __forceinline__ bool gather2(const uint64_t *src1, uint32_t n1, Ready1 ready1, Take1 take1,
-                                        const uint64_t *src2, uint32_t n2, Ready2 ready2, Take2 take2,
-                                        uint32_t spin_limit) {
-  uint32_t pending1 = 0, pending2 = 0;
+// Collects n published 64-bit entries: thread t takes entries t, t + threads, ..., polls until every one
+// is ready and hands it to take.  at(e): the address of entry e.  False when the polls ran out.  No
+// branch around a load: a thread reads its entries again until the wave has all of its own.
+template <int kPer, typename At, typename Ready, typename Take>
+__device__ __forceinline__ bool gather_per(uint32_t n, uint32_t spin_limit, At at, Ready ready, Take take) {
+  uint32_t pending = 0;
+  const uint64_t *src[kPer];
 #pragma unroll
-  for (int k = 0; k < kGatherPer; ++k) {
-    if (threadIdx.x + k * kFusedThreads < n1) pending1 |= 1u << k;
-    if (threadIdx.x + k * kFusedThreads < n2) pending2 |= 1u << k;
+  for (int k = 0; k < kPer; ++k) {
+    const uint32_t e = threadIdx.x + k * kFusedThreads;
+    if (e < n) pending |= 1u << k;
+    src[k] = at(min(e, n - 1));
   }
-  for (uint32_t spins = 0; (pending1 | pending2) != 0; ++spins) {
-    if (spins >= spin_limit) return false;
-    uint64_t v1[kGatherPer], v2[kGatherPer];
+  if (__ballot(pending != 0) == 0) return true;
+  for (uint32_t spins = 0; spins < spin_limit; ++spins) {
+    uint64_t v[kPer];
 #pragma unroll
-    for (int k = 0; k < kGatherPer; ++k) {
-      if ((pending1 >> k) & 1u) v1[k] = shared_load(src1 + threadIdx.x + k * kFusedThreads);
-      if ((pending2 >> k) & 1u) v2[k] = shared_load(src2 + threadIdx.x + k * kFusedThreads);
-    }
+    for (int k = 0; k < kPer; ++k) v[k] = shared_load(src[k]);
 #pragma unroll
-    for (int k = 0; k < kGatherPer; ++k) {
-      if (((pending1 >> k) & 1u) && ready1(v1[k])) {
-        take1(threadIdx.x + k * kFusedThreads, v1[k]);
-        pending1 &= ~(1u << k);
-      }
-      if (((pending2 >> k) & 1u) && ready2(v2[k])) {
-        take2(threadIdx.x + k * kFusedThreads, v2[k]);
-        pending2 &= ~(1u << k);
+    for (int k = 0; k < kPer; ++k) {
+      const uint32_t e = threadIdx.x + k * kFusedThreads;
+      if (((pending >> k) & 1u) && ready(e, v[k])) {
+        take(e, v[k]);
+        pending &= ~(1u << k);
       }
     }
+    if (__ballot(pending != 0) == 0) return true;
   }
-  return true;
+  return false;
 }
 
-// The same for one array.
-template <typename Ready, typename Take>
-__device__ __forceinline__ bool gather(const uint64_t *src, uint32_t n, uint32_t spin_limit, Ready ready, Take take) {
-  return gather2(src, n, ready, take, src, 0u, ready, take, spin_limit);
+template <typename At, typename Ready, typename Take>
+__device__ __forceinline__ bool gather(uint32_t n, uint32_t spin_limit, At at, Ready ready, Take take) {
+  static_assert(kGatherPer <= 4, "entries per thread");
+  switch ((n + kFusedThreads - 1) / kFusedThreads) {
+    case 1: return gather_per<1>(n, spin_limit, at, ready, take);
+    case 2: return gather_per<2>(n, spin_limit, at, ready, take);
+    case 3: return gather_per<3>(n, spin_limit, at, ready, take);
+    default: return gather_per<4>(n, spin_limit, at, ready, take);
+  }
 }
 
 // What a child or mutant draws before it needs anything of its parents: the parents' ranks and
@@ -215,16 +216,13 @@ __device__ __forceinline__ bool gather(const uint64_t *src, uint32_t n, uint32_t
 // (seed, generation, slot) only, so a wave draws for the coming generation while the scores of
 // the current generation are still arriving.
 __device__ __forceinline__ void draw_parents(const EvolveArgs &a, uint32_t t, uint32_t u, int lane, uint32_t *draws) {
-  const uint32_t K = a.K;
-  Draw d;
-  if (u < 2 * K) {                                   // child of a pair: both share the pair's parents
-    const uint32_t p0 = K + (u & ~1u);
-    d = candidate_draw(a, t, p0);
-    if (u & 1u) d.r = candidate_draw(a, t, p0 + 1).r;
-  } else {
-    d = candidate_draw(a, t, K + u);
-  }
-  if (lane == 0) { draws[0] = d.ra; draws[1] = d.rb; draws[2] = d.r; }
+  // a child of a pair shares the parents drawn for the pair's first slot, its rotation is its own:
+  // lane 0 draws for the former, lane 1 for the latter
+  const bool child = u < 2 * a.K;
+  const uint32_t p = a.K + u;
+  const Draw d = candidate_draw(a, t, child && lane == 0 ? p - (u & 1u) : p);
+  if (lane == 0) { draws[0] = d.ra; draws[1] = d.rb; }
+  if (lane == 1) draws[2] = d.r;
 }
 
 // The one row of job slots takes the first word of a Philox block.
@@ -283,6 +281,39 @@ __device__ __forceinline__ double compose_unit(const EvolveArgs &a, uint32_t t, 
   return score<1, 1>(c, s, a.term_lds, lane);
 }
 
+// ------------------------------------------------------------------ ranking --------
+// The rows that go with a ranking of the whole pool: the new survivors keep theirs, and the slots of
+// the surviving children take the rows of the survivors that dropped out, the i-th the i-th (both
+// counted in the same order by every workgroup).  changed: the pool's first K slots are refreshed
+// survivors in the spare rows, and the rows they came from are spare from now on.
+__device__ __forceinline__ void assign_rows(const Ranks &rk, uint32_t P, int cur, int nxt, bool changed) {
+  const uint32_t K = P / 4, tid = threadIdx.x, lane = tid % kLanes, wave = tid / kLanes;
+  const uint32_t words = (K + 31) / 32;
+  if (tid < words) rk.bits[tid] = 0;
+  __syncthreads();
+  const uint32_t slot = tid < K ? rk.nsel[tid] : 0u;
+  const bool child = tid < K && slot >= K;
+  if (tid < K && !child) atomicOr(&rk.bits[slot / 32], 1u << (slot % 32));
+  __syncthreads();
+  const bool dead = tid < K && ((rk.bits[tid / 32] >> (tid % 32)) & 1u) == 0;
+  const uint64_t children = __ballot(child), gone = __ballot(dead);
+  if (lane == 0) {
+    rk.wcount[wave] = static_cast<uint32_t>(__popcll(children));
+    rk.wcount[kFusedWaves + wave] = static_cast<uint32_t>(__popcll(gone));
+  }
+  auto elite_row = [&](uint32_t e) { return changed ? rk.frow[3 * K + e] : rk.srow(cur)[e]; };
+  __syncthreads();
+  const uint64_t before = (1ull << lane) - 1ull;
+  uint32_t nth_child = static_cast<uint32_t>(__popcll(children & before)), nth_gone = static_cast<uint32_t>(__popcll(gone & before));
+  for (uint32_t w = 0; w < wave; ++w) { nth_child += rk.wcount[w]; nth_gone += rk.wcount[kFusedWaves + w]; }
+  if (dead) rk.drow[nth_gone] = elite_row(tid);
+  if (tid < K) rk.srow(nxt)[tid] = child ? rk.frow[slot - K] : elite_row(slot);
+  __syncthreads();
+  if (child) rk.frow[slot - K] = rk.drow[nth_child];
+  if (changed && tid < K) rk.frow[3 * K + tid] = rk.srow(cur)[tid];
+  __syncthreads();
+}
+
 // (Argument block: FusedArgs by value, which starts with its EvolveArgs, see kernel_args.)
 static_assert(offsetof(FusedArgs, ev) == 0, "kernel_args() reads the EvolveArgs at the start of the argument block");
 // kSampled: the remaining work is drawn anew for every generation (Alg. 1, Eq. 7) and the whole
@@ -302,7 +333,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   uint64_t *coins = reinterpret_cast<uint64_t *>(s.coins + static_cast<size_t>(wave_in_block) * a.coin_stride);
   uint32_t *my_draws = rk.draws + wave_in_block * kFusedUnits * 4;
   uint32_t *my_words = rk.words + wave_in_block * kFusedUnits * kLanes;
-  uint64_t *my_keys = rk.ukeys + wave_in_block * kFusedUnits;
   auto draw_unit_parents = [&](uint32_t t) {         // for this wave's children and mutants of generation t
     for (uint32_t k = 0, u = wave; k < kFusedUnits && u < 3 * K; ++k, u += n_waves)
       draw_parents(a, t, u, opaque(lane0), my_draws + 4 * k);
@@ -311,22 +341,28 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     for (uint32_t k = 0, u = wave; k < kFusedUnits && u < 3 * K; ++k, u += n_waves)
       draw_words<kOverGpus>(a, t, u, opaque(lane0), s.prefix, my_words + kLanes * k);
   };
+  uint64_t *my_keys = rk.ukeys + wave_in_block * kFusedUnits;
+  const bool crowd = n_groups >= kCrowd;
+  auto give_up = [&] { if (tid == 0) shared_store(fa.sync + 1, 1u); };
   // Probability sampling.  The draw of a generation takes a long chain of fp64 operations (about
   // 5 us), so it is made two generations ahead, by workgroups that do nothing else (sixteen lanes
-  // per job slot, four slots per wave), and published like the scores, tagged; every computing
-  // workgroup collects the 64 values and rebuilds its LDS copy of the term table from them between
-  // two generations.  n: how many draws these launches have made for the context before.
+  // per job slot, four slots per wave), and published, tagged; every computing
+  // workgroup collects the 64 values while the scores arrive and rebuilds its LDS copy of the term
+  // table from them between two generations.  n: how many draws these launches have made for the context before.
   auto publish_draw = [&](uint32_t t, uint32_t n) {  // called by the kLanes / 4 waves of the drawing workgroups
     uint64_t *xd = fa.xdraw + static_cast<size_t>(n % kDrawBuffers) * kLanes;
     const uint32_t j = 4 * (wave - n_waves) + static_cast<uint32_t>(lane0) / kLanesPerSlot;
     const double Y = draw_remaining(fa.pr, fa.n_slots, a.key0, a.key1, t, j);
     if (lane0 % kLanesPerSlot == 0) shared_store(xd + j, static_cast<uint64_t>(__double_as_longlong(Y)) | draw_tag(n));
   };
-  auto build_terms = [&](uint32_t n) -> bool {       // whole workgroup; false when the polls ran out
+  auto collect_draw = [&](uint32_t n) -> bool {      // into ydraw; false when the polls ran out
     const uint64_t *xd = fa.xdraw + static_cast<size_t>(n % kDrawBuffers) * kLanes;
-    const bool got = gather(xd, kLanes, fa.spin_limit, [&](uint64_t v) { return (v & kTagBit) == draw_tag(n); },
+    return gather(kLanes, fa.spin_limit, [&](uint32_t j) { return xd + j; },
+                            [&](uint32_t, uint64_t v) { return (v & kTagBit) == draw_tag(n); },
                             [&](uint32_t j, uint64_t v) { rk.ydraw[j] = __longlong_as_double(static_cast<long long>(v & ~kTagBit)); });
-    if (__syncthreads_or(got ? 0 : 1)) return false;
+  };
+  auto build_terms = [&] {                           // whole workgroup, from ydraw; between two barriers of its own
+    __syncthreads();
     const uint32_t E = a.term_lds;
     for (uint32_t q = tid; q < E * kLanes; q += kFusedThreads) {
       const uint32_t e = q / kLanes, j = q % kLanes;
@@ -334,7 +370,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
           term_of(rk.model[j], rk.model[kLanes + j], rk.model[2 * kLanes + j], rk.ydraw[j], rk.blexp[j], e);
     }
     __syncthreads();
-    return true;
   };
   if (kSampled && blockIdx.x >= n_groups) {
     // A drawing workgroup: the draws of the first three generations at once, then the draw of
@@ -344,25 +379,26 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
     for (uint32_t g = 0; g < 3 && g < fa.n_generations; ++g) publish_draw(a.t + g + 1, fa.draws_before + g);
     for (uint32_t g = 1; g + 2 < fa.n_generations; ++g) {
       const uint32_t use = fa.generations_before + g - 1;
-      const bool seen = gather(fa.xkeys + static_cast<size_t>(use & 1u) * P + K, 3 * K, fa.spin_limit,
-                               [&](uint64_t v) { return (v & kTagBit) == use_tag(use); }, [&](uint32_t, uint64_t) {});
-      if (__syncthreads_or(seen ? 0 : 1)) {
-        if (tid == 0) shared_store(fa.sync + 1, 1u);
-        return;
-      }
+      const uint64_t *xk = fa.xkeys + static_cast<size_t>(use & 1u) * P + K;
+      const bool seen = gather(3 * K, fa.spin_limit, [&](uint32_t i) { return xk + i; },
+                               [&](uint32_t, uint64_t v) { return (v & kTagBit) == use_tag(use); }, [&](uint32_t, uint64_t) {});
+      if (__syncthreads_or(seen ? 0 : 1)) return give_up();
       publish_draw(a.t + g + 3, fa.draws_before + g + 2);
     }
     return;
   }
   draw_unit_parents(a.t + 1);
   stage_table<1>(a, s, a.term_lds, fa.first_changed != 0, threadIdx.x, blockDim.x);
-  // the state the last selection left: the survivors' rows and scores
+  // the state the last selection left: the survivors' rows and scores, the rows of the units
   for (uint32_t e = tid; e < K; e += kFusedThreads) {
     const uint32_t row = fa.parent_rows[e];
     rk.srow(0)[e] = static_cast<uint16_t>(row);
     rk.skey(0)[e] = static_cast<uint64_t>(__double_as_longlong(a.fit_row[row]));
+    if (a.assigned) rk.frow[3 * K + e] = static_cast<uint16_t>(a.spare[e]);
   }
-  if (tid == 0) rk.misc[0] = rk.misc[1] = 0;
+  if (a.assigned)
+    for (uint32_t u = tid; u < 3 * K; u += kFusedThreads) rk.frow[u] = static_cast<uint16_t>(a.row_of[K + u]);
+  if (tid < 4) rk.misc[tid] = 0;
   if (kSampled && tid < kLanes) {
     rk.model[tid] = a.tab.abl[tid];
     rk.model[kLanes + tid] = a.tab.cc[tid];
@@ -371,56 +407,55 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   }
   __syncthreads();
   draw_unit_words(a.t + 1);
-  list_free_rows(rk, rk.srow(0), P);
-  if (kSampled && !build_terms(fa.draws_before)) {
-    if (tid == 0) shared_store(fa.sync + 1, 1u);
-    return;
+  if (!a.assigned) list_free_rows(rk, rk.srow(0), P);
+  if (kSampled) {
+    const bool got = collect_draw(fa.draws_before);
+    if (__syncthreads_or(got ? 0 : 1)) return give_up();
+    build_terms();
   }
 
   int cur = 0;
   for (uint32_t g = 0; g < fa.n_generations; ++g) {
     const uint32_t t = a.t + g + 1;
-    const uint32_t use = fa.generations_before + g;            // how often the children's exchange buffers have been used
     const bool changed = g == 0 && fa.first_changed != 0;
     const bool new_first = changed && a.new_first != 0;
     const bool last = g + 1 == fa.n_generations;
     const bool all_new = changed || kSampled;                   // every candidate of the pool gets a new score
     const uint32_t units = all_new ? 4 * K : 3 * K;
+    const uint32_t use = fa.generations_before + g;             // how often the children's exchange buffers have been used
     const uint32_t surv_use = fa.changes_before + (kSampled ? g : 0u);   // ... uses of the survivors' exchange buffers
     uint64_t *xk = fa.xkeys + static_cast<size_t>(use & 1u) * P;
     uint64_t *xs = fa.xsurv + static_cast<size_t>(surv_use & 1u) * K;
     // ---- compose, repair, score and store this wave's candidates (at most kFusedUnits of them)
     for (uint32_t k = 0, u = wave; u < units; ++k, u += n_waves) {
       const int lane = opaque(lane0);
-      uint32_t c[1];
+      uint32_t c[1], row;
+      double f;
       if (kSampled && !changed && u >= 3 * K) {
         // the survivor of rank u - 3K keeps genome and row; only its score changes with the draw
-        const uint32_t row = rk.srow(cur)[u - 3 * K];
+        row = rk.srow(cur)[u - 3 * K];
         c[0] = shared_load(a.genes + static_cast<size_t>(row) * kLanes + lane);
-        const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(score<1, 1>(c, s, a.term_lds, lane)));
-        if (lane == 0) {
-          shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + row, bits);
-          my_keys[k] = bits;
-        }
-        continue;
+        f = score<1, 1>(c, s, a.term_lds, lane);
+      } else {
+        f = changed ? compose_unit<false, kOverGpus>(a, t, s, rk.srow(cur), u, new_first, coins, my_draws + 4 * k,
+                                                     my_words + kLanes * k, lane, c)
+                    : compose_unit<true, kOverGpus>(a, t, s, rk.srow(cur), u, false, coins, my_draws + 4 * k,
+                                                    my_words + kLanes * k, lane, c);
+        row = rk.frow[u];
+        shared_store(a.genes + static_cast<size_t>(row) * kLanes + lane, c[0]);
       }
-      const double f = changed ? compose_unit<false, kOverGpus>(a, t, s, rk.srow(cur), u, new_first, coins,
-                                                                       my_draws + 4 * k, my_words + kLanes * k, lane, c)
-                               : compose_unit<true, kOverGpus>(a, t, s, rk.srow(cur), u, false, coins,
-                                                                      my_draws + 4 * k, my_words + kLanes * k, lane, c);
-      const uint32_t row = rk.frow[u];
-      shared_store(a.genes + static_cast<size_t>(row) * kLanes + lane, c[0]);
       if (lane == 0) {
-        // (the score kept with the row goes to the point of coherence too: a row is written by
-        // different workgroups in different generations, and a plain store could linger in one
-        // XCD's cache and be written back over a later one)
         const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(f));
-        shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + row, bits);
         my_keys[k] = bits;
+        // the scores kept with the rows are only looked at after the call (to the point of coherence
+        // like the rest: a plain store could linger in one XCD's cache)
+        if (last) shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + row, bits);
       }
     }
     // the genomes have arrived before their scores are published
+    phase_fence();
     __builtin_amdgcn_s_waitcnt(0);
+    phase_fence();
     if (lane0 == 0)
       for (uint32_t k = 0, u = wave; u < units; ++k, u += n_waves) {
         if (u < 3 * K) shared_store(xk + K + u, my_keys[k] | use_tag(use));
@@ -430,35 +465,38 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       draw_unit_parents(t + 1);
       draw_unit_words(t + 1);
     }
+    bool drawn = true;                               // the draw of the next generation has been out for a while
+    if (kSampled && !last) drawn = collect_draw(fa.draws_before + g + 1);
 
-    // ---- collect the scores; a child that beats the K-th survivor raises a flag (an equal score
-    // loses to the survivor's smaller slot)
+    // ---- collect the scores (children and mutants i < 3K, then, when every score is new, the
+    // survivors); a child that beats the K-th survivor raises a flag (an equal score loses to the
+    // survivor's smaller slot).  The flags of three generations rotate, so that the next one's can be
+    // cleared before the barrier: every wave is past the barrier before, hence past the use of the
+    // flag of two generations ago.
     const uint64_t thresh = all_new ? 0ull : rk.skey(cur)[K - 1];
-    bool ok = gather2(xk + K, 3 * K, [&](uint64_t v) { return (v & kTagBit) == use_tag(use); },
-                      [&](uint32_t i, uint64_t v) {
-                        rk.ckey[K + i] = v & ~kTagBit;
-                        if ((v & ~kTagBit) < thresh) rk.misc[1] = 1;
-                      },
-                      xs, all_new ? K : 0u, [&](uint64_t v) { return (v & kTagBit) == use_tag(surv_use); },
-                      [&](uint32_t i, uint64_t v) { rk.ckey[i] = v & ~kTagBit; }, fa.spin_limit);
-    if (__syncthreads_or(ok ? 0 : 1)) {              // a poll ran out
-      if (tid == 0) shared_store(fa.sync + 1, 1u);
-      return;
-    }
+    if (crowd) { if (all_new) __builtin_amdgcn_s_sleep(48); else __builtin_amdgcn_s_sleep(8); }
+    const bool ok = gather(all_new ? P : 3 * K, fa.spin_limit,
+                           [&](uint32_t i) { return i < 3 * K ? xk + K + i : xs + (i - 3 * K); },
+                           [&](uint32_t i, uint64_t v) { return (v & kTagBit) == (i < 3 * K ? use_tag(use) : use_tag(surv_use)); },
+                           [&](uint32_t i, uint64_t v) {
+                             const uint64_t key = v & ~kTagBit;
+                             rk.ckey[i < 3 * K ? K + i : i - 3 * K] = key;
+                             if (key < thresh) rk.misc[1 + g % 3] = 1;
+                           });
+    if (tid == 0) rk.misc[0] = rk.misc[1 + (g + 1) % 3] = 0;
+    if (__syncthreads_or(ok && drawn ? 0 : 1)) return give_up();
+    const bool any = rk.misc[1 + g % 3] != 0;
 
     // every wave of this workgroup is done with the term table of this generation: the next one's
-    if (kSampled && !last && !build_terms(fa.draws_before + g + 1)) {
-      if (tid == 0) shared_store(fa.sync + 1, 1u);
-      return;
-    }
+    if (kSampled && !last) build_terms();
 
     // ---- rank the pool
-    bool moved = true;                               // the set of survivors (hence the free rows) changes
-    bool by_counting = all_new;                      // rank the whole pool, a share per workgroup
-    if (!all_new && rk.misc[1] == 0) {
-      // no child beats the K-th survivor: same survivors, same order, same free rows
+    int nxt = cur ^ 1;
+    bool whole = all_new;                            // rank the whole pool, a share per workgroup
+    if (!all_new && !any) {
+      // no child beats the K-th survivor: same survivors, same order, same rows
       if (last && blockIdx.x != 0) return;
-      moved = false;
+      nxt = cur;
       if (last) for (uint32_t e = tid; e < K; e += kFusedThreads) rk.nsel[e] = static_cast<uint16_t>(e);
     } else if (!all_new) {
       // list the children that beat the K-th survivor
@@ -470,7 +508,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
         uint32_t at = 0;
         if (lane0 == 0 && mask != 0) at = atomicAdd(&rk.misc[0], static_cast<uint32_t>(__popcll(mask)));
         at = __builtin_amdgcn_readfirstlane(at) + static_cast<uint32_t>(__popcll(mask & ((1ull << lane0) - 1ull)));
-        if (beats) { rk.mkey[at] = key; rk.mslot[at] = K + i; }
+        if (beats) { rk.lkey[at] = key; rk.lslot[at] = static_cast<uint16_t>(K + i); }
       }
       __syncthreads();
       const uint32_t M = rk.misc[0];
@@ -478,7 +516,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       // call leaves); the others stay for their share of a ranking by counting, if there is one
       if (last && blockIdx.x != 0 && M <= kMergeMax) return;
       if (M > kMergeMax) {
-        by_counting = true;
+        whole = true;
         for (uint32_t e = tid; e < K; e += kFusedThreads) rk.ckey[e] = rk.skey(cur)[e];
       } else {
         // rank of each such child among them, the comparisons dealt to all threads
@@ -488,18 +526,18 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
         {
           const uint32_t i = tid % Mp, from = (tid / Mp) * per, to = min(from + per, M);
           if (i < M) {
-            const uint64_t key = rk.mkey[i];
-            const uint32_t slot = rk.mslot[i];
+            const uint64_t key = rk.lkey[i];
+            const uint32_t slot = rk.lslot[i];
             uint32_t n = 0;
-            for (uint32_t j = from; j < to; ++j) n += key_less(rk.mkey[j], rk.mslot[j], key, slot) ? 1u : 0u;
+            for (uint32_t j = from; j < to; ++j) n += key_less(rk.lkey[j], rk.lslot[j], key, slot) ? 1u : 0u;
             if (n) atomicAdd(&rk.below[i], n);
           }
         }
         __syncthreads();
-        if (tid < M) { rk.okey[rk.below[tid]] = rk.mkey[tid]; rk.oslot[rk.below[tid]] = rk.mslot[tid]; }
+        if (tid < M) { rk.okey[rk.below[tid]] = rk.lkey[tid]; rk.oslot[rk.below[tid]] = rk.lslot[tid]; }
         __syncthreads();
-        const int nxt = cur ^ 1;
-        // child at position b: new rank = b + survivors with a score <= its own
+        // child at position b: new rank = b + survivors with a score <= its own; its slot takes the
+        // row of the last survivor but b, which drops out
         if (tid < M) {
           const uint64_t key = rk.okey[tid];
           uint32_t lo = 0, hi = K;
@@ -507,11 +545,12 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
             const uint32_t mid = (lo + hi) >> 1;
             if (rk.skey(cur)[mid] <= key) lo = mid + 1; else hi = mid;
           }
-          const uint32_t rank = tid + lo;
+          const uint32_t rank = tid + lo, u = rk.oslot[tid] - K;
           if (rank < K) {
             rk.skey(nxt)[rank] = key;
-            rk.srow(nxt)[rank] = rk.frow[rk.oslot[tid] - K];
-            rk.nsel[rank] = static_cast<uint16_t>(rk.oslot[tid]);
+            rk.srow(nxt)[rank] = rk.frow[u];
+            rk.nsel[rank] = rk.oslot[tid];
+            rk.frow[u] = rk.srow(cur)[K - 1 - tid];
           }
         }
         // survivor e: new rank = e + such children with a strictly smaller score
@@ -530,12 +569,12 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
           }
         }
       }
-      __syncthreads();
-      if (tid == 0) rk.misc[0] = rk.misc[1] = 0;     // for the next generation (read again only after further barriers)
     }
-    if (by_counting) {
+    if (whole) {
       // ckey holds the whole pool's scores by slot.  This workgroup ranks its share of the slots
       // (rank = candidates below in (score, slot) order), publishes the ranks, collects all.
+      // (Ranking all of them in every workgroup's LDS, by a sample sort there, takes 15 to 25 us at 2048
+      // candidates where this takes 5: equal scores of neighbouring slots queue up on its counters.)
       const uint32_t lo = static_cast<uint32_t>(static_cast<uint64_t>(P) * blockIdx.x / n_groups);
       const uint32_t hi = static_cast<uint32_t>(static_cast<uint64_t>(P) * (blockIdx.x + 1) / n_groups);
       const uint32_t ns = hi - lo, parts = ns ? kFusedThreads / ns : 0u;   // 0 < parts: ns <= kMergeMax
@@ -563,41 +602,36 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       const uint64_t stamp = static_cast<uint64_t>(use + 1u) << 32;     // no generation has number 0
       if (tid < ns) shared_store(fa.xrank + lo + tid, stamp | rk.below[tid]);
       if (last && blockIdx.x != 0) return;
-      const int nxt = cur ^ 1;
-      ok = gather(fa.xrank, P, fa.spin_limit, [&](uint64_t v) { return (v >> 32) == (stamp >> 32); },
-                  [&](uint32_t p, uint64_t v) {
-                    const uint32_t rank = static_cast<uint32_t>(v);
-                    if (rank < K) {
-                      rk.skey(nxt)[rank] = rk.ckey[p];
-                      rk.srow(nxt)[rank] = static_cast<uint16_t>(row_of_slot(rk, cur, p, K, changed));
-                      rk.nsel[rank] = static_cast<uint16_t>(p);
-                    }
-                  });
-      if (__syncthreads_or(ok ? 0 : 1)) {
-        if (tid == 0) shared_store(fa.sync + 1, 1u);
-        return;
-      }
+      if (crowd) __builtin_amdgcn_s_sleep(16);
+      const bool ranked = gather(P, fa.spin_limit, [&](uint32_t p) { return fa.xrank + p; },
+                                 [&](uint32_t, uint64_t v) { return (v >> 32) == (stamp >> 32); },
+                                 [&](uint32_t p, uint64_t v) {
+                                   const uint32_t rank = static_cast<uint32_t>(v);
+                                   if (rank < K) {
+                                     rk.skey(nxt)[rank] = rk.ckey[p];
+                                     rk.nsel[rank] = static_cast<uint16_t>(p);
+                                   }
+                                 });
+      if (__syncthreads_or(ranked ? 0 : 1)) return give_up();
+      assign_rows(rk, P, cur, nxt, changed);
+    } else if (any) {
+      __syncthreads();
     }
-    const int nxt = moved ? cur ^ 1 : cur;
     if (last) {
-      // the state the next call (of either kind) starts from
-      for (uint32_t p = tid; p < P; p += kFusedThreads) fa.row_of[p] = row_of_slot(rk, cur, p, K, changed);
+      // the state the next call (of either kind) starts from.  (A call runs more than one generation,
+      // so the last one is never the first under a new table: the pool's first K slots are survivors.)
       for (uint32_t e = tid; e < K; e += kFusedThreads) {
+        const uint32_t row = rk.srow(cur)[e];
+        a.row_of[e] = row;
+        if (!all_new) shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + row, rk.skey(cur)[e]);
         fa.parent_rows[e] = rk.srow(nxt)[e];
         fa.sel[e] = rk.nsel[e];
+        a.spare[e] = rk.frow[3 * K + e];
       }
-      const uint32_t words = (P + K + 31) / 32;
-      __syncthreads();
-      for (uint32_t w = tid; w < words; w += kFusedThreads) rk.occ[w] = 0;
-      __syncthreads();
-      for (uint32_t e = tid; e < K; e += kFusedThreads)
-        atomicOr(&rk.occ[rk.srow(nxt)[e] >> 5], 1u << (rk.srow(nxt)[e] & 31u));
-      __syncthreads();
-      for (uint32_t w = tid; w < words; w += kFusedThreads) fa.occupied[w] = rk.occ[w];
+      for (uint32_t u = tid; u < 3 * K; u += kFusedThreads) a.row_of[K + u] = rk.frow[u];
       if (kSampled && tid < kLanes) fa.y_out[tid] = rk.ydraw[tid];   // the remaining work the last generation was scored with
       return;
     }
-    if (moved) list_free_rows(rk, rk.srow(nxt), P);
     cur = nxt;
   }
 }
@@ -622,12 +656,19 @@ size_t fused_exchange_bytes(uint32_t P) {             // xkeys [2][P], xsurv [2]
   return (static_cast<size_t>(2) * P + 2 * (P / 4) + P + kDrawBuffers * kLanes) * 8;
 }
 
+void fused_exchange(uint64_t *base, uint32_t P, FusedArgs &fa) {
+  fa.xkeys = base;
+  fa.xsurv = fa.xkeys + static_cast<size_t>(2) * P;
+  fa.xrank = fa.xsurv + static_cast<size_t>(2) * (P / 4);
+  fa.xdraw = fa.xrank + P;
+}
+
 hipError_t launch_fused(const FusedArgs &args, hipStream_t stream) {
   FusedArgs fa = args;
-  if (fa.ev.Jp != static_cast<uint32_t>(kLanes) || fa.ev.P > kFusedMaxPool || fa.ev.P < 4 || fa.n_generations == 0)
+  if (fa.ev.Jp != static_cast<uint32_t>(kLanes) || fa.ev.P > kFusedMaxPool || fa.ev.P < 4 || fa.n_generations < 2)
     return hipErrorInvalidValue;
   const uint32_t n_wg = fused_workgroups(fa.ev.P, fa.sampled != 0);
-  // every wave keeps its units of a generation in registers, and a workgroup's share of a ranking by counting fits its counters
+  // every wave keeps its units of a generation in LDS, and a workgroup's share of a ranking by counting fits its counters
   if ((fa.ev.P + n_wg * kFusedWaves - 1) / (n_wg * kFusedWaves) > kFusedUnits || (fa.ev.P + n_wg - 1) / n_wg > kMergeMax)
     return hipErrorInvalidValue;
   fa.ev.bk.nb = 0;
