@@ -169,7 +169,10 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
           }
         }
         if (equal > 1)
-          for (uint32_t q = 0; q < n; ++q) below += (sk[q] == key && si[q] < id) ? 1u : 0u;
+          for (uint32_t q = 0; q < npad; q += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) below += (sk[q + u] == key && si[q + u] < id) ? 1u : 0u;
+          }
       }
       uint32_t lo = 0, hi = ne;
       while (lo < hi) {
@@ -313,11 +316,25 @@ __device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const d
     uint32_t n_below = 0;
     for (uint32_t tile = 0; tile < places; tile += kBucketLds) {
       __syncthreads();
-      for (uint32_t q = tid; q < static_cast<uint32_t>(kBucketLds); q += kThreads) record(tile + q, sh.sk[q], sh.si[q]);
+      // (loads first, then the stores; the comparisons in steps of eight: one at a time, each waited for
+      // its LDS read, and a bucket of 20000 took 300 us)
+      constexpr int kPer = kBucketLds / kThreads;
+      uint64_t loaded[kPer];
+      uint32_t ids[kPer];
+#pragma unroll
+      for (int v = 0; v < kPer; ++v) record(tile + tid + v * kThreads, loaded[v], ids[v]);
+#pragma unroll
+      for (int v = 0; v < kPer; ++v) { sh.sk[tid + v * kThreads] = loaded[v]; sh.si[tid + v * kThreads] = ids[v]; }
       __syncthreads();
-      const uint32_t count = min(places - tile, static_cast<uint32_t>(kBucketLds));
+      const uint32_t count = min(places - tile, static_cast<uint32_t>(kBucketLds));   // what lies beyond is never below
       if (offspring || survivor)
-        for (uint32_t q = part; q < count; q += parts) n_below += key_less(sh.sk[q], sh.si[q], key, id) ? 1u : 0u;
+        for (uint32_t q = part; q < count; q += 8 * parts) {
+#pragma unroll
+          for (uint32_t v = 0; v < 8; ++v) {
+            const uint32_t at = min(q + v * parts, static_cast<uint32_t>(kBucketLds) - 1);
+            n_below += q + v * parts < static_cast<uint32_t>(kBucketLds) && key_less(sh.sk[at], sh.si[at], key, id) ? 1u : 0u;
+          }
+        }
     }
     sh.below[tid] = 0;
     __syncthreads();
@@ -432,7 +449,10 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
             }
           }
           if (equal > 1)                             // shares its score: the slots decide
-            for (uint32_t q = 0; q < n; ++q) below += (sh.sk[q] == my_key && sh.si[q] < my_idx) ? 1u : 0u;
+            for (uint32_t q = 0; q < npad; q += 8) {
+#pragma unroll
+              for (int v = 0; v < 8; ++v) below += (sh.sk[q + v] == my_key && sh.si[q + v] < my_idx) ? 1u : 0u;
+            }
           uint32_t lo = 0, hi = ne;
           while (lo < hi) {
             const uint32_t mid = (lo + hi) >> 1;
