@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published peak
 
 # HBM bytes per evolve launch on the stress workload from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (see profiles/), valid only for the kernel source with this hash.
-MEASURED_TRAFFIC = {"source_sha256": "0b6ef20e102acdea716dafa2501ee9f1b0e5340947bc7b4bf13a3ae8b2a30dbe", "bytes_per_launch": 802626465}
+MEASURED_TRAFFIC = {"source_sha256": "8016cd8150f3935956a8575fc9738fc5fb52fe141f7ec4dad74ef6f57b188a60", "bytes_per_launch": 201907620}
 
 
 def evolve_source_hash() -> str:
