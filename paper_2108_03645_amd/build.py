@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libones.so")
-# (source, object, extra flags); the evolve kernel is built once per group of eight row counts
+# (source, object, extra flags); the evolve kernel is built once per group of two word counts (eight rows of job slots)
 UNITS = [("ones_api.hip", "ones_api.o", []), ("ones_select.hip", "ones_select.o", []),
          ("ones_sample.hip", "ones_sample.o", []), ("ones_fused.hip", "ones_fused.o", [])] + [
     ("ones_evolve.hip", f"ones_evolve_{g}.o", [f"-DONES_ROW_GROUP={g}"]) for g in range(4)]
