@@ -157,11 +157,17 @@ __device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t yes, uint32_t n
 __device__ __forceinline__ uint32_t max_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), x, y); }
 __device__ __forceinline__ uint32_t min_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), y, x); }
 
-// acc + the GPUs of the four codes.  Codes up to 7 (at most 64 GPUs per job, the usual case) become
-// counts by one byte look-up; a table with larger jobs (kWide) shifts them one by one.
-template <bool kWide>
+// What the words of codes may hold, and so how their GPUs are counted.  kNarrow: codes up to 7 (no job
+// of the table takes more than 64 GPUs, the usual case; wide_table decides), counted by one byte
+// look-up, which is wrong for any larger code.  kWide: any code, shifted one by one.  kOneRow: one row
+// of job slots, so a word holds a single gene, of any code.
+enum Genes { kNarrow, kWide, kOneRow };
+
+// acc + the GPUs of a word's codes.
+template <Genes kGenes>
 __device__ __forceinline__ uint32_t add_gpus(uint32_t codes, uint32_t acc) {
-  if (!kWide) return __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x40201008u, 0x04020100u, codes), 0u, acc);
+  if (kGenes == kOneRow) return acc + ((1u << codes) >> 1);
+  if (kGenes == kNarrow) return __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x40201008u, 0x04020100u, codes), 0u, acc);
 #pragma unroll
   for (int k = 0; k < 4; ++k) acc += (1u << ((codes >> (8 * k)) & 31u)) >> 1;
   return acc;
@@ -495,21 +501,18 @@ __device__ __forceinline__ uint32_t rows_before(uint32_t ir, int q) {
 // A lane's asks lie in one stretch of that order (lane lr's in two), so with the lanes' sums scanned
 // every lane knows whether its stretch fits as a whole, and at most one stretch is cut: its rows
 // are laid out over the lanes, a row each, scanned, and the outcome is written back to the lane.
-// kOneRow: a single row of job slots, so a stretch is a single ask and nothing is cut.
-template <int Q, bool kWide, bool kOneRow>
+// With kOneRow a stretch is a single ask and nothing is cut.
+template <int Q, Genes kGenes>
 __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32_t (&m)[Q], uint32_t limit, uint32_t lr,
                                                   uint32_t ir, int lane) {
+  static_assert(kGenes != kOneRow || Q == 1, "one row of job slots is one word");
   uint32_t run = 0;
-  if (kOneRow) {
-    run = (1u << v[0]) >> 1;
-  } else {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) run = add_gpus<kWide>(v[q], run);
-  }
+  for (int q = 0; q < Q; ++q) run = add_gpus<kGenes>(v[q], run);
   const uint32_t incl = wave_inclusive_scan(run);
   const uint32_t total = __builtin_amdgcn_readlane(incl, kLanes - 1);
   if (total <= limit) return total;                // everything fits
-  if (kOneRow) {
+  if (kGenes == kOneRow) {
     const uint32_t base = __builtin_amdgcn_readlane(incl - run, lr);             // asks visited after the wrap
     const uint32_t end = incl - base + (static_cast<uint32_t>(lane) < lr ? total : 0u);
     const bool fits = end <= limit;
@@ -522,7 +525,7 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
   uint32_t pre = 0;
 #pragma unroll
   for (int q = 0; q < Q; ++q)
-    if (ir > 4u * q) pre = add_gpus<kWide>(v[q] & rows_before(ir, q), pre);
+    if (ir > 4u * q) pre = add_gpus<kGenes>(v[q] & rows_before(ir, q), pre);
   const uint32_t skipped = __builtin_amdgcn_readlane(pre, lr);                   // visited last, after the wrap
   const uint32_t base = __builtin_amdgcn_readlane(incl - run, lr) + skipped;     // asks visited after the wrap
   const uint32_t end = incl - base + (static_cast<uint32_t>(lane) < lr ? total : 0u);
@@ -578,7 +581,7 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
 // capacity lasts, in visiting order, and the others are admitted to what is left: in visiting order
 // too, or, with time_rank (position of every job in ascending order of executed time), least executed
 // time first, so that the room is taken from the jobs with the largest T_processed.
-template <int Q, bool kWide, bool kArrivals, bool kOneRow = false>
+template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t G, uint32_t lr, uint32_t ir, int lane,
                                        uint32_t Jp, const uint32_t *time_rank) {
   uint32_t used;
@@ -590,7 +593,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
       v[q] = fresh[q] = s.start[q * kLanes + lane] & arrived;
       c[q] &= ~arrived;
     }
-    const uint32_t taken = accept_prefix<Q, kWide, kOneRow>(v, fresh, G, lr, ir, lane);
+    const uint32_t taken = accept_prefix<Q, kGenes>(v, fresh, G, lr, ir, lane);
     if (time_rank) {
       // The running sum over the ranks never decreases, so the admitted jobs are the ranks below
       // some bound: the largest n whose first n ranks ask for no more than what is left.
@@ -611,7 +614,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
         uint32_t sum = 0;
         phase_fence();                                                     // the ranks are not kept in registers
 #pragma unroll
-        for (int q = 0; q < Q; ++q) sum = add_gpus<kWide>(c[q] & ranked_below(q, mid), sum);
+        for (int q = 0; q < Q; ++q) sum = add_gpus<kGenes>(c[q] & ranked_below(q, mid), sum);
         sum = wave_sum(sum);
         if (sum <= cap) { lo = mid; fit = sum; } else { hi = mid - 1; }
       }
@@ -621,7 +624,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
     } else {
 #pragma unroll
       for (int q = 0; q < Q; ++q) v[q] = c[q];
-      used = taken + accept_prefix<Q, kWide, kOneRow>(v, c, G - taken, lr, ir, lane);
+      used = taken + accept_prefix<Q, kGenes>(v, c, G - taken, lr, ir, lane);
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) c[q] |= fresh[q];
@@ -630,7 +633,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
     uint32_t v[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) v[q] = c[q];
-    used = accept_prefix<Q, kWide, kOneRow>(v, c, G, lr, ir, lane);
+    used = accept_prefix<Q, kGenes>(v, c, G, lr, ir, lane);
   }
   // fill: a waiting job asks for its starting GPUs, a running one below its limit asks to double,
   // both only if the GPUs are there (a power of two fits when its code is not above that of the idle
@@ -650,7 +653,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
       m[q] = spread_tops(((c[q] ^ s.most[w]) + kSevens) & (fitting - cost));   // below its limit, and the GPUs are there
       v[q] = cost & m[q];
     }
-    const uint32_t got = accept_prefix<Q, kWide, kOneRow>(v, m, idle, lr, ir, lane);
+    const uint32_t got = accept_prefix<Q, kGenes>(v, m, idle, lr, ir, lane);
     if (got == 0 || got > idle) break;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {

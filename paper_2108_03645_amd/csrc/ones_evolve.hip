@@ -23,10 +23,10 @@ constexpr int kGroupFirst = 2 * ONES_ROW_GROUP + 1;   // words per lane kGroupFi
 // ----------------------------------------------------------------- kernels ---------
 template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : 8; };
 
-template <int Q, bool kWide, bool kArrivals>
+template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t lr, uint32_t ir,
                                          uint32_t (&c)[Q], int lane) {
-  repair<Q, kWide, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank);
+  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank);
   phase_fence();
   const double f = score<Q>(c, s, a.term_lds, lane);
   phase_fence();
@@ -39,7 +39,7 @@ __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uin
 
 // Initial population G_0: every gene uniform over {waiting, bmin..bmax}.
 // (Argument block: one EvolveArgs by value, see kernel_args.)
-template <int Q, bool kWide>
+template <int Q, Genes kGenes>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride);
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
       c[q] = codes_of_draws(s, q * kLanes + lane, k);
     }
     phase_fence();
-    const double f = finish<Q, kWide, false>(a, s, p, r / R, r % R, c, lane);   // slot p starts in row p
+    const double f = finish<Q, kGenes, false>(a, s, p, r / R, r % R, c, lane);   // slot p starts in row p
     note_slot_score(p, f, lane);
     if (lane == 0) a.row_of[p] = p;
   }
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
 // jobs that arrived with it are served first.  kOverGpus: the uniform crossover scans the GPUs instead of the jobs.
 // (Argument block: one EvolveArgs by value, see kernel_args.)
 enum Table { kSame, kChanged, kArrivals };
-template <int Q, Table kTable, bool kOverGpus, bool kWide>
+template <int Q, Table kTable, bool kOverGpus, Genes kGenes>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(EvolveArgs a) {
   constexpr bool kSameTable = kTable == kSame;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     phase_fence();
     for (;;) {
       const uint32_t p = slot_at(ra, n, i);
-      const double f = finish<Q, kWide, kTable == kArrivals>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane);
+      const double f = finish<Q, kGenes, kTable == kArrivals>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane);
       if (kSameTable && a.bk.nb != 0) drop_in_bucket(s, p, f, lane); else note_slot_score(p, f, lane);
       if (--children == 0) break;
       phase_fence();
@@ -266,23 +266,23 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   return hipGetLastError();
 }
 
-template <int Q, bool kWide>
+template <int Q, Genes kGenes>
 hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
   constexpr int kWaves = Shape<Q>::kWaves;
-  if (a.t == 0) return launch_persistent(init_kernel<Q, kWide>, a, Q, kWaves, a.P, a.P, n_cus, s);
+  if (a.t == 0) return launch_persistent(init_kernel<Q, kGenes>, a, Q, kWaves, a.P, a.P, n_cus, s);
   const uint32_t items = (!same_table || a.rescore ? 3 : 2) * a.K;       // a share of the ranks each
   const Table table = same_table ? kSame : a.new_first ? kArrivals : kChanged;
   auto launch = [&](auto kernel) { return launch_persistent(kernel, a, Q, kWaves, items, a.K, n_cus, s); };
   switch (table) {
-    case kSame: return a.per_gpu ? launch(evolve_kernel<Q, kSame, true, kWide>) : launch(evolve_kernel<Q, kSame, false, kWide>);
-    case kChanged: return a.per_gpu ? launch(evolve_kernel<Q, kChanged, true, kWide>) : launch(evolve_kernel<Q, kChanged, false, kWide>);
-    default: return a.per_gpu ? launch(evolve_kernel<Q, kArrivals, true, kWide>) : launch(evolve_kernel<Q, kArrivals, false, kWide>);
+    case kSame: return a.per_gpu ? launch(evolve_kernel<Q, kSame, true, kGenes>) : launch(evolve_kernel<Q, kSame, false, kGenes>);
+    case kChanged: return a.per_gpu ? launch(evolve_kernel<Q, kChanged, true, kGenes>) : launch(evolve_kernel<Q, kChanged, false, kGenes>);
+    default: return a.per_gpu ? launch(evolve_kernel<Q, kArrivals, true, kGenes>) : launch(evolve_kernel<Q, kArrivals, false, kGenes>);
   }
 }
 
 template <int Q>
 hipError_t launch_width(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
-  return wide_table(a.tab) ? launch_words<Q, true>(a, same_table, n_cus, s) : launch_words<Q, false>(a, same_table, n_cus, s);
+  return wide_table(a.tab) ? launch_words<Q, kWide>(a, same_table, n_cus, s) : launch_words<Q, kNarrow>(a, same_table, n_cus, s);
 }
 
 }  // namespace

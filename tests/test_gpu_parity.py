@@ -1048,3 +1048,48 @@ def test_gpu_counts_and_tables_between_generations(ones, ref, n_slots, n_gpus, p
             assert_same_state(gpu, cpu, tag)
         assert all(np.array_equal(x, y) for x, y in zip(gpu.placement(), cpu.placement())), tag
     gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,widest", [(8, 512, 64, 9), (39, 2100, 516, 8), (64, 4096, 2048, 20)])
+@pytest.mark.parametrize("times", ["none", "ties", "distinct"])
+@pytest.mark.parametrize("per_gpu", [False, True])
+def test_single_launch_serves_arrivals_among_jobs_on_many_gpus(ones, ref, n_slots, n_gpus, pop, widest, times, per_gpu):
+    """Calls of three and more generations right after a table with arrivals, whose jobs take up to
+    2^widest GPUs: 128 and more, counts that a byte look-up for up to 64 does not know, must be counted
+    rightly where the others are admitted to what the arrivals leave.  No candidate may hold more GPUs
+    than there are."""
+    rng = np.random.default_rng(n_slots)
+    say(f"[parity] arrivals among wide jobs: G={n_gpus} slots={n_slots} P={pop} widest=2^{widest} times={times} per_gpu={per_gpu}")
+
+    def table(jobs=None):
+        new = random_jobs(rng, n_slots, inactive_frac=0.1)
+        new.gpu_max_batch[:] = 16
+        new.bmax = (16 << rng.integers(min(7, widest), widest + 1, n_slots)).astype(np.int32)
+        new.bmin = (16 << rng.integers(0, 3, n_slots)).astype(np.int32)
+        if jobs is not None:
+            new.job_id = np.where(rng.random(n_slots) < 0.2, jobs.job_id + 1000, jobs.job_id)
+        return new
+
+    jobs, widest_held = table(), 0
+    gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=n_slots), jobs) for make in (ones.Search, ref.RefSearch))
+    for s in (gpu, cpu):
+        s.set_new_jobs_first(True)
+        s.set_crossover(per_gpu=per_gpu)
+    for step, gens in enumerate((3, 5, 3, 4)):
+        jobs = table(jobs)
+        t_processed = rng.integers(0, 4, n_slots) * 60.0 if times == "ties" else rng.permutation(n_slots) * 1.5
+        for s in (gpu, cpu):
+            s.set_jobs(jobs)
+            if times != "none":
+                s.set_processed_time(t_processed)
+            if step == 2:
+                s.set_progress(*W.progress(n_slots, seed=n_slots))
+            s.generation(gens)
+        assert_same_state(gpu, cpu, f"step {step}")
+        genes = gpu.export()[0][:, :n_slots]
+        held = np.where(genes > 0, np.maximum(1, genes // 16), 0)
+        assert (held.sum(axis=1) <= n_gpus).all(), f"step {step}: a candidate holds more GPUs than there are"
+        widest_held = max(widest_held, int(held.max()))
+        assert all(np.array_equal(x, y) for x, y in zip(gpu.placement(), cpu.placement())), f"step {step}"
+    assert widest_held >= 128
+    gpu.close(); cpu.close()
