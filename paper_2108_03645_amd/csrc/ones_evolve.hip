@@ -130,7 +130,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
         if (p < K) d.ra = d.rb = p;                              // a survivor is its own parent
         s.drawn[i] = pack_draw(min(a.parent_row[d.ra], a.P + K - 1), min(a.parent_row[d.rb], a.P + K - 1), d.r, R);
       }
-      if (assigned) s.rows[i] = checked_row(s, row, a.P + K);
+      if (assigned) s.rows[i] = row;
     }
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
@@ -148,11 +148,11 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   __syncthreads();
   // record what the slots and ranks got
   for (uint32_t i = threadIdx.x; i < 4 * n; i += blockDim.x) {
-    const uint32_t p = slot_at(ra, n, i);
+    const uint32_t p = slot_at(ra, n, i), row = checked_row(s, s.rows[i], a.P + K);
     if (i < 3 * n) {
-      if (!assigned) a.row_of[p] = checked_row(s, s.rows[i], a.P + K);
+      if (!assigned) a.row_of[p] = row;
     } else {
-      const uint32_t row = checked_row(s, s.rows[i], a.P + K), old = a.parent_row[p];
+      const uint32_t old = checked_row(s, a.parent_row[p], a.P + K);
       a.row_of[p] = kSameTable ? old : row;
       if (!kSameTable) a.spare[p] = old;
       else if (!assigned) a.spare[p] = row;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     if (kSameTable && idx >= 2 * n) {
       // the remaining work was drawn anew: the survivor of this rank keeps its genome and row
       // and only gets its score under the new draw
-      const uint32_t rank = ra + (idx - 2 * n), row = a.parent_row[rank];
+      const uint32_t rank = ra + (idx - 2 * n), row = min(a.parent_row[rank], a.P + K - 1);
       uint32_t c[Q];
       load_genes<Q>(a.genes, row, lane, c);
       const double f = score<Q>(c, s, a.term_lds, lane);
