@@ -129,7 +129,6 @@ constexpr int kBucketThreads = 256;
 constexpr int kBucketLds = 2048;      // offspring of one bucket that are sorted in LDS
 constexpr int kBucketCount = kManyInBucket;   // up to here offspring are ranked by counting, not sorted
 constexpr int kBucketElites = 1025;   // survivors of one bucket: at most ceil(2^18 / 256) + 1
-constexpr uint32_t kFewCrowded = 8;   // so many buckets above kBucketCount are ranked by all workgroups together
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 #pragma unroll
@@ -244,6 +243,7 @@ __device__ __forceinline__ void gather_bucket(uint64_t *dk, uint32_t *di, const 
 }
 
 // What the threads of a workgroup that handles buckets share.
+constexpr uint32_t kFewCrowded = 8;
 template <int kThreads>
 struct BucketShared {
   uint64_t sk[kBucketLds];
@@ -251,18 +251,80 @@ struct BucketShared {
   uint64_t ek[kBucketElites];
   uint32_t red[kThreads / kLanes];
   uint32_t below[kThreads];
-  uint32_t crowded[kMaxBuckets];       // the buckets above kBucketCount
-  uint32_t spill_cursor, n_crowded;
+  uint32_t spill_cursor;
+  uint32_t n_many, n_teams;            // buckets above kBucketCount; crowded ones that are dealt to teams
+  uint32_t counted[kFewCrowded], n_counted;   // ... that all workgroups rank by counting
+  uint32_t helps, member, team;        // the crowded bucket this workgroup helps to rank, as number `member` of `team`
+  uint32_t valid, smaller, inside;     // of that bucket: sample points; records below and inside a range
 };
 
-// A crowded bucket, ranked by all workgroups of the launch together: each takes an equal share of
-// the bucket's records (places of its storage, then of the spill list, whose records of other
-// buckets count for nothing) and ranks it by counting against all of them, a tile at a time; the
-// bucket's own workgroup ranks its survivors too.  Where children crowd, be it because a pool is
-// full of copies of one genome or because nearly all children beat its best members, one workgroup
-// alone took 0.2 to 1.8 ms (sorting network in global memory) for what takes all of them 10 to 50 us.
+// Which buckets are crowded, and how they are ranked.  A bucket is crowded when it holds more than a
+// workgroup sorts in LDS, or more than it ranks by counting while at most kFewCrowded buckets do (the
+// LDS sort of 2048 takes one workgroup 20 us; with many such buckets the workgroups are all busy anyway).
+// A few crowded buckets are ranked by counting, by all workgroups together, one after the other, as long
+// as that takes a thread no more than kCountedMost comparisons per bucket; the others are dealt to teams.
+// (An epoch of 10 generations, pool of 65536 with crowded buckets of up to 40000: 1744 us when all are
+// counted, 1531 with a limit of 2048, 1424 with 512; a pool of 4096 with buckets of up to 1500: 280 us with any
+// of these limits, 345 when all are dealt to teams.)
+constexpr uint64_t kCountedMost = 512;
+struct Crowd {
+  uint32_t many;       // most offspring of a bucket that is not crowded
+  uint64_t counted;    // most comparisons of a bucket ranked by counting
+  uint32_t spilled;    // records in the spill list
+  // places where the records of a bucket of n are: its own storage, and all of the spill list if that is full
+  __device__ __forceinline__ uint32_t places(const BucketArgs &bk, uint32_t n) const { return n > bk.seg ? bk.seg + spilled : n; }
+  __device__ __forceinline__ bool by_counting(const BucketArgs &bk, uint32_t n) const {
+    const uint64_t p = places(bk, n);
+    return n > many && p * p <= counted;
+  }
+  __device__ __forceinline__ bool by_team(const BucketArgs &bk, uint32_t n) const { return n > many && !by_counting(bk, n); }
+};
+
+// Deals the workgroups to the n_teams crowded buckets that are ranked by teams: one each, the others by
+// the number of records; a team's workgroups are consecutive.  Every workgroup computes the same shares
+// and notes its own in sh (team 0: left over).  Whole workgroup; ends with a barrier.
+template <int kThreads>
+__device__ __forceinline__ void join_team(BucketShared<kThreads> &sh, const BucketArgs &bk, const Crowd &crowd, uint32_t n_teams) {
+  const uint32_t tid = threadIdx.x, nb = bk.nb;
+  auto weight_of = [&](uint32_t c) {
+    const uint32_t n = c < nb ? bk.count[c] : 0u;
+    return crowd.by_team(bk, n) ? n : 0u;
+  };
+  if (tid == 0) sh.inside = sh.team = 0;
+  __syncthreads();
+  uint32_t w = 0;
+  for (uint32_t c = tid; c < nb; c += kThreads) w += weight_of(c);
+  if (w != 0) atomicAdd(&sh.inside, w);              // at most a pool, 2^20
+  __syncthreads();
+  const uint32_t all = sh.inside;
+  uint32_t before = 0;                               // workgroups dealt to the buckets before c0
+  for (uint32_t c0 = 0; c0 < nb; c0 += kThreads) {
+    w = weight_of(c0 + tid);
+    const uint32_t size = w != 0 ? 1u + (nb - n_teams) * w / all : 0u;            // 1024 * 2^20 fits 32 bits
+    uint32_t incl = size;
+#pragma unroll
+    for (int d = 1; d < kLanes; d <<= 1) {
+      const uint32_t up = __shfl_up(incl, d, kLanes);
+      if (tid % kLanes >= static_cast<uint32_t>(d)) incl += up;
+    }
+    if (tid % kLanes == kLanes - 1) sh.red[tid / kLanes] = incl;
+    __syncthreads();
+    uint32_t first = before + incl - size;
+    for (uint32_t v = 0; v < kThreads / kLanes; ++v) {
+      if (v < tid / kLanes) first += sh.red[v];
+      before += sh.red[v];
+    }
+    if (blockIdx.x - first < size) { sh.helps = c0 + tid; sh.member = blockIdx.x - first; sh.team = size; }
+    __syncthreads();
+  }
+}
+
+// A crowded bucket o, ranked by counting by all workgroups of the launch together: each takes an equal
+// share of the bucket's records (places of its storage, then of the spill list, whose records of other
+// buckets count for nothing) and ranks it against all of them, a tile at a time; the
+// bucket's own workgroup ranks its survivors too.
 template <bool kElites, int kThreads>
-__device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
+__device__ __forceinline__ void rank_counted(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
                                              const RowPlan &rp, uint32_t K, uint32_t o, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb, b = blockIdx.x;
   uint32_t before = 0;
@@ -369,13 +431,140 @@ __device__ __forceinline__ void rank_crowded(BucketShared<kThreads> &sh, const d
   }
 }
 
+// A crowded bucket, ranked by a team of workgroups that do not wait for each other: every member sorts
+// the same sample of the bucket's records, whose quantiles, (score, slot) pairs, cut the bucket into a
+// range per member; then it reads all records, counts those below its range, collects those inside
+// and ranks them and the survivors among them like a bucket of its own.
+// Where children crowd, be it because a pool is full of copies of one genome or because nearly all
+// children beat its best members, a bucket of about 800000 (pool of 2^20) took one workgroup alone 21 ms
+// (sorting network in global memory) and all of them by counting 93 ms; a team takes 2.3.  Without such
+// children the general selection of a pool of 2^20 leaves about a hundred buckets above 2048: 192 us when a
+// workgroup each sorted them in global memory, 545 by counting, one after the other, 98 in teams.
+constexpr uint32_t kPerMember = 256;    // records to a member, if the team is large enough
+constexpr uint32_t kSamplePoints = 8;   // ... and sample points
+template <bool kElites, int kThreads>
+__device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
+                                             const RowPlan &rp, uint32_t K, int32_t *sel) {
+  const uint32_t tid = threadIdx.x, nb = bk.nb, o = sh.helps, member = sh.member;
+  const uint32_t n = bk.count[o], n_main = min(n, bk.seg);
+  const uint32_t places = n_main + (n > n_main ? bk.count[kSpillCounter] : 0u);
+  const uint32_t parts = min(sh.team, (n + kPerMember - 1) / kPerMember);
+  if (member >= parts) return;
+  auto record = [&](uint32_t at, uint64_t &key, uint32_t &id) {      // a place of the bucket; (~0, ~0): no record of it
+    key = ~0ull;
+    id = 0xFFFFFFFFu;
+    if (at < n_main) {
+      key = bk.keys[static_cast<size_t>(o) * bk.seg + at];
+      id = bk.idx[static_cast<size_t>(o) * bk.seg + at];
+    } else if (at < places) {
+      const uint32_t owner = bk.spill_bucket[at - n_main];
+      key = bk.spill_keys[at - n_main];
+      id = bk.spill_idx[at - n_main];
+      if (owner != o) { key = ~0ull; id = 0xFFFFFFFFu; }
+    }
+  };
+  uint32_t before = 0;
+  for (uint32_t c = tid; c < o; c += kThreads) before += bk.count[c];
+  before = wave_sum_u32(before);
+  __syncthreads();                                   // the shared arrays are free
+  if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
+  const uint32_t e0 = kElites ? bucket_bound(o, K, nb) : 0u, ne = kElites ? bucket_bound(o + 1, K, nb) - e0 : 0u;
+  for (uint32_t e = tid; e < ne; e += kThreads)
+    sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0 + e]]));
+  // the sample, taken at a fixed stride; places without a record of the bucket sort behind the others
+  const uint32_t sample = min(pow2_at_least(kSamplePoints * parts), static_cast<uint32_t>(kBucketLds));
+  if (tid == 0) sh.valid = 0;
+  __syncthreads();
+  uint32_t off = e0;
+#pragma unroll
+  for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
+  if (off >= K) return;                              // nothing of this bucket survives
+  uint64_t lo_key = 0, end_key = ~0ull;              // this member's range [lo, end)
+  uint32_t lo_slot = 0, end_slot = 0xFFFFFFFFu;
+  if (parts > 1) {
+    uint32_t valid = 0;
+    for (uint32_t q = tid; q < sample; q += kThreads) {
+      uint64_t key;
+      uint32_t id;
+      record(static_cast<uint32_t>(static_cast<uint64_t>(q) * places / sample), key, id);
+      sh.sk[q] = key;
+      sh.si[q] = id;
+      valid += id != 0xFFFFFFFFu ? 1u : 0u;
+    }
+    if (valid) atomicAdd(&sh.valid, valid);
+    __syncthreads();
+    bitonic_sort(sh.sk, sh.si, sample);
+    valid = sh.valid;
+    if (valid == 0 && member != 0) return;           // no record in the sample: the first member takes the whole bucket
+    if (valid != 0) {
+      const uint32_t at = member * valid / parts, to = (member + 1) * valid / parts;
+      if (member != 0) { lo_key = sh.sk[at]; lo_slot = sh.si[at]; }
+      if (member + 1 != parts) { end_key = sh.sk[to]; end_slot = sh.si[to]; }
+    }
+  }
+  auto survivors_below = [&](uint64_t key, uint32_t slot) {          // a survivor comes before an equal score
+    uint32_t lo = 0, hi = ne;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (sh.ek[mid] < key || (sh.ek[mid] == key && slot != 0)) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+  };
+  // the range is ranked in one piece, or, if more records lie in it than fit LDS, in several
+  while (key_less(lo_key, lo_slot, end_key, end_slot)) {
+    uint64_t hi_key = end_key;
+    uint32_t hi_slot = end_slot, inside;
+    for (;;) {
+      __syncthreads();
+      if (tid == 0) sh.smaller = sh.inside = 0;
+      __syncthreads();
+      uint32_t below = 0;
+      constexpr int kPer = 8;                        // loads in flight per thread
+      for (uint32_t base = 0; base < places; base += kPer * kThreads) {
+        uint64_t key[kPer];
+        uint32_t id[kPer];
+#pragma unroll
+        for (int v = 0; v < kPer; ++v) record(base + tid + v * kThreads, key[v], id[v]);
+#pragma unroll
+        for (int v = 0; v < kPer; ++v) {
+          if (key_less(key[v], id[v], lo_key, lo_slot)) {
+            ++below;
+          } else if (key_less(key[v], id[v], hi_key, hi_slot)) {
+            const uint32_t at = atomicAdd(&sh.inside, 1u);
+            if (at < static_cast<uint32_t>(kBucketLds)) { sh.sk[at] = key[v]; sh.si[at] = id[v]; }
+          }
+        }
+      }
+      if (below) atomicAdd(&sh.smaller, below);
+      __syncthreads();
+      inside = sh.inside;
+      if (inside <= static_cast<uint32_t>(kBucketLds)) break;
+      // the kBucketLds records that were collected say where about half as many end; at least the last of
+      // them falls out, so this comes to an end
+      bitonic_sort(sh.sk, sh.si, kBucketLds);
+      const uint32_t at = max(1u, static_cast<uint32_t>(static_cast<uint64_t>(kBucketLds) * (kBucketLds / 2) / inside));
+      hi_key = sh.sk[at];
+      hi_slot = sh.si[at];
+    }
+    const uint32_t below = sh.smaller, e_lo = survivors_below(lo_key, lo_slot), e_hi = survivors_below(hi_key, hi_slot);
+    const bool sorted = inside > static_cast<uint32_t>(kBucketCount);
+    const uint32_t npad = sorted ? pow2_at_least(inside) : (inside + 7) & ~7u;
+    for (uint32_t q = inside + tid; q < npad; q += kThreads) { sh.sk[q] = ~0ull; sh.si[q] = 0xFFFFFFFFu; }
+    __syncthreads();
+    if (off + below + e_lo < K) {
+      if (sorted) bitonic_sort(sh.sk, sh.si, npad);
+      rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek + e_lo, inside, npad, e_hi - e_lo, e0 + e_lo, off + below + e_lo, sorted,
+                                     K, bk, rp, sel);
+    }
+    lo_key = hi_key;
+    lo_slot = hi_slot;
+  }
+}
+
 // kElites: the quantile buckets above, each with its share of the survivors.  Without: the last
 // step of the sample sort of the general path below, a bucket holds candidates only (fit_row,
 // rp.parents, count_next unused) and its first rank is the number of candidates before it.
 // kThreads: a bucket of at most that many offspring (nearly all) is ranked straight from registers.
-// A bucket is crowded, and left to all workgroups together, when it holds more than a workgroup
-// sorts in LDS, or more than it ranks by counting while only a few buckets do (the LDS sort of 2048
-// takes one workgroup 20 us; with many such buckets the workgroups are all busy anyway).
 template <bool kElites, int kThreads>
 __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *fit_row, BucketArgs bk, RowPlan rp,
                                                                  uint32_t K, uint32_t *count_next, int32_t *sel) {
@@ -420,17 +609,40 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     for (uint32_t e = tid; e < ne; e += kThreads)
       sh.ek[e] = static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0 + e]]));
   }
-  if (tid == 0) sh.spill_cursor = sh.n_crowded = 0;
+  if (tid == 0) sh.spill_cursor = sh.n_many = sh.n_teams = sh.n_counted = 0;
   __syncthreads();
   uint32_t off = e0;
 #pragma unroll
   for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
+  Crowd crowd{};
+  uint32_t n_teams = 0;
   bool crowded = false;                              // this workgroup's own bucket
-  if (any_many) {                               // list the buckets that hold many, in any order
-    for (uint32_t c = tid; c < nb; c += kThreads)
-      if (bk.count[c] > static_cast<uint32_t>(kBucketCount)) sh.crowded[atomicAdd(&sh.n_crowded, 1u)] = c;
+  if (any_many) {
+    constexpr int kPer = kMaxBuckets / kThreads;     // buckets this thread looks at
+    uint32_t counts[kPer], many = 0, teams = 0;
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) counts[v] = bk.count[min(tid + v * kThreads, static_cast<uint32_t>(kMaxBuckets) - 1)];
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) {
+      if (tid + v * kThreads >= nb) counts[v] = 0;
+      many += counts[v] > static_cast<uint32_t>(kBucketCount) ? 1u : 0u;
+    }
+    if (many) atomicAdd(&sh.n_many, many);
+    crowd.spilled = bk.count[kSpillCounter];
     __syncthreads();
-    crowded = n > static_cast<uint32_t>(kBucketLds) || (sorted && sh.n_crowded <= kFewCrowded);
+    const bool few = sh.n_many <= kFewCrowded;
+    crowd.many = few ? kBucketCount : kBucketLds;
+    crowd.counted = few ? kCountedMost * kThreads * nb : 0;
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) {
+      if (crowd.by_counting(bk, counts[v])) sh.counted[atomicAdd(&sh.n_counted, 1u)] = tid + v * kThreads;
+      teams += crowd.by_team(bk, counts[v]) ? 1u : 0u;
+    }
+    if (teams) atomicAdd(&sh.n_teams, teams);
+    __syncthreads();
+    n_teams = sh.n_teams;
+    if (n_teams != 0) join_team(sh, bk, crowd, n_teams);
+    crowded = n > crowd.many;
   }
   if (!crowded && off < K && n + ne != 0) {          // otherwise nothing of this bucket survives
     if (small) {
@@ -491,14 +703,9 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
       rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek, n, npad, ne, e0, off, sorted, K, bk, rp, sel);
     }
   }
-  if (any_many) {
-    const uint32_t listed = sh.n_crowded;
-    for (uint32_t k = 0; k < listed; ++k) {
-      const uint32_t o = sh.crowded[k];
-      if (listed <= kFewCrowded || bk.count[o] > static_cast<uint32_t>(kBucketLds))
-        rank_crowded<kElites, kThreads>(sh, fit_row, bk, rp, K, o, sel);
-    }
-  }
+  if (any_many)
+    for (uint32_t k = 0; k < sh.n_counted; ++k) rank_counted<kElites, kThreads>(sh, fit_row, bk, rp, K, sh.counted[k], sel);
+  if (n_teams != 0 && sh.team != 0) rank_in_team<kElites, kThreads>(sh, fit_row, bk, rp, K, sel);
   if (kElites) {                                     // the other counter set, for the next generation
     if (tid == 0) count_next[b] = 0;
     if (b == 0 && tid == 0) count_next[kSpillCounter] = count_next[kManyFlag] = 0;

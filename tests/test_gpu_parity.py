@@ -138,6 +138,25 @@ def test_selection_of_a_pool_of_copies(ones, ref, pop, n_slots, n_gpus):
         ref.set_threads(1)
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,seed", [(40, 60, 65540, 1), (8, 12, 65540, 2), (6, 9, 1 << 18, 43)])
+def test_crowded_buckets(ones, ref, n_slots, n_gpus, pop, seed):
+    """Children that crowd into a few buckets of a bucketed selection, by the oracle's populations: 585 to
+    1421 of them (ranked by counting by all workgroups); one to six buckets of 2391 to 37687 that share a
+    spill list (dealt to teams of workgroups); and 129230 in one, 2513 to 31825 beside a small one."""
+    rng = np.random.default_rng(seed)
+    jobs = random_jobs(rng, n_slots)
+    ref.set_threads(8)
+    say(f"[parity] crowded buckets: G={n_gpus} slots={n_slots} P={pop} seed={seed}")
+    try:
+        gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=seed), jobs) for make in (ones.Search, ref.RefSearch))
+        for gen in range(1, 7):
+            gpu.generation(1); cpu.generation(1)
+            assert_same_state(gpu, cpu, f"generation {gen}", genes=gen == 6)
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
 @pytest.mark.parametrize("pop", [4100, 8192, 20000, 40004])
 def test_bucketed_selection_and_table_changes(ones, ref, pop):
     """Pools above one sort chunk select through survivor-quantile buckets while the job table
