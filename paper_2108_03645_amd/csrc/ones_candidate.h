@@ -436,17 +436,17 @@ __device__ __forceinline__ KernelArgs *kernel_args() {
 
 // A row index is kept inside the genome array whatever the free-row list holds, so that a mistake
 // in it cannot turn into a stray access; but such a mistake must not pass unnoticed either.
-// Every entry of a round's list, and the row of every survivor, passes through checked_row once, when
-// the kernel records the rows of the round's slots (behind the barrier that follows the clearing of the
-// note): a clamp that changes a value is noted in LDS (s.next_item[1]) and the workgroup raises the
-// context's fault word, which ones_export reports, when it ends.
-__device__ __forceinline__ uint32_t checked_row(const Smem &s, uint32_t row, uint32_t n_rows) {
-  if (row >= n_rows) s.next_item[1] = 1;
+// Every row a slot gets passes through checked_row, when the kernel takes or records the rows of a round
+// or of a call: a clamp that changes a value raises the context's fault word, which ones_export reports.
+// (The survivors' rows are such rows.  The word is raised at once: a note in LDS needs clearing before the
+// first check, which cost a barrier, or 0.5 of 87 us on the stress workload where the check waited for one.)
+__device__ __forceinline__ uint32_t checked_row(uint32_t row, uint32_t n_rows) {
+  if (row >= n_rows) atomicOr(kernel_args()->fault, 1u);
   return min(row, n_rows - 1);
 }
 
 // Row listed at position i of the current round (wave-uniform); never outside the genome array.
-// (No note here: it reads the entries that checked_row sees.)
+// (It reads entries that checked_row sees.)
 __device__ __forceinline__ uint32_t row_at(const Smem &s, uint32_t i, const EvolveArgs &a) {
   return min(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(s.rows[i])), a.P + a.K - 1);
 }

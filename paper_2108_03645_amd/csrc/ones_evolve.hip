@@ -91,7 +91,6 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride);
   const int lane0 = threadIdx.x & (kLanes - 1);
-  if (threadIdx.x == 0) s.next_item[1] = 0;          // no row index has been out of range (checked_row)
   const bool assigned = a.assigned != 0;
   if (!assigned) {
     const IndexLoads index_loads = index_free_rows_begin(a, lane0);
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
         if (p < K) d.ra = d.rb = p;                              // a survivor is its own parent
         s.drawn[i] = pack_draw(min(a.parent_row[d.ra], a.P + K - 1), min(a.parent_row[d.rb], a.P + K - 1), d.r, R);
       }
-      if (assigned) s.rows[i] = row;
+      if (assigned) s.rows[i] = checked_row(row, a.P + K);
     }
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
@@ -148,11 +147,11 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   __syncthreads();
   // record what the slots and ranks got
   for (uint32_t i = threadIdx.x; i < 4 * n; i += blockDim.x) {
-    const uint32_t p = slot_at(ra, n, i), row = checked_row(s, s.rows[i], a.P + K);
+    const uint32_t p = slot_at(ra, n, i);
     if (i < 3 * n) {
-      if (!assigned) a.row_of[p] = row;
+      if (!assigned) a.row_of[p] = checked_row(s.rows[i], a.P + K);
     } else {
-      const uint32_t old = checked_row(s, a.parent_row[p], a.P + K);
+      const uint32_t row = checked_row(s.rows[i], a.P + K), old = a.parent_row[p];
       a.row_of[p] = kSameTable ? old : row;
       if (!kSameTable) a.spare[p] = old;
       else if (!assigned) a.spare[p] = row;
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     if (kSameTable && idx >= 2 * n) {
       // the remaining work was drawn anew: the survivor of this rank keeps its genome and row
       // and only gets its score under the new draw
-      const uint32_t rank = ra + (idx - 2 * n), row = min(a.parent_row[rank], a.P + K - 1);
+      const uint32_t rank = ra + (idx - 2 * n), row = a.parent_row[rank];
       uint32_t c[Q];
       load_genes<Q>(a.genes, row, lane, c);
       const double f = score<Q>(c, s, a.term_lds, lane);
@@ -241,8 +240,6 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     }
   }
   }
-  __syncthreads();
-  if (threadIdx.x == 0 && s.next_item[1] != 0) atomicOr(kernel_args()->fault, 1u);
 }
 
 template <typename Kernel>

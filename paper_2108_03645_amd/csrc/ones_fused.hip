@@ -389,22 +389,16 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
   }
   draw_unit_parents(a.t + 1);
   stage_table<1>(a, s, a.term_lds, fa.first_changed != 0, threadIdx.x, blockDim.x);
-  // the state the last selection left: the survivors' rows and scores, the rows of the units (kept inside
-  // the genome array like every row index, see checked_row; the ranking only moves them)
-  bool stray = false;
-  auto checked = [&](uint32_t row) {
-    stray |= row >= P + K;
-    return min(row, P + K - 1);
-  };
+  // the state the last selection left: the survivors' rows and scores, the rows of the units (the
+  // ranking only moves the rows)
   for (uint32_t e = tid; e < K; e += kFusedThreads) {
-    const uint32_t row = checked(fa.parent_rows[e]);
+    const uint32_t row = checked_row(fa.parent_rows[e], P + K);
     rk.srow(0)[e] = static_cast<uint16_t>(row);
     rk.skey(0)[e] = static_cast<uint64_t>(__double_as_longlong(a.fit_row[row]));
-    if (a.assigned) rk.frow[3 * K + e] = static_cast<uint16_t>(checked(a.spare[e]));
+    if (a.assigned) rk.frow[3 * K + e] = static_cast<uint16_t>(checked_row(a.spare[e], P + K));
   }
   if (a.assigned)
-    for (uint32_t u = tid; u < 3 * K; u += kFusedThreads) rk.frow[u] = static_cast<uint16_t>(checked(a.row_of[K + u]));
-  if (stray) atomicOr(a.fault, 1u);
+    for (uint32_t u = tid; u < 3 * K; u += kFusedThreads) rk.frow[u] = static_cast<uint16_t>(checked_row(a.row_of[K + u], P + K));
   if (tid < 4) rk.misc[tid] = 0;
   if (kSampled && tid < kLanes) {
     rk.model[tid] = a.tab.abl[tid];
