@@ -185,6 +185,8 @@ struct Smem {
   double   *abl, *cc, *d, *Y;   // [Q*256] model parameters (when the term table does not fit)
   double   *terms;   // [E][4Q][64] T_j c_j of job (row, lane) at GPU-count code e, or null
   uint64_t *split;   // [kMaxBuckets] bucket splitters, then [1] the K-th survivor's score bits
+  uint2    *rank;    // [Q][64] in the same place, when a new table is served by executed time (no buckets then):
+                     // ranks of the four rows, 16 bits each, the top one set
   uint8_t  *coins;   // [waves][coin_stride] the coins of a crossover over the GPUs
   uint32_t *free_in_group; // [groups] free rows in each group of kRowGroupWords bitmap words
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
@@ -219,6 +221,8 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.Y = s.d + 4 * kWords;
   s.terms = E ? s.abl : nullptr;
   s.split = reinterpret_cast<uint64_t *>(s.abl + static_cast<size_t>(4 * kWords) * (E ? E : 4));
+  static_assert(kWords <= kMaxBuckets, "the ranks fit in the splitters' place");
+  s.rank = reinterpret_cast<uint2 *>(s.split);
   s.drawn = s.split + kMaxBuckets + 1;
   s.prefix = reinterpret_cast<uint2 *>(s.drawn + 4 * kRound);
   s.start = reinterpret_cast<uint32_t *>(s.prefix + kWords);
@@ -285,6 +289,7 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
   };
   load_splits(tid);
   load_terms(tid / kLanes);
+  const bool by_time = changed && a.new_first && a.time_rank != nullptr;       // the buckets are off: no splitters
   for (uint32_t w = tid; w < kWords; w += threads) {
     const uint32_t start = tab.start[w], most = tab.most[w], draws = tab.draws[w], base = tab.base[w];
     s.prefix[w] = philox_prefix(w, a.key1);
@@ -303,6 +308,15 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
       s.shift[w] = shift;
       s.fresh[w] = fresh;
       s.bl[w] = bl;
+    }
+    if (by_time) {
+      uint32_t rank[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t row = w / kLanes * 4 + k;
+        rank[k] = row < R ? a.time_rank[row * kLanes + w % kLanes] | 0x8000u : 0xFFFFu;
+      }
+      s.rank[w] = make_uint2(rank[0] | rank[1] << 16, rank[2] | rank[3] << 16);
     }
     s.start[w] = start;
     s.most[w] = most;
@@ -580,11 +594,11 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
 // kArrivals (only in the generation after a table change): the jobs that arrived with the table
 // are served first (refresh (3)): each starts on the GPUs a waiting job resumes with while the
 // capacity lasts, in visiting order, and the others are admitted to what is left: in visiting order
-// too, or, with time_rank (position of every job in ascending order of executed time), least executed
+// too, or, with by_time (s.rank: position of every job in ascending order of executed time), least executed
 // time first, so that the room is taken from the jobs with the largest T_processed.
 template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t G, uint32_t lr, uint32_t ir, int lane,
-                                       uint32_t Jp, const uint32_t *time_rank) {
+                                       uint32_t Jp, bool by_time) {
   uint32_t used;
   if (kArrivals) {
     uint32_t v[Q], fresh[Q];
@@ -595,19 +609,18 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
       c[q] &= ~arrived;
     }
     const uint32_t taken = accept_prefix<Q, kGenes>(v, fresh, G, lr, ir, lane);
-    if (time_rank) {
+    if (by_time) {
       // The running sum over the ranks never decreases, so the admitted jobs are the ranks below
       // some bound: the largest n whose first n ranks ask for no more than what is left.
+      // The ranks are read from LDS, four with a load, in each of the search's up to log2(Jp) + 1 steps:
+      // there is no room for them in registers, and from global memory, a rank a load, the generation
+      // that serves the arrivals of 1608 jobs took 96 us where it now takes 44.
       const uint32_t cap = G - taken;
-      // 0xFF for the jobs of word q with a rank below n
+      // 0x7F for the jobs of word q with a rank below n (n <= 2048)
       auto ranked_below = [&](int q, uint32_t n) {
-        uint32_t mask = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t j = (4 * q + k) * kLanes + lane;
-          mask |= j < Jp && time_rank[j] < n ? 0xFFu << (8 * k) : 0u;
-        }
-        return mask;
+        const uint2 rank = s.rank[q * kLanes + lane];
+        const uint32_t lower = rank.x - n * 0x10001u, upper = rank.y - n * 0x10001u;    // top bits: not below
+        return spread_tops(~__builtin_amdgcn_perm(upper, lower, 0x07050301u));
       };
       uint32_t lo = 0, hi = Jp, fit = 0;                                   // the first lo ranks fit (sum fit)
       while (lo < hi) {                                                    // at most log2(Jp) + 1 steps

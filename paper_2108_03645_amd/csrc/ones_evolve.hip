@@ -26,7 +26,7 @@ template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : 8; };
 template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t lr, uint32_t ir,
                                          uint32_t (&c)[Q], int lane) {
-  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank);
+  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, kArrivals && a.time_rank != nullptr);
   phase_fence();
   const double f = score<Q>(c, s, a.term_lds, lane);
   phase_fence();

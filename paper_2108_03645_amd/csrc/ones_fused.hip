@@ -276,8 +276,8 @@ __device__ __forceinline__ double compose_unit(const EvolveArgs &a, uint32_t t, 
     c[0] = gene_of(srow[p]);
     to_new_table<1>(s, lane, c);
   }
-  if (!kSameTable && new_first) repair<1, kOneRow, true>(c, s, a.G, r, 0, lane, kLanes, a.time_rank);
-  else repair<1, kOneRow, false>(c, s, a.G, r, 0, lane, kLanes, nullptr);
+  if (!kSameTable && new_first) repair<1, kOneRow, true>(c, s, a.G, r, 0, lane, kLanes, a.time_rank != nullptr);
+  else repair<1, kOneRow, false>(c, s, a.G, r, 0, lane, kLanes, false);
   return score<1, 1>(c, s, a.term_lds, lane);
 }
 
