@@ -157,21 +157,34 @@ __device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t yes, uint32_t n
 __device__ __forceinline__ uint32_t max_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), x, y); }
 __device__ __forceinline__ uint32_t min_bytes(uint32_t x, uint32_t y) { return pick(spread_tops((x | kTops) - y), y, x); }
 
-// What the words of codes may hold, and so how their GPUs are counted.  kNarrow: codes up to 7 (no job
-// of the table takes more than 64 GPUs, the usual case; wide_table decides), counted by one byte
-// look-up, which is wrong for any larger code.  kWide: any code, shifted one by one.  kOneRow: one row
+// What the words of codes may hold, and so how their GPUs are counted (the launcher of the evolve kernels decides by the table).
+// kNarrow: codes up to 7 (no job of the table takes more than 64 GPUs, the usual case), counted by one
+// byte look-up, which is wrong for any larger code.  kMiddle: codes up to 12 (2048 GPUs), by two: the
+// first knows the codes up to 7 and counts 8 to 12 as 0 (those selectors of v_perm_b32 pick no byte of this
+// table), the second, which counts in 128 GPUs, the other way round (selector 12 - code).  kWide: any code,
+// shifted one by one, which takes 14 instructions a word where kMiddle takes 5.  kOneRow: one row
 // of job slots, so a word holds a single gene, of any code.
-enum Genes { kNarrow, kWide, kOneRow };
+enum Genes { kNarrow, kMiddle, kWide, kOneRow };
+constexpr uint32_t kNarrowCodes = 7, kMiddleCodes = 12;
 
-// acc + the GPUs of a word's codes.
+// The GPUs of words of codes, added up.
 template <Genes kGenes>
-__device__ __forceinline__ uint32_t add_gpus(uint32_t codes, uint32_t acc) {
-  if (kGenes == kOneRow) return acc + ((1u << codes) >> 1);
-  if (kGenes == kNarrow) return __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x40201008u, 0x04020100u, codes), 0u, acc);
+struct GpuSum {
+  uint32_t sum = 0, high = 0;
+  __device__ __forceinline__ void add(uint32_t codes) {
+    if (kGenes == kOneRow) {
+      sum += (1u << codes) >> 1;
+    } else if (kGenes == kWide) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) acc += (1u << ((codes >> (8 * k)) & 31u)) >> 1;
-  return acc;
-}
+      for (int k = 0; k < 4; ++k) sum += (1u << ((codes >> (8 * k)) & 31u)) >> 1;
+    } else {
+      sum = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x40201008u, 0x04020100u, codes), 0u, sum);
+      if (kGenes == kMiddle)
+        high = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x00000001u, 0x02040810u, 0x0C0C0C0Cu - codes), 0u, high);
+    }
+  }
+  __device__ __forceinline__ uint32_t total() const { return kGenes == kMiddle ? sum + (high << 7) : sum; }
+};
 
 // ------------------------------------------------------------- job table in LDS ----
 struct Smem {
@@ -521,9 +534,10 @@ template <int Q, Genes kGenes>
 __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32_t (&m)[Q], uint32_t limit, uint32_t lr,
                                                   uint32_t ir, int lane) {
   static_assert(kGenes != kOneRow || Q == 1, "one row of job slots is one word");
-  uint32_t run = 0;
+  GpuSum<kGenes> lane_sum;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) run = add_gpus<kGenes>(v[q], run);
+  for (int q = 0; q < Q; ++q) lane_sum.add(v[q]);
+  const uint32_t run = lane_sum.total();
   const uint32_t incl = wave_inclusive_scan(run);
   const uint32_t total = __builtin_amdgcn_readlane(incl, kLanes - 1);
   if (total <= limit) return total;                // everything fits
@@ -537,11 +551,11 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
     return __builtin_amdgcn_readlane(end - run, __ffsll(static_cast<long long>(after ? after : beyond)) - 1);
   }
   // lane lr's rows before ir (only that lane's value is used); ir is wave-uniform
-  uint32_t pre = 0;
+  GpuSum<kGenes> pre;
 #pragma unroll
   for (int q = 0; q < Q; ++q)
-    if (ir > 4u * q) pre = add_gpus<kGenes>(v[q] & rows_before(ir, q), pre);
-  const uint32_t skipped = __builtin_amdgcn_readlane(pre, lr);                   // visited last, after the wrap
+    if (ir > 4u * q) pre.add(v[q] & rows_before(ir, q));
+  const uint32_t skipped = __builtin_amdgcn_readlane(pre.total(), lr);           // visited last, after the wrap
   const uint32_t base = __builtin_amdgcn_readlane(incl - run, lr) + skipped;     // asks visited after the wrap
   const uint32_t end = incl - base + (static_cast<uint32_t>(lane) < lr ? total : 0u);
   const uint32_t begin = end - (run - (static_cast<uint32_t>(lane) == lr ? skipped : 0u));
@@ -625,11 +639,11 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
       uint32_t lo = 0, hi = Jp, fit = 0;                                   // the first lo ranks fit (sum fit)
       while (lo < hi) {                                                    // at most log2(Jp) + 1 steps
         const uint32_t mid = (lo + hi + 1) / 2;
-        uint32_t sum = 0;
+        GpuSum<kGenes> below;
         phase_fence();                                                     // the ranks are not kept in registers
 #pragma unroll
-        for (int q = 0; q < Q; ++q) sum = add_gpus<kGenes>(c[q] & ranked_below(q, mid), sum);
-        sum = wave_sum(sum);
+        for (int q = 0; q < Q; ++q) below.add(c[q] & ranked_below(q, mid));
+        const uint32_t sum = wave_sum(below.total());
         if (sum <= cap) { lo = mid; fit = sum; } else { hi = mid - 1; }
       }
 #pragma unroll

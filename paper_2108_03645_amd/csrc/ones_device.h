@@ -238,8 +238,6 @@ inline hipError_t launch_evolve(const EvolveArgs &a, int rows, bool same_table, 
     default: return hipErrorInvalidValue;
   }
 }
-// A table whose largest job takes more than 64 GPUs: codes above 7 (see add_gpus).
-inline bool wide_table(const JobTable &tab) { return tab.term_E > 8; }
 // General selection (any scores).  store: the bucket storage (count, keys, idx and spill arrays,
 // split and split_slot as scratch for the splitters, nb * seg entries of bucket space); used by pools
 // too large for the single launch that ranks a whole pool.  slot_score: the pool's scores by slot

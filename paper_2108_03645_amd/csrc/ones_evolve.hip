@@ -279,7 +279,9 @@ hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStre
 
 template <int Q>
 hipError_t launch_width(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
-  return wide_table(a.tab) ? launch_words<Q, kWide>(a, same_table, n_cus, s) : launch_words<Q, kNarrow>(a, same_table, n_cus, s);
+  const uint32_t largest = a.tab.term_E - 1;         // largest code under this table
+  if (largest <= kNarrowCodes) return launch_words<Q, kNarrow>(a, same_table, n_cus, s);
+  return largest <= kMiddleCodes ? launch_words<Q, kMiddle>(a, same_table, n_cus, s) : launch_words<Q, kWide>(a, same_table, n_cus, s);
 }
 
 }  // namespace

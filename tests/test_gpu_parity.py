@@ -1112,3 +1112,42 @@ def test_single_launch_serves_arrivals_among_jobs_on_many_gpus(ones, ref, n_slot
         assert all(np.array_equal(x, y) for x, y in zip(gpu.placement(), cpu.placement())), f"step {step}"
     assert widest_held >= 128
     gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(65, 6000, 64), (300, 30000, 300), (1100, 8192, 64), (2048, 1 << 20, 128)])
+def test_gpu_counts_at_the_edges_of_the_look_ups(ones, ref, n_slots, n_gpus, pop):
+    """Tables whose largest job takes 64, 128, 2048 and 4096 GPUs (2^6, 2^7, 2^11, 2^12: the last count of
+    one look-up, the first and the last of two, the first beyond), a third of the jobs at that limit, with
+    arrivals served first, by executed time every other time."""
+    rng = np.random.default_rng(n_slots + 1)
+
+    def table(widest, jobs=None):
+        new = random_jobs(rng, n_slots, inactive_frac=0.1)
+        wide = np.where(rng.random(n_slots) < 0.35, widest, rng.integers(0, widest + 1, n_slots))
+        mu = rng.integers(0, 31 - wide)
+        new.gpu_max_batch = (1 << mu).astype(np.int32)
+        new.bmax = (1 << (mu + wide)).astype(np.int32)
+        new.bmin = (1 << rng.integers(0, mu + wide + 1)).astype(np.int32)
+        if jobs is not None:
+            new.job_id = np.where(rng.random(n_slots) < 0.2, jobs.job_id + 1000, jobs.job_id)
+        return new
+
+    jobs = table(11)
+    gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=n_slots, theta=0.3), jobs) for make in (ones.Search, ref.RefSearch))
+    for s in (gpu, cpu):
+        s.set_new_jobs_first(True)
+    for step, widest in enumerate((6, 11, 12, 7, 11)):
+        tag = f"look-ups slots={n_slots} G={n_gpus} P={pop} step={step} widest=2^{widest}"
+        say(f"[parity] {tag}")
+        jobs, t_processed = table(widest, jobs), rng.permutation(n_slots) * 1.5
+        for s in (gpu, cpu):
+            s.set_jobs(jobs)
+            s.set_processed_time(t_processed if step % 2 == 0 else None)
+            s.set_crossover(per_gpu=n_gpus <= 8192 and step >= 3)
+        for gens in (1, 2):
+            gpu.generation(gens); cpu.generation(gens)
+            assert_same_state(gpu, cpu, tag)
+        genes, mu = gpu.export()[0][:, :n_slots], jobs.gpu_max_batch
+        held = np.where(genes > 0, np.maximum(1, genes // mu), 0)
+        assert (held.sum(axis=1) <= n_gpus).all() and held.max() == 1 << widest, tag
+    gpu.close(); cpu.close()
