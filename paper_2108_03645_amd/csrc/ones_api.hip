@@ -77,7 +77,7 @@ struct ScratchLayout {
 
 struct Layout {
   size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
-  size_t unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
+  size_t export_err, export_sel, export_fit, unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
 
@@ -156,7 +156,9 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   // under probability sampling the draws of that many generations are made in one launch, and
   // generation g is scored with pair g mod kDrawRing
   for (int k = 0; k < kDrawRing; ++k) { L.Y[k] = take(Jp * 8); L.terms[k] = take(static_cast<size_t>(Jp) * kMaxTermEntries * 8); }
-  // ones_export: batch sizes of a run of pool slots on their way to the host
+  // ones_export: error words, survivors, scores by slot and the batch sizes of a run of pool slots on their way
+  // to the host, next to each other
+  L.export_err = take(8); L.export_sel = take(static_cast<size_t>(P / 4) * 4); L.export_fit = take(static_cast<size_t>(P) * 8);
   L.unpacked = take(static_cast<size_t>(unpack_slots(P, Jp)) * Jp * 4);
   L.rawinfo = take(Jp * 4);
   L.ra = take(Jp * 8); L.rc = take(Jp * 8); L.rd = take(Jp * 8); L.rY = take(Jp * 8);
@@ -814,39 +816,47 @@ static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_g
   return ONES_OK;
 }
 
+// A state of up to this size comes to the host in one copy (each costs about 10 us), through a buffer.
+constexpr size_t kOneCopyExport = 1u << 20;
+
 static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, int64_t *generation) {
   if (!c) return ONES_E_INVALID_ARG;
+  if (c->poisoned) { HIP_TRY(hipStreamSynchronize(c->stream)); return poisoned_error(); }
+  // candidates live in physical rows, their genes as codes: the device puts scores and genomes in slot order
+  const Layout &L = c->L;
+  const ExportArgs x{c->at<uint32_t>(L.genes), c->at<double>(L.fit_row), c->at<uint32_t>(L.row_of), c->at<int32_t>(L.sel),
+                     survivor_rows(c), c->at<uint32_t>(L.info[c->info_stored]), c->at<uint32_t>(L.fsync) + 1, c->P, c->K, c->Jp,
+                     c->at<double>(L.export_fit), c->at<int32_t>(L.export_sel), c->at<uint32_t>(L.export_err),
+                     c->at<int32_t>(L.unpacked)};
+  const size_t fit_bytes = static_cast<size_t>(c->P) * 8, sel_bytes = static_cast<size_t>(c->K) * 4;
+  const size_t row_bytes = static_cast<size_t>(c->Jp) * 4, genes_bytes = c->P * row_bytes;
+  const uint32_t most = unpack_slots(c->P, c->Jp);
+  const size_t all_bytes = genes ? L.unpacked + genes_bytes - L.export_err : L.export_fit + fit_bytes - L.export_err;
+  const bool one_copy = all_bytes <= kOneCopyExport && most == c->P;
+  const size_t head_bytes = one_copy ? all_bytes : L.export_sel + sel_bytes - L.export_err;
+  if (genes && one_copy) HIP_TRY(launch_export_genes(x, 0, c->P, true, c->stream));
+  else HIP_TRY(launch_export_scores(x, c->stream));
+  const std::unique_ptr<char[]> head(new char[head_bytes]);
+  HIP_TRY(hipMemcpyAsync(head.get(), c->ws + L.export_err, head_bytes, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (int rc = check_waits(c)) return rc;
-  // candidates live in physical rows, their genes as codes: the genomes are unpacked on the device,
-  // a run of pool slots at a time, the scores put in slot order on the host
-  const size_t rows = static_cast<size_t>(c->P) + c->K;
-  const uint32_t *row_of = c->at<uint32_t>(c->L.row_of);
-  if (genes) {
-    const uint32_t most = unpack_slots(c->P, c->Jp);
-    for (uint32_t first = 0; first < c->P; first += most) {
+  auto fetched = [&](size_t off) { return head.get() + (off - L.export_err); };
+  uint32_t words[2] = {0, 0};
+  memcpy(words, fetched(L.export_err), 8);
+  if (words[0]) return wait_gave_up(c);
+  if (words[1]) return row_fault(c);
+  if (sel) memcpy(sel, fetched(L.export_sel), sel_bytes);
+  if (one_copy) {
+    if (fit) memcpy(fit, fetched(L.export_fit), fit_bytes);
+    if (genes) memcpy(genes, fetched(L.unpacked), genes_bytes);
+  } else {
+    if (fit) HIP_TRY(hipMemcpy(fit, c->ws + L.export_fit, fit_bytes, hipMemcpyDeviceToHost));
+    for (uint32_t first = 0; genes && first < c->P; first += most) {
       const uint32_t count = std::min(most, c->P - first);
-      HIP_TRY(launch_unpack(c->at<uint32_t>(c->L.genes), row_of, c->at<int32_t>(c->L.sel), survivor_rows(c), c->K,
-                            c->at<uint32_t>(c->L.info[c->info_stored]), c->Jp, first, count,
-                            c->at<int32_t>(c->L.unpacked), c->stream));
-      HIP_TRY(hipMemcpyAsync(genes + static_cast<size_t>(first) * c->Jp, c->ws + c->L.unpacked,
-                             static_cast<size_t>(count) * c->Jp * 4, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(launch_export_genes(x, first, count, false, c->stream));
+      HIP_TRY(hipMemcpyAsync(genes + static_cast<size_t>(first) * c->Jp, c->ws + L.unpacked, count * row_bytes,
+                             hipMemcpyDeviceToHost, c->stream));
       HIP_TRY(hipStreamSynchronize(c->stream));
     }
-  }
-  if (fit || sel) {
-    std::vector<int32_t> best(c->K);
-    HIP_TRY(hipMemcpy(best.data(), c->ws + c->L.sel, static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
-    if (fit) {
-      std::vector<uint32_t> row(c->P), parents(c->K);
-      std::vector<double> f(rows);
-      HIP_TRY(hipMemcpy(row.data(), row_of, static_cast<size_t>(c->P) * 4, hipMemcpyDeviceToHost));
-      HIP_TRY(hipMemcpy(parents.data(), survivor_rows(c), static_cast<size_t>(c->K) * 4, hipMemcpyDeviceToHost));
-      HIP_TRY(hipMemcpy(f.data(), c->ws + c->L.fit_row, rows * 8, hipMemcpyDeviceToHost));
-      for (uint32_t p = 0; p < c->P; ++p) fit[p] = f[row[p]];
-      for (uint32_t g = 0; g < c->K; ++g) fit[best[g]] = f[parents[g]];   // their slots may have been handed other rows
-    }
-    if (sel) memcpy(sel, best.data(), static_cast<size_t>(c->K) * 4);
   }
   if (generation) *generation = c->t;
   return ONES_OK;

@@ -258,9 +258,25 @@ hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const u
 hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *best, const uint32_t *stored,
                        const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
                        double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s);
-// Batch sizes of the pool slots [first, first + count), in slot order: out[count][Jp].  The rows of the
-// survivors, slot sel[g] in row parents[g], go by parents, those of the other slots by row_of.
-hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *parents, uint32_t K,
-                         const uint32_t *stored, uint32_t Jp, uint32_t first, uint32_t count, int32_t *out, hipStream_t s);
+// The state as ones_export hands it out.  The rows of the survivors, slot sel[g] in row parents[g], go by
+// parents, those of the other slots by row_of.
+struct ExportArgs {
+  const uint32_t *genes;
+  const double   *fit_row;
+  const uint32_t *row_of;
+  const int32_t  *sel;
+  const uint32_t *parents;
+  const uint32_t *stored;     // info of the table the genomes are stored under
+  const uint32_t *err_in;     // [2] the error words
+  uint32_t        P, K, Jp;
+  double         *fit_out;    // [P] in slot order
+  int32_t        *sel_out;    // [K]
+  uint32_t       *err_out;    // [2]
+  int32_t        *genes_out;  // [count][Jp] batch sizes of the slots [first, first + count)
+};
+// Scores, survivors and error words.
+hipError_t launch_export_scores(const ExportArgs &x, hipStream_t s);
+// The genomes of a run of slots; with_scores: and, the slots being the whole pool, everything else.
+hipError_t launch_export_genes(const ExportArgs &x, uint32_t first, uint32_t count, bool with_scores, hipStream_t s);
 
 }  // namespace ones

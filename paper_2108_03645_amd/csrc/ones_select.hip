@@ -926,26 +926,41 @@ __global__ void best_kernel(const uint32_t *genes, const double *fit_row, const 
   }
 }
 
-// The genomes of a run of pool slots as batch sizes, in slot order; one workgroup per slot (the first
-// `count` workgroups, rows by row_of) and then per survivor (a survivor's slot may have been
-// handed another row already).
-constexpr int kUnpackThreads = 256;
-__device__ __forceinline__ void unpack_row(const uint32_t *row, const uint32_t *stored, uint32_t Jp, int32_t *out) {
-  for (uint32_t j = threadIdx.x; j < Jp; j += kUnpackThreads) out[j] = static_cast<int32_t>(stored_batch(row, stored, j));
+// The state in slot order.  Two launches each, the second for the survivors (a survivor's slot may have been
+// handed another row already, so what the first one wrote for it does not count).
+constexpr int kExportThreads = 256;
+__device__ __forceinline__ uint32_t exported_row(const ExportArgs &x, uint32_t row) { return min(row, x.P + x.K - 1); }
+__device__ __forceinline__ void unpack_row(const ExportArgs &x, uint32_t row, uint32_t at) {
+  const uint32_t *genome = x.genes + static_cast<size_t>(row) * (words_of(x.Jp / kLanes) * kLanes);
+  int32_t *out = x.genes_out + static_cast<size_t>(at) * x.Jp;
+  for (uint32_t j = threadIdx.x; j < x.Jp; j += kExportThreads) out[j] = static_cast<int32_t>(stored_batch(genome, x.stored, j));
 }
-__global__ __launch_bounds__(kUnpackThreads) void unpack_slots_kernel(const uint32_t *genes, const uint32_t *row_of,
-                                                                      const uint32_t *stored, uint32_t Jp,
-                                                                      uint32_t row_words, uint32_t first, int32_t *out) {
-  unpack_row(genes + static_cast<size_t>(row_of[first + blockIdx.x]) * row_words, stored, Jp,
-             out + static_cast<size_t>(blockIdx.x) * Jp);
+__device__ __forceinline__ void export_survivor(const ExportArgs &x, uint32_t g, uint32_t row) {
+  const uint32_t slot = static_cast<uint32_t>(x.sel[g]);
+  x.sel_out[g] = static_cast<int32_t>(slot);
+  if (slot < x.P) x.fit_out[slot] = x.fit_row[row];
+  if (g == 0) { x.err_out[0] = x.err_in[0]; x.err_out[1] = x.err_in[1]; }
 }
-__global__ __launch_bounds__(kUnpackThreads) void unpack_survivors_kernel(const uint32_t *genes, const int32_t *sel,
-                                                                          const uint32_t *parents, const uint32_t *stored,
-                                                                          uint32_t Jp, uint32_t row_words, uint32_t first,
-                                                                          uint32_t count, int32_t *out) {
-  const uint32_t at = static_cast<uint32_t>(sel[blockIdx.x]) - first;
-  if (at < count)
-    unpack_row(genes + static_cast<size_t>(parents[blockIdx.x]) * row_words, stored, Jp, out + static_cast<size_t>(at) * Jp);
+// One workgroup per slot, then per survivor.
+__global__ __launch_bounds__(kExportThreads) void export_slots_kernel(ExportArgs x, uint32_t first, bool with_scores) {
+  const uint32_t row = exported_row(x, x.row_of[first + blockIdx.x]);
+  unpack_row(x, row, blockIdx.x);
+  if (with_scores && threadIdx.x == 0) x.fit_out[blockIdx.x] = x.fit_row[row];
+}
+__global__ __launch_bounds__(kExportThreads) void export_survivors_kernel(ExportArgs x, uint32_t first, uint32_t count,
+                                                                         bool with_scores) {
+  const uint32_t g = blockIdx.x, at = static_cast<uint32_t>(x.sel[g]) - first, row = exported_row(x, x.parents[g]);
+  if (at < count) unpack_row(x, row, at);
+  if (with_scores && threadIdx.x == 0) export_survivor(x, g, row);
+}
+// One thread per slot, then per survivor.
+__global__ __launch_bounds__(kExportThreads) void export_slot_scores_kernel(ExportArgs x) {
+  const uint32_t p = blockIdx.x * kExportThreads + threadIdx.x;
+  if (p < x.P) x.fit_out[p] = x.fit_row[exported_row(x, x.row_of[p])];
+}
+__global__ __launch_bounds__(kExportThreads) void export_survivor_scores_kernel(ExportArgs x) {
+  const uint32_t g = blockIdx.x * kExportThreads + threadIdx.x;
+  if (g < x.K) export_survivor(x, g, exported_row(x, x.parents[g]));
 }
 
 // The winner unrolled over the GPUs (Eq. 1, reorder): every workgroup scans the jobs' GPU
@@ -1017,15 +1032,19 @@ hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(const uint32_t *genes, const uint32_t *row_of, const int32_t *sel, const uint32_t *parents, uint32_t K,
-                         const uint32_t *stored, uint32_t Jp, uint32_t first, uint32_t count, int32_t *out, hipStream_t s) {
-  const uint32_t row_words = static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes);
-  hipLaunchKernelGGL(unpack_slots_kernel, dim3(count), dim3(kUnpackThreads), 0, s, genes, row_of, stored, Jp, row_words,
-                     first, out);
+hipError_t launch_export_scores(const ExportArgs &x, hipStream_t s) {
+  hipLaunchKernelGGL(export_slot_scores_kernel, dim3((x.P + kExportThreads - 1) / kExportThreads), dim3(kExportThreads), 0, s, x);
   const hipError_t rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
-  hipLaunchKernelGGL(unpack_survivors_kernel, dim3(K), dim3(kUnpackThreads), 0, s, genes, sel, parents, stored, Jp,
-                     row_words, first, count, out);
+  hipLaunchKernelGGL(export_survivor_scores_kernel, dim3((x.K + kExportThreads - 1) / kExportThreads), dim3(kExportThreads), 0, s, x);
+  return hipGetLastError();
+}
+
+hipError_t launch_export_genes(const ExportArgs &x, uint32_t first, uint32_t count, bool with_scores, hipStream_t s) {
+  hipLaunchKernelGGL(export_slots_kernel, dim3(count), dim3(kExportThreads), 0, s, x, first, with_scores);
+  const hipError_t rc = hipGetLastError();
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(export_survivors_kernel, dim3(x.K), dim3(kExportThreads), 0, s, x, first, count, with_scores);
   return hipGetLastError();
 }
 
