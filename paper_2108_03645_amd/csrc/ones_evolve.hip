@@ -252,8 +252,12 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
                    ? a.tab.term_E : 0u;
   const size_t lds = smem_bytes(words, waves, a.term_lds, rows, a.coin_stride);
   if (lds > kLdsBudget) return hipErrorInvalidValue;
-  // as many workgroups as can be resident (LDS- and wave-limited), at most one wave per item
-  const size_t per_cu = std::max<size_t>(1, std::min<size_t>(kLdsBudget / lds, 32 / waves));
+  // as many workgroups as can be resident (LDS- and wave-limited), at most one wave per item.  Of eight waves
+  // three, though a fourth has room: what it costs to stage its tables is more than its waves hide
+  // (epochs of 10 sampled generations, 130 slots, pool 16384: 526 us with four, 485 with three, 492 with
+  // two; pool 65536: 845, 799, 841; unsampled 512 slots, 16384: 19 us a generation's launch with four, 16.5 with three)
+  const size_t resident = waves == 8 ? 3 : 32 / waves;
+  const size_t per_cu = std::max<size_t>(1, std::min<size_t>(kLdsBudget / lds, resident));
   const uint32_t blocks = std::max<uint32_t>(
       1u, std::min<uint32_t>({(items + waves - 1) / waves, static_cast<uint32_t>(n_cus * per_cu), max_blocks}));
   hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
