@@ -207,15 +207,19 @@ struct Smem {
   uint32_t *next_item;     // [1] the next work item of the round that no wave has taken yet
 };
 
-constexpr uint32_t kRound = 256;                     // survivors' ranks a workgroup covers between two barriers
-constexpr uint32_t kCoinStride = kMaxCoinGpus / 32 * 8;   // the 256 coin words with their running counts
+constexpr uint32_t kRound = 128;                     // survivors' ranks a workgroup covers between two barriers
 
 inline uint32_t row_groups(uint32_t rows) {
   return ((rows + 31) / 32 + kRowGroupWords - 1) / kRowGroupWords;
 }
 
-// LDS scratch per wave: only the crossover over the GPUs needs any
-inline uint32_t coin_stride(bool per_gpu) { return per_gpu ? kCoinStride : 0u; }
+// LDS scratch per wave: the coin words of the cluster's GPUs with their running counts, for the crossover
+// over the GPUs; one more than they fill, for the count below the GPU after the last.  (With room for
+// kMaxCoinGpus on every cluster, and rounds of 256 ranks, one workgroup was resident where two are: 585 slots,
+// 3767 GPUs, pool 17084, 35 us a generation's launch; now 30.)
+inline uint32_t coin_stride(const EvolveArgs &a) {
+  return a.per_gpu ? std::min<uint32_t>(a.G / 32 + 1, kMaxCoinGpus / 32) * 8 : 0u;
+}
 
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
 inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride) {
@@ -779,21 +783,21 @@ __device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double
 // among the GPUs it inherited for it, inside the job's window.  On return cA holds the first
 // child and cB the second.
 // Coin of GPU i: bit i mod 32 of word (i mod 128) div 32 of Philox block (i div 128, p0, t, 3);
-// lane l draws the coins of GPUs 128 l .. 128 l + 127.  coins: this wave's kMaxCoinGpus / 32
-// entries of LDS, each a coin word and, above it, the number of heads on the GPUs before it.
+// lane l draws the coins of GPUs 128 l .. 128 l + 127.  coins: this wave's entries of LDS (coin_stride),
+// each a coin word and, above it, the number of heads on the GPUs before it.
 // kFeasible: both parents are known to fit the cluster (they were repaired under the current
 // job table), so no GPU position needs to be cut off at the cluster's size.
 template <int Q, bool kFeasible>
 __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_t t, const Smem &s, uint64_t *coins, uint32_t p0,
                                                     int lane, uint32_t (&cA)[Q], uint32_t (&cB)[Q]) {
-  const uint32_t R = a.Jp / kLanes;
+  const uint32_t R = a.Jp / kLanes, entries = a.coin_stride / 8;
   {
     const Words w = philox4x32_10(static_cast<uint32_t>(lane), p0, t, 3u, a.key0, a.key1);
     const uint32_t heads = __popc(w.w[0]) + __popc(w.w[1]) + __popc(w.w[2]) + __popc(w.w[3]);
     uint32_t before = wave_inclusive_scan(heads) - heads;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      coins[4 * lane + k] = (static_cast<uint64_t>(before) << 32) | w.w[k];
+      if (4u * lane + k < entries) coins[4 * lane + k] = (static_cast<uint64_t>(before) << 32) | w.w[k];
       before += __popc(w.w[k]);
     }
   }
@@ -802,7 +806,7 @@ __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_
   phase_fence();
   // heads among the GPUs below x, x <= G <= kMaxCoinGpus
   auto heads_below = [&](uint32_t x) {
-    const uint32_t word = min(x >> 5, static_cast<uint32_t>(kMaxCoinGpus / 32 - 1));
+    const uint32_t word = min(x >> 5, entries - 1);
     const uint32_t bits = x - (word << 5);                       // 0 .. 32
     const uint64_t e = coins[word];
     const uint32_t mask = bits >= 32u ? 0xFFFFFFFFu : (1u << bits) - 1u;

@@ -247,7 +247,7 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
                              hipStream_t s) {
   // the term table goes to LDS when it fits beside the rest
   const uint32_t rows = a.P + a.K;
-  a.coin_stride = coin_stride(a.per_gpu != 0);
+  a.coin_stride = coin_stride(a);
   a.term_lds = (a.tab.term_E != 0 && smem_bytes(words, waves, a.tab.term_E, rows, a.coin_stride) <= kLdsBudget)
                    ? a.tab.term_E : 0u;
   const size_t lds = smem_bytes(words, waves, a.term_lds, rows, a.coin_stride);

@@ -673,7 +673,7 @@ hipError_t launch_fused(const FusedArgs &args, hipStream_t stream) {
   if ((fa.ev.P + n_wg * kFusedWaves - 1) / (n_wg * kFusedWaves) > kFusedUnits || (fa.ev.P + n_wg - 1) / n_wg > kMergeMax)
     return hipErrorInvalidValue;
   fa.ev.bk.nb = 0;
-  fa.ev.coin_stride = coin_stride(fa.ev.per_gpu != 0);
+  fa.ev.coin_stride = coin_stride(fa.ev);
   fa.ev.term_lds = fa.ev.tab.term_E;                  // 64 job columns: the term table always fits
   fa.table_lds = static_cast<uint32_t>(table_lds_bytes(fa.ev));
   const size_t lds = fa.table_lds + ranks_bytes(fa.ev.P);
