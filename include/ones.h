@@ -166,7 +166,7 @@ int ones_generation(ones_ctx *ctx, int32_t n_generations);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): ones_generation with the selection's scratch (splitters, counters,
- * bucket storage, spill list, sort pool) in a static device array of ONES_STATIC_SCRATCH_BYTES
+ * bucket storage, spill list) in a static device array of ONES_STATIC_SCRATCH_BYTES
  * that the library's code object holds on every GPU it runs on until the process ends, instead of
  * the caller's workspace.  The population, scores and survivor list stay in the workspace as
  * always, and the results are those of ones_generation bit for bit; the two calls may be mixed
@@ -175,7 +175,9 @@ int ones_generation(ones_ctx *ctx, int32_t n_generations);
  * Every context on a GPU shares that GPU's array, which keeps the last call's contents: each call
  * sets up by itself what it reads (its first generation ranks the pool without relying on
  * anything left there), so calls may follow each other in any order, but two calls that overlap
- * in time on one GPU (different streams or threads) race.  Must be called with the context's
+ * in time on one GPU (different streams or threads) race.  A call recorded into a graph is that
+ * one call, its generation numbers and the rows it writes included: launch the graph once, before
+ * the context's next call.  Must be called with the context's
  * device current.  Errors: ONES_E_STATIC_LIMIT when the population's scratch exceeds the array
  * (populations up to 65536 fit; nothing is launched), ONES_E_INVALID_ARG (null context, negative
  * count, another device current), ONES_E_HIP. */

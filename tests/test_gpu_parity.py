@@ -108,8 +108,9 @@ def test_stress_reduced_population(ones, ref):
 @pytest.mark.parametrize("pop,n_jobs,n_gpus", [(4096 * 3 + 8, 6, 5), (4100, 6, 5), (5000, 9, 7), (8192, 12, 9),
                                                (20000, 5, 4)])
 def test_selection_with_massive_ties(ones, ref, pop, n_jobs, n_gpus):
-    """Pools larger than one LDS sort chunk with few distinct genomes, hence few distinct scores:
-    single buckets overflow into the spill list."""
+    """Pools larger than what one launch ranks, with few distinct genomes, hence few distinct scores: the
+    general selection splits equal scores by slot.  (Buckets that overflow into the spill list:
+    test_crowded_buckets, and the larger pools of test_selection_of_a_pool_of_copies.)"""
     rng = np.random.default_rng(pop)
     jobs = make_jobs(n_jobs, bmin=256, bmax=512, remaining=rng.uniform(1e5, 1e7, n_jobs))
     run_pair(ones, ref, cluster(n_gpus, n_jobs, pop, seed=12), jobs, 4, 1, f"ties/P={pop}")
@@ -119,7 +120,7 @@ def test_selection_with_massive_ties(ones, ref, pop, n_jobs, n_gpus):
 def test_selection_of_a_pool_of_copies(ones, ref, pop, n_slots, n_gpus):
     """A search that has nearly converged, under a new table and again: thousands of copies of one
     genome share a score.  The splitters of the sample sort tell them apart by their slots, and the
-    children that crowd into one quantile bucket (513 and more) are ranked by all workgroups together."""
+    children that crowd into one quantile bucket (513 and more) are ranked by several workgroups together."""
     ref.set_threads(8)
     rng = np.random.default_rng(pop + n_slots)
     jobs = make_jobs(n_slots, bmin=256, bmax=512, remaining=rng.uniform(1e5, 1e7, n_slots))
@@ -705,8 +706,10 @@ def test_full_size_stress_with_sampled_remaining_work_matches_oracle(ones, ref):
 
 
 def test_shares_of_more_than_one_round(ones, ref):
-    """A pool so large that a workgroup's share of the ranks exceeds what it lists free rows for at
-    a time (more than 256 ranks per workgroup at 18 rows), with a table change in between."""
+    """A pool so large that a workgroup's share of the ranks exceeds what it prepares at a time (128 ranks
+    per round; 273 per workgroup at 18 rows): shares whose rows are listed, rows that the bucketed
+    selection has assigned, and both again across a table change, before which the survivors' spare rows
+    are assigned ones."""
     import os
     cl = cluster(3000, 1100, 280000, seed=41)
     jobs = random_jobs(np.random.default_rng(41), 1100)
@@ -716,16 +719,20 @@ def test_shares_of_more_than_one_round(ones, ref):
         gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
         assert_same_state(gpu, cpu, "large shares generation 0")
         gpu.generation(1); cpu.generation(1)
-        assert_same_state(gpu, cpu, "large shares generation 1")
+        assert_same_state(gpu, cpu, "large shares generation 1 (rows listed, general selection)")
+        for gen in (2, 3):
+            gpu.generation(1); cpu.generation(1)
+            assert_same_state(gpu, cpu, f"large shares generation {gen} (buckets; the second from assigned rows)", genes=gen == 3)
         j2 = make_jobs(cl.n_slots, **{k: np.array(getattr(jobs, k)) for k in
                                       ("job_id", "active", "bmin", "bmax", "gpu_max_batch", "a", "c", "d", "remaining")})
         j2.job_id[5] += 7
         j2.remaining[:] = j2.remaining * 0.9
         gpu.set_jobs(j2); cpu.set_jobs(j2)
         gpu.generation(1); cpu.generation(1)
-        assert_same_state(gpu, cpu, "large shares after a table change")
-        gpu.generation(1); cpu.generation(1)
-        assert_same_state(gpu, cpu, "large shares, bucketed generation")
+        assert_same_state(gpu, cpu, "large shares after a table change (refreshed into assigned rows)")
+        for where in ("rows listed, general selection", "buckets", "buckets, assigned rows"):
+            gpu.generation(1); cpu.generation(1)
+            assert_same_state(gpu, cpu, f"large shares, {where}", genes=where.startswith("buckets,"))
         gpu.close(); cpu.close()
     finally:
         ref.set_threads(1)
