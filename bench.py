@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published peak
 
 # HBM bytes per evolve launch on the stress workload from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (see profiles/), valid only for the kernel source with this hash.
-MEASURED_TRAFFIC = {"source_sha256": "6d03b87d4f4eaaa98cb5971e74ec1a78a14573d853aa93576e888daa98f99fb1", "bytes_per_launch": 201856126}
+MEASURED_TRAFFIC = {"source_sha256": "6ee68d728692c6cd3ad50e98718c164ad31f34b7e2a767795e79a9fd94976f06", "bytes_per_launch": 201884948}
 
 
 def evolve_source_hash() -> str:

@@ -214,11 +214,11 @@ inline uint32_t row_groups(uint32_t rows) {
 }
 
 // LDS scratch per wave: the coin words of the cluster's GPUs with their running counts, for the crossover
-// over the GPUs; one more than they fill, for the count below the GPU after the last.  (With room for
+// over the GPUs; one more than they fill, for the count below the GPU after the last, and whole lanes of four.  (With room for
 // kMaxCoinGpus on every cluster, and rounds of 256 ranks, one workgroup was resident where two are: 585 slots,
 // 3767 GPUs, pool 17084, 35 us a generation's launch; now 30.)
 inline uint32_t coin_stride(const EvolveArgs &a) {
-  return a.per_gpu ? std::min<uint32_t>(a.G / 32 + 1, kMaxCoinGpus / 32) * 8 : 0u;
+  return a.per_gpu ? std::min<uint32_t>((a.G / 32 + 4) / 4 * 4, kMaxCoinGpus / 32) * 8 : 0u;
 }
 
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
@@ -790,15 +790,17 @@ __device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double
 template <int Q, bool kFeasible>
 __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_t t, const Smem &s, uint64_t *coins, uint32_t p0,
                                                     int lane, uint32_t (&cA)[Q], uint32_t (&cB)[Q]) {
-  const uint32_t R = a.Jp / kLanes, entries = a.coin_stride / 8;
+  const uint32_t R = a.Jp / kLanes, entries = kernel_args()->coin_stride / 8;
   {
     const Words w = philox4x32_10(static_cast<uint32_t>(lane), p0, t, 3u, a.key0, a.key1);
     const uint32_t heads = __popc(w.w[0]) + __popc(w.w[1]) + __popc(w.w[2]) + __popc(w.w[3]);
     uint32_t before = wave_inclusive_scan(heads) - heads;
+    if (4u * lane < entries) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (4u * lane + k < entries) coins[4 * lane + k] = (static_cast<uint64_t>(before) << 32) | w.w[k];
-      before += __popc(w.w[k]);
+      for (int k = 0; k < 4; ++k) {
+        coins[4 * lane + k] = (static_cast<uint64_t>(before) << 32) | w.w[k];
+        before += __popc(w.w[k]);
+      }
     }
   }
   // the lanes read each other's entries: one wave, whose LDS operations complete in order
