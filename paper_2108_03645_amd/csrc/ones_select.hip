@@ -242,8 +242,9 @@ __device__ __forceinline__ void gather_bucket(uint64_t *dk, uint32_t *di, const 
   __syncthreads();
 }
 
+constexpr uint32_t kFewCrowded = 8;   // so few crowded buckets may be ranked by counting (see Crowd)
+
 // What the threads of a workgroup that handles buckets share.
-constexpr uint32_t kFewCrowded = 8;
 template <int kThreads>
 struct BucketShared {
   uint64_t sk[kBucketLds];
