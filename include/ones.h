@@ -183,9 +183,10 @@ int ones_generation(ones_ctx *ctx, int32_t n_generations);
  * count, another device current), ONES_E_HIP. */
 int ones_generation_static(ones_ctx *ctx, int32_t n_generations);
 
-/* Pools of at most 64 job slots and 2048 candidates with a fixed remaining work run all
- * generations of a ones_generation call of three or more generations in ONE launch whose
- * workgroups exchange results while it runs; a workgroup polls for the others' results at most
+/* Pools of at most 64 job slots and 2048 candidates run all generations of a ones_generation call of
+ * three or more generations in ONE launch whose workgroups exchange results while it runs, and so do
+ * pools of up to 1024 job slots and 8192 candidates (as far as they fit a compute unit's LDS; not
+ * under graph capture) with calls of four or more, ten under probability sampling; a workgroup polls for the others' results at most
  * `polls` times (at first 2^22, a few seconds) and then gives up: the launch ends, the next call
  * that synchronises (ones_best, ones_export, ones_placement) returns ONES_E_HIP, and the context
  * only accepts ones_destroy from then on.  This never happens on a healthy device; polls = 0
@@ -224,7 +225,7 @@ int32_t ones_padded_jobs(int32_t n_slots);
  * A small pool (at most 64 job slots and 2048 candidates, fixed remaining work) runs all
  * generations of a ones_generation call of three or more generations in one launch: that
  * launch counts as one evolve launch (every n-th call is bracketed) and there is no select
- * launch.
+ * launch.  While the hook is on, larger pools take two launches per generation.
  * ones_profile_read synchronises and returns the accumulated kernel time in milliseconds
  * and the number of bracketed launches since the last ones_profile_enable call (any output
  * may be NULL). */

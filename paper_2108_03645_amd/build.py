@@ -13,7 +13,8 @@ LIB = os.path.join(HERE, "libones.so")
 # (source, object, extra flags); the evolve kernel is built once per group of two word counts (eight rows of job slots)
 UNITS = [("ones_api.hip", "ones_api.o", []), ("ones_select.hip", "ones_select.o", []),
          ("ones_sample.hip", "ones_sample.o", []), ("ones_fused.hip", "ones_fused.o", [])] + [
-    ("ones_evolve.hip", f"ones_evolve_{g}.o", [f"-DONES_ROW_GROUP={g}"]) for g in range(4)]
+    ("ones_evolve.hip", f"ones_evolve_{g}.o", [f"-DONES_ROW_GROUP={g}"]) for g in range(4)] + [
+    ("ones_resident.hip", f"ones_resident_{q}.o", [f"-DONES_RESIDENT_WORDS={q}"]) for q in range(1, 5)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -21,7 +22,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          *os.environ.get("ONES_EXTRA_FLAGS", "").split()]
 
 
-HEADERS = [os.path.join(CSRC, h) for h in ("ones_device.h", "ones_sample.h", "ones_candidate.h", "ones_sort.h")] + [
+HEADERS = [os.path.join(CSRC, h) for h in ("ones_device.h", "ones_sample.h", "ones_candidate.h", "ones_exchange.h", "ones_sort.h")] + [
            os.path.join(INCLUDE, "ones.h"),
            os.path.abspath(__file__)]
 

@@ -76,7 +76,7 @@ struct ScratchLayout {
 };
 
 struct Layout {
-  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
+  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, flags, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
   size_t export_err, export_sel, export_fit, unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
@@ -106,7 +106,16 @@ BucketPlan bucket_plan(uint32_t P) {
 // launch is a cooperative one, which costs about 20 us where an ordinary launch costs 2.5, so
 // calls of one or two generations are cheaper as two ordinary launches per generation.
 constexpr int32_t kFusedMinGenerations = 3;
+// The same for larger pools (ones_resident.hip).  What a call of four generations gains by one launch, up to 30 %, pays
+// for that launch; under probability sampling a small pool of few rows of slots only does so from ten on, its two launches
+// a generation being short (130 slots, pool 260 and 1024, epochs of 4, 6 and 10 generations: 0.89, 0.92, 0.99 and
+// 0.91, 0.94, 1.04 of the speed; 1000 slots: 1.03, 1.08, 1.17; pool 4096: 1.16, 1.26, 1.42).
+int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) { return sampled && P <= 1024 && Jp <= 4u * kLanes ? 10 : 4; }
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
+bool resident_pool(uint32_t P, uint32_t Jp) {
+  return !fused_pool(P, Jp) && P <= static_cast<uint32_t>(kResidentMaxPool) && words_of(static_cast<int>(Jp / kLanes)) <= kResidentMaxWords;
+}
+int ring_places(uint32_t P, uint32_t Jp) { return resident_pool(P, Jp) ? kDrawRing : kDrawAhead; }
 
 ScratchLayout make_scratch_layout(uint32_t P) {
   ScratchLayout S;
@@ -145,17 +154,18 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   L.sel = take(static_cast<size_t>(P / 4) * 4);
   // single-launch generations of small pools: error words, scores, ranks and draws exchanged
   L.fsync = take(256);
-  L.xkeys = take(fused_pool(P, Jp) ? fused_exchange_bytes(P) : 0);
+  L.flags = take(kResidentMaxGroups * 4);
+  L.xkeys = take(fused_pool(P, Jp) || resident_pool(P, Jp) ? fused_exchange_bytes(P) : 0);
   // the selection's scratch: splitters, counters, bucket storage, spill list
   L.S = make_scratch_layout(P);
   L.scratch = take(L.S.total);
   L.start = take(row_bytes); L.most = take(row_bytes); L.draws = take(row_bytes); L.base = take(row_bytes);
   L.info[0] = take(Jp * 4); L.info[1] = take(Jp * 4);
   L.abl = take(Jp * 8); L.cc = take(Jp * 8); L.d = take(Jp * 8);
-  // remaining work and the term table built from it, a ring of kDrawRing pairs at equal distances:
+  // remaining work and the term table built from it, a ring of pairs at equal distances:
   // under probability sampling the draws of that many generations are made in one launch, and
-  // generation g is scored with pair g mod kDrawRing
-  for (int k = 0; k < kDrawRing; ++k) { L.Y[k] = take(Jp * 8); L.terms[k] = take(static_cast<size_t>(Jp) * kMaxTermEntries * 8); }
+  // generation g is scored with pair g mod their number
+  for (int k = 0; k < ring_places(P, Jp); ++k) { L.Y[k] = take(Jp * 8); L.terms[k] = take(static_cast<size_t>(Jp) * kMaxTermEntries * 8); }
   // ones_export: error words, survivors, scores by slot and the batch sizes of a run of pool slots on their way
   // to the host, next to each other
   L.export_err = take(8); L.export_sel = take(static_cast<size_t>(P / 4) * 4); L.export_fit = take(static_cast<size_t>(P) * 8);
@@ -275,6 +285,7 @@ struct ones_ctx {
                               // and cleared counter sets: a bucketed generation may follow
   bool poisoned;              // a launch failed in the middle of a generation: the state is inconsistent
   bool fused;                 // small pool: all generations of a call in one cooperative launch
+  bool resident;              // ... the same for larger pools, as far as the job table leaves room (resident_plan)
   uint32_t fused_generations; // generations those launches have run so far
   uint32_t fused_changes;     // ... of them generations that also exchanged the survivors' scores
   uint32_t fused_draws;       // ... of them generations with a drawn remaining work
@@ -338,6 +349,21 @@ int timed(ones_ctx *c, std::vector<EventPair> &pool, size_t &used, bool begin) {
   return ONES_OK;
 }
 
+// Distance of two places of the ring of draws (make_layout), in doubles.
+uint32_t ring_stride(const ones_ctx *c) { return static_cast<uint32_t>((c->L.Y[1] - c->L.Y[0]) / 8); }
+
+// The ring holds the draw of generation t, and, if it has to be made, those of up to `ahead` generations from t on.
+int make_draws(ones_ctx *c, uint32_t t, int ahead) {
+  if (c->drawn_from <= static_cast<int64_t>(t) && static_cast<int64_t>(t) < c->drawn_to) return ONES_OK;
+  const Progress pr{c->at<double>(c->L.alpha), c->at<double>(c->L.beta), c->at<double>(c->L.processed)};
+  const uint32_t count = static_cast<uint32_t>(std::min<int64_t>(ahead, 0x100000000ll - static_cast<int64_t>(t)));
+  HIP_TRY(launch_sample_remaining(pr, c->table(0), ring_stride(c), ring_places(c->P, c->Jp), c->Jn, c->Jp, static_cast<uint32_t>(c->cfg.seed),
+                                  static_cast<uint32_t>(c->cfg.seed >> 32), t, count, c->stream));
+  c->drawn_from = t;
+  c->drawn_to = static_cast<int64_t>(t) + count;
+  return ONES_OK;
+}
+
 // scratch: base of the selection's scratch block (the workspace's, or the static array);
 // splitters_valid: that block holds the current survivors' splitters and cleared counters.
 int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid, bool events) {
@@ -356,7 +382,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   // remaining-work arrays and term tables: a launch of an earlier generation has filled it
   // already, or the draws of this and the next generations are made now.
   const bool sampled = t != 0 && c->sampling;
-  const int y_this = sampled ? static_cast<int>(t % kDrawRing) : c->y_cur;
+  const int y_this = sampled ? static_cast<int>(t % ring_places(c->P, c->Jp)) : c->y_cur;
   a.tab = c->table(y_this);
   a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
   a.key0 = static_cast<uint32_t>(c->cfg.seed);
@@ -393,15 +419,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   rp.parent_next = c->at<uint32_t>(c->L.parent_row[next ^ 1]);
   rp.occupied = a.occupied_other;
   int rc;
-  const Progress pr{c->at<double>(c->L.alpha), c->at<double>(c->L.beta), c->at<double>(c->L.processed)};
-  if (sampled && !(c->drawn_from <= static_cast<int64_t>(t) && static_cast<int64_t>(t) < c->drawn_to)) {
-    const uint32_t count = static_cast<uint32_t>(std::min<int64_t>(kDrawRing, 0x100000000ll - static_cast<int64_t>(t)));
-    // places lie at equal distances (make_layout); counted in doubles
-    const uint32_t ring_stride = static_cast<uint32_t>((c->L.Y[1] - c->L.Y[0]) / 8);
-    HIP_TRY(launch_sample_remaining(pr, c->table(0), ring_stride, c->Jn, c->Jp, a.key0, a.key1, t, count, c->stream));
-    c->drawn_from = t;
-    c->drawn_to = static_cast<int64_t>(t) + count;
-  }
+  if (sampled && (rc = make_draws(c, t, kDrawAhead))) return rc;
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, true))) return rc;
   HIP_TRY(launch_evolve(a, static_cast<int>(c->R), same_table, c->n_cus, c->stream));
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
@@ -513,7 +531,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   c->bucket_phase = 0;
   c->splitters_valid = false;
   c->poisoned = false;
-  c->fused = false;
+  c->fused = c->resident = false;
   c->fused_generations = 0;
   c->fused_changes = 0;
   c->fused_draws = 0;
@@ -532,14 +550,15 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     // the single-launch path needs a launch whose workgroups are all resident at once
     c->fused = fused_pool(c->P, c->Jp) && prop.cooperativeLaunch != 0 &&
                fused_grid_limit(c->P) <= static_cast<uint32_t>(c->n_cus);
+    c->resident = resident_pool(c->P, c->Jp) && prop.cooperativeLaunch != 0;
   }
   c->profiling = false; c->profile_every = 1; c->profile_tick = 0; c->evolve_used = c->select_used = 0;
   {
     const uint32_t words = (c->P + c->K + 31) / 32;
     hipError_t e = launch_zero_words(c->at<uint32_t>(c->L.occupied[0]), words, c->stream);
     if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.occupied[1]), words, c->stream);
-    if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.fsync), 64, c->stream);
-    if (e == hipSuccess && fused_pool(c->P, c->Jp))   // the exchange buffers of the single-launch path: every tag starts at 0
+    if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.fsync), 64 + kResidentMaxGroups, c->stream);   // and the flags behind them
+    if (e == hipSuccess && (fused_pool(c->P, c->Jp) || resident_pool(c->P, c->Jp)))   // the exchange buffers of the single-launch path: every tag starts at 0
       e = launch_zero_words(c->at<uint32_t>(c->L.xkeys), static_cast<uint32_t>(fused_exchange_bytes(c->P) / 4), c->stream);
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
@@ -707,9 +726,76 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   return ONES_OK;
 }
 
+// The problem as the kernels of a whole call see it.
+static EvolveArgs whole_call_args(const ones_ctx *c) {
+  EvolveArgs a{};
+  a.genes = c->at<uint32_t>(c->L.genes);
+  a.fit_row = c->at<double>(c->L.fit_row);
+  a.row_of = c->at<uint32_t>(c->L.row_of);
+  a.spare = c->at<uint32_t>(c->L.spare);
+  a.assigned = c->rows_assigned ? 1u : 0u;
+  a.tab = c->table();
+  a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
+  a.key0 = static_cast<uint32_t>(c->cfg.seed);
+  a.key1 = static_cast<uint32_t>(c->cfg.seed >> 32);
+  a.t = static_cast<uint32_t>(c->t);
+  a.T_mut = c->T_mut; a.T_x = c->T_x;
+  a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
+  a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
+  a.per_gpu = c->per_gpu ? 1u : 0u;
+  a.fault = c->at<uint32_t>(c->L.fsync) + 2;
+  return a;
+}
+
+// The next n generations in one cooperative launch (pools beyond those of run_fused).  Under probability
+// sampling n is at most kDrawRing, and their draws are in the ring.
+static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
+  ResidentArgs ra{};
+  ra.ev = whole_call_args(c);
+  ra.ev.coin_stride = plan.coin_stride;
+  ra.ev.term_lds = c->term_E;
+  if (c->sampling) ra.ev.tab = c->table(static_cast<int>((c->t + 1) % kDrawRing));
+  FusedArgs fa{};
+  fused_exchange(c->at<uint64_t>(c->L.xkeys), c->P, fa);
+  ra.xkeys = fa.xkeys; ra.xrank = fa.xrank;
+  ra.flags = c->at<uint32_t>(c->L.flags);
+  ra.parent_rows = c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]);
+  ra.sel = c->at<int32_t>(c->L.sel);
+  ra.sync = c->at<uint32_t>(c->L.fsync);
+  ra.generations_before = c->fused_generations;
+  ra.sampled = c->sampling ? 1u : 0u;
+  ra.ring_terms = c->at<double>(c->L.terms[0]);
+  ra.ring_stride = ring_stride(c);
+  ra.n_generations = n;
+  ra.first_changed = c->table_changed ? 1u : 0u;
+  ra.spin_limit = c->spin_limit;
+  ra.table_lds = plan.table_lds; ra.unit_waves = plan.unit_waves; ra.child_units = plan.child_units;
+  switch (words_of(static_cast<int>(c->R))) {
+    case 1: HIP_TRY(launch_resident_words1(ra, plan, c->stream)); break;
+    case 2: HIP_TRY(launch_resident_words2(ra, plan, c->stream)); break;
+    case 3: HIP_TRY(launch_resident_words3(ra, plan, c->stream)); break;
+    default: HIP_TRY(launch_resident_words4(ra, plan, c->stream)); break;
+  }
+  c->fused_generations += n;
+  if (c->sampling) c->y_cur = static_cast<int>((c->t + n) % kDrawRing);
+  c->rows_assigned = true;
+  c->info_stored = c->info_now;
+  c->table_changed = false;
+  c->no_schedule = false;
+  c->splitters_valid = false;       // the two-launch path ranks the pool in full before it uses buckets again
+  c->profile_tick += 1;
+  return ONES_OK;
+}
+
 static int poisoned_error() {
   snprintf(g_hip_msg, sizeof(g_hip_msg), "an earlier launch failed in the middle of a generation; destroy the context");
   return ONES_E_HIP;
+}
+
+// A launch that is being recorded into a graph must not need a resident grid.
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
 static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_scratch) {
@@ -733,7 +819,27 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
     c->t += n_generations;
     return ONES_OK;
   }
-  for (int32_t i = 0; i < n_generations; ++i) {
+  int32_t left = n_generations;
+  ResidentPlan plan;
+  const int32_t least = resident_min_generations(c->P, c->Jp, c->sampling);
+  const bool by_kernel = c->profiling && !in_static_scratch;       // the measurement hook sees evolve and select launches
+  if (c->resident && left >= least && !by_kernel && resident_plan(whole_call_args(c), c->sampling, c->n_cus, plan) &&
+      !capturing(c->stream)) {
+    while (left >= least) {
+      int32_t n = left;
+      if (c->sampling) {
+        const int rc = make_draws(c, static_cast<uint32_t>(c->t + 1), std::min<int32_t>(left, kDrawRing));
+        if (rc) { c->poisoned = true; return rc; }
+        n = static_cast<int32_t>(std::min<int64_t>(left, c->drawn_to - (c->t + 1)));
+        if (n < least) break;
+      }
+      const int rc = run_resident(c, static_cast<uint32_t>(n), plan);
+      if (rc) { c->poisoned = true; return rc; }
+      c->t += n;
+      left -= n;
+    }
+  }
+  for (; left > 0; --left) {
     int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block,
                             in_static_scratch ? static_valid : c->splitters_valid, !in_static_scratch);
     if (rc) { c->poisoned = true; return rc; }

@@ -108,10 +108,11 @@ struct BucketArgs {
 struct Progress {
   const double *alpha, *beta, *processed;   // [Jp]
 };
-// The draws depend on nothing but (seed, slot, generation), so they are made ahead, kDrawRing
-// generations in one launch: generation g's remaining work and term table sit at place
-// g mod kDrawRing of a ring of (Y, terms) pairs.
-constexpr int kDrawRing = 8;
+// The draws depend on nothing but (seed, slot, generation), so they are made ahead, those of many
+// generations in one launch: generation g's remaining work and term table sit at place g mod n of a ring of
+// n (Y, terms) pairs, n = kDrawRing, or kDrawAhead for a context whose generations are all launched one by one.
+constexpr int kDrawRing = 32;
+constexpr int kDrawAhead = 8;       // generations drawn at a time for the kernels of one generation
 
 // Genomes live in physical rows; a candidate keeps its row for as long as it survives, so a
 // survivor is never copied.  The pool of P slots uses P + K rows.  While a generation is computed
@@ -189,6 +190,36 @@ size_t fused_exchange_bytes(uint32_t P);    // xkeys, xsurv, xrank and xdraw, co
 void fused_exchange(uint64_t *base, uint32_t P, FusedArgs &fa);   // their addresses
 hipError_t launch_fused(const FusedArgs &fa, hipStream_t s);
 
+// The same for pools beyond those (ones_resident.hip): at most kResidentMaxPool candidates of up to
+// 256 * kResidentMaxWords job slots, as far as a compute unit's LDS holds them (resident_plan).
+constexpr int kResidentMaxPool = 8192;
+constexpr int kResidentMaxWords = 4;
+constexpr uint32_t kResidentMaxGroups = 1024;   // workgroups of a launch: flags in the workspace
+struct ResidentArgs {
+  EvolveArgs ev;
+  uint32_t *parent_rows;    // as in FusedArgs, as are the following, but for
+  int32_t  *sel;
+  uint64_t *xkeys;          // [2][P] score bits by pool slot, a buffer per generation parity
+  uint32_t *flags;          // [workgroups] generations of the context a workgroup has published the scores of
+  uint64_t *xrank;          // [K] slots of the survivors by rank, from a ranking by counting, stamped with the generation
+  uint32_t *sync;
+  uint32_t generations_before;
+  uint32_t sampled;
+  const double *ring_terms; // the term tables of the draws, generation t's at place t mod kDrawRing, made before the launch
+  uint32_t ring_stride;     // doubles between two places
+  uint32_t n_generations;   // > 1; under probability sampling at most kDrawRing
+  uint32_t first_changed, spin_limit;
+  uint32_t table_lds, unit_waves, child_units;   // from the plan: LDS bytes of the job table, waves of a workgroup that
+                                                 // compute candidates, children a wave computes in a generation, at most
+};
+struct ResidentPlan { uint32_t groups, unit_waves, child_units, coin_stride, table_lds; size_t lds; };
+// How a launch for ev's pool and job table would be shaped; false: it does not fit.
+bool resident_plan(const EvolveArgs &ev, bool sampled, int n_cus, ResidentPlan &plan);
+hipError_t launch_resident_words1(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t s);
+hipError_t launch_resident_words2(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t s);
+hipError_t launch_resident_words3(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t s);
+hipError_t launch_resident_words4(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t s);
+
 // What a selection records besides the survivor list: the survivors keep their rows.
 struct RowPlan {
   uint32_t       *row_of;       // [P] row of every slot of the pool being ranked
@@ -218,9 +249,9 @@ struct RawJobs {              // uploaded by the host after validation, [Jp] eac
 // in tab.stored (unless the genomes are, or will be, stored under this table); one launch.
 hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, hipStream_t s);
 hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s);
-// ring: the job table with Y and terms pointing at place 0 of the ring, whose places lie
-// ring_stride doubles apart; draws generations t .. t + count - 1 (count <= kDrawRing).
-hipError_t launch_sample_remaining(const Progress &pr, const JobTable &ring, uint32_t ring_stride, uint32_t Jn,
+// ring: the job table with Y and terms pointing at place 0 of a ring of `places`, which lie
+// ring_stride doubles apart; draws generations t .. t + count - 1 (count <= places).
+hipError_t launch_sample_remaining(const Progress &pr, const JobTable &ring, uint32_t ring_stride, uint32_t places, uint32_t Jn,
                                    uint32_t Jp, uint32_t key0, uint32_t key1, uint32_t t, uint32_t count,
                                    hipStream_t s);
 // same_table: the job table is the one the previous generation was repaired and scored with

@@ -444,6 +444,57 @@ def test_single_launch_long_calls(ones, ref, name, calls, per_call):
         ref.set_threads(1)
 
 
+@pytest.mark.parametrize("sampled", [False, True])
+@pytest.mark.parametrize("n_slots,n_gpus,pop,seed,per_gpu,new_first,widest", [
+    (1, 4, 2052, 1, False, False, 0), (65, 90, 4, 2, False, True, 0), (66, 5, 2048, 3, False, False, 0),
+    (130, 90, 260, 4, True, True, 0), (40, 64, 4096, 5, True, False, 0), (200, 300, 8192, 6, False, True, 0),
+    (257, 400, 5460, 7, False, False, 0), (700, 5000, 2052, 8, True, True, 8), (513, 20000, 1028, 9, False, True, 14),
+    (1000, 1500, 1024, 10, False, False, 0)])
+def test_single_launch_of_pools_beyond_one_row(ones, ref, n_slots, n_gpus, pop, seed, per_gpu, new_first, widest, sampled):
+    """Calls of four and more generations of pools that a compute unit's LDS holds, one launch each, between calls
+    of fewer, two launches a generation: every word count the launch serves, pools from a wave's work to three rounds
+    of all waves, children that crowd (few jobs on fewer GPUs than they want: copies of one genome), table
+    changes, both crossovers, arrivals with and without executed times, every look-up of GPU counts, the remaining work
+    fixed or drawn (a call of 37 draws in two portions)."""
+    rng = np.random.default_rng(seed)
+    say(f"[single launch] G={n_gpus} slots={n_slots} P={pop} seed={seed} per_gpu={per_gpu} new_first={new_first} sampled={sampled}")
+
+    def table(jobs=None):
+        new = random_jobs(rng, n_slots)
+        if widest:
+            new.gpu_max_batch[:] = 16
+            new.bmax = (16 << rng.integers(min(7, widest), widest + 1, n_slots)).astype(np.int32)
+            new.bmin = (16 << rng.integers(0, 3, n_slots)).astype(np.int32)
+        if jobs is not None:
+            new.job_id = np.where(rng.random(n_slots) < 0.3, jobs.job_id + 1000, jobs.job_id)
+        return new
+
+    jobs = table()
+    ref.set_threads(8)
+    try:
+        gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=seed + 900), jobs) for make in (ones.Search, ref.RefSearch))
+        for s in (gpu, cpu):
+            s.set_crossover(per_gpu=per_gpu)
+            s.set_new_jobs_first(new_first)
+            if sampled:
+                s.set_progress(*W.progress(n_slots, seed=seed))
+        for step, n in enumerate([4, 1, 6, 2, 37, 5, 9]):
+            gpu.generation(n); cpu.generation(n)
+            assert_same_state(gpu, cpu, f"call {step} of {n} generations")
+            assert np.array_equal(gpu.export_remaining().view(np.uint64), cpu.export_remaining().view(np.uint64)), f"call {step}"
+            if step in (1, 2, 5):                    # before the calls of 6, 2 and 9
+                jobs = table(jobs)
+                for s in (gpu, cpu):
+                    s.set_jobs(jobs)
+                    if new_first and step != 2:
+                        s.set_processed_time(rng_times(seed, step, n_slots))
+        gb, cb = gpu.best(), cpu.best()
+        assert gb[0].tolist() == cb[0].tolist() and gb[1].tolist() == cb[1].tolist() and gb[2] == cb[2]
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
 def rng_times(seed, step, n_slots):
     return np.random.default_rng([seed, step]).integers(0, 5, n_slots) * 60.0
 
