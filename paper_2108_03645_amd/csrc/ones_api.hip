@@ -76,7 +76,7 @@ struct ScratchLayout {
 };
 
 struct Layout {
-  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, flags, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
+  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
   size_t export_err, export_sel, export_fit, unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
@@ -111,10 +111,16 @@ constexpr int32_t kFusedMinGenerations = 3;
 // a generation being short (130 slots, pool 260 and 1024, epochs of 4, 6 and 10 generations: 0.89, 0.92, 0.99 and
 // 0.91, 0.94, 1.04 of the speed; 1000 slots: 1.03, 1.08, 1.17; pool 4096: 1.16, 1.26, 1.42).
 int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) { return sampled && P <= 1024 && Jp <= 4u * kLanes ? 10 : 4; }
+// From random genomes so many children beat the K-th survivor that a large pool has to be ranked as a whole, which two
+// launches do in less time (16384 candidates: 26 us a generation, 37 in the single launch): more than 3072, which that launch
+// can list, for the first 26 generations of 16384 candidates, never of 8192.
+constexpr uint32_t kResidentListed = 8192;
+constexpr int64_t kResidentSettled = 24;
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {
   return !fused_pool(P, Jp) && P <= static_cast<uint32_t>(kResidentMaxPool) && words_of(static_cast<int>(Jp / kLanes)) <= kResidentMaxWords;
 }
+size_t exchange_bytes(uint32_t P, uint32_t Jp) { return fused_pool(P, Jp) ? fused_exchange_bytes(P) : resident_pool(P, Jp) ? resident_exchange_bytes(P) : 0; }
 int ring_places(uint32_t P, uint32_t Jp) { return resident_pool(P, Jp) ? kDrawRing : kDrawAhead; }
 
 ScratchLayout make_scratch_layout(uint32_t P) {
@@ -154,8 +160,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   L.sel = take(static_cast<size_t>(P / 4) * 4);
   // single-launch generations of small pools: error words, scores, ranks and draws exchanged
   L.fsync = take(256);
-  L.flags = take(kResidentMaxGroups * 4);
-  L.xkeys = take(fused_pool(P, Jp) || resident_pool(P, Jp) ? fused_exchange_bytes(P) : 0);
+  L.xkeys = take(exchange_bytes(P, Jp));
   // the selection's scratch: splitters, counters, bucket storage, spill list
   L.S = make_scratch_layout(P);
   L.scratch = take(L.S.total);
@@ -557,9 +562,10 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     const uint32_t words = (c->P + c->K + 31) / 32;
     hipError_t e = launch_zero_words(c->at<uint32_t>(c->L.occupied[0]), words, c->stream);
     if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.occupied[1]), words, c->stream);
-    if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.fsync), 64 + kResidentMaxGroups, c->stream);   // and the flags behind them
-    if (e == hipSuccess && (fused_pool(c->P, c->Jp) || resident_pool(c->P, c->Jp)))   // the exchange buffers of the single-launch path: every tag starts at 0
-      e = launch_zero_words(c->at<uint32_t>(c->L.xkeys), static_cast<uint32_t>(fused_exchange_bytes(c->P) / 4), c->stream);
+    if (e == hipSuccess) e = launch_zero_words(c->at<uint32_t>(c->L.fsync), 64, c->stream);
+    const size_t exchange = exchange_bytes(c->P, c->Jp);
+    if (e == hipSuccess && exchange != 0)   // the exchange buffers of the single-launch paths: every tag starts at 0
+      e = launch_zero_words(c->at<uint32_t>(c->L.xkeys), static_cast<uint32_t>(exchange / 4), c->stream);
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
   if ((rc = upload_table(c, h)) ||
@@ -755,10 +761,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.ev.coin_stride = plan.coin_stride;
   ra.ev.term_lds = c->term_E;
   if (c->sampling) ra.ev.tab = c->table(static_cast<int>((c->t + 1) % kDrawRing));
-  FusedArgs fa{};
-  fused_exchange(c->at<uint64_t>(c->L.xkeys), c->P, fa);
-  ra.xkeys = fa.xkeys; ra.xrank = fa.xrank;
-  ra.flags = c->at<uint32_t>(c->L.flags);
+  resident_exchange(c->at<uint64_t>(c->L.xkeys), c->P, ra);
   ra.parent_rows = c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]);
   ra.sel = c->at<int32_t>(c->L.sel);
   ra.sync = c->at<uint32_t>(c->L.fsync);
@@ -769,7 +772,8 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.n_generations = n;
   ra.first_changed = c->table_changed ? 1u : 0u;
   ra.spin_limit = c->spin_limit;
-  ra.table_lds = plan.table_lds; ra.unit_waves = plan.unit_waves; ra.child_units = plan.child_units;
+  ra.paired = plan.paired; ra.unit_waves = plan.unit_waves; ra.child_items = plan.child_items;
+  ra.segment = plan.segment; ra.list = plan.list; ra.table_lds = plan.table_lds;
   switch (words_of(static_cast<int>(c->R))) {
     case 1: HIP_TRY(launch_resident_words1(ra, plan, c->stream)); break;
     case 2: HIP_TRY(launch_resident_words2(ra, plan, c->stream)); break;
@@ -820,11 +824,21 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
     return ONES_OK;
   }
   int32_t left = n_generations;
+  bool &splitters_valid = in_static_scratch ? static_valid : c->splitters_valid;
+  auto launched_generation = [&] {
+    const int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block, splitters_valid, !in_static_scratch);
+    if (rc) { c->poisoned = true; return rc; }
+    c->t += 1;
+    left -= 1;
+    return static_cast<int>(ONES_OK);
+  };
   ResidentPlan plan;
   const int32_t least = resident_min_generations(c->P, c->Jp, c->sampling);
   const bool by_kernel = c->profiling && !in_static_scratch;       // the measurement hook sees evolve and select launches
   if (c->resident && left >= least && !by_kernel && resident_plan(whole_call_args(c), c->sampling, c->n_cus, plan) &&
       !capturing(c->stream)) {
+    while (!c->sampling && c->P > kResidentListed && c->t < kResidentSettled && left > 0)
+      if (const int rc = launched_generation()) return rc;
     while (left >= least) {
       int32_t n = left;
       if (c->sampling) {
@@ -835,16 +849,13 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
       }
       const int rc = run_resident(c, static_cast<uint32_t>(n), plan);
       if (rc) { c->poisoned = true; return rc; }
+      splitters_valid = false;
       c->t += n;
       left -= n;
     }
   }
-  for (; left > 0; --left) {
-    int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block,
-                            in_static_scratch ? static_valid : c->splitters_valid, !in_static_scratch);
-    if (rc) { c->poisoned = true; return rc; }
-    c->t += 1;
-  }
+  while (left > 0)
+    if (const int rc = launched_generation()) return rc;
   return ONES_OK;
 }
 

@@ -192,7 +192,7 @@ hipError_t launch_fused(const FusedArgs &fa, hipStream_t s);
 
 // The same for pools beyond those (ones_resident.hip): at most kResidentMaxPool candidates of up to
 // 256 * kResidentMaxWords job slots, as far as a compute unit's LDS holds them (resident_plan).
-constexpr int kResidentMaxPool = 8192;
+constexpr int kResidentMaxPool = 16384;
 constexpr int kResidentMaxWords = 4;
 constexpr uint32_t kResidentMaxGroups = 1024;   // workgroups of a launch: flags in the workspace
 struct ResidentArgs {
@@ -200,8 +200,12 @@ struct ResidentArgs {
   uint32_t *parent_rows;    // as in FusedArgs, as are the following, but for
   int32_t  *sel;
   uint64_t *xkeys;          // [2][P] score bits by pool slot, a buffer per generation parity
-  uint32_t *flags;          // [workgroups] generations of the context a workgroup has published the scores of
-  uint64_t *xrank;          // [K] slots of the survivors by rank, from a ranking by counting, stamped with the generation
+  uint32_t *xrow;           // [2][P] ... and rows
+  uint64_t *flags;          // [2][kResidentMaxGroups] the generation of the context a workgroup has published the candidates of
+                            // and, below it, how many of its children beat the K-th survivor
+  uint64_t *lists;          // [2][P + 2 kResidentMaxGroups][2] score bits of those children; slot, row and the row's place among the
+                            // workgroup's; `segment` entries per workgroup
+  uint64_t *xrank;          // [K] slot and row of the survivors by rank, from a ranking by counting, stamped with the generation
   uint32_t *sync;
   uint32_t generations_before;
   uint32_t sampled;
@@ -209,10 +213,14 @@ struct ResidentArgs {
   uint32_t ring_stride;     // doubles between two places
   uint32_t n_generations;   // > 1; under probability sampling at most kDrawRing
   uint32_t first_changed, spin_limit;
-  uint32_t table_lds, unit_waves, child_units;   // from the plan: LDS bytes of the job table, waves of a workgroup that
-                                                 // compute candidates, children a wave computes in a generation, at most
+  uint32_t paired, unit_waves, child_items, segment, list, table_lds;    // from the plan
 };
-struct ResidentPlan { uint32_t groups, unit_waves, child_units, coin_stride, table_lds; size_t lds; };
+// paired: a wave's item is a pair or a mutant, not a child.  unit_waves: waves of a workgroup that start with an item each;
+// child_items: items of a workgroup that are no survivors, segment: children they make, list: children that beat the K-th
+// survivor a workgroup can rank, all at most; table_lds: LDS bytes of the job table.
+struct ResidentPlan { uint32_t groups, paired, unit_waves, child_items, segment, list, coin_stride, table_lds; size_t lds; };
+size_t resident_exchange_bytes(uint32_t P);     // lists, xkeys, xrank, flags and xrow, consecutive
+void resident_exchange(uint64_t *base, uint32_t P, ResidentArgs &ra);      // their addresses
 // How a launch for ev's pool and job table would be shaped; false: it does not fit.
 bool resident_plan(const EvolveArgs &ev, bool sampled, int n_cus, ResidentPlan &plan);
 hipError_t launch_resident_words1(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t s);
