@@ -185,8 +185,8 @@ int ones_generation_static(ones_ctx *ctx, int32_t n_generations);
 
 /* Pools of at most 64 job slots and 2048 candidates run all generations of a ones_generation call of
  * three or more generations in ONE launch whose workgroups exchange results while it runs, and so do
- * pools of up to 1024 job slots and 8192 candidates (as far as they fit a compute unit's LDS; not
- * under graph capture) with calls of four or more, ten under probability sampling; a workgroup polls for the others' results at most
+ * pools of up to 1024 job slots and 16384 candidates (as far as they fit a compute unit's LDS; not
+ * under graph capture) with calls of four or more, longer ones under probability sampling; a workgroup polls for the others' results at most
  * `polls` times (at first 2^22, a few seconds) and then gives up: the launch ends, the next call
  * that synchronises (ones_best, ones_export, ones_placement) returns ONES_E_HIP, and the context
  * only accepts ones_destroy from then on.  This never happens on a healthy device; polls = 0

@@ -107,10 +107,15 @@ BucketPlan bucket_plan(uint32_t P) {
 // calls of one or two generations are cheaper as two ordinary launches per generation.
 constexpr int32_t kFusedMinGenerations = 3;
 // The same for larger pools (ones_resident.hip).  What a call of four generations gains by one launch, up to 30 %, pays
-// for that launch; under probability sampling a small pool of few rows of slots only does so from ten on, its two launches
-// a generation being short (130 slots, pool 260 and 1024, epochs of 4, 6 and 10 generations: 0.89, 0.92, 0.99 and
-// 0.91, 0.94, 1.04 of the speed; 1000 slots: 1.03, 1.08, 1.17; pool 4096: 1.16, 1.26, 1.42).
-int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) { return sampled && P <= 1024 && Jp <= 4u * kLanes ? 10 : 4; }
+// for that launch; under probability sampling, where the launched kernels rank a small pool by counting, only longer calls do,
+// and a pool of 257 to 1024 on few rows of slots never (speed of calls of 4, 10, 16 and 30 generations against launched ones:
+// pool 128 on 200 slots 0.93, 1.07, 1.15, 1.24; 260 0.84, 0.89, 0.90, 0.94, on 500 slots 0.93, 0.99, 1.01, 1.05;
+// 1024 0.91, 0.99, 1.01, 1.05, on 500 slots 0.98, 1.06, 1.07, 1.10; 1500 0.99, 1.12, 1.18, 1.22; 4096 1.16 from 4 on).
+int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) {
+  if (!sampled || P > 2048) return 4;
+  if (P <= 256 || P > 1024) return 6;
+  return Jp > 4u * kLanes ? 16 : INT32_MAX;
+}
 // From random genomes so many children beat the K-th survivor that a large pool has to be ranked as a whole, which two
 // launches do in less time (16384 candidates: 26 us a generation, 37 in the single launch): more than 3072, which that launch
 // can list, for the first 26 generations of 16384 candidates, never of 8192.

@@ -45,6 +45,7 @@ constexpr int kResListed = 3;                // listed children a thread handles
 constexpr uint32_t kResLeastList = 2 * kResInside;        // children that the list holds at least
 constexpr int kResElites = kResidentMaxPool / 4 / kResThreads;           // survivors a thread handles, at most
 constexpr int kResPool = kResidentMaxPool / kResThreads;
+[[maybe_unused]] constexpr size_t kResLds = kLdsBudget - 512;   // what is left beside the 256 bytes that the or over a workgroup takes
 static_assert(kResidentMaxPool % (4 * kResThreads) == 0, "whole numbers of survivors and candidates per thread");
 static_assert(kResidentMaxPool <= 1 << 14, "a slot and a row in 32 bits");
 static_assert(kResLocal <= kResInside && kResSample <= kResInside, "one set of counters, one set of records");
@@ -948,10 +949,10 @@ bool resident_plan(const EvolveArgs &ev, bool sampled, int n_cus, ResidentPlan &
   // the list of the children takes what is left
   plan.list = kResLeastList;
   const size_t least = plan.table_lds + ranking_bytes(Q, ev.P, plan);
-  if (least > kLdsBudget) return false;
-  plan.list = std::min<uint32_t>({std::max(ev.P, kResLeastList), kResList, static_cast<uint32_t>(plan.list + (kLdsBudget - least) / 12)});
+  if (least > kResLds) return false;
+  plan.list = std::min<uint32_t>({std::max(ev.P, kResLeastList), kResList, static_cast<uint32_t>(plan.list + (kResLds - least) / 12)});
   plan.lds = plan.table_lds + ranking_bytes(Q, ev.P, plan);
-  return plan.lds <= kLdsBudget;
+  return plan.lds <= kResLds;
 }
 #endif
 

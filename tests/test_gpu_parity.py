@@ -450,7 +450,8 @@ def test_single_launch_long_calls(ones, ref, name, calls, per_call):
     (130, 90, 260, 4, True, True, 0), (40, 64, 4096, 5, True, False, 0), (200, 300, 8192, 6, False, True, 0),
     (257, 400, 5460, 7, False, False, 0), (700, 5000, 2052, 8, True, True, 8), (513, 20000, 1028, 9, False, True, 14),
     (1000, 1500, 1024, 10, False, False, 0), (512, 1024, 16384, 11, False, False, 0), (300, 700, 12292, 12, True, True, 0),
-    (20, 12, 16380, 13, False, True, 0), (64, 40, 5464, 14, False, False, 0)])
+    (20, 12, 16380, 13, False, True, 0), (64, 40, 5464, 14, False, False, 0),
+    (1000, 1500, 8192, 15, False, False, 0), (512, 4096, 16384, 16, True, False, 10), (400, 900, 15000, 17, False, True, 6)])
 def test_single_launch_of_pools_beyond_one_row(ones, ref, n_slots, n_gpus, pop, seed, per_gpu, new_first, widest, sampled):
     """Calls of four and more generations of pools that a compute unit's LDS holds, one launch each, between calls
     of fewer, two launches a generation: every word count the launch serves, pools from a wave's work to two rounds
