@@ -120,7 +120,7 @@ int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) {
 // launches do in less time (16384 candidates: 26 us a generation, 37 in the single launch): more than 3072, which that launch
 // can list, for the first 26 generations of 16384 candidates, never of 8192.
 constexpr uint32_t kResidentListed = 8192;
-constexpr int64_t kResidentSettled = 24;
+constexpr int64_t kResidentSettled = 28;
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {
   return !fused_pool(P, Jp) && P <= static_cast<uint32_t>(kResidentMaxPool) && words_of(static_cast<int>(Jp / kLanes)) <= kResidentMaxWords;
