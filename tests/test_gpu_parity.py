@@ -528,6 +528,23 @@ def test_single_launch_waits_are_bounded(ones):
     s.close()
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(130, 90, 260), (200, 300, 8192)])
+def test_single_launch_beyond_one_row_gives_up(ones, n_slots, n_gpus, pop):
+    """The same for the launch of larger pools: with no polls allowed it ends by itself and the error surfaces."""
+    s = ones.Search(cluster(n_gpus, n_slots, pop, seed=31), random_jobs(np.random.default_rng(31), n_slots))
+    s.generation(5)
+    assert s.export(genes=False)[3] == 5
+    s.set_wait_limit(0)
+    say(f"[single launch] wait limit 0, pool {pop}")
+    s.generation(5)
+    with pytest.raises(ones.OnesError) as e:
+        s.best()
+    assert e.value.code == -6 and b"gave up" in ones.load().ones_strerror(-6)
+    with pytest.raises(ones.OnesError):
+        s.generation(1)
+    s.close()
+
+
 # ---- the five configurations at their stated size and length ----
 
 def host_threads():
