@@ -32,7 +32,8 @@ namespace {
 
 constexpr int kResWaves = 16;
 constexpr int kResThreads = kResWaves * kLanes;
-constexpr uint32_t kResPlace = 128;          // children that share a place among the survivors, at most
+constexpr uint32_t kResPlace = 128;          // children that share a place among the survivors, at most (an epoch of 16384 candidates on
+                                             // 512 jobs, 50 generations: 1136 us, with 320 of them 1192, with 64 no difference)
 constexpr uint32_t kResSample = 256;         // sample points of a pool that is ranked as a whole
 constexpr uint32_t kResFirst = 128;          // ... those of them that are ranked first
 constexpr uint32_t kResBound = kResFirst / 4 + 24;     // ... of which the one of this rank bounds what can survive: the K-th is a quarter
