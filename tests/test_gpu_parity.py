@@ -545,6 +545,44 @@ def test_single_launch_beyond_one_row_gives_up(ones, n_slots, n_gpus, pop):
     s.close()
 
 
+def ends_in_single_launch(ones, search, n):
+    """Whether a call of n generations makes a single launch of several: such a launch polls for the other workgroups'
+    results, so with no polls allowed it gives up, and the next call that synchronises says so.  Closes the search."""
+    search.set_wait_limit(0)
+    search.generation(n)
+    try:
+        search.best()
+        return False
+    except ones.OnesError as e:
+        assert e.code == -6 and b"gave up" in ones.load().ones_strerror(-6)
+        return True
+    finally:
+        search.close()
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,before,n", [
+    (200, 300, 4096, [1] * 5, 30), (200, 300, 4096, [7], 4), (1000, 1500, 1024, [2], 37), (130, 90, 256, [1, 2], 9)])
+def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, n_slots, n_gpus, pop, before, n):
+    """Draws of the remaining work are made for several generations at a time.  A call that finds some that an earlier,
+    shorter call left runs like one that finds none: in a single launch, with the same results."""
+    jobs = random_jobs(np.random.default_rng(pop), n_slots)
+    say(f"[draws left] slots={n_slots} P={pop} calls of {before}, then {n}")
+    gpu, again, cpu = (make(cluster(n_gpus, n_slots, pop, seed=70), jobs) for make in (ones.Search, ones.Search, ref.RefSearch))
+    ref.set_threads(8)
+    try:
+        for s in (gpu, again, cpu):
+            s.set_progress(*W.progress(n_slots, seed=70))
+            for k in before:
+                s.generation(k)
+        gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, "after the longer call")
+        assert np.array_equal(gpu.export_remaining().view(np.uint64), cpu.export_remaining().view(np.uint64))
+    finally:
+        ref.set_threads(1)
+    gpu.close(); cpu.close()
+    assert ends_in_single_launch(ones, again, n)
+
+
 # ---- the five configurations at their stated size and length ----
 
 def host_threads():
