@@ -679,6 +679,15 @@ static int export_remaining_impl(ones_ctx *c, double *remaining_out) {
   return ONES_OK;
 }
 
+// What run_fused and run_resident return when the runtime refuses the launch: nothing has run and no state has changed,
+// and the kernels of one generation, which any GPU runs, take the call.
+constexpr int kLaunchRefused = 1;
+static int refused(bool &whole_calls) {
+  whole_calls = false;              // not asked for again by this context
+  (void)hipGetLastError();
+  return kLaunchRefused;
+}
+
 // All n generations in one cooperative launch (small pools).
 static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   FusedArgs fa;
@@ -720,7 +729,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   fa.spin_limit = c->spin_limit;
   int rc;
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, true))) return rc;
-  HIP_TRY(launch_fused(fa, c->stream));
+  if (launch_fused(fa, c->stream) != hipSuccess) return refused(c->fused);
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
   c->fused_generations += n;
   c->fused_changes += c->sampling ? n : fa.first_changed;
@@ -779,12 +788,14 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.spin_limit = c->spin_limit;
   ra.paired = plan.paired; ra.unit_waves = plan.unit_waves; ra.child_items = plan.child_items;
   ra.segment = plan.segment; ra.list = plan.list; ra.table_lds = plan.table_lds;
+  hipError_t launched;
   switch (words_of(static_cast<int>(c->R))) {
-    case 1: HIP_TRY(launch_resident_words1(ra, plan, c->stream)); break;
-    case 2: HIP_TRY(launch_resident_words2(ra, plan, c->stream)); break;
-    case 3: HIP_TRY(launch_resident_words3(ra, plan, c->stream)); break;
-    default: HIP_TRY(launch_resident_words4(ra, plan, c->stream)); break;
+    case 1: launched = launch_resident_words1(ra, plan, c->stream); break;
+    case 2: launched = launch_resident_words2(ra, plan, c->stream); break;
+    case 3: launched = launch_resident_words3(ra, plan, c->stream); break;
+    default: launched = launch_resident_words4(ra, plan, c->stream); break;
   }
+  if (launched != hipSuccess) return refused(c->resident);
   c->fused_generations += n;
   if (c->sampling) c->y_cur = static_cast<int>((c->t + n) % kDrawRing);
   c->rows_assigned = true;
@@ -823,10 +834,12 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   }
   if (c->fused && n_generations >= kFusedMinGenerations) {
     // uses no scratch at all: every workgroup ranks the pool in its LDS
-    int rc = run_fused(c, static_cast<uint32_t>(n_generations), !in_static_scratch);
-    if (rc) { c->poisoned = true; return rc; }
-    c->t += n_generations;
-    return ONES_OK;
+    const int rc = run_fused(c, static_cast<uint32_t>(n_generations), !in_static_scratch);
+    if (rc != kLaunchRefused) {
+      if (rc) { c->poisoned = true; return rc; }
+      c->t += n_generations;
+      return ONES_OK;
+    }
   }
   int32_t left = n_generations;
   bool &splitters_valid = in_static_scratch ? static_valid : c->splitters_valid;
@@ -857,6 +870,7 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
         if (n < least) break;
       }
       const int rc = run_resident(c, static_cast<uint32_t>(n), plan);
+      if (rc == kLaunchRefused) break;
       if (rc) { c->poisoned = true; return rc; }
       splitters_valid = false;
       c->t += n;

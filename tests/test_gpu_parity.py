@@ -1,6 +1,8 @@
 """GPU parity: libones (HIP, through the C ABI) against the CPU oracle on the same seeded
 inputs.  Genomes and survivor lists must match bit for bit every generation; scores within
 1e-12 relative (they are expected to be bit-identical too, which is asserted separately)."""
+import os
+import subprocess
 import sys
 from types import SimpleNamespace
 
@@ -581,6 +583,48 @@ def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, 
         ref.set_threads(1)
     gpu.close(); cpu.close()
     assert ends_in_single_launch(ones, again, n)
+
+
+REFUSING_RUNTIME = """
+int refused = 0;
+int hipLaunchCooperativeKernel(const void *f, ...) { (void)f; ++refused; return 720; }   /* hipErrorCooperativeLaunchTooLarge */
+"""
+
+WITH_REFUSED_LAUNCHES = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)          # found before the runtime's own entry point
+sys.path[:0] = [sys.argv[2], sys.argv[2] + "/tests"]
+import numpy as np
+from test_gpu_parity import assert_same_state, cluster, random_jobs, say, W
+from oracle import ones_ref
+from paper_2108_03645_amd import ones
+for i, (n_slots, n_gpus, pop, sampled) in enumerate([(40, 64, 256, False), (40, 64, 256, True), (130, 90, 260, False), (200, 300, 4096, True)]):
+    say(f"[refused launch] slots={n_slots} P={pop} sampled={sampled}")
+    jobs = random_jobs(np.random.default_rng(pop), n_slots)
+    gpu, cpu = ones.Search(cluster(n_gpus, n_slots, pop, seed=8), jobs), ones_ref.RefSearch(cluster(n_gpus, n_slots, pop, seed=8), jobs)
+    for s in (gpu, cpu):
+        if sampled:
+            s.set_progress(*W.progress(n_slots, seed=8))
+    for n in (6, 1, 12):
+        gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, f"slots={n_slots} P={pop}")
+    assert ctypes.c_int.in_dll(shim, "refused").value == i + 1       # asked once per context
+    gpu.close()
+print("all refused, all right")
+"""
+
+
+def test_a_refused_single_launch_is_run_by_generation(ones, ref, tmp_path):
+    """The runtime may refuse a launch whose workgroups have to be resident at once.  Nothing has run then, so the call
+    goes on with the kernels of one generation.  (In a process of its own, which finds an entry point that refuses
+    before the runtime's.)"""
+    (tmp_path / "refuse.c").write_text(REFUSING_RUNTIME)
+    shim = str(tmp_path / "librefuse.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", shim, str(tmp_path / "refuse.c")], check=True, timeout=60)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-u", "-c", WITH_REFUSED_LAUNCHES, shim, root], capture_output=True, text=True, timeout=100)
+    say(run.stdout + run.stderr)
+    assert run.returncode == 0 and "all refused, all right" in run.stdout
 
 
 # ---- the five configurations at their stated size and length ----
