@@ -768,10 +768,16 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
 }
 
 // The next n generations in one cooperative launch (pools beyond those of run_fused).  Under probability
-// sampling n is at most kDrawRing, and their draws are in the ring.
-static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
+// sampling n is at most kDrawRing, and their draws are in the ring.  Without, the launch leaves the survivors' splitters
+// in the selection's scratch (see run_generation).
+static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan, char *scratch, bool &splitters_valid) {
   ResidentArgs ra{};
   ra.ev = whole_call_args(c);
+  const ScratchLayout &S = c->L.S;
+  ra.n_buckets = c->sampling ? 0 : c->bp.nb;
+  ra.split = reinterpret_cast<uint64_t *>(scratch + S.split);
+  ra.thresh = reinterpret_cast<uint64_t *>(scratch + S.thresh);
+  for (int set = 0; set < 2; ++set) ra.count[set] = reinterpret_cast<uint32_t *>(scratch + S.bcount[set]);
   ra.ev.coin_stride = plan.coin_stride;
   ra.ev.term_lds = c->term_E;
   if (c->sampling) ra.ev.tab = c->table(static_cast<int>((c->t + 1) % kDrawRing));
@@ -802,7 +808,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   c->info_stored = c->info_now;
   c->table_changed = false;
   c->no_schedule = false;
-  c->splitters_valid = false;       // the two-launch path ranks the pool in full before it uses buckets again
+  splitters_valid = ra.n_buckets != 0;
   c->profile_tick += 1;
   return ONES_OK;
 }
@@ -869,10 +875,9 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
         n = static_cast<int32_t>(std::min<int64_t>(left, c->drawn_to - (c->t + 1)));
         if (n < least) break;
       }
-      const int rc = run_resident(c, static_cast<uint32_t>(n), plan);
+      const int rc = run_resident(c, static_cast<uint32_t>(n), plan, block, splitters_valid);
       if (rc == kLaunchRefused) break;
       if (rc) { c->poisoned = true; return rc; }
-      splitters_valid = false;
       c->t += n;
       left -= n;
     }

@@ -102,6 +102,13 @@ struct BucketArgs {
   uint32_t        nb, seg;
 };
 
+// Boundary rank of bucket c (c = 0..nb); bucket b owns survivor ranks [bound(b), bound(b+1)).
+__device__ __forceinline__ uint32_t bucket_bound(uint32_t c, uint32_t K, uint32_t nb) {
+  return (c * K) / nb;          // c <= 1024, K <= 2^18: the product fits 32 bits
+}
+
+constexpr uint64_t kNoSplitter = 0x7FF0000000000000ull;       // +infinity pads the table of splitters
+
 // Remaining work of slot j under probability sampling (Alg. 1, Eq. 7) for generation t:
 // tab.Y[j] = processed[j] * (1/rho - 1), rho ~ Be(alpha[j], beta[j]), for j < Jn; then the
 // slot's entries of the term table.
@@ -196,7 +203,7 @@ constexpr int kResidentMaxPool = 16384;
 constexpr int kResidentMaxWords = 4;
 constexpr uint32_t kResidentMaxGroups = 1024;   // workgroups of a launch: flags in the workspace
 struct ResidentArgs {
-  EvolveArgs ev;
+  EvolveArgs ev;            // ev.bk.nb is 0: no buckets while the launch runs
   uint32_t *parent_rows;    // as in FusedArgs, as are the following, but for
   int32_t  *sel;
   uint64_t *xkeys;          // [2][P] score bits by pool slot, a buffer per generation parity
@@ -206,6 +213,9 @@ struct ResidentArgs {
   uint64_t *lists;          // [2][P + 2 kResidentMaxGroups][2] score bits of those children; slot, row and the row's place among the
                             // workgroup's; `segment` entries per workgroup
   uint64_t *xrank;          // [K] slot and row of the survivors by rank, from a ranking by counting, stamped with the generation
+  uint32_t n_buckets;       // 0, or, for the generation after the launch: buckets whose splitters, ...
+  uint64_t *split, *thresh; // ... threshold ...
+  uint32_t *count[2];       // ... and cleared counters the launch leaves, see BucketArgs
   uint32_t *sync;
   uint32_t generations_before;
   uint32_t sampled;

@@ -111,11 +111,6 @@ __global__ __launch_bounds__(kSortThreads) void rank_pool_kernel(const double *f
 // bucket sorts those few and merges them with its survivors.  Buckets concatenate to the
 // global order.
 
-// Boundary rank of bucket c (c = 0..nb); bucket b owns survivor ranks [bound(b), bound(b+1)).
-__device__ __forceinline__ uint32_t bucket_bound(uint32_t c, uint32_t K, uint32_t nb) {
-  return (c * K) / nb;          // c <= 1024, K <= 2^18: the product fits 32 bits
-}
-
 // Records the next generation's splitters when an element lands on a boundary rank.
 __device__ __forceinline__ void note_rank(uint32_t g, uint64_t bits, uint32_t K, uint32_t nb, uint64_t *split,
                                           uint64_t *thresh) {
@@ -835,8 +830,7 @@ __global__ void splitters_kernel(const double *fit_row, const uint32_t *row_of, 
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c < static_cast<uint32_t>(kBucketCounters)) { count0[c] = 0; count1[c] = 0; }
   if (c < static_cast<uint32_t>(kMaxBuckets))
-    split[c] = (c + 1 < nb) ? static_cast<uint64_t>(__double_as_longlong(fit_row[row_of[sel[bucket_bound(c + 1, K, nb)]]]))
-                            : 0x7FF0000000000000ull;          // +infinity pads the table
+    split[c] = (c + 1 < nb) ? static_cast<uint64_t>(__double_as_longlong(fit_row[row_of[sel[bucket_bound(c + 1, K, nb)]]])) : kNoSplitter;
   if (c == 0) *thresh = static_cast<uint64_t>(__double_as_longlong(fit_row[row_of[sel[K - 1]]]));
 }
 

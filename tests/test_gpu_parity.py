@@ -585,6 +585,33 @@ def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, 
     assert ends_in_single_launch(ones, again, n)
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(200, 300, 4096), (512, 1024, 16384), (1000, 1500, 1024)])
+def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_slots, n_gpus, pop):
+    """A launched generation behind a single launch selects through buckets, like one behind a launched generation, and
+    does not rank the whole pool: its selection takes about as long as that of the next one (a ranking of the pool with
+    the splitters' launch takes 1.8 times as long for 1024 candidates and nearly four times for 4096 and more)."""
+    cl, jobs = W.large() if pop == 16384 else (cluster(n_gpus, n_slots, pop, seed=33), random_jobs(np.random.default_rng(33), n_slots))
+    say(f"[buckets behind a single launch] slots={n_slots} P={pop}")
+    gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+    ref.set_threads(host_threads())
+    try:
+        gpu.generation(70); cpu.generation(70)
+        first, second = [], []
+        for _ in range(5):
+            gpu.generation(4); cpu.generation(4)
+            for took in (first, second):
+                gpu.profile_enable(1)
+                gpu.generation(1); cpu.generation(1)
+                took.append(gpu.profile_read()["select_ms"])
+            gpu.profile_enable(0)
+            assert_same_state(gpu, cpu, "behind a single launch", genes=False)
+    finally:
+        ref.set_threads(1)
+    say(f"selections: {first} behind a single launch, {second} behind those")
+    assert sorted(first)[2] < 1.5 * sorted(second)[2]
+    gpu.close(); cpu.close()
+
+
 REFUSING_RUNTIME = """
 int refused = 0;
 int hipLaunchCooperativeKernel(const void *f, ...) { (void)f; ++refused; return 720; }   /* hipErrorCooperativeLaunchTooLarge */
