@@ -116,11 +116,16 @@ int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) {
   if (P <= 256 || P > 1024) return 6;
   return Jp > 4u * kLanes ? 16 : INT32_MAX;
 }
-// From random genomes so many children beat the K-th survivor that a large pool has to be ranked as a whole, which two
-// launches do in less time (16384 candidates: 26 us a generation, 37 in the single launch): more than 3072, which that launch
-// can list, for the first 26 generations of 16384 candidates, never of 8192.
-constexpr uint32_t kResidentListed = 8192;
-constexpr int64_t kResidentSettled = 28;
+// A search starts from random genomes, and while its pool is as mixed as that, many children beat the K-th survivor.
+// Pools above 8192 are faster by generation then (16384 candidates on 512 slots, the first 50 generations: 1280 us, 1370 with
+// one launch for those after the 28th, although it lists all of the children from there on), until fewer than about an
+// eighth of the pool do: after 8 generations on 100 slots, 10 on 200, 30 to 60 on 512, so after so many that grow with the
+// rows of slots.  Smaller pools gain by one launch from the first generation on (8192: 1.1 for the first 20 on
+// 1000 slots, 1.2 on 100).
+int64_t resident_from(uint32_t P, uint32_t Jp) { return P > 8192u ? 8 * (Jp / kLanes) : 0; }
+// Of a call that begins earlier, so many generations have to come after that one: a launch behind queued ones waits for
+// them, and 4 to 16 do not make up for it (a call of 20 that ends with four: 0.88 on 100 slots, with eight 0.94 on 200).
+constexpr int32_t kResidentRest = 24;
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {
   return !fused_pool(P, Jp) && P <= static_cast<uint32_t>(kResidentMaxPool) && words_of(static_cast<int>(Jp / kLanes)) <= kResidentMaxWords;
@@ -861,8 +866,12 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   const bool by_kernel = c->profiling && !in_static_scratch;       // the measurement hook sees evolve and select launches
   if (c->resident && left >= least && !by_kernel && resident_plan(whole_call_args(c), c->sampling, c->n_cus, plan) &&
       !capturing(c->stream)) {
-    while (!c->sampling && c->P > kResidentListed && c->t < kResidentSettled && left > 0)
-      if (const int rc = launched_generation()) return rc;
+    const int64_t settled = resident_from(c->P, c->Jp);
+    if (!c->sampling && c->t < settled) {
+      const int64_t rest = c->t + left - settled;
+      while (left > (rest < kResidentRest ? 0 : rest))
+        if (const int rc = launched_generation()) return rc;
+    }
     while (left >= least) {
       int32_t n = left;
       if (c->sampling) {

@@ -612,6 +612,29 @@ def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_
     gpu.close(); cpu.close()
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,age,n,single", [
+    (512, 1024, 16384, 0, 50, False), (512, 1024, 16384, 50, 20, False), (512, 1024, 16384, 50, 38, True), (512, 1024, 16384, 64, 9, True),
+    (400, 900, 15000, 30, 40, False), (400, 900, 15000, 56, 11, True), (100, 200, 12000, 0, 39, False), (100, 200, 12000, 0, 40, True),
+    (100, 200, 12000, 16, 8, True), (20, 12, 16380, 8, 8, True), (1000, 1500, 8192, 0, 4, True)])
+def test_young_searches_of_large_pools_are_launched_by_generation(ones, ref, n_slots, n_gpus, pop, age, n, single):
+    """Pools above 8192 take the single launch once their genomes are no longer random, after eight generations per row of
+    job slots, and in a call that begins earlier only if 24 of its generations come after those.  Both ways are compared
+    with the oracle, with a generation of the other kind and another call behind."""
+    cl, jobs = cluster(n_gpus, n_slots, pop, seed=61), random_jobs(np.random.default_rng(61), n_slots)
+    say(f"[young searches] slots={n_slots} P={pop}: {n} generations after {age}")
+    ref.set_threads(host_threads())
+    try:
+        gpu, again, cpu = (make(cl, jobs) for make in (ones.Search, ones.Search, ref.RefSearch))
+        again.generation(age)
+        for k in (age, n, 1, 30):
+            gpu.generation(k); cpu.generation(k)
+            assert_same_state(gpu, cpu, f"after a call of {k}", genes=k == n)
+    finally:
+        ref.set_threads(1)
+    gpu.close(); cpu.close()
+    assert ends_in_single_launch(ones, again, n) == single
+
+
 REFUSING_RUNTIME = """
 int refused = 0;
 int hipLaunchCooperativeKernel(const void *f, ...) { (void)f; ++refused; return 720; }   /* hipErrorCooperativeLaunchTooLarge */
