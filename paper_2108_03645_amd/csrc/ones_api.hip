@@ -126,6 +126,14 @@ int64_t resident_from(uint32_t P, uint32_t Jp) { return P > 8192u ? 8 * (Jp / kL
 // Of a call that begins earlier, so many generations have to come after that one: a launch behind queued ones waits for
 // them, and 4 to 16 do not make up for it (a call of 20 that ends with four: 0.88 on 100 slots, with eight 0.94 on 200).
 constexpr int32_t kResidentRest = 24;
+// The same after a table in which `changed` of the n slots changed hands: the generations that its pool stays mixed.  From a
+// twelfth of the slots on, beyond four rows of them (16384 candidates on 512 slots, calls of 20 behind a table that changes
+// three in ten of them: 531 and 430 us by generation, 676 and 508 in one launch each).  On up to four rows one launch is
+// the faster way all the same (12000 on 200, three in ten: 428 and 570 us against 384 and 392).
+int64_t mixed_by(uint32_t P, uint32_t Jp, uint32_t changed, uint32_t n) {
+  if (Jp <= 4u * kLanes || 12 * changed < n) return 0;
+  return resident_from(P, Jp) * std::min(n, 4 * changed) / n;
+}
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {
   return !fused_pool(P, Jp) && P <= static_cast<uint32_t>(kResidentMaxPool) && words_of(static_cast<int>(Jp / kLanes)) <= kResidentMaxWords;
@@ -301,6 +309,7 @@ struct ones_ctx {
   bool poisoned;              // a launch failed in the middle of a generation: the state is inconsistent
   bool fused;                 // small pool: all generations of a call in one cooperative launch
   bool resident;              // ... the same for larger pools, as far as the job table leaves room (resident_plan)
+  int64_t settled;            // ... from this generation on
   uint32_t fused_generations; // generations those launches have run so far
   uint32_t fused_changes;     // ... of them generations that also exchanged the survivors' scores
   uint32_t fused_draws;       // ... of them generations with a drawn remaining work
@@ -566,6 +575,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     c->fused = fused_pool(c->P, c->Jp) && prop.cooperativeLaunch != 0 &&
                fused_grid_limit(c->P) <= static_cast<uint32_t>(c->n_cus);
     c->resident = resident_pool(c->P, c->Jp) && prop.cooperativeLaunch != 0;
+    c->settled = resident_from(c->P, c->Jp);
   }
   c->profiling = false; c->profile_every = 1; c->profile_tick = 0; c->evolve_used = c->select_used = 0;
   {
@@ -592,8 +602,10 @@ static int set_jobs_impl(ones_ctx *c, const ones_jobs *jobs) {
   HostJobs h;
   int rc = stage_jobs(static_cast<int>(c->Jn), static_cast<int>(c->Jp), jobs, h);
   if (rc) return rc;
+  uint32_t changed = 0;
   for (uint32_t j = 0; j < c->Jn; ++j)
     if (h.id[j] != c->ids[j]) {                                  // the slot changed hands
+      changed += 1;
       h.rawinfo[j] |= 1u << 17;
       if ((h.rawinfo[j] >> 15) & 1u) h.rawinfo[j] |= 1u << 16;   // an active job arrived in it
     }
@@ -603,6 +615,7 @@ static int set_jobs_impl(ones_ctx *c, const ones_jobs *jobs) {
   c->ids = h.id;
   c->table_changed = true;
   c->no_schedule = true;
+  c->settled = std::max(c->settled, c->t + mixed_by(c->P, c->Jp, changed, c->Jn));
   c->drawn_from = c->drawn_to = 0;   // the draws made ahead built their term tables from the old job table
   return ONES_OK;
 }
@@ -866,9 +879,8 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   const bool by_kernel = c->profiling && !in_static_scratch;       // the measurement hook sees evolve and select launches
   if (c->resident && left >= least && !by_kernel && resident_plan(whole_call_args(c), c->sampling, c->n_cus, plan) &&
       !capturing(c->stream)) {
-    const int64_t settled = resident_from(c->P, c->Jp);
-    if (!c->sampling && c->t < settled) {
-      const int64_t rest = c->t + left - settled;
+    if (!c->sampling && c->t < c->settled) {
+      const int64_t rest = c->t + left - c->settled;
       while (left > (rest < kResidentRest ? 0 : rest))
         if (const int rc = launched_generation()) return rc;
     }

@@ -635,6 +635,35 @@ def test_young_searches_of_large_pools_are_launched_by_generation(ones, ref, n_s
     assert ends_in_single_launch(ones, again, n) == single
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,changed,n,single", [
+    (512, 1024, 16384, 0.03, 20, True), (512, 1024, 16384, 0.3, 20, False), (512, 1024, 16384, 1.0, 50, False), (512, 1024, 16384, 0.15, 63, True),
+    (200, 300, 12000, 1.0, 20, True), (700, 900, 8192, 1.0, 20, True)])
+def test_a_table_that_changes_much_makes_a_large_pool_young_again(ones, ref, n_slots, n_gpus, pop, changed, n, single):
+    """A table in which a twelfth of more than 256 slots or more change hands puts the single launch of a pool above 8192 off,
+    for as many generations as at the start of a search (a quarter of the slots or more changed) or a part of that."""
+    rng = np.random.default_rng(62)
+    cl, jobs = cluster(n_gpus, n_slots, pop, seed=62), random_jobs(rng, n_slots)
+    new = random_jobs(rng, n_slots)
+    stays = np.arange(n_slots) >= round(changed * n_slots)
+    for name in ("active", "bmin", "bmax", "gpu_max_batch", "a", "c", "d", "remaining"):
+        getattr(new, name)[stays] = getattr(jobs, name)[stays]
+    new.job_id = np.where(stays, jobs.job_id, jobs.job_id + 1000)
+    say(f"[changed tables] slots={n_slots} P={pop} changed={changed}: a call of {n}")
+    ref.set_threads(host_threads())
+    try:
+        gpu, again, cpu = (make(cl, jobs) for make in (ones.Search, ones.Search, ref.RefSearch))
+        for s in (gpu, again, cpu):
+            s.generation(104)
+            s.set_jobs(new)
+        for k in (n, 1, 30):
+            gpu.generation(k); cpu.generation(k)
+            assert_same_state(gpu, cpu, f"after a call of {k}", genes=k == n)
+    finally:
+        ref.set_threads(1)
+    gpu.close(); cpu.close()
+    assert ends_in_single_launch(ones, again, n) == single
+
+
 REFUSING_RUNTIME = """
 int refused = 0;
 int hipLaunchCooperativeKernel(const void *f, ...) { (void)f; ++refused; return 720; }   /* hipErrorCooperativeLaunchTooLarge */
