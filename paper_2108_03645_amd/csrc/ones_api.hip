@@ -111,7 +111,11 @@ constexpr int32_t kFusedMinGenerations = 3;
 // and a pool of 257 to 1024 on few rows of slots never (speed of calls of 4, 10, 16 and 30 generations against launched ones:
 // pool 128 on 200 slots 0.93, 1.07, 1.15, 1.24; 260 0.84, 0.89, 0.90, 0.94, on 500 slots 0.93, 0.99, 1.01, 1.05;
 // 1024 0.91, 0.99, 1.01, 1.05, on 500 slots 0.98, 1.06, 1.07, 1.10; 1500 0.99, 1.12, 1.18, 1.22; 4096 1.16 from 4 on).
-int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled) {
+// Where neither the table has changed nor draws are made, launched generations select through buckets, and four to six of
+// a large pool on many slots are the faster ones (calls of 4, 6 and 10 generations, 16384 on 512 slots 0.90, 0.97, 1.36; 12000 on
+// 512 0.93, 1.01, 1.36; 16384 on 200 1.17, 1.11, 1.25; 8192 on 512 1.05, 1.13, 1.48).
+int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled, bool table_changed) {
+  if (!sampled && !table_changed && P > 8192 && Jp > 4u * kLanes) return 8;
   if (!sampled || P > 2048) return 4;
   if (P <= 256 || P > 1024) return 6;
   return Jp > 4u * kLanes ? 16 : INT32_MAX;
@@ -875,7 +879,7 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
     return static_cast<int>(ONES_OK);
   };
   ResidentPlan plan;
-  const int32_t least = resident_min_generations(c->P, c->Jp, c->sampling);
+  const int32_t least = resident_min_generations(c->P, c->Jp, c->sampling, c->table_changed);
   const bool by_kernel = c->profiling && !in_static_scratch;       // the measurement hook sees evolve and select launches
   if (c->resident && left >= least && !by_kernel && resident_plan(whole_call_args(c), c->sampling, c->n_cus, plan) &&
       !capturing(c->stream)) {

@@ -664,6 +664,22 @@ def test_a_table_that_changes_much_makes_a_large_pool_young_again(ones, ref, n_s
     assert ends_in_single_launch(ones, again, n) == single
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,n,single,single_after_change", [
+    (512, 1024, 16384, 7, False, True), (512, 1024, 16384, 8, True, True), (257, 400, 8200, 4, False, True),
+    (200, 300, 12000, 4, True, True), (512, 1024, 8192, 4, True, True), (200, 300, 12000, 3, False, False)])
+def test_short_calls_of_large_pools(ones, n_slots, n_gpus, pop, n, single, single_after_change):
+    """Of pools above 8192 on more than 256 slots, a call under the table of the call before takes the single launch from eight
+    generations on, one under a new table from four on, like all calls of smaller pools."""
+    cl, jobs = cluster(n_gpus, n_slots, pop, seed=63), random_jobs(np.random.default_rng(63), n_slots)
+    say(f"[short calls] slots={n_slots} P={pop}: {n} generations")
+    for change in (False, True):
+        s = ones.Search(cl, jobs)
+        s.generation(80)
+        if change:
+            s.set_jobs(jobs)
+        assert ends_in_single_launch(ones, s, n) == (single_after_change if change else single)
+
+
 REFUSING_RUNTIME = """
 int refused = 0;
 int hipLaunchCooperativeKernel(const void *f, ...) { (void)f; ++refused; return 720; }   /* hipErrorCooperativeLaunchTooLarge */
