@@ -110,15 +110,20 @@ constexpr int32_t kFusedMinGenerations = 3;
 // for that launch; under probability sampling, where the launched kernels rank a small pool by counting, only longer calls do,
 // and a pool of 257 to 1024 on few rows of slots never (speed of calls of 4, 10, 16 and 30 generations against launched ones:
 // pool 128 on 200 slots 0.93, 1.07, 1.15, 1.24; 260 0.84, 0.89, 0.90, 0.94, on 500 slots 0.93, 0.99, 1.01, 1.05;
-// 1024 0.91, 0.99, 1.01, 1.05, on 500 slots 0.98, 1.06, 1.07, 1.10; 1500 0.99, 1.12, 1.18, 1.22; 4096 1.16 from 4 on).
+// 1024 0.91, 0.99, 1.01, 1.05, on 500 slots 0.98, 1.06, 1.07, 1.10; 1500 0.99, 1.12, 1.18, 1.22; 4096 1.16 from 4 on; of calls
+// of 6, 8, 10, 16 and 32: pool 64 on 100 slots 0.94, 0.99, 1.05, 1.13, 1.24, on 500 1.06, 1.12, 1.17, 1.26, 1.40;
+// 192 0.91, 0.95, 0.98, 1.03, 1.10 and 0.96, 0.98, 1.02, 1.07, 1.14; 256 0.90, 0.92, 0.95, 0.99, 1.05 and 0.95, 0.97, 1.00, 1.04, 1.11).
 // Where neither the table has changed nor draws are made, launched generations select through buckets, and four to six of
 // a large pool on many slots are the faster ones (calls of 4, 6 and 10 generations, 16384 on 512 slots 0.90, 0.97, 1.36; 12000 on
 // 512 0.93, 1.01, 1.36; 16384 on 200 1.17, 1.11, 1.25; 8192 on 512 1.05, 1.13, 1.48).
 int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled, bool table_changed) {
   if (!sampled && !table_changed && P > 8192 && Jp > 4u * kLanes) return 8;
   if (!sampled || P > 2048) return 4;
-  if (P <= 256 || P > 1024) return 6;
-  return Jp > 4u * kLanes ? 16 : INT32_MAX;
+  const bool many_rows = Jp > 4u * kLanes;
+  if (P > 1024) return 6;
+  if (P > 256) return many_rows ? 16 : INT32_MAX;
+  if (P > 128) return many_rows ? 10 : 16;
+  return many_rows ? 6 : 8;
 }
 // A search starts from random genomes, and while its pool is as mixed as that, many children beat the K-th survivor.
 // Pools above 8192 are faster by generation then (16384 candidates on 512 slots, the first 50 generations: 1280 us, 1370 with

@@ -563,7 +563,7 @@ def ends_in_single_launch(ones, search, n):
 
 
 @pytest.mark.parametrize("n_slots,n_gpus,pop,before,n", [
-    (200, 300, 4096, [1] * 5, 30), (200, 300, 4096, [7], 4), (1000, 1500, 1024, [2], 37), (130, 90, 256, [1, 2], 9)])
+    (200, 300, 4096, [1] * 5, 30), (200, 300, 4096, [7], 4), (1000, 1500, 1024, [2], 37), (130, 90, 128, [1, 2], 9)])
 def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, n_slots, n_gpus, pop, before, n):
     """Draws of the remaining work are made for several generations at a time.  A call that finds some that an earlier,
     shorter call left runs like one that finds none: in a single launch, with the same results."""
@@ -678,6 +678,19 @@ def test_short_calls_of_large_pools(ones, n_slots, n_gpus, pop, n, single, singl
         if change:
             s.set_jobs(jobs)
         assert ends_in_single_launch(ones, s, n) == (single_after_change if change else single)
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,least", [
+    (130, 200, 128, 8), (300, 400, 64, 6), (200, 300, 132, 16), (130, 90, 256, 16), (300, 400, 132, 10), (257, 400, 256, 10), (256, 400, 260, None),
+    (257, 400, 1024, 16), (200, 300, 1028, 6), (130, 90, 2052, 4)])
+def test_short_sampled_calls(ones, n_slots, n_gpus, pop, least):
+    """From how many generations on a call under probability sampling takes the single launch."""
+    cl, jobs = cluster(n_gpus, n_slots, pop, seed=64), random_jobs(np.random.default_rng(64), n_slots)
+    say(f"[short sampled calls] slots={n_slots} P={pop}")
+    for n in (least - 1, least) if least else (32, 70):
+        s = ones.Search(cl, jobs)
+        s.set_progress(*W.progress(n_slots, seed=64))
+        assert ends_in_single_launch(ones, s, n) == (least is not None and n >= least), n
 
 
 REFUSING_RUNTIME = """
