@@ -796,11 +796,12 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
 
 // The next n generations in one cooperative launch (pools beyond those of run_fused).  Under probability
 // sampling n is at most kDrawRing, and their draws are in the ring.  Without, the launch leaves the survivors' splitters
-// in the selection's scratch (see run_generation).
-static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan, char *scratch, bool &splitters_valid) {
+// in the workspace's scratch for ones_generation, whichever entry point made it: it needs no scratch itself.
+static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ResidentArgs ra{};
   ra.ev = whole_call_args(c);
   const ScratchLayout &S = c->L.S;
+  char *scratch = c->ws + c->L.scratch;
   ra.n_buckets = c->sampling ? 0 : c->bp.nb;
   ra.split = reinterpret_cast<uint64_t *>(scratch + S.split);
   ra.thresh = reinterpret_cast<uint64_t *>(scratch + S.thresh);
@@ -835,7 +836,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan, char 
   c->info_stored = c->info_now;
   c->table_changed = false;
   c->no_schedule = false;
-  splitters_valid = ra.n_buckets != 0;
+  c->splitters_valid = ra.n_buckets != 0;
   c->profile_tick += 1;
   return ONES_OK;
 }
@@ -905,7 +906,7 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
         n = static_cast<int32_t>(std::min<int64_t>(left, c->drawn_to - (c->t + 1)));
         if (n < least) break;
       }
-      const int rc = run_resident(c, static_cast<uint32_t>(n), plan, block, splitters_valid);
+      const int rc = run_resident(c, static_cast<uint32_t>(n), plan);
       if (rc == kLaunchRefused) break;
       if (rc) { c->poisoned = true; return rc; }
       c->t += n;

@@ -585,8 +585,9 @@ def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, 
     assert ends_in_single_launch(ones, again, n)
 
 
-@pytest.mark.parametrize("n_slots,n_gpus,pop", [(200, 300, 4096), (512, 1024, 16384), (1000, 1500, 1024)])
-def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_slots, n_gpus, pop):
+@pytest.mark.parametrize("n_slots,n_gpus,pop,entry", [
+    (200, 300, 4096, "generation"), (512, 1024, 16384, "generation"), (1000, 1500, 1024, "generation"), (200, 300, 4096, "generation_static")])
+def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_slots, n_gpus, pop, entry):
     """A launched generation behind a single launch selects through buckets, like one behind a launched generation, and
     does not rank the whole pool: its selection takes about as long as that of the next one (a ranking of the pool with
     the splitters' launch takes 1.8 times as long for 1024 candidates and nearly four times for 4096 and more)."""
@@ -598,7 +599,7 @@ def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_
         gpu.generation(70); cpu.generation(70)
         first, second = [], []
         for _ in range(5):
-            gpu.generation(4); cpu.generation(4)
+            getattr(gpu, entry)(8); cpu.generation(8)
             for took in (first, second):
                 gpu.profile_enable(1)
                 gpu.generation(1); cpu.generation(1)
