@@ -455,7 +455,8 @@ def test_single_launch_long_calls(ones, ref, name, calls, per_call):
     (20, 12, 16380, 13, False, True, 0), (64, 40, 5464, 14, False, False, 0),
     (1000, 1500, 8192, 15, False, False, 0), (512, 4096, 16384, 16, True, False, 10), (400, 900, 15000, 17, False, True, 6)])
 def test_single_launch_of_pools_beyond_one_row(ones, ref, n_slots, n_gpus, pop, seed, per_gpu, new_first, widest, sampled):
-    """Calls of four and more generations of pools that a compute unit's LDS holds, one launch each, between calls
+    """Calls of four and more generations of pools that a compute unit's LDS holds, in one launch each as far as the rules for
+    young searches and short sampled calls let them (which is checked below), between calls
     of fewer, two launches a generation: every word count the launch serves, pools from a wave's work to two rounds
     of all waves, waves that take children and waves that take pairs, children that crowd (few jobs on fewer GPUs than they want: copies of one genome), table
     changes, both crossovers, arrivals with and without executed times, every look-up of GPU counts, the remaining work
@@ -560,6 +561,154 @@ def ends_in_single_launch(ones, search, n):
         return True
     finally:
         search.close()
+
+
+def wide_table(rng, n_slots, widest):
+    """Random jobs; widest > 0: on up to 2^widest GPUs each."""
+    jobs = random_jobs(rng, n_slots)
+    if widest:
+        jobs.gpu_max_batch[:] = 16
+        jobs.bmax = (16 << rng.integers(min(7, widest), widest + 1, n_slots)).astype(np.int32)
+        jobs.bmin = (16 << rng.integers(0, 3, n_slots)).astype(np.int32)
+    return jobs
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,per_gpu,widest,fixed,sampled", [
+    (1, 4, 2052, False, 0, True, True), (65, 90, 4, False, 0, True, True), (66, 5, 2048, False, 0, True, True),
+    (130, 90, 260, True, 0, True, False), (300, 400, 260, True, 0, True, True), (40, 64, 4096, True, 0, True, True),
+    (200, 300, 8192, False, 0, True, True), (257, 400, 5460, False, 0, True, True), (700, 5000, 2052, True, 8, True, True),
+    (513, 20000, 1028, False, 14, True, True), (1000, 1500, 1024, False, 0, True, True), (512, 1024, 16384, False, 0, True, True),
+    (300, 700, 12292, True, 0, True, True), (20, 12, 16380, False, 0, True, True), (64, 40, 5464, False, 0, True, True),
+    (1000, 1500, 8192, False, 0, True, True), (512, 4096, 16384, True, 10, False, False), (512, 4096, 16384, True, 8, True, True),
+    (400, 900, 15000, False, 6, True, True)])
+def test_which_pools_beyond_one_row_take_the_single_launch(ones, n_slots, n_gpus, pop, per_gpu, widest, fixed, sampled):
+    """The shapes of the tests around this one in calls of 37 generations (of a search that is not young any more): with
+    the remaining work fixed and sampled.  All but a small pool under sampling, and a job table that does not fit."""
+    say(f"[takes the single launch] G={n_gpus} slots={n_slots} P={pop}")
+    for draws, single in ((False, fixed), (True, sampled)):
+        s = ones.Search(cluster(n_gpus, n_slots, pop, seed=5), wide_table(np.random.default_rng(5), n_slots, widest))
+        s.set_crossover(per_gpu=per_gpu)
+        s.generation(8 * (ones.padded_jobs(n_slots) // 64) if pop > 8192 else 1)
+        if draws:
+            s.set_progress(*W.progress(n_slots, seed=5))
+        assert ends_in_single_launch(ones, s, 37) == single, draws
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,seed,per_gpu,new_first,widest", [
+    (512, 1024, 16384, 21, False, False, 0), (512, 4096, 16384, 22, True, True, 8), (400, 900, 15000, 23, False, True, 6),
+    (300, 700, 12292, 24, True, True, 0), (300, 400, 260, 25, True, True, 0), (20, 12, 16380, 26, False, True, 0)])
+def test_single_launch_of_older_searches(ones, ref, n_slots, n_gpus, pop, seed, per_gpu, new_first, widest):
+    """The same for pools above 8192 that are past the generations they are launched one by one for (and a small pool on
+    many slots): calls in one launch between launched generations, and tables in which a few slots change hands."""
+    rng = np.random.default_rng(seed)
+    say(f"[older searches] G={n_gpus} slots={n_slots} P={pop} seed={seed} per_gpu={per_gpu} new_first={new_first}")
+    jobs = wide_table(rng, n_slots, widest)
+    ref.set_threads(host_threads())
+    try:
+        gpu, cpu = (make(cluster(n_gpus, n_slots, pop, seed=seed), jobs) for make in (ones.Search, ref.RefSearch))
+        for s in (gpu, cpu):
+            s.set_crossover(per_gpu=per_gpu)
+            s.set_new_jobs_first(new_first)
+        for step, n in enumerate([70, 9, 1, 8, 4, 20, 3, 33]):
+            gpu.generation(n); cpu.generation(n)
+            assert_same_state(gpu, cpu, f"call {step} of {n} generations", genes=step in (1, 5))
+            if step in (3, 4, 6):                    # before the calls of 4, 20 and 33
+                new = wide_table(rng, n_slots, widest)
+                stays = rng.random(n_slots) >= 0.03
+                for name in ("active", "bmin", "bmax", "gpu_max_batch", "a", "c", "d", "remaining"):
+                    getattr(new, name)[stays] = getattr(jobs, name)[stays]
+                new.job_id = np.where(stays, jobs.job_id, jobs.job_id + 1000)
+                new.remaining = new.remaining * rng.uniform(0.8, 1.0, n_slots)
+                jobs = new
+                for s in (gpu, cpu):
+                    s.set_jobs(jobs)
+                    if new_first and step != 4:
+                        s.set_processed_time(rng_times(seed, step, n_slots))
+        gb, cb = gpu.best(), cpu.best()
+        assert gb[0].tolist() == cb[0].tolist() and gb[1].tolist() == cb[1].tolist() and gb[2] == cb[2]
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
+@pytest.mark.parametrize("sampled", [False, True])
+def test_searches_at_the_same_time(ones, ref, sampled):
+    """Three threads, each with a search and a stream of its own: calls in one launch of pools of three sizes wait for
+    each other and change nothing."""
+    import threading
+
+    import torch
+    shapes = [(130, 90, 260), (200, 300, 4096), (300, 400, 1024)]
+    say(f"[at the same time] {shapes} sampled={sampled}")
+    searches = []
+    for k, (n_slots, n_gpus, pop) in enumerate(shapes):
+        jobs = random_jobs(np.random.default_rng(80 + k), n_slots)
+        pair = [ones.Search(cluster(n_gpus, n_slots, pop, seed=80 + k), jobs, stream=torch.cuda.Stream()),
+                ref.RefSearch(cluster(n_gpus, n_slots, pop, seed=80 + k), jobs)]
+        for s in pair:
+            if sampled:
+                s.set_progress(*W.progress(n_slots, seed=80 + k))
+        searches.append((jobs, *pair))
+    calls, start = [20, 3, 17, 1, 6] * 4, threading.Barrier(len(shapes))
+
+    def loop(jobs, gpu):
+        start.wait()
+        for i, n in enumerate(calls):
+            if i % 5 == 2:
+                gpu.set_jobs(jobs)
+            gpu.generation(n)
+            gpu.best()
+
+    threads = [threading.Thread(target=loop, args=(jobs, gpu)) for jobs, gpu, _ in searches]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    ref.set_threads(8)
+    try:
+        for k, (jobs, gpu, cpu) in enumerate(searches):
+            for i, n in enumerate(calls):
+                if i % 5 == 2:
+                    cpu.set_jobs(jobs)
+                cpu.generation(n)
+            assert_same_state(gpu, cpu, f"search {k}")
+            gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,sampled,entry", [
+    (130, 90, 260, False, "generation"), (200, 300, 4096, False, "generation"), (200, 300, 4096, False, "generation_static"),
+    (300, 400, 2052, True, "generation")])
+def test_a_captured_call_is_launched_by_generation(ones, ref, n_slots, n_gpus, pop, sampled, entry):
+    """A launch whose workgroups have to be resident at once is not recorded into a graph: the call goes by generation there.
+    The graph is launched once, as the one call that it is, with eager calls before and behind it."""
+    import torch
+    jobs = random_jobs(np.random.default_rng(90), n_slots)
+    say(f"[captured] slots={n_slots} P={pop} sampled={sampled} {entry}")
+    side = torch.cuda.Stream()
+    gpu = ones.Search(cluster(n_gpus, n_slots, pop, seed=90), jobs, stream=side)
+    cpu = ref.RefSearch(cluster(n_gpus, n_slots, pop, seed=90), jobs)
+    ref.set_threads(8)
+    try:
+        for s in (gpu, cpu):
+            if sampled:
+                s.set_progress(*W.progress(n_slots, seed=90))
+            s.generation(9)
+        assert_same_state(gpu, cpu, "before")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            getattr(gpu, entry)(20)
+        cpu.generation(20)
+        with torch.cuda.stream(side):
+            graph.replay()
+        assert_same_state(gpu, cpu, "the captured call")
+        for n in (6, 2, 12):
+            gpu.generation(n); cpu.generation(n)
+            assert_same_state(gpu, cpu, f"call of {n} behind it")
+    finally:
+        ref.set_threads(1)
+    gpu.close(); cpu.close()
 
 
 @pytest.mark.parametrize("n_slots,n_gpus,pop,before,n", [
