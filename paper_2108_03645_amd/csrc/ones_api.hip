@@ -706,6 +706,27 @@ static int export_remaining_impl(ones_ctx *c, double *remaining_out) {
   return ONES_OK;
 }
 
+// The problem as the kernels of a whole call see it.
+static EvolveArgs whole_call_args(const ones_ctx *c) {
+  EvolveArgs a{};
+  a.genes = c->at<uint32_t>(c->L.genes);
+  a.fit_row = c->at<double>(c->L.fit_row);
+  a.row_of = c->at<uint32_t>(c->L.row_of);
+  a.spare = c->at<uint32_t>(c->L.spare);
+  a.assigned = c->rows_assigned ? 1u : 0u;
+  a.tab = c->table();
+  a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
+  a.key0 = static_cast<uint32_t>(c->cfg.seed);
+  a.key1 = static_cast<uint32_t>(c->cfg.seed >> 32);
+  a.t = static_cast<uint32_t>(c->t);
+  a.T_mut = c->T_mut; a.T_x = c->T_x;
+  a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
+  a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
+  a.per_gpu = c->per_gpu ? 1u : 0u;
+  a.fault = c->at<uint32_t>(c->L.fsync) + 2;
+  return a;
+}
+
 // What run_fused and run_resident return when the runtime refuses the launch: nothing has run and no state has changed,
 // and the kernels of one generation, which any GPU runs, take the call.
 constexpr int kLaunchRefused = 1;
@@ -717,30 +738,9 @@ static int refused(bool &whole_calls) {
 
 // All n generations in one cooperative launch (small pools).
 static int run_fused(ones_ctx *c, uint32_t n, bool events) {
-  FusedArgs fa;
-  EvolveArgs &a = fa.ev;
-  a.genes = c->at<uint32_t>(c->L.genes);
-  a.fit_row = c->at<double>(c->L.fit_row);
-  a.parent_row = nullptr; a.occupied = nullptr; a.occupied_other = nullptr;
-  a.row_of = c->at<uint32_t>(c->L.row_of);
-  a.spare = c->at<uint32_t>(c->L.spare);
-  a.assigned = c->rows_assigned ? 1u : 0u;
-  a.slot_score = nullptr;                              // no selection kernel follows
-  a.tab = c->table();
-  a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
-  a.key0 = static_cast<uint32_t>(c->cfg.seed);
-  a.key1 = static_cast<uint32_t>(c->cfg.seed >> 32);
-  a.t = static_cast<uint32_t>(c->t);
-  a.T_mut = c->T_mut; a.T_x = c->T_x;
-  a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
-  a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
-  a.rescore = 0;
-  a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.coin_stride = 0; a.term_lds = 0;
-  a.fault = c->at<uint32_t>(c->L.fsync) + 2;
-  a.bk = BucketArgs{};
-  const int next = c->cur ^ 1;
-  fa.parent_rows = c->at<uint32_t>(c->L.parent_row[next]);
+  FusedArgs fa{};
+  fa.ev = whole_call_args(c);
+  fa.parent_rows = c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]);
   fa.sel = c->at<int32_t>(c->L.sel);
   fused_exchange(c->at<uint64_t>(c->L.xkeys), c->P, fa);
   fa.changes_before = c->fused_changes;
@@ -771,27 +771,6 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   c->splitters_valid = false;       // the two-launch path ranks the pool in full before it uses buckets again
   c->profile_tick += 1;
   return ONES_OK;
-}
-
-// The problem as the kernels of a whole call see it.
-static EvolveArgs whole_call_args(const ones_ctx *c) {
-  EvolveArgs a{};
-  a.genes = c->at<uint32_t>(c->L.genes);
-  a.fit_row = c->at<double>(c->L.fit_row);
-  a.row_of = c->at<uint32_t>(c->L.row_of);
-  a.spare = c->at<uint32_t>(c->L.spare);
-  a.assigned = c->rows_assigned ? 1u : 0u;
-  a.tab = c->table();
-  a.G = c->G; a.P = c->P; a.K = c->K; a.Jp = c->Jp;
-  a.key0 = static_cast<uint32_t>(c->cfg.seed);
-  a.key1 = static_cast<uint32_t>(c->cfg.seed >> 32);
-  a.t = static_cast<uint32_t>(c->t);
-  a.T_mut = c->T_mut; a.T_x = c->T_x;
-  a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
-  a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
-  a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.fault = c->at<uint32_t>(c->L.fsync) + 2;
-  return a;
 }
 
 // The next n generations in one cooperative launch (pools beyond those of run_fused).  Under probability

@@ -117,33 +117,30 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kLanes - 1);
 }
 
-// What a xor butterfly 32, 16, .., 1 over the lanes leaves in every lane (for sums: each step adds the
+// The sum that a xor butterfly 32, 16, .., 1 over the lanes leaves in every lane (each step adds the
 // partner's value, so the order of the additions is that of the butterfly), without LDS: gfx950 swaps
 // halves and rows of 16 lanes between two registers; below that, what a lane holds only depends
 // on its place among the last 2^k lanes, so a rotation of the row stands for the xor.
-// op(x of this lane, x of its partner)
-template <typename Op>
-__device__ __forceinline__ double butterfly(double v, Op op) {
-  auto halves = [&](double x, auto swap) {            // x of this lane's half (row) of a pair, x of the other's
+__device__ __forceinline__ double butterfly_sum(double v) {
+  auto halves = [](double x, auto swap) {             // x of this lane's half (row) of a pair, x of the other's
     const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(x));
     const auto lo = swap(static_cast<uint32_t>(bits)), hi = swap(static_cast<uint32_t>(bits >> 32));
-    return op(__hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0])),
-              __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1])));
+    return __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0])) +
+           __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
   };
   v = halves(v, [](uint32_t w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
   v = halves(v, [](uint32_t w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
-  auto from = [&](double x, auto ctrl) {
+  auto add_from = [](double x, auto ctrl) {
     constexpr int kCtrl = decltype(ctrl)::value;
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, 0xF, 0xF, true);
-    return op(x, __hiloint2double(hi, lo));
+    return x + __hiloint2double(hi, lo);
   };
-  v = from(v, std::integral_constant<int, 0x128>{});    // row_ror:8
-  v = from(v, std::integral_constant<int, 0x124>{});    // row_ror:4
-  v = from(v, std::integral_constant<int, 0x4E>{});     // quad_perm 2,3,0,1
-  return from(v, std::integral_constant<int, 0xB1>{});  // quad_perm 1,0,3,2
+  v = add_from(v, std::integral_constant<int, 0x128>{});    // row_ror:8
+  v = add_from(v, std::integral_constant<int, 0x124>{});    // row_ror:4
+  v = add_from(v, std::integral_constant<int, 0x4E>{});     // quad_perm 2,3,0,1
+  return add_from(v, std::integral_constant<int, 0xB1>{});  // quad_perm 1,0,3,2
 }
-__device__ __forceinline__ double butterfly_sum(double v) { return butterfly(v, [](double x, double y) { return x + y; }); }
 
 // ------------------------------------------------------------- four genes at once --
 // All byte values below are under 128, so that sums and differences with the top bits set do not

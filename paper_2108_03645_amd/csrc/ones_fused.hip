@@ -54,6 +54,10 @@ constexpr uint32_t kCrowd = 32;
 constexpr int kGatherPer = (kFusedMaxPool + kFusedThreads - 1) / kFusedThreads;   // entries per thread when a workgroup collects P values
 static_assert(kFusedMaxPool / 4 <= kFusedThreads, "a thread per survivor");
 
+// Tag of the n-th use (n = 0, 1, ..) of a pair of exchange buffers that start out zeroed: use n
+// goes to buffer n & 1 and flips the tag that buffer's entries carried before.
+__device__ __forceinline__ uint64_t use_tag(uint32_t n) { return static_cast<uint64_t>(((n >> 1) & 1u) ^ 1u) << 63; }
+constexpr uint64_t kTagBit = 1ull << 63;
 // The draws of the remaining work are published two generations ahead, so they rotate through
 // four buffers instead of two.
 constexpr uint32_t kDrawBuffers = 4;
@@ -157,16 +161,45 @@ __device__ __forceinline__ void list_free_rows(const Ranks &rk, const uint16_t *
   __syncthreads();
 }
 
-// Collects n published entries, see gather_per.
+// Collects n published 64-bit entries: thread t takes entries t, t + threads, ..., polls until every one
+// is ready and hands it to take.  at(e): the address of entry e.  False when the polls ran out.  No
+// branch around a load: a thread reads its entries again until the wave has all of its own.
+template <int kPer, typename At, typename Ready, typename Take>
+__device__ __forceinline__ bool gather_per(uint32_t n, uint32_t spin_limit, At at, Ready ready, Take take) {
+  uint32_t pending = 0;
+  const uint64_t *src[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const uint32_t e = threadIdx.x + k * kFusedThreads;
+    if (e < n) pending |= 1u << k;
+    src[k] = at(min(e, n - 1));
+  }
+  if (__ballot(pending != 0) == 0) return true;
+  for (uint32_t spins = 0; spins < spin_limit; ++spins) {
+    uint64_t v[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) v[k] = shared_load(src[k]);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const uint32_t e = threadIdx.x + k * kFusedThreads;
+      if (((pending >> k) & 1u) && ready(e, v[k])) {
+        take(e, v[k]);
+        pending &= ~(1u << k);
+      }
+    }
+    if (__ballot(pending != 0) == 0) return true;
+  }
+  return false;
+}
+
 template <typename At, typename Ready, typename Take>
 __device__ __forceinline__ bool gather(uint32_t n, uint32_t spin_limit, At at, Ready ready, Take take) {
   static_assert(kGatherPer <= 4, "entries per thread");
-  auto taken = [&](uint32_t e, uint64_t v, bool now) { if (now) take(e, v); };
   switch ((n + kFusedThreads - 1) / kFusedThreads) {
-    case 1: return gather_per<1, kFusedThreads>(n, spin_limit, at, ready, taken);
-    case 2: return gather_per<2, kFusedThreads>(n, spin_limit, at, ready, taken);
-    case 3: return gather_per<3, kFusedThreads>(n, spin_limit, at, ready, taken);
-    default: return gather_per<4, kFusedThreads>(n, spin_limit, at, ready, taken);
+    case 1: return gather_per<1>(n, spin_limit, at, ready, take);
+    case 2: return gather_per<2>(n, spin_limit, at, ready, take);
+    case 3: return gather_per<3>(n, spin_limit, at, ready, take);
+    default: return gather_per<4>(n, spin_limit, at, ready, take);
   }
 }
 
