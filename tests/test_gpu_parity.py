@@ -631,6 +631,38 @@ def test_single_launch_of_older_searches(ones, ref, n_slots, n_gpus, pop, seed, 
         ref.set_threads(1)
 
 
+def test_a_range_of_the_whole_pool_that_is_ranked_in_portions(ones, ref):
+    """A single launch that ranks a whole pool divides what can survive into ranges, between the points of a sample (every
+    64th slot here), and counts up to 768 candidates of a range against each other at once.  A range of a pool of 16384 holds
+    64 on average, and more than 768 about once in 2500 rankings: in the first generation of this search one holds 781."""
+    n_slots, pop, seed = 20, 16384, 3494
+    cl, jobs = cluster(30, n_slots, pop, seed=seed), random_jobs(np.random.default_rng(seed), n_slots)
+    say(f"[range in portions] slots={n_slots} P={pop} seed={seed}")
+    ref.set_threads(8)
+    try:
+        gpu, again, cpu = (make(cl, jobs) for make in (ones.Search, ones.Search, ref.RefSearch))
+        for s in (gpu, again, cpu):
+            s.set_progress(*W.progress(n_slots, seed=seed))
+        gpu.generation(4)
+        cpu.generation(1)
+        fit = cpu.export(genes=False)[1]
+        rank = np.empty(pop, np.int64)
+        rank[np.lexsort((np.arange(pop), fit))] = np.arange(pop)
+        points = rank[::pop // 256]
+        bound = np.sort(points[::2])[128 // 4 + 24]                     # every second point, and the one that bounds what can survive
+        edges = np.concatenate([[0], np.sort(points[points < bound]), [pop]])
+        assert max(np.diff(edges)[edges[:-1] < pop // 4]) > 768
+        cpu.generation(3)
+        assert_same_state(gpu, cpu, "after a call of four")
+        for s in (gpu, cpu):
+            s.generation(9)
+        assert_same_state(gpu, cpu, "nine more")
+    finally:
+        ref.set_threads(1)
+    gpu.close(); cpu.close()
+    assert ends_in_single_launch(ones, again, 4)
+
+
 @pytest.mark.parametrize("sampled", [False, True])
 def test_searches_at_the_same_time(ones, ref, sampled):
     """Three threads, each with a search and a stream of its own: calls in one launch of pools of three sizes wait for
