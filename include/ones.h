@@ -171,7 +171,9 @@ int ones_generation(ones_ctx *ctx, int32_t n_generations);
  * the caller's workspace.  The population, scores and survivor list stay in the workspace as
  * always, and the results are those of ones_generation bit for bit; the two calls may be mixed
  * freely on one context.  Calls no hipMalloc, hipFree, hipHostMalloc, event or other allocating
- * routine and takes no HIP events (the measurement hook does not see these generations).
+ * routine and takes no HIP events (the measurement hook does not see these generations); a call that
+ * runs in a single launch (see ones_set_wait_limit) makes a cooperative one, whose private memory
+ * the runtime provides as for any kernel.
  * Every context on a GPU shares that GPU's array, which keeps the last call's contents: each call
  * sets up by itself what it reads (its first generation ranks the pool without relying on
  * anything left there), so calls may follow each other in any order, but two calls that overlap
@@ -183,14 +185,27 @@ int ones_generation(ones_ctx *ctx, int32_t n_generations);
  * count, another device current), ONES_E_HIP. */
 int ones_generation_static(ones_ctx *ctx, int32_t n_generations);
 
-/* Pools of at most 64 job slots and 2048 candidates run all generations of a ones_generation call of
- * three or more generations in ONE launch whose workgroups exchange results while it runs, and so do
- * pools of up to 1024 job slots and 16384 candidates (as far as they fit a compute unit's LDS; not
- * under graph capture) with calls of four or more, longer ones under probability sampling; a workgroup polls for the others' results at most
- * `polls` times (at first 2^22, a few seconds) and then gives up: the launch ends, the next call
- * that synchronises (ones_best, ones_export, ones_placement) returns ONES_E_HIP, and the context
- * only accepts ones_destroy from then on.  This never happens on a healthy device; polls = 0
- * makes every wait give up at once, which is how the error path is tested. */
+/* How a call runs.  Pools of at most 64 job slots and 2048 candidates run all generations of a ones_generation (or
+ * ones_generation_static) call of three or more generations in ONE launch whose workgroups exchange results while it
+ * runs.  Larger pools, of up to 1024 job slots and 16384 candidates as far as job table and ranking fit a compute unit's
+ * LDS, do so in the calls that are faster for it:
+ *   - of four or more generations; under an unchanged table, pools above 8192 on more than 256 slots: of eight or more;
+ *   - under probability sampling (32 generations to a launch) of four or more above 2048 candidates, of six or more from
+ *     1025 on, never of 257 to 1024 candidates on up to 256 slots, else of six to sixteen or more;
+ *   - without it, pools above 8192 only once the search has run eight generations per 64 slots, or in a call of which 24
+ *     generations come after those; on more than 256 slots a table in which a twelfth of the slots or more change hands
+ *     puts it off again, for as many generations at most.
+ * Everything else is two to five launches a generation; so are all calls of a context that the runtime has refused such
+ * a launch, and the larger pools' calls under graph capture or while the measurement hook is on.  The results are the
+ * same bits.
+ * A launch of the larger pools holds a workgroup with up to 160 KB of LDS on every compute unit until the call ends:
+ * work on other streams, and other contexts' launches of this kind, run before or after it, not beside it.
+ *
+ * A workgroup polls for the others' results at most `polls` times (at first 2^22, a few seconds) and then gives up: the
+ * launch ends, the next call that synchronises (ones_best, ones_export, ones_placement) returns ONES_E_HIP, and the
+ * context only accepts ones_destroy from then on.  On a healthy device this only happens if a kernel of another stream
+ * or process keeps a compute unit occupied for that long; polls = 0 makes every wait give up at once, which is how
+ * the error path is tested. */
 int ones_set_wait_limit(ones_ctx *ctx, uint32_t polls);
 
 /* The winner S* (Alg. 1: smallest score): global batch and GPU count per slot (HOST
@@ -222,10 +237,11 @@ int32_t ones_padded_jobs(int32_t n_slots);
 /* Measurement hook.  With every = n > 0 the evolve and the select kernels of every n-th
  * generation are bracketed by HIP events on the context's stream (n = 1: every generation;
  * an event costs a few microseconds of stream time); every <= 0 switches it off.
- * A small pool (at most 64 job slots and 2048 candidates, fixed remaining work) runs all
- * generations of a ones_generation call of three or more generations in one launch: that
- * launch counts as one evolve launch (every n-th call is bracketed) and there is no select
- * launch.  While the hook is on, larger pools take two launches per generation.
+ * A small pool (at most 64 job slots and 2048 candidates) runs all generations of a
+ * ones_generation call of three or more generations in one launch: that launch counts as one
+ * evolve launch (every n-th call is bracketed) and there is no select launch.  Larger pools are
+ * launched by generation while the hook is on, also in calls that take a single launch
+ * otherwise: what a program's calls take is timed with the hook off.
  * ones_profile_read synchronises and returns the accumulated kernel time in milliseconds
  * and the number of bracketed launches since the last ones_profile_enable call (any output
  * may be NULL). */

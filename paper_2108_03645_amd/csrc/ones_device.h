@@ -117,7 +117,8 @@ struct Progress {
 };
 // The draws depend on nothing but (seed, slot, generation), so they are made ahead, those of many
 // generations in one launch: generation g's remaining work and term table sit at place g mod n of a ring of
-// n (Y, terms) pairs, n = kDrawRing, or kDrawAhead for a context whose generations are all launched one by one.
+// n (Y, terms) pairs, n = kDrawRing for pools of resident_kernel, else kDrawAhead (the kernels of one generation; the
+// whole calls of fused_kernel draw for themselves).
 constexpr int kDrawRing = 32;
 constexpr int kDrawAhead = 8;       // generations drawn at a time for the kernels of one generation
 
