@@ -135,13 +135,15 @@ int64_t resident_from(uint32_t P, uint32_t Jp) { return P > 8192u ? 8 * (Jp / kL
 // Of a call that begins earlier, so many generations have to come after that one: a launch behind queued ones waits for
 // them, and 4 to 16 do not make up for it (a call of 20 that ends with four: 0.88 on 100 slots, with eight 0.94 on 200).
 constexpr int32_t kResidentRest = 24;
-// The same after a table in which `changed` of the n slots changed hands: the generations that its pool stays mixed.  From a
-// twelfth of the slots on, beyond four rows of them (16384 candidates on 512 slots, calls of 20 behind a table that changes
-// three in ten of them: 531 and 430 us by generation, 676 and 508 in one launch each).  On up to four rows one launch is
-// the faster way all the same (12000 on 200, three in ten: 428 and 570 us against 384 and 392).
+// The same after a table in which `changed` of the n slots changed hands: the generations that its pool stays mixed.  Beyond
+// four rows of slots, and from a sixth of them on (16384 candidates on 512 slots, two calls of 20 behind a table with new
+// jobs on a sixth of them: 525 and 500 us by generation, 645 and 515 in one launch each; on a quarter 543 and 506, 713 and
+// 545; on a half 707 and 525, 769 and 646; on all 899 and 547, 787 and 695).  An eighth gains as well (520 and 606 the first call),
+// but a table whose jobs the pool has met before leaves it as settled as it was, and then one launch takes 323 of 431.
+// On up to four rows one launch is the faster way all the same (12000 on 200, three in ten: 428 and 570 us against 384 and 392).
 int64_t mixed_by(uint32_t P, uint32_t Jp, uint32_t changed, uint32_t n) {
-  if (Jp <= 4u * kLanes || 12 * changed < n) return 0;
-  return resident_from(P, Jp) * std::min(n, 4 * changed) / n;
+  if (Jp <= 4u * kLanes || 6 * changed < n) return 0;
+  return resident_from(P, Jp) * std::min(n, 2 * changed) / n;
 }
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {

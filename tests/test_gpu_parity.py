@@ -818,11 +818,12 @@ def test_young_searches_of_large_pools_are_launched_by_generation(ones, ref, n_s
 
 
 @pytest.mark.parametrize("n_slots,n_gpus,pop,changed,n,single", [
-    (512, 1024, 16384, 0.03, 20, True), (512, 1024, 16384, 0.3, 20, False), (512, 1024, 16384, 1.0, 50, False), (512, 1024, 16384, 0.15, 63, True),
+    (512, 1024, 16384, 0.03, 20, True), (512, 1024, 16384, 0.16, 20, True), (512, 1024, 16384, 0.17, 20, False), (512, 1024, 16384, 0.17, 45, True),
+    (512, 1024, 16384, 0.3, 61, False), (512, 1024, 16384, 1.0, 50, False),
     (200, 300, 12000, 1.0, 20, True), (700, 900, 8192, 1.0, 20, True)])
 def test_a_table_that_changes_much_makes_a_large_pool_young_again(ones, ref, n_slots, n_gpus, pop, changed, n, single):
-    """A table in which a twelfth of more than 256 slots or more change hands puts the single launch of a pool above 8192 off,
-    for as many generations as at the start of a search (a quarter of the slots or more changed) or a part of that."""
+    """A table in which a sixth of more than 256 slots or more change hands puts the single launch of a pool above 8192 off,
+    for as many generations as at the start of a search (half of the slots or more changed) or a part of that."""
     rng = np.random.default_rng(62)
     cl, jobs = cluster(n_gpus, n_slots, pop, seed=62), random_jobs(rng, n_slots)
     new = random_jobs(rng, n_slots)
