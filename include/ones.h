@@ -193,12 +193,12 @@ int ones_generation_static(ones_ctx *ctx, int32_t n_generations);
  *   - under probability sampling (32 generations to a launch) of four or more above 2048 candidates, of six or more from
  *     1025 on, never of 257 to 1024 candidates on up to 256 slots, else of six to sixteen or more;
  *   - without it, pools above 8192 only once the search has run eight generations per 64 slots, or in a call of which 24
- *     generations come after those; on more than 256 slots a table in which a twelfth of the slots or more change hands
+ *     generations come after those; on more than 256 slots a table in which a sixth of the slots or more change hands
  *     puts it off again, for as many generations at most.
  * Everything else is two to five launches a generation; so are all calls of a context that the runtime has refused such
  * a launch, and the larger pools' calls under graph capture or while the measurement hook is on.  The results are the
  * same bits.
- * A launch of the larger pools holds a workgroup with up to 160 KB of LDS on every compute unit until the call ends:
+ * A launch of the larger pools holds up to all compute units, each with up to 160 KB of LDS, until the call ends:
  * work on other streams, and other contexts' launches of this kind, run before or after it, not beside it.
  *
  * A workgroup polls for the others' results at most `polls` times (at first 2^22, a few seconds) and then gives up: the
