@@ -348,7 +348,7 @@ def main() -> int:
         "best_fitness": best_fit,
         "kernels": {"evolve_ms": evolve_ms, "select_ms": select_ms,
                     "launches_per_generation": "one launch for all timed generations" if single_launch else "evolve + select",
-                    "measured_in": "a run of their own, by generation" if hook_apart else "the timed runs"},
+                    "measured_in": None if args.no_events else "a run of their own, by generation" if hook_apart else "the timed runs"},
         # the rate is set against HBM's; what the kernel runs into first is limited_by
         "roofline": {"bound": "hbm", "kernel": "fused_kernel" if single_launch else "evolve_kernel",
                      "limited_by": "exchange between workgroups" if single_launch else "vector instruction issue",
