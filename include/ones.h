@@ -192,9 +192,9 @@ int ones_generation_static(ones_ctx *ctx, int32_t n_generations);
  *   - of four or more generations; under an unchanged table, pools above 8192 on more than 256 slots: of eight or more;
  *   - under probability sampling (32 generations to a launch) of four or more above 2048 candidates, of six or more from
  *     1025 on, never of 257 to 1024 candidates on up to 256 slots, else of six to sixteen or more;
- *   - without it, pools above 8192 only once the search has run eight generations per 64 slots, or in a call of which 24
- *     generations come after those; on more than 256 slots a table in which a sixth of the slots or more change hands
- *     puts it off again, for as many generations at most.
+ *   - without it, pools above 8192 only once the search has run up to eight generations per 64 slots (in proportion to
+ *     the candidates above 8192), or in a call of which 24 generations come after those; on more than 256 slots a table
+ *     in which a sixth to a half of the slots change hands puts it off again, for as many generations at most.
  * Everything else is two to five launches a generation; so are all calls of a context that the runtime has refused such
  * a launch, and the larger pools' calls under graph capture or while the measurement hook is on.  The results are the
  * same bits.

@@ -126,24 +126,30 @@ int32_t resident_min_generations(uint32_t P, uint32_t Jp, bool sampled, bool tab
   return many_rows ? 6 : 8;
 }
 // A search starts from random genomes, and while its pool is as mixed as that, many children beat the K-th survivor.
-// Pools above 8192 are faster by generation then (16384 candidates on 512 slots, the first 50 generations: 1280 us, 1370 with
-// one launch for those after the 28th, although it lists all of the children from there on), until fewer than about an
-// eighth of the pool do: after 8 generations on 100 slots, 10 on 200, 30 to 60 on 512, so after so many that grow with the
-// rows of slots.  Smaller pools gain by one launch from the first generation on (8192: 1.1 for the first 20 on
-// 1000 slots, 1.2 on 100).
-int64_t resident_from(uint32_t P, uint32_t Jp) { return P > 8192u ? 8 * (Jp / kLanes) : 0; }
+// Pools above 8192 are faster by generation then, the larger and the more slots the longer (16384 candidates on 512 slots, the
+// first 50 generations: 1282 us, 1338 with one launch for those after the 28th, 1459 in one launch; two calls of 20 by
+// generation and in one launch: 625 and 546 against 767 and 596; 12000 on 600 642 and 554, 773 and 638; 12000 on 200 488 and 437,
+// 519 and 383; 9000 on 420 541 and 485, 531 and 403).  Smaller pools gain by one launch from the first generation on (8192:
+// 1.1 for the first 20 on 1000 slots, 1.2 on 100), and those that would be launched for a few generations only as well.
+int64_t resident_from(uint32_t P, uint32_t Jp) {
+  const uint32_t n = P > 8192u ? 8 * (Jp / kLanes) * (P - 8192u) / 8192u : 0u;
+  return n < 7 ? 0 : n;
+}
 // Of a call that begins earlier, so many generations have to come after that one: a launch behind queued ones waits for
 // them, and 4 to 16 do not make up for it (a call of 20 that ends with four: 0.88 on 100 slots, with eight 0.94 on 200).
 constexpr int32_t kResidentRest = 24;
 // The same after a table in which `changed` of the n slots changed hands: the generations that its pool stays mixed.  Beyond
 // four rows of slots, and from a sixth of them on (16384 candidates on 512 slots, two calls of 20 behind a table with new
 // jobs on a sixth of them: 525 and 500 us by generation, 645 and 515 in one launch each; on a quarter 543 and 506, 713 and
-// 545; on a half 707 and 525, 769 and 646; on all 899 and 547, 787 and 695).  An eighth gains as well (520 and 606 the first call),
-// but a table whose jobs the pool has met before leaves it as settled as it was, and then one launch takes 323 of 431.
-// On up to four rows one launch is the faster way all the same (12000 on 200, three in ten: 428 and 570 us against 384 and 392).
+// 545; on a half 707 and 525, 769 and 646).  An eighth gains as well (520 and 606 the first call), but a table whose jobs the
+// pool has met before leaves it as settled as it was, and then one launch takes 323 of 431.  Behind one that changes more than
+// a half, launched generations are crowded themselves (all 899 and 547, 787 and 695; 14000 on 700, three quarters, 50
+// generations: 1661 and 1594), and one launch is the faster way for smaller pools, whose children the list holds (9000 on 420,
+// a quarter: 481 and 442, 453 and 370), and on up to four rows (12000 on 200, three in ten: 428 and 570 against 384 and 392).
 int64_t mixed_by(uint32_t P, uint32_t Jp, uint32_t changed, uint32_t n) {
-  if (Jp <= 4u * kLanes || 6 * changed < n) return 0;
-  return resident_from(P, Jp) * std::min(n, 2 * changed) / n;
+  if (Jp <= 4u * kLanes || 6 * changed < n || 2 * changed > n) return 0;
+  const int64_t mixed = resident_from(P, Jp) * 2 * changed / n;
+  return mixed < 12 ? 0 : mixed;
 }
 bool fused_pool(uint32_t P, uint32_t Jp) { return Jp == static_cast<uint32_t>(kLanes) && P <= kFusedMaxPool; }
 bool resident_pool(uint32_t P, uint32_t Jp) {

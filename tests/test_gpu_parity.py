@@ -796,11 +796,13 @@ def test_a_single_launch_leaves_the_buckets_of_the_next_generation(ones, ref, n_
 
 @pytest.mark.parametrize("n_slots,n_gpus,pop,age,n,single", [
     (512, 1024, 16384, 0, 50, False), (512, 1024, 16384, 50, 20, False), (512, 1024, 16384, 50, 38, True), (512, 1024, 16384, 64, 9, True),
-    (400, 900, 15000, 30, 40, False), (400, 900, 15000, 56, 11, True), (100, 200, 12000, 0, 39, False), (100, 200, 12000, 0, 40, True),
-    (100, 200, 12000, 16, 8, True), (20, 12, 16380, 8, 8, True), (1000, 1500, 8192, 0, 4, True)])
+    (400, 900, 15000, 30, 39, False), (400, 900, 15000, 46, 11, True), (100, 200, 16384, 0, 39, False), (100, 200, 16384, 0, 40, True),
+    (100, 200, 12000, 0, 30, False), (100, 200, 12000, 0, 31, True), (200, 400, 12000, 0, 37, False), (200, 400, 12000, 14, 4, True),
+    (420, 900, 9000, 0, 20, True), (20, 12, 16380, 8, 8, True), (1000, 1500, 8192, 0, 4, True)])
 def test_young_searches_of_large_pools_are_launched_by_generation(ones, ref, n_slots, n_gpus, pop, age, n, single):
-    """Pools above 8192 take the single launch once their genomes are no longer random, after eight generations per row of
-    job slots, and in a call that begins earlier only if 24 of its generations come after those.  Both ways are compared
+    """Pools above 8192 take the single launch once their genomes are no longer random, after up to eight generations per row of
+    job slots, in proportion to what of 8192 they have above that (none if those would be fewer than seven), and in a call that
+    begins earlier only if 24 of its generations come after those.  Both ways are compared
     with the oracle, with a generation of the other kind and another call behind."""
     cl, jobs = cluster(n_gpus, n_slots, pop, seed=61), random_jobs(np.random.default_rng(61), n_slots)
     say(f"[young searches] slots={n_slots} P={pop}: {n} generations after {age}")
@@ -819,11 +821,11 @@ def test_young_searches_of_large_pools_are_launched_by_generation(ones, ref, n_s
 
 @pytest.mark.parametrize("n_slots,n_gpus,pop,changed,n,single", [
     (512, 1024, 16384, 0.03, 20, True), (512, 1024, 16384, 0.16, 20, True), (512, 1024, 16384, 0.17, 20, False), (512, 1024, 16384, 0.17, 45, True),
-    (512, 1024, 16384, 0.3, 61, False), (512, 1024, 16384, 1.0, 50, False),
+    (512, 1024, 16384, 0.3, 61, False), (512, 1024, 16384, 0.5, 50, False), (512, 1024, 16384, 0.52, 20, True), (420, 900, 9000, 0.3, 20, True),
     (200, 300, 12000, 1.0, 20, True), (700, 900, 8192, 1.0, 20, True)])
 def test_a_table_that_changes_much_makes_a_large_pool_young_again(ones, ref, n_slots, n_gpus, pop, changed, n, single):
-    """A table in which a sixth of more than 256 slots or more change hands puts the single launch of a pool above 8192 off,
-    for as many generations as at the start of a search (half of the slots or more changed) or a part of that."""
+    """A table in which a sixth to a half of more than 256 slots change hands puts the single launch of a pool above 8192 off,
+    for as many generations as at the start of a search (half of the slots changed) or a part of that, if those are twelve."""
     rng = np.random.default_rng(62)
     cl, jobs = cluster(n_gpus, n_slots, pop, seed=62), random_jobs(rng, n_slots)
     new = random_jobs(rng, n_slots)
