@@ -897,12 +897,16 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
       each_own_row([&](uint32_t slot, uint16_t row) { a.row_of[slot] = row; });
       // and, if that is one of the launched kernels, the splitters of its buckets, as a selection of theirs would have left them
       // (without them its first one ranks the pool in full: a selection of 24 us in place of 6.4, 16384 candidates)
-      if (!kSampled && ra.n_buckets != 0 && deal.me + 1 == deal.groups)
+      // (their addresses are read from the argument block here, see kernel_args, not carried through the generations)
+      const auto *late = (const __attribute__((address_space(4))) ResidentArgs *)kernel_args();
+      if (!kSampled && deal.me + 1 == deal.groups && late->n_buckets != 0) {
+        const uint32_t nb = late->n_buckets;
         for (uint32_t c = tid; c < static_cast<uint32_t>(kBucketCounters); c += kResThreads) {
-          ra.count[0][c] = ra.count[1][c] = 0;
-          if (c < static_cast<uint32_t>(kMaxBuckets)) ra.split[c] = c + 1 < ra.n_buckets ? rk.ckey[bucket_bound(c + 1, K, ra.n_buckets)] : kNoSplitter;
-          if (c == 0) *ra.thresh = rk.ckey[K - 1];
+          late->count[0][c] = late->count[1][c] = 0;
+          if (c < static_cast<uint32_t>(kMaxBuckets)) late->split[c] = c + 1 < nb ? rk.ckey[bucket_bound(c + 1, K, nb)] : kNoSplitter;
+          if (c == 0) *late->thresh = rk.ckey[K - 1];
         }
+      }
       return;
     }
   }
