@@ -435,7 +435,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.rescore = same_table && sampled ? 1u : 0u;
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;   // the table's "arrived" marks are fresh
   a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.coin_stride = 0;                                             // the launcher sets it
+  a.coin_stride = a.walk = 0;                                    // the launcher sets them
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   a.slot_score = c->at<double>(c->L.slot_score);
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
@@ -794,6 +794,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.thresh = reinterpret_cast<uint64_t *>(scratch + S.thresh);
   for (int set = 0; set < 2; ++set) ra.count[set] = reinterpret_cast<uint32_t *>(scratch + S.bcount[set]);
   ra.ev.coin_stride = plan.coin_stride;
+  ra.ev.walk = plan.walk;
   ra.ev.term_lds = c->term_E;
   if (c->sampling) ra.ev.tab = c->table(static_cast<int>((c->t + 1) % kDrawRing));
   resident_exchange(c->at<uint64_t>(c->L.xkeys), c->P, ra);

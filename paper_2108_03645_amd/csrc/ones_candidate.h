@@ -200,7 +200,10 @@ struct Smem {
   uint64_t *split;   // [kMaxBuckets] bucket splitters, then [1] the K-th survivor's score bits
   uint2    *rank;    // [Q][64] in the same place, when a new table is served by executed time (no buckets then):
                      // ranks of the four rows, 16 bits each, the top one set
-  uint8_t  *coins;   // [waves][coin_stride] the coins of a crossover over the GPUs
+  // start and most again, a byte per slot in the order the repair visits them from lane 0, row 0 on, the first
+  // kWindowAhead once more behind the last (only where the repair walks, see Window)
+  uint8_t  *start_at, *most_at;
+  uint8_t  *coins;   // [waves][coin_stride] the coins of a crossover over the GPUs, then the genes near the start of a repair
   uint32_t *free_in_group; // [groups] free rows in each group of kRowGroupWords bitmap words
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
   uint64_t *drawn;         // [4 * kRound] the draws of those slots (PackedDraw)
@@ -221,15 +224,32 @@ inline uint32_t coin_stride(const EvolveArgs &a) {
   return a.per_gpu ? std::min<uint32_t>((a.G / 32 + 4) / 4 * 4, kMaxCoinGpus / 32) * 8 : 0u;
 }
 
+// The genes near the job a repair starts from, in visiting order: kSide lanes' columns before that job's lane and
+// kSide from it on, 4Q bytes each (see in_window).
+template <int Q>
+struct Window {
+  static constexpr int kSide = Q <= 2 ? 32 : Q <= 4 ? 16 : 8;
+  static constexpr int kPositions = kSide * 4 * Q;   // of either side
+  static constexpr int kBytes = 2 * kPositions;
+};
+constexpr uint32_t kWindowAhead = 256;               // largest kPositions
+constexpr uint32_t window_bytes(uint32_t Q) { return (Q <= 2 ? 64 : Q <= 4 ? 32 : 16) * 4 * Q; }
+static_assert(Window<1>::kBytes == window_bytes(1) && Window<2>::kBytes == window_bytes(2) && Window<3>::kBytes == window_bytes(3) &&
+              Window<4>::kBytes == window_bytes(4) && Window<5>::kBytes == window_bytes(5) && Window<8>::kBytes == window_bytes(8), "the same window");
+static_assert(Window<2>::kPositions <= kWindowAhead && Window<4>::kPositions <= kWindowAhead && Window<8>::kPositions <= kWindowAhead,
+              "start_at and most_at reach as far as the window");
+// Their LDS beside the wave's scratch.
+constexpr size_t walk_table_bytes(uint32_t Q) { return 2 * (static_cast<size_t>(Q) * 4 * kLanes + kWindowAhead); }
+
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
-inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride) {
+inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride, bool walk = false) {
   const size_t words = static_cast<size_t>(Q) * kLanes;
-  return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 +
+  return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 + (walk ? walk_table_bytes(Q) : 0) +
          static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16;
 }
 
 template <int Q>
-__device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t waves, uint32_t stride) {
+__device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t waves, uint32_t stride, bool walk = false) {
   constexpr uint32_t kWords = Q * kLanes;
   Smem s;
   s.abl = reinterpret_cast<double *>(at);
@@ -249,7 +269,9 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.shift = s.base + kWords;
   s.fresh = s.shift + kWords;
   s.bl = s.fresh + kWords;
-  s.coins = reinterpret_cast<uint8_t *>(s.bl + kWords);
+  s.start_at = reinterpret_cast<uint8_t *>(s.bl + kWords);
+  s.most_at = s.start_at + 4 * kWords + kWindowAhead;
+  s.coins = s.start_at + (walk ? walk_table_bytes(Q) : 0);
   s.rows = reinterpret_cast<uint32_t *>(s.coins + static_cast<size_t>(waves) * stride);
   s.next_item = s.rows + 4 * kRound;
   s.free_in_group = s.next_item + 4;
@@ -269,7 +291,7 @@ constexpr uint32_t kBias = 31;
 constexpr int kStageBatch = 4;
 template <int Q>
 __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, uint32_t E, bool changed, uint32_t tid,
-                                            uint32_t threads) {
+                                            uint32_t threads, bool walk = false) {
   const JobTable &tab = a.tab;
   const uint32_t R = a.Jp / kLanes;
   constexpr uint32_t kWords = Q * kLanes;
@@ -337,6 +359,16 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
     }
     s.start[w] = start;
     s.most[w] = most;
+    if (walk) {
+      const uint32_t at = w % kLanes * Q + w / kLanes;               // of the word in visiting order
+      uint32_t *start_at = reinterpret_cast<uint32_t *>(s.start_at), *most_at = reinterpret_cast<uint32_t *>(s.most_at);
+      start_at[at] = start;
+      most_at[at] = most;
+      if (at < kWindowAhead / 4) {
+        start_at[kWords + at] = start;
+        most_at[kWords + at] = most;
+      }
+    }
     s.draws[w] = draws;
     s.base[w] = base;
   }
@@ -608,16 +640,116 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
   return got;
 }
 
+// What the repair changes lies near the job it starts from.  A candidate beyond the capacity loses the jobs at the end of
+// the visiting order, just before that job, and the idle GPUs are used up by the first asks after it: on the stress
+// workload 46 asks are accepted of 1270, in a stretch of some 75 positions, on the large one 17 of 430.  So the genes on both sides
+// of it are laid out in LDS in visiting order, and the wave walks along them, a gene per lane, 64 positions a step of some 25
+// instructions; a cut and a fill round over whole genomes are 150 and 270 at eight words.
+// The kernels are bound by the issue of vector instructions: a generation of the stress workload issued 5.0e7 with whole genomes
+// and issues 3.8e7 now (86 -> 74 us in a search's first 300 generations); epochs: 200 slots, pool 8192 205 -> 192 us, 512 slots,
+// pool 16384 820 -> 779, stress 1771 -> 1679.  A window that the walk leaves (few asks, or many idle GPUs) costs it some 100
+// instructions; the round then goes on over whole genomes.  Where more than kPositions GPUs are idle it is not tried.
+template <int Q>
+__device__ __forceinline__ bool in_window(uint32_t lr, int lane, uint32_t &at) {
+  at = (static_cast<uint32_t>(lane) - lr + Window<Q>::kSide) % kLanes;
+  return 2 * Window<Q>::kSide >= kLanes || at < 2u * Window<Q>::kSide;
+}
+template <int Q>
+__device__ __forceinline__ void stage_window(const uint32_t (&c)[Q], uint8_t *window, uint32_t lr, int lane) {
+  uint32_t at;
+  if (in_window<Q>(lr, lane, at)) {
+    uint32_t *column = reinterpret_cast<uint32_t *>(window) + at * Q;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) column[q] = c[q];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");         // the lanes read each other's bytes: one wave, whose LDS operations complete in order
+}
+template <int Q>
+__device__ __forceinline__ void take_window(uint32_t (&c)[Q], const uint8_t *window, uint32_t lr, int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  uint32_t at;
+  if (in_window<Q>(lr, lane, at)) {
+    const uint32_t *column = reinterpret_cast<const uint32_t *>(window) + at * Q;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) c[q] = column[q];
+  }
+}
+
+// Jobs from the end of the visiting order wait until the candidate has shed `excess` GPUs: those that more than
+// the capacity are held up to, which is those with less than the excess after them.  Returns what they held, at least
+// `excess`; 0 if the window ends before that (the registers hold the genes as they were).
+template <int Q>
+__device__ __forceinline__ uint32_t shed_excess(uint8_t *window, uint32_t excess, uint32_t ir, int lane) {
+  const int32_t behind = Window<Q>::kPositions + static_cast<int32_t>(ir);       // positions of the window before the start
+  uint32_t before = 0;
+  for (int32_t at = behind - 1 - lane, steps = behind; steps > 0; at -= kLanes, steps -= kLanes) {
+    const uint32_t code = at >= 0 ? window[at] : 0u, gpus = (1u << code) >> 1;
+    const uint32_t incl = wave_inclusive_scan(gpus) + before;
+    const bool waits = incl - gpus < excess;
+    if (waits && at >= 0) window[at] = 0;
+    before = __builtin_amdgcn_readlane(incl, kLanes - 1);
+    if (before >= excess) return __builtin_amdgcn_readlane(incl, __popcll(__ballot(waits)) - 1);
+  }
+  return 0;
+}
+
+// Fill rounds as long as they end inside the window.  On return idle is what the last round that began found idle, and left what
+// it has not handed out: 0, or that round has gone past the window and goes on behind it.
+template <int Q>
+__device__ __forceinline__ void fill_window(const Smem &s, uint8_t *window, uint32_t lr, uint32_t ir, int lane, uint32_t &idle, uint32_t &left) {
+  const uint32_t ahead = Window<Q>::kPositions - ir;             // positions of the window from the start on
+  static_assert(Window<Q>::kPositions - 4 * Q >= kLanes, "the first step lies inside the window");
+  const uint32_t base = lr * (4 * Q) + ir + lane;
+  uint8_t *genes = window + Window<Q>::kPositions + ir + lane;
+  const uint8_t *starts = s.start_at + base, *mosts = s.most_at + base;
+  uint32_t code = genes[0];                                      // the first step's stay in registers
+  const uint32_t start = starts[0], most = mosts[0];
+  for (;;) {
+    left = idle;
+    const uint32_t fit = 32 - __clz(static_cast<int>(idle));     // a power of two fits when its code is not above that of the idle GPUs
+    // one step; true: the round ends in it
+    auto step = [&](uint32_t &gene, uint32_t its_start, uint32_t its_most, bool inside, uint32_t from) {
+      const bool waits = gene == 0;
+      const uint32_t cost = waits ? its_start : gene;
+      const bool asks = gene != its_most && cost <= fit && inside;
+      if (__ballot(asks) == 0) return false;
+      const uint32_t gpus = asks ? (1u << cost) >> 1 : 0u, incl = wave_inclusive_scan(gpus);
+      const uint64_t beyond = __ballot(asks && incl > left);
+      if (asks && incl <= left) {
+        gene = waits ? its_start : gene + 1;
+        genes[from] = static_cast<uint8_t>(gene);
+      }
+      if (beyond == 0) {
+        left -= __builtin_amdgcn_readlane(incl, kLanes - 1);
+        return left == 0;
+      }
+      left -= __builtin_amdgcn_readlane(incl - gpus, __ffsll(static_cast<long long>(beyond)) - 1);
+      return true;
+    };
+    bool ends = step(code, start, most, true, 0);
+    for (uint32_t from = kLanes; !ends && from < ahead; from += kLanes) {
+      uint32_t gene = genes[from];
+      ends = step(gene, starts[from], mosts[from], from + lane < ahead, from);
+    }
+    if (!ends || left == 0) return;
+    idle = left;
+  }
+}
+
 // Refresh + fill (Section 3.2.2) on codes c[]; window and lift already applied.
 // kArrivals (only in the generation after a table change): the jobs that arrived with the table
 // are served first (refresh (3)): each starts on the GPUs a waiting job resumes with while the
 // capacity lasts, in visiting order, and the others are admitted to what is left: in visiting order
 // too, or, with by_time (s.rank: position of every job in ascending order of executed time), least executed
 // time first, so that the room is taken from the jobs with the largest T_processed.
+// window: this wave's LDS for the genes near the start of the repair, with walk.
 template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t G, uint32_t lr, uint32_t ir, int lane,
-                                       uint32_t Jp, bool by_time) {
-  uint32_t used;
+                                       uint32_t Jp, bool by_time, uint8_t *window, bool walk) {
+  constexpr bool kWalks = kGenes != kOneRow;         // there one gene per lane is the whole genome
+  lane = opaque(lane);                               // (nothing derived from it is kept from one candidate to the next)
+  uint32_t used = 0;
+  bool staged = false;
   if (kArrivals) {
     uint32_t v[Q], fresh[Q];
 #pragma unroll
@@ -662,20 +794,46 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
     for (int q = 0; q < Q; ++q) c[q] |= fresh[q];
   } else {
     // admit: jobs beyond the capacity in visiting order wait (Eq. 4)
-    uint32_t v[Q];
+    bool shed = false;
+    if (kWalks && walk) {
+      GpuSum<kGenes> held;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) v[q] = c[q];
-    used = accept_prefix<Q, kGenes>(v, c, G, lr, ir, lane);
+      for (int q = 0; q < Q; ++q) held.add(c[q]);
+      used = wave_sum(held.total());
+      shed = used <= G;
+      // (a window that is expected to hold twice the jobs that have to wait)
+      if (!shed && used - G <= used / (4 * kLanes / Window<Q>::kSide)) {
+        stage_window<Q>(c, window, lr, lane);
+        const uint32_t gone = shed_excess<Q>(window, used - G, ir, lane);
+        shed = staged = gone != 0;
+        used -= gone;
+      }
+    }
+    if (!shed) {
+      uint32_t v[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = c[q];
+      used = accept_prefix<Q, kGenes>(v, c, G, lr, ir, lane);
+    }
   }
   // fill: a waiting job asks for its starting GPUs, a running one below its limit asks to double,
   // both only if the GPUs are there (a power of two fits when its code is not above that of the idle
   // GPUs).  Every round that accepts anything uses up idle GPUs, and a round that accepts nothing ends it.
-  uint32_t idle = G - used;
-  if (idle == 0) return;
+  uint32_t idle = G - used, left = idle;
+  bool behind = false;                               // the round that goes on has gone past the window
+  if (kWalks && walk && idle != 0 && idle <= static_cast<uint32_t>(Window<Q>::kPositions)) {
+    if (!staged) stage_window<Q>(c, window, lr, lane);
+    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    staged = true;
+    fill_window<Q>(s, window, lr, ir, lane, idle, left);
+    behind = left != 0;
+  }
+  if (kWalks && staged) take_window<Q>(c, window, lr, lane);
+  if (left == 0) return;
   uint32_t waits[Q];                                 // 0x7F for the jobs that wait
 #pragma unroll
   for (int q = 0; q < Q; ++q) waits[q] = ~nonzero_bytes(c[q]) & kSevens;
-  while (idle > 0) {
+  for (;;) {
     const uint32_t fitting = kTops | (static_cast<uint32_t>(32 - __clz(static_cast<int>(idle))) * kOnes);
     uint32_t v[Q], m[Q];
 #pragma unroll
@@ -685,15 +843,26 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
       m[q] = spread_tops(((c[q] ^ s.most[w]) + kSevens) & (fitting - cost));   // below its limit, and the GPUs are there
       v[q] = cost & m[q];
     }
-    const uint32_t got = accept_prefix<Q, kGenes>(v, m, idle, lr, ir, lane);
-    if (got == 0 || got > idle) break;
+    if (kWalks && behind) {                          // what lies in the window has had its turn
+      const uint32_t at = (static_cast<uint32_t>(lane) - lr) % kLanes;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t later = at >= static_cast<uint32_t>(Window<Q>::kSide) ? 0xFFFFFFFFu : at != 0 || ir <= 4u * q ? 0u : rows_before(ir, q);
+        m[q] &= later;
+        v[q] &= later;
+      }
+    }
+    const uint32_t got = accept_prefix<Q, kGenes>(v, m, left, lr, ir, lane);
+    if ((got == 0 && left == idle) || got > left) break;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const int w = q * kLanes + lane;
       c[q] += pick(waits[q], s.start[w], kOnes) & m[q];          // a running job's code goes up by one
       waits[q] &= ~m[q];
     }
-    idle -= got;
+    idle = left -= got;
+    behind = false;
+    if (idle == 0) break;
   }
 }
 
@@ -703,6 +872,7 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
 template <int Q, int kRows = 4 * Q>
 __device__ __forceinline__ double score(const uint32_t (&c)[Q], const Smem &s, uint32_t E, int lane) {
   double acc = 0.0;
+  lane = opaque(lane);
   if (E != 0) {
     // the job's term only depends on the code of its GPU count, and the table holds exactly the
     // value the formula below produces

@@ -154,6 +154,7 @@ struct EvolveArgs {
   uint32_t       rescore;     // the survivors' scores are stale (remaining work redrawn): score them again
   uint32_t       per_gpu;     // the uniform crossover scans the GPUs (Eq. 1) instead of the jobs; needs G <= kMaxCoinGpus
   uint32_t       coin_stride; // set by the launcher: bytes of LDS scratch per wave
+  uint32_t       walk;        // set by the launcher: LDS holds what the repair needs to walk along the genes near its start
   uint32_t       term_lds;    // set by the launcher: entries per job of the term table in LDS, 0 = none
   uint32_t       *fault;      // [1] raised when a row index had to be pulled back into the genome array
   double         *slot_score; // [P] the score of every candidate this launch scores, by pool slot (written when
@@ -228,8 +229,8 @@ struct ResidentArgs {
 };
 // paired: a wave's item is a pair or a mutant, not a child.  unit_waves: waves of a workgroup that start with an item each;
 // child_items: items of a workgroup that are no survivors, segment: children they make, list: children that beat the K-th
-// survivor a workgroup can rank, all at most; table_lds: LDS bytes of the job table.
-struct ResidentPlan { uint32_t groups, paired, unit_waves, child_items, segment, list, coin_stride, table_lds; size_t lds; };
+// survivor a workgroup can rank, all at most; walk: see EvolveArgs; table_lds: LDS bytes of the job table.
+struct ResidentPlan { uint32_t groups, paired, unit_waves, child_items, segment, list, coin_stride, walk, table_lds; size_t lds; };
 size_t resident_exchange_bytes(uint32_t P);     // lists, xkeys, xrank, flags and xrow, consecutive
 void resident_exchange(uint64_t *base, uint32_t P, ResidentArgs &ra);      // their addresses
 // How a launch for ev's pool and job table would be shaped; false: it does not fit.

@@ -25,8 +25,8 @@ template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : 8; };
 
 template <int Q, Genes kGenes, bool kArrivals>
 __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t lr, uint32_t ir,
-                                         uint32_t (&c)[Q], int lane) {
-  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, kArrivals && a.time_rank != nullptr);
+                                         uint32_t (&c)[Q], int lane, uint8_t *window) {
+  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, kArrivals && a.time_rank != nullptr, window, a.walk != 0);
   phase_fence();
   const double f = score<Q>(c, s, a.term_lds, lane);
   phase_fence();
@@ -42,8 +42,9 @@ __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uin
 template <int Q, Genes kGenes>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride);
-  stage_table<Q>(a, s, a.term_lds, false, threadIdx.x, blockDim.x);
+  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, a.walk != 0);
+  stage_table<Q>(a, s, a.term_lds, false, threadIdx.x, blockDim.x, a.walk != 0);
+  uint8_t *window = s.coins + static_cast<size_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * a.coin_stride;
   if (threadIdx.x == 0) *s.next_item = 0;
   __syncthreads();
   const int lane0 = threadIdx.x & (kLanes - 1);
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
       c[q] = codes_of_draws(s, q * kLanes + lane, k);
     }
     phase_fence();
-    const double f = finish<Q, kGenes, false>(a, s, p, r / R, r % R, c, lane);   // slot p starts in row p
+    const double f = finish<Q, kGenes, false>(a, s, p, r / R, r % R, c, lane, window);   // slot p starts in row p
     note_slot_score(p, f, lane);
     if (lane == 0) a.row_of[p] = p;
   }
@@ -89,7 +90,7 @@ template <int Q, Table kTable, bool kOverGpus, Genes kGenes>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(EvolveArgs a) {
   constexpr bool kSameTable = kTable == kSame;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride);
+  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, a.walk != 0);
   const int lane0 = threadIdx.x & (kLanes - 1);
   const bool assigned = a.assigned != 0;
   if (!assigned) {
@@ -98,7 +99,8 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   }
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t K = a.K;
-  uint64_t *coins = reinterpret_cast<uint64_t *>(s.coins + static_cast<size_t>(wave_in_block) * a.coin_stride);
+  uint8_t *window = s.coins + static_cast<size_t>(wave_in_block) * a.coin_stride;     // this wave's scratch
+  uint64_t *coins = reinterpret_cast<uint64_t *>(window);
   // This workgroup's share of the ranks 0..K-1: for each rank a pair, a mutant and, after a
   // table change, a survivor, a round of kRound ranks at a time.  The rows the round fills are read
   // where the selection has assigned them; otherwise the slots K + 2 ra .., 3K + ra .. and the ranks
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     }
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
-  if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing);
+  if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing, a.walk != 0);
   if (a.occupied_other != nullptr)
     for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < (a.P + K + 31) / 32; w += gridDim.x * blockDim.x)
       a.occupied_other[w] = 0;
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     phase_fence();
     for (;;) {
       const uint32_t p = slot_at(ra, n, i);
-      const double f = finish<Q, kGenes, kTable == kArrivals>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane);
+      const double f = finish<Q, kGenes, kTable == kArrivals>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane, window);
       if (kSameTable && a.bk.nb != 0) drop_in_bucket(s, p, f, lane); else note_slot_score(p, f, lane);
       if (--children == 0) break;
       phase_fence();
@@ -250,7 +252,7 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   a.coin_stride = coin_stride(a);
   a.term_lds = (a.tab.term_E != 0 && smem_bytes(words, waves, a.tab.term_E, rows, a.coin_stride) <= kLdsBudget)
                    ? a.tab.term_E : 0u;
-  const size_t lds = smem_bytes(words, waves, a.term_lds, rows, a.coin_stride);
+  size_t lds = smem_bytes(words, waves, a.term_lds, rows, a.coin_stride);
   if (lds > kLdsBudget) return hipErrorInvalidValue;
   // as many workgroups as can be resident (LDS- and wave-limited), at most one wave per item.  Of eight waves
   // three, though a fourth has room: what it costs to stage its tables is more than its waves hide
@@ -258,6 +260,11 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   // two; pool 65536: 845, 799, 841; unsampled 512 slots, 16384: 19 us a generation's launch with four, 16.5 with three)
   const size_t resident = waves == 8 ? 3 : 32 / waves;
   const size_t per_cu = std::max<size_t>(1, std::min<size_t>(kLdsBudget / lds, resident));
+  // the repair walks where what that takes of LDS costs no workgroup its place on the compute unit
+  const uint32_t scratch = std::max<uint32_t>(a.coin_stride, window_bytes(words));
+  const size_t walking = smem_bytes(words, waves, a.term_lds, rows, scratch, true);
+  a.walk = walking * per_cu <= kLdsBudget ? 1u : 0u;
+  if (a.walk) { a.coin_stride = scratch; lds = walking; }
   const uint32_t blocks = std::max<uint32_t>(
       1u, std::min<uint32_t>({(items + waves - 1) / waves, static_cast<uint32_t>(n_cus * per_cu), max_blocks}));
   hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,

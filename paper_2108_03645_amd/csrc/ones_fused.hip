@@ -268,8 +268,8 @@ __device__ __forceinline__ double compose_unit(const EvolveArgs &a, uint32_t t, 
     c[0] = gene_of(srow[p]);
     to_new_table<1>(s, lane, c);
   }
-  if (!kSameTable && new_first) repair<1, kOneRow, true>(c, s, a.G, r, 0, lane, kLanes, a.time_rank != nullptr);
-  else repair<1, kOneRow, false>(c, s, a.G, r, 0, lane, kLanes, false);
+  if (!kSameTable && new_first) repair<1, kOneRow, true>(c, s, a.G, r, 0, lane, kLanes, a.time_rank != nullptr, nullptr, false);
+  else repair<1, kOneRow, false>(c, s, a.G, r, 0, lane, kLanes, false, nullptr, false);
   return score<1, 1>(c, s, a.term_lds, lane);
 }
 

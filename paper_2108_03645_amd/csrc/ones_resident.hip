@@ -114,12 +114,12 @@ __device__ __forceinline__ Ranking carve_ranking(unsigned char *base, uint32_t Q
 }
 
 // The job table in LDS without what only the kernels of one generation need.
-[[maybe_unused]] inline size_t table_bytes(uint32_t Q, uint32_t E, uint32_t stride) {
+[[maybe_unused]] inline size_t table_bytes(uint32_t Q, uint32_t E, uint32_t stride, bool walk) {
   const size_t words = static_cast<size_t>(Q) * kLanes;
-  return words * (4 * 8 * static_cast<size_t>(E) + 8 + 8 + 7 * 4) + static_cast<size_t>(kResWaves) * stride;
+  return words * (4 * 8 * static_cast<size_t>(E) + 8 + 8 + 7 * 4) + (walk ? walk_table_bytes(Q) : 0) + static_cast<size_t>(kResWaves) * stride;
 }
 template <int Q>
-__device__ __forceinline__ Smem carve_table(unsigned char *at, uint32_t E) {
+__device__ __forceinline__ Smem carve_table(unsigned char *at, uint32_t E, bool walk) {
   constexpr uint32_t kWords = Q * kLanes;
   Smem s{};
   s.terms = reinterpret_cast<double *>(at);
@@ -132,7 +132,9 @@ __device__ __forceinline__ Smem carve_table(unsigned char *at, uint32_t E) {
   s.shift = s.base + kWords;
   s.fresh = s.shift + kWords;
   s.bl = s.fresh + kWords;
-  s.coins = reinterpret_cast<uint8_t *>(s.bl + kWords);
+  s.start_at = reinterpret_cast<uint8_t *>(s.bl + kWords);
+  s.most_at = s.start_at + 4 * kWords + kWindowAhead;
+  s.coins = s.start_at + (walk ? walk_table_bytes(Q) : 0);
   return s;
 }
 
@@ -245,8 +247,9 @@ __device__ __forceinline__ void compose_item(const EvolveArgs &a, uint32_t t, co
   for (uint32_t which = 0;; ++which) {
     phase_fence();
     const uint32_t lr = start & 0xFFFFu, ir = start >> 16;
-    if (!kSameTable && new_first) repair<Q, kGenes, true>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank != nullptr);
-    else repair<Q, kGenes, false>(c, s, a.G, lr, ir, lane, a.Jp, false);
+    uint8_t *window = reinterpret_cast<uint8_t *>(coins);
+    if (!kSameTable && new_first) repair<Q, kGenes, true>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank != nullptr, window, a.walk != 0);
+    else repair<Q, kGenes, false>(c, s, a.G, lr, ir, lane, a.Jp, false, window, a.walk != 0);
     phase_fence();
     const double f = score<Q>(c, s, a.term_lds, lane);
     uint32_t *at = a.genes + static_cast<size_t>(row) * (Q * kLanes) + lane;
@@ -425,7 +428,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
   const EvolveArgs &a = ra.ev;
   const uint32_t P = a.P, K = a.K, tid = threadIdx.x, E = a.term_lds;
   const Deal deal{K, gridDim.x, blockIdx.x, ra.paired, (ra.paired ? 2u : 3u) * K};
-  const Smem s = carve_table<Q>(smem_raw, E);
+  const Smem s = carve_table<Q>(smem_raw, E, a.walk != 0);
   const Ranking rk = carve_ranking(smem_raw + ra.table_lds, Q, P, deal.groups, ra.list, ra.child_items);
   const int lane0 = tid & (kLanes - 1);
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -450,7 +453,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
     }
   };
 
-  stage_table<Q>(a, s, E, ra.first_changed != 0, tid, kResThreads);
+  stage_table<Q>(a, s, E, ra.first_changed != 0, tid, kResThreads, a.walk != 0);
   // the state the last selection left: the survivors' rows and scores, the rows of the units
   for (uint32_t e = tid; e < K; e += kResThreads) {
     const uint32_t row = checked_row(ra.parent_rows[e], P + K);
@@ -957,12 +960,16 @@ bool resident_plan(const EvolveArgs &ev, bool sampled, int n_cus, ResidentPlan &
   plan.groups = std::min<uint32_t>(plan.groups, (items + plan.unit_waves - 1) / plan.unit_waves);
   plan.child_items = (children + plan.groups - 1) / plan.groups;
   plan.segment = (plan.paired ? 2 : 1) * plan.child_items;
-  plan.coin_stride = coin_stride(ev);
-  plan.table_lds = static_cast<uint32_t>((table_bytes(Q, ev.tab.term_E, plan.coin_stride) + 15) & ~size_t(15));
-  // the list of the children takes what is left
   plan.list = kResLeastList;
-  const size_t least = plan.table_lds + ranking_bytes(Q, ev.P, plan);
-  if (least > kResLds) return false;
+  size_t least = 0;
+  for (plan.walk = 1;; plan.walk = 0) {              // the repair walks where there is room for it
+    plan.coin_stride = plan.walk ? std::max<uint32_t>(coin_stride(ev), window_bytes(Q)) : coin_stride(ev);
+    plan.table_lds = static_cast<uint32_t>((table_bytes(Q, ev.tab.term_E, plan.coin_stride, plan.walk != 0) + 15) & ~size_t(15));
+    least = plan.table_lds + ranking_bytes(Q, ev.P, plan);
+    if (least <= kResLds) break;
+    if (plan.walk == 0) return false;
+  }
+  // the list of the children takes what is left
   plan.list = std::min<uint32_t>({std::max(ev.P, kResLeastList), kResList, static_cast<uint32_t>(plan.list + (kResLds - least) / 12)});
   plan.lds = plan.table_lds + ranking_bytes(Q, ev.P, plan);
   return plan.lds <= kResLds;

@@ -1603,3 +1603,21 @@ def test_gpu_counts_at_the_edges_of_the_look_ups(ones, ref, n_slots, n_gpus, pop
         held = np.where(genes > 0, np.maximum(1, genes // mu), 0)
         assert (held.sum(axis=1) <= n_gpus).all() and held.max() == 1 << widest, tag
     gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots", [66, 256, 300, 512, 700, 1024, 1300, 1500, 1700, 2048])
+@pytest.mark.parametrize("share", [0.02, 0.5, 0.97, 1.0, 1.05])
+def test_repair_walks_near_its_start(ones, ref, n_slots, share):
+    """Every word count with whole and with ragged rows; clusters that hold a part of what the jobs could take: excess and idle
+    GPUs inside the window near the start of the repair, beyond it, and idle GPUs that few jobs or none ask for."""
+    rng = np.random.default_rng([n_slots, int(100 * share)])
+    jobs = wide_table(rng, n_slots, 3 if share < 1 else 6)
+    most = np.where(jobs.active != 0, np.maximum(jobs.bmax // jobs.gpu_max_batch, 1), 0).sum()
+    cl = cluster(max(1, int(share * most)), n_slots, 64, seed=n_slots)
+    say(f"[parity] repair near its start: slots={n_slots} G={cl.n_gpus} of {most}")
+    gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+    assert_same_state(gpu, cpu, "generation 0")
+    for n in (1, 1, 4):                                # launched by generation, then, up to 1024 slots, in one launch
+        gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, f"generation {gpu.export(genes=False)[3]}")
+    gpu.close(); cpu.close()
