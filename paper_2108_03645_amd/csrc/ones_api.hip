@@ -72,7 +72,7 @@ int static_scratch_of(int device, char **out) {
 // (ctx->splitters_valid).  Offsets from the block's base, which lies in the caller's workspace
 // or, for ones_generation_static, in the library's static array.
 struct ScratchLayout {
-  size_t split, split_slot, thresh, bcount[2], bkeys, bidx, skeys, sidx, sbucket, total;
+  size_t split, split_slot, thresh, bcount[2], ties[2], bkeys, bidx, skeys, sidx, sbucket, total;
 };
 
 struct Layout {
@@ -165,6 +165,8 @@ ScratchLayout make_scratch_layout(uint32_t P) {
   const BucketPlan bp = bucket_plan(P);
   S.split = take(kMaxBuckets * 8); S.split_slot = take(kMaxBuckets * 4); S.thresh = take(8);
   S.bcount[0] = take(kBucketCounters * 4); S.bcount[1] = take(kBucketCounters * 4);
+  const size_t ties = bp.nb ? (static_cast<size_t>(kTieClasses) * tie_words(P / 4) + kTieMask) * 4 : 0;
+  S.ties[0] = take(ties); S.ties[1] = take(ties);
   S.bkeys = take(static_cast<size_t>(bp.nb) * bp.seg * 8);
   S.bidx = take(static_cast<size_t>(bp.nb) * bp.seg * 4);
   S.skeys = take(static_cast<size_t>(bp.spill) * 8);
@@ -321,6 +323,7 @@ struct ones_ctx {
   bool has_times;             // executed times known (ones_set_processed_time): their ranks are on the device
   BucketPlan bp;              // nb == 0: pool small enough for the single-chunk sort
   int bucket_phase;           // which counter set the next bucketed generation fills
+  int cleared_phase;          // a phase whose counters and bitmaps are cleared in the workspace's scratch
   bool splitters_valid;       // the workspace's selection scratch holds the splitters of the current survivors
                               // and cleared counter sets: a bucketed generation may follow
   bool poisoned;              // a launch failed in the middle of a generation: the state is inconsistent
@@ -453,6 +456,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.bk.spill_idx = reinterpret_cast<uint32_t *>(sc(S.sidx));
   a.bk.spill_bucket = reinterpret_cast<uint32_t *>(sc(S.sbucket));
   a.bk.split_slot = reinterpret_cast<uint32_t *>(sc(S.split_slot));
+  a.bk.ties = reinterpret_cast<uint32_t *>(sc(S.ties[c->bucket_phase]));
   // the selection notes the rows the survivors keep, the next generation's parents
   RowPlan rp;
   rp.row_of = a.row_of;
@@ -468,8 +472,10 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   if (buckets) {
     HIP_TRY(launch_bucket_select(a.fit_row, a.bk, rp, c->K,
                                  reinterpret_cast<uint32_t *>(sc(S.bcount[c->bucket_phase ^ 1])),
+                                 reinterpret_cast<uint32_t *>(sc(S.ties[c->bucket_phase ^ 1])),
                                  c->at<int32_t>(c->L.sel), c->stream));
     c->bucket_phase ^= 1;
+    if (scratch == c->ws + c->L.scratch) c->cleared_phase = c->bucket_phase;
   } else {
     BucketArgs store = a.bk;                       // same storage; always the first counter set
     store.nb = c->bp.nb;
@@ -490,7 +496,8 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
       HIP_TRY(launch_splitters(a.fit_row, a.row_of, c->at<int32_t>(c->L.sel), c->K, c->bp.nb,
                                reinterpret_cast<uint64_t *>(sc(S.split)), reinterpret_cast<uint64_t *>(sc(S.thresh)),
                                reinterpret_cast<uint32_t *>(sc(S.bcount[0])),
-                               reinterpret_cast<uint32_t *>(sc(S.bcount[1])), c->stream));
+                               reinterpret_cast<uint32_t *>(sc(S.bcount[1])), reinterpret_cast<uint32_t *>(sc(S.ties[0])),
+                               static_cast<uint32_t>((S.bkeys - S.ties[0]) / 4), c->stream));
       splitters_valid = true;
     }
   }
@@ -569,7 +576,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   c->has_times = false;
   c->per_gpu = false;
   c->bp = bucket_plan(c->P);
-  c->bucket_phase = 0;
+  c->bucket_phase = c->cleared_phase = 0;
   c->splitters_valid = false;
   c->poisoned = false;
   c->fused = c->resident = false;
@@ -603,6 +610,8 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     const size_t exchange = exchange_bytes(c->P, c->Jp);
     if (e == hipSuccess && exchange != 0)   // the exchange buffers of the single-launch paths: every tag starts at 0
       e = launch_zero_words(c->at<uint32_t>(c->L.xkeys), static_cast<uint32_t>(exchange / 4), c->stream);
+    if (e == hipSuccess && c->resident && c->bp.nb != 0)   // bitmaps of the buckets that may follow a launch of theirs
+      e = launch_zero_words(c->at<uint32_t>(c->L.scratch + L.S.ties[0]), static_cast<uint32_t>((L.S.bkeys - L.S.ties[0]) / 4), c->stream);
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
   if ((rc = upload_table(c, h)) ||
@@ -825,6 +834,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   c->table_changed = false;
   c->no_schedule = false;
   c->splitters_valid = ra.n_buckets != 0;
+  c->bucket_phase = c->cleared_phase;       // (the launch clears both sets of counters, but no bitmaps)
   c->profile_tick += 1;
   return ONES_OK;
 }

@@ -208,6 +208,8 @@ struct Smem {
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
   uint64_t *drawn;         // [4 * kRound] the draws of those slots (PackedDraw)
   uint32_t *next_item;     // [1] the next work item of the round that no wave has taken yet
+  uint32_t *tie_count;     // [kTieClasses] children of this workgroup that are copies of a class of survivors (see kTieRun)
+  uint32_t *tie_bucket;    // [kTieClasses] ... and the bucket they belong to
 };
 
 constexpr uint32_t kRound = 128;                     // survivors' ranks a workgroup covers between two barriers
@@ -245,7 +247,7 @@ constexpr size_t walk_table_bytes(uint32_t Q) { return 2 * (static_cast<size_t>(
 inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride, bool walk = false) {
   const size_t words = static_cast<size_t>(Q) * kLanes;
   return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 + (walk ? walk_table_bytes(Q) : 0) +
-         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16;
+         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16 + 2 * kTieClasses * 4;
 }
 
 template <int Q>
@@ -274,7 +276,9 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.coins = s.start_at + (walk ? walk_table_bytes(Q) : 0);
   s.rows = reinterpret_cast<uint32_t *>(s.coins + static_cast<size_t>(waves) * stride);
   s.next_item = s.rows + 4 * kRound;
-  s.free_in_group = s.next_item + 4;
+  s.tie_count = s.next_item + 4;
+  s.tie_bucket = s.tie_count + kTieClasses;
+  s.free_in_group = s.tie_bucket + kTieClasses;
   return s;
 }
 
@@ -923,6 +927,17 @@ __device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double
   const uint32_t block = kStep * static_cast<uint32_t>(__popcll(__ballot(s.split[lane * kStep + kStep - 1] <= bits)));
   const uint32_t b = block + static_cast<uint32_t>(__popcll(
                                  __ballot(lane < kStep && s.split[min(block + lane, kMaxBuckets - 1u)] <= bits)));
+  // (split[b - 1] is the largest splitter that is not above the score)
+  if (b >= static_cast<uint32_t>(kTieRun) && s.split[b - kTieRun] == bits && s.split[b - 1] == bits) {
+    if (lane == 0) {
+      KernelArgs *ka = kernel_args();
+      const uint32_t c = (b - 1) / kTieRun, q = p - ka->K;
+      atomicAdd(&s.tie_count[c], 1u);
+      s.tie_bucket[c] = b;
+      atomicOr(&ka->bk.ties[static_cast<size_t>(c) * tie_words(ka->K) + q / 32], 1u << (q % 32));
+    }
+    return;
+  }
   if (lane == 0) {
     // The pointers of the bucket storage are read from the kernel's argument block here, where
     // the few candidates that get this far need them, instead of being carried (and spilled)

@@ -84,7 +84,23 @@ constexpr uint32_t kInfoReset = 1u << 23;
 constexpr int kMaxBuckets = 1024;
 constexpr int kSpillCounter = kMaxBuckets;       // count[kSpillCounter]: records in the spill list
 constexpr int kManyFlag = kMaxBuckets + 1;       // count[kManyFlag]: a bucket was given more than kManyInBucket records
-constexpr int kBucketCounters = kMaxBuckets + 2;
+// Copies.  A pool that has been searched for a while fills with copies of one genome, or of a few, and then most children that
+// beat the K-th survivor have exactly the score of many survivors.  Such a child of a class of survivors that takes up kTieRun
+// splitters in a row is not stored: its slot is marked in the class's bitmap, and its rank follows from the number of
+// marks before its own.  Class c's last splitter lies among splitters [c * kTieRun, (c + 1) * kTieRun), so there are at most
+// kTieClasses of them and no two share a bitmap.  count[kTieCount + c]: its children; count[kTieBucket + c]: the bucket
+// they would be in, of which they are the first offspring.
+// (A bucket's counter takes 9 ns per child: on the stress workload, where up to 28000 children share one score while a better genome
+// takes the pool over, the kernel of such a generation took up to 390 us, and the selection 127 in the median of those generations,
+// 270 at most.  Now 71 and 19, 61 at most, and other generations take the 0.3 us longer that the look for the flag costs; runs of
+// 16 splitters leave classes of up to 1500 children to the buckets, and 26 us.)
+constexpr int kTieRun = 8, kTieClasses = kMaxBuckets / kTieRun;
+constexpr int kTieFlag = kMaxBuckets + 2;        // count[kTieFlag]: there is such a child
+constexpr int kTieCount = kTieFlag + 1, kTieBucket = kTieCount + kTieClasses;
+static_assert(kTieClasses == 2 * kLanes, "two classes to a lane");
+constexpr int kBucketCounters = kTieBucket + kTieClasses;
+constexpr uint32_t kTieMask = kTieClasses / 32;      // words of the classes' bits
+__host__ __device__ inline uint32_t tie_words(uint32_t K) { return (3 * K + 31) / 32; }     // of a class's bitmap, over the slots from K on
 constexpr uint32_t kManyInBucket = 512;
 constexpr int kRowGroupWords = 64;               // bitmap words per entry of the free-row index (one per lane)
 struct BucketArgs {
@@ -97,6 +113,8 @@ struct BucketArgs {
   uint32_t       *spill_idx;
   uint32_t       *spill_bucket;
   uint32_t       *split_slot; // [kMaxBuckets] general selection: the pool slots that go with the splitters' scores
+  uint32_t       *ties;       // [kTieClasses][tie_words] the children of each class, by slot, then [kTieMask] a bit per class that has
+                              // any; zero when a generation begins
   uint64_t       *split_next; // splitters and threshold for the next generation (same arrays)
   uint64_t       *thresh_next;
   uint32_t        nb, seg;
@@ -296,11 +314,12 @@ inline hipError_t launch_evolve(const EvolveArgs &a, int rows, bool same_table, 
 hipError_t launch_select(const double *fit_row, const double *slot_score, const RowPlan &rp, uint32_t P, uint32_t K,
                          const BucketArgs &store, int32_t *sel, hipStream_t s);
 hipError_t launch_zero_words(uint32_t *words, uint32_t n, hipStream_t s);
+// count_next, ties_next: the other set of counters and bitmaps, cleared for the next generation.
 hipError_t launch_bucket_select(const double *fit_row, const BucketArgs &bk, const RowPlan &rp, uint32_t K,
-                                uint32_t *count_next, int32_t *sel, hipStream_t s);
+                                uint32_t *count_next, uint32_t *ties_next, int32_t *sel, hipStream_t s);
 hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const int32_t *sel, uint32_t K,
                             uint32_t nb, uint64_t *split, uint64_t *thresh, uint32_t *count0, uint32_t *count1,
-                            hipStream_t s);
+                            uint32_t *ties, uint32_t ties_words, hipStream_t s);
 // Eq. 1 for the winner: GPU i runs slot slot_of_gpu[i] (-1 = idle) with batch_of_gpu[i] samples;
 // jobs in slot order on consecutive GPUs.  G entries each.  best: row of the winner.
 hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,

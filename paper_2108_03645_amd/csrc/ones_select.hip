@@ -131,13 +131,21 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   return v;
 }
 
+// A bucket's copies of a class of survivors (see kTieRun): n children with the score of the bucket's first survivor, ranked
+// behind the survivors with that score and before all other offspring of the bucket.
+struct Copies {
+  uint32_t n = 0;
+  uint64_t key = 0;
+  __device__ __forceinline__ uint32_t before(uint64_t survivor) const { return survivor > key ? n : 0u; }
+};
+
 // Ranks one bucket: offspring in (sk, si)[0..n) (padded with never-smaller keys up to npad, a
 // multiple of 8), survivors' score bits in ek[0..ne).  Writes the survivor list entries that
 // fall below K and notes the next generation's splitters.
 template <bool kElites, int kThreads>
 __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *si, const uint64_t *ek, uint32_t n, uint32_t npad,
                                             uint32_t ne, uint32_t e0, uint32_t off, bool sorted, uint32_t K,
-                                            const BucketArgs &bk, const RowPlan &rp, int32_t *sel) {
+                                            const BucketArgs &bk, const RowPlan &rp, const Copies &copies, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb;
   // offspring i: rank = offspring before it + survivors with score <= its score (a survivor
   // wins a tie: smaller slot)
@@ -173,12 +181,12 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
         const uint32_t mid = (lo + hi) >> 1;
         if (ek[mid] <= key) lo = mid + 1; else hi = mid;
       }
-      g = off + below + lo;
+      g = off + copies.n + below + lo;
       if (g < K) {
         sel[g] = static_cast<int32_t>(id);
         if (kElites) {
           note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
-          keep_child(rp, g, row, id, off - e0 + below, K);
+          keep_child(rp, g, row, id, off + copies.n - e0 + below, K);
         }
       }
     }
@@ -204,7 +212,7 @@ __device__ __forceinline__ void rank_bucket(const uint64_t *sk, const uint32_t *
           if (sk[mid] < key) lo = mid + 1; else hi = mid;
         }
       }
-      const uint32_t g = off + e + lo;
+      const uint32_t g = off + e + lo + copies.before(key);
       if (g < K) {
         sel[g] = static_cast<int32_t>(e0 + e);
         note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
@@ -252,7 +260,25 @@ struct BucketShared {
   uint32_t counted[kFewCrowded], n_counted;   // ... that all workgroups rank by counting
   uint32_t helps, member, team;        // the crowded bucket this workgroup helps to rank, as number `member` of `team`
   uint32_t valid, smaller, inside;     // of that bucket: sample points; records below and inside a range
+  uint32_t tie_count[kTieClasses], tie_bucket[kTieClasses];   // see BucketArgs
 };
+
+// Children in the buckets before o, this thread's share of them: to be added up over the workgroup.
+template <int kThreads>
+__device__ __forceinline__ uint32_t children_before(const BucketShared<kThreads> &sh, const BucketArgs &bk, bool any_copies, uint32_t o) {
+  uint32_t before = 0;
+  for (uint32_t c = threadIdx.x; c < o; c += kThreads) before += bk.count[c];
+  if (any_copies && threadIdx.x < static_cast<uint32_t>(kTieClasses) && sh.tie_bucket[threadIdx.x] < o) before += sh.tie_count[threadIdx.x];
+  return before;
+}
+// Copies in bucket o.  Called by whole waves.
+template <int kThreads>
+__device__ __forceinline__ uint32_t copies_in(const BucketShared<kThreads> &sh, uint32_t o) {
+  const uint32_t lane = threadIdx.x % kLanes, one = sh.tie_bucket[lane] == o ? sh.tie_count[lane] : 0u;
+  const uint32_t n = one + (sh.tie_bucket[kLanes + lane] == o ? sh.tie_count[kLanes + lane] : 0u);     // one of them at most
+  const uint64_t found = __ballot(n != 0);
+  return found ? __builtin_amdgcn_readlane(n, __ffsll(static_cast<long long>(found)) - 1) : 0u;
+}
 
 // Which buckets are crowded, and how they are ranked.  A bucket is crowded when it holds more than a
 // workgroup sorts in LDS, or more than it ranks by counting while at most kFewCrowded buckets do (the
@@ -321,11 +347,9 @@ __device__ __forceinline__ void join_team(BucketShared<kThreads> &sh, const Buck
 // bucket's own workgroup ranks its survivors too.
 template <bool kElites, int kThreads>
 __device__ __forceinline__ void rank_counted(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
-                                             const RowPlan &rp, uint32_t K, uint32_t o, int32_t *sel) {
+                                             const RowPlan &rp, uint32_t K, uint32_t o, bool any_copies, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb, b = blockIdx.x;
-  uint32_t before = 0;
-  for (uint32_t c = tid; c < o; c += kThreads) before += bk.count[c];
-  before = wave_sum_u32(before);
+  const uint32_t before = wave_sum_u32(children_before(sh, bk, any_copies, o));
   __syncthreads();                                   // the shared arrays are free
   if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
   const uint32_t e0 = kElites ? bucket_bound(o, K, nb) : 0u, ne = kElites ? bucket_bound(o + 1, K, nb) - e0 : 0u;
@@ -336,6 +360,8 @@ __device__ __forceinline__ void rank_counted(BucketShared<kThreads> &sh, const d
 #pragma unroll
   for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
   if (off >= K) return;                              // nothing of this bucket survives
+  Copies copies;
+  if (any_copies) { copies.n = copies_in(sh, o); copies.key = sh.ek[0]; }
   const uint32_t n = bk.count[o], n_main = min(n, bk.seg);
   const uint32_t places = n_main + (n > n_main ? bk.count[kSpillCounter] : 0u);
   auto record = [&](uint32_t at, uint64_t &key, uint32_t &id) {      // a place of the bucket; id ~0: no record of it
@@ -403,8 +429,9 @@ __device__ __forceinline__ void rank_counted(BucketShared<kThreads> &sh, const d
       const uint32_t below = sh.below[i];
       g = off + below;
       if (survivor) {
-        g += e;
+        g += e + copies.before(key);
       } else {                                       // survivors with a score at or below its own come before it
+        g += copies.n;
         uint32_t lo = 0, hi = ne;
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
@@ -419,7 +446,7 @@ __device__ __forceinline__ void rank_counted(BucketShared<kThreads> &sh, const d
           rp.parent_next[g] = rp.parents[e0 + e];
         } else {
           row = rp.row_of[id];
-          if (kElites) keep_child(rp, g, row, id, off - e0 + below, K);
+          if (kElites) keep_child(rp, g, row, id, off + copies.n - e0 + below, K);
         }
       }
     }
@@ -440,7 +467,7 @@ constexpr uint32_t kPerMember = 256;    // records to a member, if the team is l
 constexpr uint32_t kSamplePoints = 8;   // ... and sample points
 template <bool kElites, int kThreads>
 __device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk,
-                                             const RowPlan &rp, uint32_t K, int32_t *sel) {
+                                             const RowPlan &rp, uint32_t K, bool any_copies, int32_t *sel) {
   const uint32_t tid = threadIdx.x, nb = bk.nb, o = sh.helps, member = sh.member;
   const uint32_t n = bk.count[o], n_main = min(n, bk.seg);
   const uint32_t places = n_main + (n > n_main ? bk.count[kSpillCounter] : 0u);
@@ -459,9 +486,7 @@ __device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const d
       if (owner != o) { key = ~0ull; id = 0xFFFFFFFFu; }
     }
   };
-  uint32_t before = 0;
-  for (uint32_t c = tid; c < o; c += kThreads) before += bk.count[c];
-  before = wave_sum_u32(before);
+  const uint32_t before = wave_sum_u32(children_before(sh, bk, any_copies, o));
   __syncthreads();                                   // the shared arrays are free
   if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
   const uint32_t e0 = kElites ? bucket_bound(o, K, nb) : 0u, ne = kElites ? bucket_bound(o + 1, K, nb) - e0 : 0u;
@@ -475,6 +500,8 @@ __device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const d
 #pragma unroll
   for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
   if (off >= K) return;                              // nothing of this bucket survives
+  Copies copies;
+  if (any_copies) { copies.n = copies_in(sh, o); copies.key = sh.ek[0]; }
   uint64_t lo_key = 0, end_key = ~0ull;              // this member's range [lo, end)
   uint32_t lo_slot = 0, end_slot = 0xFFFFFFFFu;
   if (parts > 1) {
@@ -550,10 +577,72 @@ __device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const d
     if (off + below + e_lo < K) {
       if (sorted) bitonic_sort(sh.sk, sh.si, npad);
       rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek + e_lo, inside, npad, e_hi - e_lo, e0 + e_lo, off + below + e_lo, sorted,
-                                     K, bk, rp, sel);
+                                     K, bk, rp, copies, sel);
     }
     lo_key = hi_key;
     lo_slot = hi_slot;
+  }
+}
+
+// The copies: the workgroups are dealt to the classes that have any, in turn, and a class's words to its workgroups.  A
+// child's place is the number of marks before its own.
+template <int kThreads>
+__device__ __forceinline__ void rank_copies(BucketShared<kThreads> &sh, const double *fit_row, const BucketArgs &bk, const RowPlan &rp,
+                                            uint32_t K, uint64_t lower, uint64_t upper, int32_t *sel) {
+  const uint32_t tid = threadIdx.x, lane = tid % kLanes, wave = tid / kLanes, nb = bk.nb, b = blockIdx.x;
+  const uint32_t n_lower = static_cast<uint32_t>(__popcll(lower)), n_classes = n_lower + static_cast<uint32_t>(__popcll(upper));
+  const uint32_t member = b / n_classes, turn = b % n_classes, team = (nb - turn + n_classes - 1) / n_classes;
+  uint64_t half = turn < n_lower ? lower : upper;
+  for (uint32_t k = turn < n_lower ? 0u : n_lower; k < turn; ++k) half &= half - 1;
+  const uint32_t c = (turn < n_lower ? 0u : kLanes) + __ffsll(static_cast<long long>(half)) - 1, o = sh.tie_bucket[c], words = tie_words(K);
+  const uint32_t *marks = bk.ties + static_cast<size_t>(c) * words;
+  const uint32_t first = words * member / team, last = words * (member + 1) / team;     // 24576 * 1024 fits 32 bits
+  const uint32_t e0 = bucket_bound(o, K, nb), ne = bucket_bound(o + 1, K, nb) - e0;
+  const uint64_t key = static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0]]));
+  // children before the bucket; survivors of the bucket with the same score; marks before this workgroup's words
+  uint32_t before = children_before(sh, bk, true, o), equal = 0, marked = 0;
+  for (uint32_t e = tid; e < ne; e += kThreads) equal += static_cast<uint64_t>(__double_as_longlong(fit_row[rp.parents[e0 + e]])) == key ? 1u : 0u;
+  for (uint32_t w = tid; w < first; w += kThreads) marked += __popc(marks[w]);
+  before = wave_sum_u32(before);
+  equal = wave_sum_u32(equal);
+  marked = wave_sum_u32(marked);
+  constexpr uint32_t kWaves = kThreads / kLanes;
+  static_assert(3 * kWaves <= kThreads, "room for the sums");
+  __syncthreads();                                   // the shared arrays are free
+  if (lane == 0) { sh.below[wave] = before; sh.below[kWaves + wave] = equal; sh.below[2 * kWaves + wave] = marked; }
+  __syncthreads();
+  before = equal = marked = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kWaves; ++w) { before += sh.below[w]; equal += sh.below[kWaves + w]; marked += sh.below[2 * kWaves + w]; }
+  const uint32_t base = e0 + before + equal;         // rank of the first copy
+  for (uint32_t at = first; at < last && base + marked < K; at += kThreads) {
+    const uint32_t n = min(last - at, static_cast<uint32_t>(kThreads)), word = tid < n ? marks[at + tid] : 0u;
+    uint32_t incl = __popc(word);
+#pragma unroll
+    for (int d = 1; d < kLanes; d <<= 1) {
+      const uint32_t up = __shfl_up(incl, d, kLanes);
+      if (lane >= static_cast<uint32_t>(d)) incl += up;
+    }
+    __syncthreads();
+    if (lane == kLanes - 1) sh.red[wave] = incl;
+    sh.si[tid] = word;
+    __syncthreads();
+    uint32_t upto = marked + incl - __popc(word);
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+      if (w < wave) upto += sh.red[w];
+      marked += sh.red[w];
+    }
+    sh.below[tid] = upto;
+    __syncthreads();
+    for (uint32_t q = tid; q < n * 32; q += kThreads) {
+      const uint32_t bits = sh.si[q / 32], i = sh.below[q / 32] + __popc(bits & ((1u << (q % 32)) - 1u)), g = base + i;
+      if (((bits >> (q % 32)) & 1u) == 0 || g >= K) continue;
+      const uint32_t p = K + at * 32 + q, row = rp.row_of[p];
+      sel[g] = static_cast<int32_t>(p);
+      note_rank(g, key, K, nb, bk.split_next, bk.thresh_next);
+      keep_child(rp, g, row, p, before + i, K);
+    }
   }
 }
 
@@ -563,7 +652,7 @@ __device__ __forceinline__ void rank_in_team(BucketShared<kThreads> &sh, const d
 // kThreads: a bucket of at most that many offspring (nearly all) is ranked straight from registers.
 template <bool kElites, int kThreads>
 __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *fit_row, BucketArgs bk, RowPlan rp,
-                                                                 uint32_t K, uint32_t *count_next, int32_t *sel) {
+                                                                 uint32_t K, uint32_t *count_next, uint32_t *ties_next, int32_t *sel) {
   __shared__ BucketShared<kThreads> sh;
   const uint32_t b = blockIdx.x, nb = bk.nb, tid = threadIdx.x;
   // offset of this bucket = its first survivor rank + all offspring of the buckets before it
@@ -572,6 +661,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
   before = wave_sum_u32(before);
   if ((tid & (kLanes - 1)) == 0) sh.red[tid / kLanes] = before;
   const bool any_many = bk.count[kManyFlag] != 0;    // a bucket holds more than kBucketCount
+  const bool any_copies = kElites && bk.count[kTieFlag] != 0;
   const uint32_t e0 = kElites ? bucket_bound(b, K, nb) : 0u, ne = kElites ? bucket_bound(b + 1, K, nb) - e0 : 0u;
   const uint32_t n = bk.count[b];
   // Every global load a small bucket needs is issued here, before anything waits for one: an
@@ -589,6 +679,13 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
   if (se < ne) elite_row = rp.parents[e0 + se];
   if (se < ne) elite_key = static_cast<uint64_t>(__double_as_longlong(fit_row[elite_row]));   // survivors stayed in their rows
   if (my_idx < 4 * K) my_row = rp.row_of[my_idx];
+  if (any_copies && tid < static_cast<uint32_t>(kTieClasses)) {
+    const uint32_t n_copies = bk.count[kTieCount + tid], in = bk.count[kTieBucket + tid];
+    sh.tie_count[tid] = n_copies;
+    sh.tie_bucket[tid] = in;
+    const uint32_t more = wave_sum_u32(in < b ? n_copies : 0u);
+    if (tid % kLanes == 0) sh.red[tid / kLanes] += more;
+  }
   static_assert(kThreads <= kBucketCount, "a small bucket is ranked by counting");
   const bool small = n <= static_cast<uint32_t>(kThreads) && n <= seg && ne <= static_cast<uint32_t>(kThreads);
   // counting loops run in steps of 8 over padding; the sorting network needs a power of two
@@ -610,6 +707,8 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
   uint32_t off = e0;
 #pragma unroll
   for (int w = 0; w < kThreads / kLanes; ++w) off += sh.red[w];
+  Copies copies;
+  if (any_copies) { copies.n = copies_in(sh, b); copies.key = sh.ek[0]; }
   Crowd crowd{};
   uint32_t n_teams = 0;
   bool crowded = false;                              // this workgroup's own bucket
@@ -666,12 +765,12 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
             const uint32_t mid = (lo + hi) >> 1;
             if (sh.ek[mid] <= my_key) lo = mid + 1; else hi = mid;
           }
-          g = off + below + lo;
+          g = off + copies.n + below + lo;
           if (g < K) {
             sel[g] = static_cast<int32_t>(my_idx);
             if (kElites) {
               note_rank(g, my_key, K, nb, bk.split_next, bk.thresh_next);
-              keep_child(rp, g, my_row, my_idx, off - e0 + below, K);
+              keep_child(rp, g, my_row, my_idx, off + copies.n - e0 + below, K);
             }
           }
         }
@@ -685,7 +784,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
 #pragma unroll
             for (int v = 0; v < 8; ++v) lo += sh.sk[q + v] < elite_key ? 1u : 0u;
           }
-          const uint32_t g = off + se + lo;
+          const uint32_t g = off + se + lo + copies.before(elite_key);
           if (g < K) {
             sel[g] = static_cast<int32_t>(e0 + se);
             note_rank(g, elite_key, K, nb, bk.split_next, bk.thresh_next);
@@ -696,15 +795,32 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     } else {
       gather_bucket(sh.sk, sh.si, bk, b, n, npad, &sh.spill_cursor);
       if (sorted) bitonic_sort(sh.sk, sh.si, npad);
-      rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek, n, npad, ne, e0, off, sorted, K, bk, rp, sel);
+      rank_bucket<kElites, kThreads>(sh.sk, sh.si, sh.ek, n, npad, ne, e0, off, sorted, K, bk, rp, copies, sel);
     }
   }
   if (any_many)
-    for (uint32_t k = 0; k < sh.n_counted; ++k) rank_counted<kElites, kThreads>(sh, fit_row, bk, rp, K, sh.counted[k], sel);
-  if (n_teams != 0 && sh.team != 0) rank_in_team<kElites, kThreads>(sh, fit_row, bk, rp, K, sel);
-  if (kElites) {                                     // the other counter set, for the next generation
+    for (uint32_t k = 0; k < sh.n_counted; ++k) rank_counted<kElites, kThreads>(sh, fit_row, bk, rp, K, sh.counted[k], any_copies, sel);
+  if (n_teams != 0 && sh.team != 0) rank_in_team<kElites, kThreads>(sh, fit_row, bk, rp, K, any_copies, sel);
+  if (kElites) {
+    uint64_t classes[2] = {0, 0};
+    if (any_copies) {
+      classes[0] = __ballot(sh.tie_count[tid % kLanes] != 0);
+      classes[1] = __ballot(sh.tie_count[kLanes + tid % kLanes] != 0);
+      rank_copies(sh, fit_row, bk, rp, K, classes[0], classes[1], sel);
+    }
+    // the other counter set and bitmaps, for the next generation
     if (tid == 0) count_next[b] = 0;
-    if (b == 0 && tid == 0) count_next[kSpillCounter] = count_next[kManyFlag] = 0;
+    if (b == 0 && tid < static_cast<uint32_t>(kBucketCounters - kMaxBuckets)) count_next[kMaxBuckets + tid] = 0;
+    // (only the classes that it was used for: clearing all of them took 0.8 of the kernel's 6 us on the stress workload)
+    const uint32_t words = tie_words(K), from = words * b / nb, to = words * (b + 1) / nb;        // 24576 * 1024 fits 32 bits
+    const uint32_t *mask = ties_next + kTieClasses * words;
+#pragma unroll
+    for (uint32_t k = 0; k < kTieMask; ++k)
+      for (uint32_t used = mask[k]; used != 0; used &= used - 1) {
+        uint32_t *marks = ties_next + (32 * k + __ffs(static_cast<int>(used)) - 1) * words;
+        for (uint32_t w = from + tid; w < to; w += kThreads) marks[w] = 0;
+      }
+    if (b == 0 && tid < kTieMask) bk.ties[kTieClasses * words + tid] = static_cast<uint32_t>(classes[tid / 2] >> (32 * (tid % 2)));
   }
 }
 
@@ -826,8 +942,9 @@ __global__ void zero_words_kernel(uint32_t *words, uint32_t n) {
 // Splitters after a selection by the general path.
 __global__ void splitters_kernel(const double *fit_row, const uint32_t *row_of, const int32_t *sel, uint32_t K,
                                  uint32_t nb, uint64_t *split, uint64_t *thresh, uint32_t *count0,
-                                 uint32_t *count1) {
+                                 uint32_t *count1, uint32_t *ties, uint32_t ties_words) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+  for (uint32_t w = c; w < ties_words; w += gridDim.x * blockDim.x) ties[w] = 0;
   if (c < static_cast<uint32_t>(kBucketCounters)) { count0[c] = 0; count1[c] = 0; }
   if (c < static_cast<uint32_t>(kMaxBuckets))
     split[c] = (c + 1 < nb) ? static_cast<uint64_t>(__double_as_longlong(fit_row[row_of[sel[bucket_bound(c + 1, K, nb)]]])) : kNoSplitter;
@@ -1077,22 +1194,23 @@ hipError_t launch_select(const double *fit, const double *slot_score, const RowP
   rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL((bucket_select_kernel<false, kBucketCount>), dim3(nb), dim3(kBucketCount), 0, s, nullptr,
-                     bk, rp, K, nullptr, sel);
+                     bk, rp, K, nullptr, nullptr, sel);
   return hipGetLastError();
 }
 
 hipError_t launch_bucket_select(const double *fit_row, const BucketArgs &bk, const RowPlan &rp, uint32_t K,
-                                uint32_t *count_next, int32_t *sel, hipStream_t s) {
+                                uint32_t *count_next, uint32_t *ties_next, int32_t *sel, hipStream_t s) {
   hipLaunchKernelGGL((bucket_select_kernel<true, kBucketThreads>), dim3(bk.nb), dim3(kBucketThreads), 0, s, fit_row, bk,
-                     rp, K, count_next, sel);
+                     rp, K, count_next, ties_next, sel);
   return hipGetLastError();
 }
 
 hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const int32_t *sel, uint32_t K,
                             uint32_t nb, uint64_t *split, uint64_t *thresh, uint32_t *count0, uint32_t *count1,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(splitters_kernel, dim3((kBucketCounters + 255) / 256), dim3(256), 0, s, fit_row, row_of, sel, K,
-                     nb, split, thresh, count0, count1);
+                            uint32_t *ties, uint32_t ties_words, hipStream_t s) {
+  const uint32_t blocks = std::max<uint32_t>((kBucketCounters + 255) / 256, std::min<uint32_t>(ties_words / 1024, 1024u));
+  hipLaunchKernelGGL(splitters_kernel, dim3(blocks), dim3(256), 0, s, fit_row, row_of, sel, K,
+                     nb, split, thresh, count0, count1, ties, ties_words);
   return hipGetLastError();
 }
 

@@ -160,6 +160,42 @@ def test_crowded_buckets(ones, ref, n_slots, n_gpus, pop, seed):
         ref.set_threads(1)
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,seed,gens", [
+    (20, 30, 4356, 7, 16), (24, 40, 4100, 1, 8), (24, 40, 8192, 2, 20), (66, 90, 16384, 6, 25), (40, 64, 20004, 3, 22), (40, 64, 65536, 4, 5),
+    (30, 40, 70000, 5, 14)])
+def test_children_that_copy_many_survivors(ones, ref, n_slots, n_gpus, pop, seed, gens):
+    """Children with the score of so many survivors that these take up eight splitters of the buckets in a row: one class of
+    them up to two dozen, 90 to 30000 children, from K / 16 = 64 buckets on; launched by generation with either entry point, and
+    with whole calls in one launch in between.  (By the oracle: a class like that beats the K-th survivor in some generation.)"""
+    rng = np.random.default_rng(seed)
+    jobs = random_jobs(rng, n_slots)
+    K, cl = pop // 4, cluster(n_gpus, n_slots, pop, seed=seed)
+    nb = min(1024, K // 16)
+    bounds = np.arange(1, nb) * K // nb
+    say(f"[parity] copies of many survivors: G={n_gpus} slots={n_slots} P={pop} seed={seed}")
+    ref.set_threads(8)
+    try:
+        gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+        seen = 0
+        for gen in range(gens):
+            _, fit, sel, _ = cpu.export(genes=False)
+            split, worst = fit[sel[bounds]], fit[sel[-1]]
+            cpu.generation(1)
+            if gen % 5 == 3: gpu.generation_static(1)
+            else: gpu.generation(1)
+            assert_same_state(gpu, cpu, f"generation {gen + 1}", genes=gen + 1 == gens)
+            children = cpu.export(genes=False)[1][K:]
+            runs = split[7:][split[7:] == split[:-7]]
+            seen += np.isin(children[children < worst], runs).sum()
+            if gen % 5 == 4:                           # the bitmaps of the generations before do not show through
+                gpu.generation(4); cpu.generation(4)
+                assert_same_state(gpu, cpu, f"after generation {gen + 1}", genes=False)
+        assert seen > 0
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
 @pytest.mark.parametrize("pop", [4100, 8192, 20000, 40004])
 def test_bucketed_selection_and_table_changes(ones, ref, pop):
     """Pools above one sort chunk select through survivor-quantile buckets while the job table
