@@ -4,6 +4,8 @@
 #include "ones_device.h"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -222,15 +224,20 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   return L;
 }
 
-// Host transfers go through one pinned staging buffer, a single copy per call: the arrays that
-// travel together lie next to each other in the workspace (every size below is a multiple of the
-// 256-byte alignment except the last of a group).
-size_t stage_bytes(const Layout &L, uint32_t Jp, uint32_t G) {
+// Host transfers go through one pinned staging buffer, which the kernels read and write themselves: laid out like the arrays
+// that travel together, which lie next to each other in the workspace (every size below is a multiple of the
+// 256-byte alignment except the last of a group).  Behind them HostWords.
+struct HostWords { uint32_t flag, pad, err[2]; };              // see HostSignal; error words that come with a placement
+// A state of up to so much is exported that way too (a larger one is copied).
+constexpr size_t kStagedExport = 256u << 10;
+size_t export_bytes(const Layout &L, uint32_t P, uint32_t Jp) { return L.unpacked + static_cast<size_t>(P) * Jp * 4 - L.export_err; }
+size_t stage_bytes(const Layout &L, uint32_t P, uint32_t Jp, uint32_t G) {
   const size_t table = L.rY + static_cast<size_t>(Jp) * 8 - L.rawinfo;        // rawinfo, a, c, d, Y
   const size_t progress = L.processed + static_cast<size_t>(Jp) * 8 - L.alpha; // alpha, beta, processed
   const size_t best = L.best_err + 8 - L.best_batch;                           // batch, gpus, fitness, error words
   const size_t place = L.place_batch + static_cast<size_t>(G) * 4 - L.place_slot;
-  return std::max({table, progress, best, place, static_cast<size_t>(Jp) * 4});
+  const size_t all = export_bytes(L, P, Jp);
+  return align_up(std::max({table, progress, best, place, static_cast<size_t>(Jp) * 4, all <= kStagedExport ? all : 0}));
 }
 
 int check_config(const ones_config *cfg) {
@@ -307,7 +314,9 @@ struct ones_ctx {
   hipStream_t stream;
   char *ws;
   char *stage;                // pinned host staging buffer (stage_bytes), free between calls
-  char *stage_dev;            // the same buffer as the device addresses it (ones_best's kernel writes the winner there)
+  char *stage_dev;            // the same buffer as the device addresses it
+  size_t words_at;            // HostWords in it
+  uint32_t signals, tickets;  // HostSignal: the value of the last one, the tickets of all
   Layout L;
   int cur;                    // the survivors of the current generation are in parent_row[cur ^ 1]
   int occ;                    // which bitmap holds the survivors' rows, unless
@@ -354,9 +363,34 @@ struct ones_ctx {
                     at<double>(L.terms[which]), term_E};
   }
   JobTable table() const { return table(y_cur); }
+  volatile HostWords *host_words() const { return reinterpret_cast<volatile HostWords *>(stage + words_at); }
+  HostWords *host_words_dev() const { return reinterpret_cast<HostWords *>(stage_dev + words_at); }
 };
 
 namespace {
+
+// For a launch of so many workgroups.
+HostSignal next_signal(ones_ctx *c, uint32_t blocks) {
+  c->signals += 1;
+  if (blocks > 1) c->tickets += blocks;
+  return HostSignal{c->at<uint32_t>(c->L.fsync) + 8, &c->host_words_dev()->flag, c->tickets, c->signals};
+}
+// Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
+constexpr std::chrono::milliseconds kPollTime(4);
+int wait_signal(ones_ctx *c) {
+  const auto from = std::chrono::steady_clock::now();
+  do {
+    for (int i = 0; i < 256; ++i) {
+      if (c->host_words()->flag == c->signals) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return ONES_OK;
+      }
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() - from < kPollTime);
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  return ONES_OK;
+}
 
 int upload_table(ones_ctx *c, const HostJobs &h) {
   const size_t n4 = static_cast<size_t>(c->Jp) * 4, n8 = static_cast<size_t>(c->Jp) * 8;
@@ -367,13 +401,25 @@ int upload_table(ones_ctx *c, const HostJobs &h) {
   memcpy(staged(L.rc), h.c.data(), n8);
   memcpy(staged(L.rd), h.d.data(), n8);
   memcpy(staged(L.rY), h.Y.data(), n8);
-  HIP_TRY(hipMemcpyAsync(c->ws + L.rawinfo, c->stage, L.rY + n8 - L.rawinfo, hipMemcpyHostToDevice, c->stream));
-  RawJobs raw{c->at<uint32_t>(c->L.rawinfo), c->at<double>(c->L.ra), c->at<double>(c->L.rc),
-              c->at<double>(c->L.rd), c->at<double>(c->L.rY)};
+  auto mapped = [&](size_t off) { return c->stage_dev + (off - L.rawinfo); };
+  RawJobs raw{reinterpret_cast<uint32_t *>(mapped(L.rawinfo)), reinterpret_cast<double *>(mapped(L.ra)), reinterpret_cast<double *>(mapped(L.rc)),
+              reinterpret_cast<double *>(mapped(L.rd)), reinterpret_cast<double *>(mapped(L.rY))};
   c->term_E = h.term_E;
-  HIP_TRY(launch_table_change(raw, c->table(), c->Jp, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));     // the staging buffer is free again
-  return ONES_OK;
+  HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(L.rY), c->Jp, next_signal(c, table_change_blocks(c->Jp)), c->stream));
+  return wait_signal(c);                        // the staging buffer is free again
+}
+
+// `bytes` (a multiple of 16) of the staging buffer's beginning to the workspace.
+int fetch_staged(ones_ctx *c, size_t to, size_t bytes) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != c->device) {    // a kernel needs the context's device to be current, a copy does not
+    HIP_TRY(hipMemcpyAsync(c->ws + to, c->stage, bytes, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return ONES_OK;
+  }
+  const uint32_t n = static_cast<uint32_t>(bytes / 16);
+  HIP_TRY(launch_fetch(c->stage_dev, c->ws + to, n, next_signal(c, fetch_blocks(n)), c->stream));
+  return wait_signal(c);                        // the staging buffer is free again
 }
 
 int timed(ones_ctx *c, std::vector<EventPair> &pool, size_t &used, bool begin) {
@@ -556,9 +602,10 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   c->stage_dev = nullptr;
   {
     void *pinned = nullptr;
-    HIP_TRY(hipHostMalloc(&pinned, stage_bytes(L, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus)),
-                          hipHostMallocDefault));
+    c->words_at = stage_bytes(L, c->P, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
+    HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords), hipHostMallocDefault));
     c->stage = static_cast<char *>(pinned);
+    c->host_words()->flag = c->signals = c->tickets = 0;
     void *mapped = nullptr;
     HIP_TRY(hipHostGetDevicePointer(&mapped, pinned, 0));
     c->stage_dev = static_cast<char *>(mapped);
@@ -674,9 +721,7 @@ static int set_progress_impl(ones_ctx *c, const double *alpha, const double *bet
     const bool real = j < c->Jn;
     ha[j] = real ? alpha[j] : 1.0; hb[j] = real ? beta[j] : 1.0; hp[j] = real ? processed[j] : 0.0;
   }
-  HIP_TRY(hipMemcpyAsync(c->ws + L.alpha, c->stage, L.processed + static_cast<size_t>(c->Jp) * 8 - L.alpha,
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));     // the staging buffer is free again
+  if (int rc = fetch_staged(c, L.alpha, L.processed + static_cast<size_t>(c->Jp) * 8 - L.alpha)) return rc;
   c->sampling = true;
   c->drawn_from = c->drawn_to = 0;   // the draws made ahead used the old parameters
   return ONES_OK;
@@ -709,9 +754,7 @@ static int set_processed_time_impl(ones_ctx *c, const double *t_processed) {
   auto time_of = [&](uint32_t j) { return j < c->Jn ? t_processed[j] : 0.0; };
   std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return time_of(x) < time_of(y); });
   for (uint32_t pos = 0; pos < c->Jp; ++pos) rank[order[pos]] = pos;
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.time_rank, rank, static_cast<size_t>(c->Jp) * 4, hipMemcpyHostToDevice,
-                         c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));     // the staging buffer is free again
+  if (int rc = fetch_staged(c, c->L.time_rank, static_cast<size_t>(c->Jp) * 4)) return rc;
   c->has_times = true;
   return ONES_OK;
 }
@@ -932,17 +975,6 @@ static int row_fault(ones_ctx *c) {
   return ONES_E_HIP;
 }
 
-// For the calls that synchronise without reading the winner: fetches the error words the
-// kernels leave (a wait of a single-launch generation gave up; a row index was out of range).
-// The stream must be idle.
-static int check_waits(ones_ctx *c) {
-  if (c->poisoned) return poisoned_error();
-  uint32_t words[2] = {0, 0};
-  HIP_TRY(hipMemcpy(words, c->ws + c->L.fsync + 4, 8, hipMemcpyDeviceToHost));
-  if (words[0]) return wait_gave_up(c);
-  return words[1] ? row_fault(c) : ONES_OK;
-}
-
 // Rows of the current generation's survivors, best first.
 static const uint32_t *survivor_rows(const ones_ctx *c) { return c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]); }
 
@@ -959,8 +991,8 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
                       c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, reinterpret_cast<int32_t *>(mapped(L.best_batch)),
                       reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
                       reinterpret_cast<double *>(mapped(L.best_fit)), c->at<uint32_t>(c->L.fsync) + 1,
-                      reinterpret_cast<uint32_t *>(mapped(L.best_err)), c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
+                      reinterpret_cast<uint32_t *>(mapped(L.best_err)), next_signal(c, 1), c->stream));
+  if (int rc = wait_signal(c)) return rc;
   auto staged = [&](size_t off) { return c->stage + (off - L.best_batch); };   // laid out as in the workspace
   uint32_t words[2] = {0, 0};
   memcpy(words, staged(L.best_err), 8);
@@ -976,21 +1008,22 @@ static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_g
   if (!c || c->no_schedule) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
   const size_t n4 = static_cast<size_t>(c->G) * 4;
-  HIP_TRY(launch_placement(c->at<uint32_t>(c->L.genes), survivor_rows(c), c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->G, c->at<int32_t>(c->L.place_slot),
-                           c->at<int32_t>(c->L.place_batch), c->stream));
   const Layout &L = c->L;
-  if (c->G)
-    HIP_TRY(hipMemcpyAsync(c->stage, c->ws + L.place_slot, L.place_batch + n4 - L.place_slot, hipMemcpyDeviceToHost,
-                           c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  if (int rc = check_waits(c)) return rc;
+  auto mapped = [&](size_t off) { return reinterpret_cast<int32_t *>(c->stage_dev + (off - L.place_slot)); };
+  HIP_TRY(launch_placement(c->at<uint32_t>(L.genes), survivor_rows(c), c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, c->G, mapped(L.place_slot),
+                           mapped(L.place_batch), c->at<uint32_t>(L.fsync) + 1, c->host_words_dev()->err,
+                           next_signal(c, placement_blocks(c->G)), c->stream));
+  if (int rc = wait_signal(c)) return rc;
+  if (c->host_words()->err[0]) return wait_gave_up(c);
+  if (c->host_words()->err[1]) return row_fault(c);
   auto staged = [&](size_t off) { return c->stage + (off - L.place_slot); };   // laid out as in the workspace
   if (slot_of_gpu && c->G) memcpy(slot_of_gpu, staged(L.place_slot), n4);
   if (batch_of_gpu && c->G) memcpy(batch_of_gpu, staged(L.place_batch), n4);
   return ONES_OK;
 }
 
-// A state of up to this size comes to the host in one copy (each costs about 10 us), through a buffer.
+// A state of up to this size comes to the host in one copy (each costs about 10 us), through a buffer; of up to kStagedExport
+// without any.
 constexpr size_t kOneCopyExport = 1u << 20;
 
 static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, int64_t *generation) {
@@ -998,22 +1031,36 @@ static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, i
   if (c->poisoned) { HIP_TRY(hipStreamSynchronize(c->stream)); return poisoned_error(); }
   // candidates live in physical rows, their genes as codes: the device puts scores and genomes in slot order
   const Layout &L = c->L;
-  const ExportArgs x{c->at<uint32_t>(L.genes), c->at<double>(L.fit_row), c->at<uint32_t>(L.row_of), c->at<int32_t>(L.sel),
+  ExportArgs x{c->at<uint32_t>(L.genes), c->at<double>(L.fit_row), c->at<uint32_t>(L.row_of), c->at<int32_t>(L.sel),
                      survivor_rows(c), c->at<uint32_t>(L.info[c->info_stored]), c->at<uint32_t>(L.fsync) + 1, c->P, c->K, c->Jp,
                      c->at<double>(L.export_fit), c->at<int32_t>(L.export_sel), c->at<uint32_t>(L.export_err),
-                     c->at<int32_t>(L.unpacked)};
+                     c->at<int32_t>(L.unpacked), HostSignal{}};
   const size_t fit_bytes = static_cast<size_t>(c->P) * 8, sel_bytes = static_cast<size_t>(c->K) * 4;
   const size_t row_bytes = static_cast<size_t>(c->Jp) * 4, genes_bytes = c->P * row_bytes;
   const uint32_t most = unpack_slots(c->P, c->Jp);
   const size_t all_bytes = genes ? L.unpacked + genes_bytes - L.export_err : L.export_fit + fit_bytes - L.export_err;
-  const bool one_copy = all_bytes <= kOneCopyExport && most == c->P;
+  const bool one_copy = all_bytes <= kOneCopyExport && most == c->P, staged = genes && export_bytes(L, c->P, c->Jp) <= kStagedExport;
   const size_t head_bytes = one_copy ? all_bytes : L.export_sel + sel_bytes - L.export_err;
-  if (genes && one_copy) HIP_TRY(launch_export_genes(x, 0, c->P, true, c->stream));
-  else HIP_TRY(launch_export_scores(x, c->stream));
-  const std::unique_ptr<char[]> head(new char[head_bytes]);
-  HIP_TRY(hipMemcpyAsync(head.get(), c->ws + L.export_err, head_bytes, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  auto fetched = [&](size_t off) { return head.get() + (off - L.export_err); };
+  std::unique_ptr<char[]> copied;
+  const char *head = c->stage;
+  if (staged) {
+    auto mapped = [&](size_t off) { return c->stage_dev + (off - L.export_err); };
+    x.fit_out = reinterpret_cast<double *>(mapped(L.export_fit));
+    x.sel_out = reinterpret_cast<int32_t *>(mapped(L.export_sel));
+    x.err_out = reinterpret_cast<uint32_t *>(mapped(L.export_err));
+    x.genes_out = reinterpret_cast<int32_t *>(mapped(L.unpacked));
+    x.done = next_signal(c, c->K);
+    HIP_TRY(launch_export_genes(x, 0, c->P, true, c->stream));
+    if (int rc = wait_signal(c)) return rc;
+  } else {
+    if (genes && one_copy) HIP_TRY(launch_export_genes(x, 0, c->P, true, c->stream));
+    else HIP_TRY(launch_export_scores(x, c->stream));
+    copied.reset(new char[head_bytes]);
+    head = copied.get();
+    HIP_TRY(hipMemcpyAsync(copied.get(), c->ws + L.export_err, head_bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+  }
+  auto fetched = [&](size_t off) { return head + (off - L.export_err); };
   uint32_t words[2] = {0, 0};
   memcpy(words, fetched(L.export_err), 8);
   if (words[0]) return wait_gave_up(c);

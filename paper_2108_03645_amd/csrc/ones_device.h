@@ -282,10 +282,23 @@ struct RawJobs {              // uploaded by the host after validation, [Jp] eac
   const double   *a, *c, *d, *Y;
 };
 
+// How a kernel tells the host that it, and so everything before it on the stream, is done: its last workgroup writes `value` to a
+// word of pinned memory that the host polls.  (A kernel and a wait of this kind take 5.9 us alone, with hipStreamSynchronize 9.3; a
+// copy from or to pinned memory is another 5 to 6, so these kernels read and write it themselves.)
+struct HostSignal {
+  uint32_t *tickets;          // of workgroups that are done, over all signals of more than one workgroup
+  uint32_t *flag;
+  uint32_t  target, value;    // the last workgroup's ticket
+};
+
 // launchers (each returns the hipGetLastError of its launch)
 // The per-slot values and the term table from the raw table, and the slots that changed hands marked
-// in tab.stored (unless the genomes are, or will be, stored under this table); one launch.
-hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, hipStream_t s);
+// in tab.stored (unless the genomes are, or will be, stored under this table); one launch.  remaining: the raw table's, kept.
+uint32_t table_change_blocks(uint32_t Jp);
+hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, double *remaining, uint32_t Jp, const HostSignal &done, hipStream_t s);
+// n 16-byte words.
+uint32_t fetch_blocks(uint32_t n);
+hipError_t launch_fetch(const void *from, void *to, uint32_t n, const HostSignal &done, hipStream_t s);
 hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s);
 // ring: the job table with Y and terms pointing at place 0 of a ring of `places`, which lie
 // ring_stride doubles apart; draws generations t .. t + count - 1 (count <= places).
@@ -322,12 +335,14 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
                             uint32_t *ties, uint32_t ties_words, hipStream_t s);
 // Eq. 1 for the winner: GPU i runs slot slot_of_gpu[i] (-1 = idle) with batch_of_gpu[i] samples;
 // jobs in slot order on consecutive GPUs.  G entries each.  best: row of the winner.
+uint32_t placement_blocks(uint32_t G);
 hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
-                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, hipStream_t s);
+                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, const uint32_t *err_in, uint32_t *err_out,
+                            const HostSignal &done, hipStream_t s);
 // stored: info of the table the genomes are stored under, info: of the table in force.
 hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *best, const uint32_t *stored,
                        const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
-                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s);
+                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, const HostSignal &done, hipStream_t s);
 // The state as ones_export hands it out.  The rows of the survivors, slot sel[g] in row parents[g], go by
 // parents, those of the other slots by row_of.
 struct ExportArgs {
@@ -343,6 +358,7 @@ struct ExportArgs {
   int32_t        *sel_out;    // [K]
   uint32_t       *err_out;    // [2]
   int32_t        *genes_out;  // [count][Jp] batch sizes of the slots [first, first + count)
+  HostSignal      done;       // given by the last kernel of launch_export_genes, flag null: by none
 };
 // Scores, survivors and error words.
 hipError_t launch_export_scores(const ExportArgs &x, hipStream_t s);

@@ -951,11 +951,21 @@ __global__ void splitters_kernel(const double *fit_row, const uint32_t *row_of, 
   if (c == 0) *thresh = static_cast<uint64_t>(__double_as_longlong(fit_row[row_of[sel[K - 1]]]));
 }
 
+// The whole workgroup calls it when what it writes for the host, or reads of the host's, is written or read.
+__device__ __forceinline__ void signal_host(const HostSignal &done) {
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  if (gridDim.x == 1 || __hip_atomic_fetch_add(done.tickets, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == done.target)
+    __hip_atomic_store(done.flag, done.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // What the kernels need of one job slot, derived from the validated raw table.
 struct SlotValues { uint32_t start, most, draws, base, info; double abl, cc, d, Y; };
 
 __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j) {
   const uint32_t w = raw.rawinfo[j];
+  const double a = raw.a[j], c = raw.c[j], d = raw.d[j], Y = raw.Y[j];         // (also of an empty slot: nothing waits for w)
   const int lo = w & 31, hi = (w >> 5) & 31, mu = (w >> 10) & 31;
   if (!((w >> 15) & 1u)) return SlotValues{0u, 0u, 0u, 0u, 0u, 0.0, 0.0, 0.0, 0.0};
   const int bl = min(mu, hi);                       // log2 of the local batch of a running job
@@ -967,28 +977,26 @@ __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j
   v.base = static_cast<uint32_t>(lo - mu + 31);     // code of the batch 2^(lo + k - 1): lo + k - mu, kept above 0
   v.info = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo + 2) << 5) | (static_cast<uint32_t>(mu) << 11) |
            (static_cast<uint32_t>(bl) << 16) | (1u << 21) | (((w >> 16) & 1u) << 22);
-  v.abl = raw.a[j] * static_cast<double>(1u << bl);
-  v.cc = raw.c[j];
-  v.d = raw.d[j];
-  v.Y = raw.Y[j];
+  v.abl = a * static_cast<double>(1u << bl);
+  v.cc = c;
+  v.d = d;
+  v.Y = Y;
   return v;
 }
 
-// A new job table in one launch.  Thread q: entry q of the term table; the thread of a slot's code 0
-// also writes the slot's values, marks the slot in tab.stored if it changed hands (the genomes,
+// A new job table in one launch, a thread per slot and a wave per row.  The raw table lies in pinned host memory, so every value
+// is read once, and all of a thread's are on their way together.  The thread writes the slot's values and its entries of the
+// term table, marks the slot in tab.stored if it changed hands (the genomes,
 // stored under another table, hold a gene of its former job: whoever reads one from then on takes
 // it as "waiting"; resetting the genes themselves was a scattered store per row and slot, 80 to 240 us
 // on the stress cluster) and clears the bytes of the rows beyond the job slots.
-constexpr int kTableThreads = 256;
-__global__ __launch_bounds__(kTableThreads) void table_change_kernel(RawJobs raw, JobTable tab, uint32_t Jp) {
-  const uint32_t q = blockIdx.x * kTableThreads + threadIdx.x;
-  const uint32_t E = tab.term_E;
-  if (q >= Jp * E) return;
-  const uint32_t lane = q % kLanes, e = (q / kLanes) % E, row = q / (kLanes * E);
-  const uint32_t j = row * kLanes + lane;
+__global__ __launch_bounds__(kLanes) void table_change_kernel(RawJobs raw, JobTable tab, double *remaining, uint32_t Jp, HostSignal done) {
+  const uint32_t lane = threadIdx.x, row = blockIdx.x, E = tab.term_E, j = row * kLanes + lane;
+  const uint32_t flags = raw.rawinfo[j];
+  const double raw_Y = raw.Y[j];
   const SlotValues v = derive_slot(raw, j);
-  tab.terms[q] = term_of(v.abl, v.cc, v.d, v.Y, info_blexp(v.info), e);
-  if (e != 0) return;
+  for (uint32_t e = 0; e < E; ++e) tab.terms[(row * E + e) * kLanes + lane] = term_of(v.abl, v.cc, v.d, v.Y, info_blexp(v.info), e);
+  remaining[j] = raw_Y;
   uint8_t *arrays[4] = {reinterpret_cast<uint8_t *>(tab.start), reinterpret_cast<uint8_t *>(tab.most),
                         reinterpret_cast<uint8_t *>(tab.draws), reinterpret_cast<uint8_t *>(tab.base)};
   const uint32_t values[4] = {v.start, v.most, v.draws, v.base};
@@ -1001,7 +1009,15 @@ __global__ __launch_bounds__(kTableThreads) void table_change_kernel(RawJobs raw
       for (int k = 0; k < 4; ++k) arrays[k][at - at % 4 + beyond] = 0;
   tab.info[j] = v.info;
   tab.abl[j] = v.abl; tab.cc[j] = v.cc; tab.d[j] = v.d; tab.Y[j] = v.Y;
-  if (tab.stored != tab.info && ((raw.rawinfo[j] >> 17) & 1u)) tab.stored[j] |= kInfoReset;
+  if (tab.stored != tab.info && ((flags >> 17) & 1u)) tab.stored[j] |= kInfoReset;
+  signal_host(done);
+}
+
+constexpr int kFetchThreads = 256;
+__global__ __launch_bounds__(kFetchThreads) void fetch_kernel(const uint4 *from, uint4 *to, uint32_t n, HostSignal done) {
+  const uint32_t i = blockIdx.x * kFetchThreads + threadIdx.x;
+  if (i < n) to[i] = from[i];
+  signal_host(done);
 }
 
 // Term table: the score formula evaluated once per (slot, GPU-count code), same operations in
@@ -1023,7 +1039,7 @@ __device__ __forceinline__ uint32_t stored_batch(const uint32_t *row, const uint
 
 __global__ void best_kernel(const uint32_t *genes, const double *fit_row, const uint32_t *best_row, const uint32_t *stored,
                             const uint32_t *info, uint32_t Jn, uint32_t row_words, int32_t *batch_out, int32_t *gpus_out, double *fit_out, const uint32_t *err_in,
-                            uint32_t *err_out) {
+                            uint32_t *err_out, HostSignal done) {
   const uint32_t best = *best_row;
   const uint32_t *row = genes + static_cast<size_t>(best) * row_words;
   for (uint32_t j = threadIdx.x; j < Jn; j += blockDim.x) {
@@ -1036,6 +1052,7 @@ __global__ void best_kernel(const uint32_t *genes, const double *fit_row, const 
     err_out[0] = err_in[0];                          // the two error words travel to the host with the winner
     err_out[1] = err_in[1];
   }
+  signal_host(done);
 }
 
 // The state in slot order.  Two launches each, the second for the survivors (a survivor's slot may have been
@@ -1064,6 +1081,7 @@ __global__ __launch_bounds__(kExportThreads) void export_survivors_kernel(Export
   const uint32_t g = blockIdx.x, at = static_cast<uint32_t>(x.sel[g]) - first, row = exported_row(x, x.parents[g]);
   if (at < count) unpack_row(x, row, at);
   if (with_scores && threadIdx.x == 0) export_survivor(x, g, row);
+  if (x.done.flag != nullptr) signal_host(x.done);
 }
 // One thread per slot, then per survivor.
 __global__ __launch_bounds__(kExportThreads) void export_slot_scores_kernel(ExportArgs x) {
@@ -1082,7 +1100,8 @@ constexpr int kPlaceThreads = 1024;
 __global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const uint32_t *genes, const uint32_t *best_row,
                                                                  const uint32_t *info, uint32_t Jn,
                                                                  uint32_t row_words, uint32_t G, int32_t *slot_of_gpu,
-                                                                 int32_t *batch_of_gpu) {
+                                                                 int32_t *batch_of_gpu, const uint32_t *err_in,
+                                                                 uint32_t *err_out, HostSignal done) {
   __shared__ uint32_t first[2 * kPlaceThreads + 1];    // first GPU of every slot, then the GPUs in use
   __shared__ uint32_t per_gpu[2 * kPlaceThreads];      // local batch of every slot's workers
   __shared__ uint32_t wave_total[kPlaceThreads / kLanes];
@@ -1125,9 +1144,11 @@ __global__ __launch_bounds__(kPlaceThreads) void placement_kernel(const uint32_t
       slot = static_cast<int32_t>(lo);
       batch = static_cast<int32_t>(per_gpu[lo]);
     }
-    if (slot_of_gpu) slot_of_gpu[i] = slot;
-    if (batch_of_gpu) batch_of_gpu[i] = batch;
+    slot_of_gpu[i] = slot;
+    batch_of_gpu[i] = batch;
   }
+  if (blockIdx.x == 0 && t < 2) err_out[t] = err_in[t];
+  signal_host(done);
 }
 
 }  // namespace
@@ -1138,9 +1159,16 @@ hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, uint32_t Jp, hipStream_t s) {
-  const uint32_t blocks = (Jp * tab.term_E + kTableThreads - 1) / kTableThreads;
-  hipLaunchKernelGGL(table_change_kernel, dim3(blocks), dim3(kTableThreads), 0, s, raw, tab, Jp);
+uint32_t table_change_blocks(uint32_t Jp) { return Jp / kLanes; }
+hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, double *remaining, uint32_t Jp, const HostSignal &done, hipStream_t s) {
+  hipLaunchKernelGGL(table_change_kernel, dim3(table_change_blocks(Jp)), dim3(kLanes), 0, s, raw, tab, remaining, Jp, done);
+  return hipGetLastError();
+}
+
+uint32_t fetch_blocks(uint32_t n) { return (n + kFetchThreads - 1) / kFetchThreads; }
+hipError_t launch_fetch(const void *from, void *to, uint32_t n, const HostSignal &done, hipStream_t s) {
+  hipLaunchKernelGGL(fetch_kernel, dim3(fetch_blocks(n)), dim3(kFetchThreads), 0, s, static_cast<const uint4 *>(from), static_cast<uint4 *>(to),
+                     n, done);
   return hipGetLastError();
 }
 
@@ -1214,19 +1242,20 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
   return hipGetLastError();
 }
 
+uint32_t placement_blocks(uint32_t G) { return std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u)); }
 hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
-                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, hipStream_t s) {
-  const uint32_t blocks = std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u));
-  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, best, info, Jn,
-                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), G, slot_of_gpu, batch_of_gpu);
+                            uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, const uint32_t *err_in, uint32_t *err_out,
+                            const HostSignal &done, hipStream_t s) {
+  hipLaunchKernelGGL(placement_kernel, dim3(placement_blocks(G)), dim3(kPlaceThreads), 0, s, genes, best, info, Jn,
+                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), G, slot_of_gpu, batch_of_gpu, err_in, err_out, done);
   return hipGetLastError();
 }
 
 hipError_t launch_best(const uint32_t *genes, const double *fit_row, const uint32_t *best, const uint32_t *stored,
                        const uint32_t *info, uint32_t Jn, uint32_t Jp, int32_t *batch_out, int32_t *gpus_out,
-                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, hipStream_t s) {
+                       double *fit_out, const uint32_t *err_in, uint32_t *err_out, const HostSignal &done, hipStream_t s) {
   hipLaunchKernelGGL(best_kernel, dim3(1), dim3(256), 0, s, genes, fit_row, best, stored, info, Jn,
-                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), batch_out, gpus_out, fit_out, err_in, err_out);
+                     static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), batch_out, gpus_out, fit_out, err_in, err_out, done);
   return hipGetLastError();
 }
 

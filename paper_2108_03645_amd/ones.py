@@ -119,10 +119,19 @@ def make_config(cluster) -> ones_config:
                        float(cluster.crossover_rate))
 
 
+def _address(a) -> int:
+    """Of the array's data.  (The attribute costs 1.9 us, a table has nine arrays; a buffer over read-only or empty data cannot
+    be had.)"""
+    try:
+        return C.addressof(C.c_char.from_buffer(a))
+    except (TypeError, ValueError, BufferError):
+        return a.ctypes.data
+
+
 def make_jobs(jobs):
     """Returns (struct, keepalive list) for any object carrying the nine job arrays."""
     keep = [np.ascontiguousarray(getattr(jobs, k), dtype=dt) for k, dt in _JOB_DTYPES.items()]
-    return ones_jobs(*[a.ctypes.data for a in keep]), keep
+    return ones_jobs(*map(_address, keep)), keep
 
 
 def workspace_bytes(cluster) -> int:
@@ -152,6 +161,7 @@ class Search:
         nbytes = int(L.ones_workspace_bytes(C.byref(cfg)))
         if nbytes == 0:
             raise OnesError(-1, "invalid configuration")
+        self._index = self.device.index if self.device.index is not None else torch.cuda.current_device()
         with torch.cuda.device(self.device):
             self.stream = stream if stream is not None else torch.cuda.current_stream()
             self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
@@ -163,34 +173,38 @@ class Search:
             _check(L.ones_init(C.byref(self._h), C.byref(cfg), C.byref(js), C.c_void_p(self._ws_ptr),
                                nbytes, C.c_void_p(self.stream.cuda_stream)))
 
+    def _call(self, function, *args):
+        """A call of the library with the search's device current; it mostly is already."""
+        if self._torch.cuda.current_device() == self._index:
+            _check(function(self._h, *args))
+        else:
+            with self._torch.cuda.device(self.device):
+                _check(function(self._h, *args))
+
     def set_jobs(self, jobs):
         js, keep = make_jobs(jobs)
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_set_jobs(self._h, C.byref(js)))
+        self._call(load().ones_set_jobs, C.byref(js))
 
     def generation(self, n: int = 1):
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_generation(self._h, int(n)))
+        self._call(load().ones_generation, int(n))
 
     def generation_static(self, n: int = 1):
         """ones_generation_static: the same generations with the selection's scratch in the library's
         static device array (for callers that cannot allocate)."""
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_generation_static(self._h, int(n)))
+        self._call(load().ones_generation_static, int(n))
 
     def set_wait_limit(self, polls: int):
         _check(load().ones_set_wait_limit(self._h, int(polls)))
 
     def set_progress(self, alpha=None, beta=None, processed=None):
         """ones_set_progress: one entry per slot each; all None switches the sampling off."""
-        with self._torch.cuda.device(self.device):
-            if alpha is None and beta is None and processed is None:
-                _check(load().ones_set_progress(self._h, None, None, None))
-                return
-            arrs = [np.ascontiguousarray(x, np.float64) for x in (alpha, beta, processed)]
-            if any(a.shape != (self.n_slots,) for a in arrs):
-                raise ValueError("alpha, beta, processed: one entry per slot")
-            _check(load().ones_set_progress(self._h, *[a.ctypes.data for a in arrs]))
+        if alpha is None and beta is None and processed is None:
+            self._call(load().ones_set_progress, None, None, None)
+            return
+        arrs = [np.ascontiguousarray(x, np.float64) for x in (alpha, beta, processed)]
+        if any(a.shape != (self.n_slots,) for a in arrs):
+            raise ValueError("alpha, beta, processed: one entry per slot")
+        self._call(load().ones_set_progress, *map(_address, arrs))
 
     def set_new_jobs_first(self, on=True):
         _check(load().ones_set_new_jobs_first(self._h, int(bool(on))))
@@ -205,38 +219,33 @@ class Search:
         t = np.ascontiguousarray(t_processed, np.float64)
         if len(t) != self.n_slots:
             raise ValueError("t_processed: one entry per slot")
-        _check(load().ones_set_processed_time(self._h, t.ctypes.data))
+        _check(load().ones_set_processed_time(self._h, _address(t)))
 
     def export_remaining(self):
         y = np.zeros(max(self.n_slots, 1), np.float64)
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_export_remaining(self._h, y.ctypes.data))
+        self._call(load().ones_export_remaining, _address(y))
         return y[:self.n_slots]
 
     def best(self):
         b = np.zeros(self.n_slots, np.int32)
         g = np.zeros(self.n_slots, np.int32)
         f = C.c_double(0.0)
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_best(self._h, b.ctypes.data, g.ctypes.data, C.byref(f)))
+        self._call(load().ones_best, _address(b), _address(g), C.byref(f))
         return b, g, f.value
 
     def placement(self):
         """(slot of every GPU, -1 = idle; batch of every GPU's worker): Eq. 1 for the winner."""
         slot = np.zeros(max(self.n_gpus, 1), np.int32)
         batch = np.zeros(max(self.n_gpus, 1), np.int32)
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_placement(self._h, slot.ctypes.data, batch.ctypes.data))
+        self._call(load().ones_placement, _address(slot), _address(batch))
         return slot[:self.n_gpus], batch[:self.n_gpus]
 
     def export(self, genes=True):
-        g = np.zeros((self.population, self.jp), np.int32) if genes else None
-        fit = np.zeros(self.population, np.float64)
-        sel = np.zeros(self.population // 4, np.int32)
+        g = np.empty((self.population, self.jp), np.int32) if genes else None       # the call writes all of it
+        fit = np.empty(self.population, np.float64)
+        sel = np.empty(self.population // 4, np.int32)
         t = C.c_int64(0)
-        with self._torch.cuda.device(self.device):
-            _check(load().ones_export(self._h, g.ctypes.data if genes else None, fit.ctypes.data,
-                                      sel.ctypes.data, C.byref(t)))
+        self._call(load().ones_export, _address(g) if genes else None, _address(fit), _address(sel), C.byref(t))
         return g, fit, sel, t.value
 
     def profile_enable(self, every: int = 1):

@@ -1657,3 +1657,36 @@ def test_repair_walks_near_its_start(ones, ref, n_slots, share):
         gpu.generation(n); cpu.generation(n)
         assert_same_state(gpu, cpu, f"generation {gpu.export(genes=False)[3]}")
     gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(1, 0, 8), (64, 64, 64), (130, 90, 260), (2047, 70000, 64), (65, 2000, 1028)])
+def test_calls_that_wait_in_quick_succession(ones, ref, n_slots, n_gpus, pop):
+    """Every call that goes through the pinned buffer, one after the other with new values each time: one workgroup or many to a
+    signal, no GPU to place, a state that is staged whole (up to 256 KB: the first three) and one that is copied, a wait longer
+    than the poll."""
+    rng = np.random.default_rng(n_slots)
+    jobs = random_jobs(rng, n_slots)
+    cl = cluster(n_gpus, n_slots, pop, seed=n_slots)
+    say(f"[parity] waiting calls: slots={n_slots} G={n_gpus} P={pop}")
+    gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+    for step in range(6):
+        jobs.remaining = jobs.remaining * rng.uniform(0.5, 1.0, n_slots)
+        times = np.round(rng.uniform(0, 9, n_slots))
+        progress = W.progress(n_slots, seed=step)
+        for s in (gpu, cpu):
+            s.set_jobs(jobs)
+            s.set_new_jobs_first(step % 2 == 1)
+            s.set_processed_time(times)
+            if step % 3 != 2: s.set_progress(*progress)
+            else: s.set_progress()
+            s.generation(2)
+        gb, gg, gf = gpu.best()
+        cb, cg, cf = cpu.best()
+        assert gb.tolist() == cb.tolist() and gg.tolist() == cg.tolist() and gf == cf, step
+        assert all(np.array_equal(x, y) for x, y in zip(gpu.placement(), cpu.placement())), step
+        assert_same_state(gpu, cpu, f"step {step}")
+    gpu.set_progress(); cpu.set_progress()
+    gpu.generation(400)                                # longer than the poll on most of these
+    cpu.generation(400)
+    assert gpu.best()[2] == cpu.best()[2]
+    gpu.close(); cpu.close()
