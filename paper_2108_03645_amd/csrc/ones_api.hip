@@ -227,7 +227,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
 // Host transfers go through one pinned staging buffer, which the kernels read and write themselves: laid out like the arrays
 // that travel together, which lie next to each other in the workspace (every size below is a multiple of the
 // 256-byte alignment except the last of a group).  Behind them HostWords.
-struct HostWords { uint32_t flag, pad, err[2]; };              // see HostSignal; error words that come with a placement
+struct HostWords { uint32_t flag, winner, err[2]; double fit; };      // see HostSignal and WinnerOut; behind them its arrays
 // A state of up to so much is exported that way too (a larger one is copied).
 constexpr size_t kStagedExport = 256u << 10;
 size_t export_bytes(const Layout &L, uint32_t P, uint32_t Jp) { return L.unpacked + static_cast<size_t>(P) * Jp * 4 - L.export_err; }
@@ -317,6 +317,7 @@ struct ones_ctx {
   char *stage_dev;            // the same buffer as the device addresses it
   size_t words_at;            // HostWords in it
   uint32_t signals, tickets;  // HostSignal: the value of the last one, the tickets of all
+  uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0
   Layout L;
   int cur;                    // the survivors of the current generation are in parent_row[cur ^ 1]
   int occ;                    // which bitmap holds the survivors' rows, unless
@@ -374,6 +375,12 @@ HostSignal next_signal(ones_ctx *c, uint32_t blocks) {
   c->signals += 1;
   if (blocks > 1) c->tickets += blocks;
   return HostSignal{c->at<uint32_t>(c->L.fsync) + 8, &c->host_words_dev()->flag, c->tickets, c->signals};
+}
+// For a launch that runs a whole call.
+WinnerOut next_winner(ones_ctx *c, uint32_t blocks) {
+  HostWords *words = c->host_words_dev();
+  int32_t *batch = reinterpret_cast<int32_t *>(words + 1);
+  return WinnerOut{batch, batch + c->Jp, &words->fit, &words->winner, words->err, c->Jn, next_signal(c, blocks)};
 }
 // Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
 constexpr std::chrono::milliseconds kPollTime(4);
@@ -555,6 +562,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   c->info_stored = c->info_now;     // every genome of the new pool was made under the current table
   c->table_changed = false;
   c->no_schedule = false;
+  c->winner = 0;
   c->profile_tick += 1;
   return ONES_OK;
 }
@@ -603,9 +611,9 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   {
     void *pinned = nullptr;
     c->words_at = stage_bytes(L, c->P, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
-    HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords), hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords) + 8 * static_cast<size_t>(Jp), hipHostMallocDefault));
     c->stage = static_cast<char *>(pinned);
-    c->host_words()->flag = c->signals = c->tickets = 0;
+    c->host_words()->flag = c->host_words()->winner = c->signals = c->tickets = c->winner = 0;
     void *mapped = nullptr;
     HIP_TRY(hipHostGetDevicePointer(&mapped, pinned, 0));
     c->stage_dev = static_cast<char *>(mapped);
@@ -688,6 +696,7 @@ static int set_jobs_impl(ones_ctx *c, const ones_jobs *jobs) {
   c->ids = h.id;
   c->table_changed = true;
   c->no_schedule = true;
+  c->winner = 0;
   c->settled = std::max(c->settled, c->t + mixed_by(c->P, c->Jp, changed, c->Jn));
   c->drawn_from = c->drawn_to = 0;   // the draws made ahead built their term tables from the old job table
   return ONES_OK;
@@ -790,8 +799,10 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
 // What run_fused and run_resident return when the runtime refuses the launch: nothing has run and no state has changed,
 // and the kernels of one generation, which any GPU runs, take the call.
 constexpr int kLaunchRefused = 1;
-static int refused(bool &whole_calls) {
+static int refused(ones_ctx *c, bool &whole_calls, uint32_t tickets) {
   whole_calls = false;              // not asked for again by this context
+  c->signals -= 1;                  // nor will the signal come
+  c->tickets = tickets;
   (void)hipGetLastError();
   return kLaunchRefused;
 }
@@ -814,10 +825,13 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   fa.n_generations = n;
   fa.first_changed = c->table_changed ? 1u : 0u;
   fa.spin_limit = c->spin_limit;
+  const uint32_t tickets = c->tickets;
   int rc;
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, true))) return rc;
-  if (launch_fused(fa, c->stream) != hipSuccess) return refused(c->fused);
+  fa.winner = next_winner(c, 1);
+  if (launch_fused(fa, c->stream) != hipSuccess) return refused(c, c->fused, tickets);
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
+  c->winner = c->signals;
   c->fused_generations += n;
   c->fused_changes += c->sampling ? n : fa.first_changed;
   if (c->sampling) {
@@ -862,6 +876,8 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.spin_limit = c->spin_limit;
   ra.paired = plan.paired; ra.unit_waves = plan.unit_waves; ra.child_items = plan.child_items;
   ra.segment = plan.segment; ra.list = plan.list; ra.table_lds = plan.table_lds;
+  const uint32_t tickets = c->tickets;
+  ra.winner = next_winner(c, plan.groups);
   hipError_t launched;
   switch (words_of(static_cast<int>(c->R))) {
     case 1: launched = launch_resident_words1(ra, plan, c->stream); break;
@@ -869,7 +885,8 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
     case 3: launched = launch_resident_words3(ra, plan, c->stream); break;
     default: launched = launch_resident_words4(ra, plan, c->stream); break;
   }
-  if (launched != hipSuccess) return refused(c->resident);
+  if (launched != hipSuccess) return refused(c, c->resident, tickets);
+  c->winner = c->signals;
   c->fused_generations += n;
   if (c->sampling) c->y_cur = static_cast<int>((c->t + n) % kDrawRing);
   c->rows_assigned = true;
@@ -981,6 +998,24 @@ static const uint32_t *survivor_rows(const ones_ctx *c) { return c->at<uint32_t>
 static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double *fitness_out) {
   if (!c) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
+  auto hand_out = [&](const volatile void *batch, const volatile void *gpus, const volatile void *fit) {
+    if (batch_out && c->Jn) memcpy(batch_out, const_cast<const void *>(batch), c->Jn * 4);
+    if (gpus_out && c->Jn) memcpy(gpus_out, const_cast<const void *>(gpus), c->Jn * 4);
+    if (fitness_out) memcpy(fitness_out, const_cast<const void *>(fit), 8);
+    return ONES_OK;
+  };
+  if (c->winner != 0) {
+    // the launch that ran the last call leaves the winner in the pinned buffer
+    if (int rc = wait_signal(c)) return rc;
+    volatile HostWords *words = c->host_words();
+    if (words->winner == c->winner) {
+      if (words->err[0]) return wait_gave_up(c);
+      if (words->err[1]) return row_fault(c);
+      const volatile int32_t *batch = reinterpret_cast<const volatile int32_t *>(words + 1);
+      return hand_out(batch, batch + c->Jp, &words->fit);
+    }
+    c->winner = 0;                  // it has given up
+  }
   // The kernel writes the winner and the two error words straight into the pinned host buffer
   // (a few hundred bytes to a few kilobytes), laid out as the best_* block of the workspace:
   // one launch and one wait, no copy.
@@ -998,10 +1033,7 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
   memcpy(words, staged(L.best_err), 8);
   if (words[0]) return wait_gave_up(c);
   if (words[1]) return row_fault(c);
-  if (batch_out && c->Jn) memcpy(batch_out, staged(L.best_batch), c->Jn * 4);
-  if (gpus_out && c->Jn) memcpy(gpus_out, staged(L.best_gpus), c->Jn * 4);
-  if (fitness_out) memcpy(fitness_out, staged(L.best_fit), 8);
-  return ONES_OK;
+  return hand_out(staged(L.best_batch), staged(L.best_gpus), staged(L.best_fit));
 }
 
 static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_gpu) {

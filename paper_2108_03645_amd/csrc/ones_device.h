@@ -140,6 +140,24 @@ struct Progress {
 constexpr int kDrawRing = 32;
 constexpr int kDrawAhead = 8;       // generations drawn at a time for the kernels of one generation
 
+// How a kernel tells the host that it, and so everything before it on the stream, is done: its last workgroup writes `value` to a
+// word of pinned memory that the host polls.  (A kernel and a wait of this kind take 5.9 us alone, with hipStreamSynchronize 9.3; a
+// copy from or to pinned memory is another 5 to 6, so these kernels read and write it themselves.)
+struct HostSignal {
+  uint32_t *tickets;          // of workgroups that are done, over all signals of more than one workgroup
+  uint32_t *flag;
+  uint32_t  target, value;    // the last workgroup's ticket
+};
+// What a launch that runs a whole call leaves in pinned memory: the winner, as ones_best hands it out, and the error words.
+struct WinnerOut {
+  int32_t  *batch, *gpus;     // [n_slots]
+  double   *fit;
+  uint32_t *of;               // the value of the launch's signal
+  uint32_t *err;              // [2]
+  uint32_t  n_slots;
+  HostSignal done;
+};
+
 // Genomes live in physical rows; a candidate keeps its row for as long as it survives, so a
 // survivor is never copied.  The pool of P slots uses P + K rows.  While a generation is computed
 // the K survivors hold theirs (parent_row); 3K rows are for the new children and mutants, by slot
@@ -209,6 +227,7 @@ struct FusedArgs {
   uint32_t spin_limit;      // polls before a wait gives up (0: gives up at once; for tests of that path)
   uint32_t table_lds;       // set by the launcher: bytes of LDS the staged job table takes
   uint32_t work_groups;     // set by the launcher: workgroups that compute candidates (the grid's first ones)
+  WinnerOut winner;         // its signal is given by one workgroup
 };
 // Workgroups to launch for a pool of P (the launch must be co-resident: cooperative).
 uint32_t fused_workgroups(uint32_t P, bool sampled);
@@ -244,6 +263,7 @@ struct ResidentArgs {
   uint32_t n_generations;   // > 1; under probability sampling at most kDrawRing
   uint32_t first_changed, spin_limit;
   uint32_t paired, unit_waves, child_items, segment, list, table_lds;    // from the plan
+  WinnerOut winner;         // its signal is given by all workgroups
 };
 // paired: a wave's item is a pair or a mutant, not a child.  unit_waves: waves of a workgroup that start with an item each;
 // child_items: items of a workgroup that are no survivors, segment: children they make, list: children that beat the K-th
@@ -280,15 +300,6 @@ __device__ __forceinline__ double term_of(double abl, double cc, double d, doubl
 struct RawJobs {              // uploaded by the host after validation, [Jp] each
   const uint32_t *rawinfo;    // bits 0-4 lo, 5-9 hi, 10-14 mu, 15 active, 16 arrived with this table, 17 changed hands
   const double   *a, *c, *d, *Y;
-};
-
-// How a kernel tells the host that it, and so everything before it on the stream, is done: its last workgroup writes `value` to a
-// word of pinned memory that the host polls.  (A kernel and a wait of this kind take 5.9 us alone, with hipStreamSynchronize 9.3; a
-// copy from or to pinned memory is another 5 to 6, so these kernels read and write it themselves.)
-struct HostSignal {
-  uint32_t *tickets;          // of workgroups that are done, over all signals of more than one workgroup
-  uint32_t *flag;
-  uint32_t  target, value;    // the last workgroup's ticket
 };
 
 // launchers (each returns the hipGetLastError of its launch)

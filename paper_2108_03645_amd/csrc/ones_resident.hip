@@ -314,7 +314,7 @@ __device__ __forceinline__ void list_free_rows(const Ranking &rk, const Deal &de
       if (own != ~0u) rk.rows[own] = static_cast<uint16_t>(row);
     } else if (at < P) {
       if (changed) rk.spare[at - 3 * K] = static_cast<uint16_t>(row);
-      else if (deal.me == 0) spare[at - 3 * K] = row;
+      else if (deal.me == 0) shared_store(spare + (at - 3 * K), row);
     }
     free_bits &= free_bits - 1;
     ++at;
@@ -342,7 +342,7 @@ __device__ __forceinline__ void settle(const Ranking &rk, const Deal &deal, uint
     was[k] = rk.srow[e];
     mine[k] = changed ? static_cast<uint32_t>(rk.spare[e]) : was[k];
     if (slot < K) atomicOr(&rk.bits[slot / 32], 1u << (slot % 32));
-    if (sel) sel[e] = static_cast<int32_t>(slot);
+    if (sel) shared_store(sel + e, static_cast<int32_t>(slot));
   }
   __syncthreads();
   uint64_t children[kResElites], gone[kResElites];
@@ -376,7 +376,7 @@ __device__ __forceinline__ void settle(const Ranking &rk, const Deal &deal, uint
     if (e >= K) continue;
     const uint32_t own = slot >= K ? deal.own(slot) : ~0u;
     if (own != ~0u) rk.rows[own] = rk.drow[nth[k]];
-    if (changed && deal.me == 0) spare[e] = was[k];
+    if (changed && deal.me == 0) shared_store(spare + e, was[k]);
   }
   __syncthreads();
 }
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
     // unless every score is new, the scores, which the generation that made them did not store with the rows
     if (last && deal.me == 0)
       for (uint32_t e = tid; e < K; e += kResThreads) {
-        a.row_of[e] = rk.srow[e];
+        shared_store(a.row_of + e, static_cast<uint32_t>(rk.srow[e]));
         if (!all_new) shared_store(reinterpret_cast<uint64_t *>(a.fit_row) + rk.srow[e], rk.ckey[e]);
       }
 
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
     bool crowded = !all_new && M > ra.list;          // so many children that the whole pool is ranked
     if (!all_new && M == 0) {
       // no child beats the K-th survivor: same survivors, same order, same rows
-      if (last && deal.me == 0) for (uint32_t e = tid; e < K; e += kResThreads) ra.sel[e] = static_cast<int32_t>(e);
+      if (last && deal.me == 0) for (uint32_t e = tid; e < K; e += kResThreads) shared_store(ra.sel + e, static_cast<int32_t>(e));
     } else if (!all_new && !crowded) {
       const uint32_t id = opaque(tid);
       __syncthreads();
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
           rk.ckey[place[k]] = key[k];
           rk.srow[place[k]] = static_cast<uint16_t>(about[k] >> 16);
           if (own[k] != ~0u) rk.rows[own[k]] = static_cast<uint16_t>(next_row[k]);
-          if (last && deal.me == 0) ra.sel[place[k]] = static_cast<int32_t>(about[k] & 0xFFFFu);
+          if (last && deal.me == 0) shared_store(ra.sel + place[k], static_cast<int32_t>(about[k] & 0xFFFFu));
         }
 #pragma unroll
         for (int k = 0; k < kResElites; ++k) {
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
           if (elite_rank[k] >= K) continue;
           rk.ckey[elite_rank[k]] = elite_key[k];
           rk.srow[elite_rank[k]] = static_cast<uint16_t>(elite_row[k]);
-          if (last && deal.me == 0) ra.sel[elite_rank[k]] = static_cast<int32_t>(e);
+          if (last && deal.me == 0) shared_store(ra.sel + elite_rank[k], static_cast<int32_t>(e));
         }
         __syncthreads();
       }
@@ -896,8 +896,8 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
     }
     if (last) {
       // the state the next call (of either kind) starts from
-      if (deal.me == 0) for (uint32_t e = tid; e < K; e += kResThreads) ra.parent_rows[e] = rk.srow[e];
-      each_own_row([&](uint32_t slot, uint16_t row) { a.row_of[slot] = row; });
+      if (deal.me == 0) for (uint32_t e = tid; e < K; e += kResThreads) shared_store(ra.parent_rows + e, static_cast<uint32_t>(rk.srow[e]));
+      each_own_row([&](uint32_t slot, uint16_t row) { shared_store(a.row_of + slot, static_cast<uint32_t>(row)); });
       // and, if that is one of the launched kernels, the splitters of its buckets, as a selection of theirs would have left them
       // (without them its first one ranks the pool in full: a selection of 24 us in place of 6.4, 16384 candidates)
       // (their addresses are read from the argument block here, see kernel_args, not carried through the generations)
@@ -905,11 +905,24 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
       if (!kSampled && deal.me + 1 == deal.groups && late->n_buckets != 0) {
         const uint32_t nb = late->n_buckets;
         for (uint32_t c = tid; c < static_cast<uint32_t>(kBucketCounters); c += kResThreads) {
-          late->count[0][c] = late->count[1][c] = 0;
-          if (c < static_cast<uint32_t>(kMaxBuckets)) late->split[c] = c + 1 < nb ? rk.ckey[bucket_bound(c + 1, K, nb)] : kNoSplitter;
-          if (c == 0) *late->thresh = rk.ckey[K - 1];
+          shared_store(late->count[0] + c, 0u);
+          shared_store(late->count[1] + c, 0u);
+          if (c < static_cast<uint32_t>(kMaxBuckets)) shared_store(late->split + c, c + 1 < nb ? rk.ckey[bucket_bound(c + 1, K, nb)] : static_cast<uint64_t>(kNoSplitter));
+          if (c == 0) shared_store(late->thresh, rk.ckey[K - 1]);
         }
       }
+      if (deal.me == 0) {
+        const uint32_t row = rk.srow[0];
+        publish_winner<Q>(late->winner, a.genes, row, a.tab.info, kSampled ? shared_load(reinterpret_cast<const uint64_t *>(a.fit_row) + row) : rk.ckey[0]);
+      }
+      // The last workgroup tells the host.  Nothing of the workspace is written any more then: what the launch stores there goes
+      // to the point of coherence, and has arrived before the ticket is taken.
+      phase_fence();
+      __builtin_amdgcn_s_waitcnt(0);
+      phase_fence();
+      __syncthreads();
+      if (tid == 0 && (deal.groups == 1 || __hip_atomic_fetch_add(late->winner.done.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == late->winner.done.target))
+        signal_call_done(late->winner, late->sync + 1);
       return;
     }
   }
