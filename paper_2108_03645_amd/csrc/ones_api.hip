@@ -78,7 +78,7 @@ struct ScratchLayout {
 };
 
 struct Layout {
-  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, base, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
+  size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, lift, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
   size_t export_err, export_sel, export_fit, unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
   ScratchLayout S;
 };
@@ -203,7 +203,7 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   // the selection's scratch: splitters, counters, bucket storage, spill list
   L.S = make_scratch_layout(P);
   L.scratch = take(L.S.total);
-  L.start = take(row_bytes); L.most = take(row_bytes); L.draws = take(row_bytes); L.base = take(row_bytes);
+  L.start = take(row_bytes); L.most = take(row_bytes); L.draws = take(row_bytes); L.lift = take(row_bytes);
   L.info[0] = take(Jp * 4); L.info[1] = take(Jp * 4);
   L.abl = take(Jp * 8); L.cc = take(Jp * 8); L.d = take(Jp * 8);
   // remaining work and the term table built from it, a ring of pairs at equal distances:
@@ -359,7 +359,7 @@ struct ones_ctx {
 
   template <typename T> T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
   JobTable table(int which) const {     // with the remaining work and term table number `which`
-    return JobTable{at<uint32_t>(L.start), at<uint32_t>(L.most), at<uint32_t>(L.draws), at<uint32_t>(L.base),
+    return JobTable{at<uint32_t>(L.start), at<uint32_t>(L.most), at<uint32_t>(L.draws), at<uint32_t>(L.lift),
                     at<uint32_t>(L.info[info_now]), at<uint32_t>(L.info[info_stored]), at<double>(L.abl), at<double>(L.cc), at<double>(L.d), at<double>(L.Y[which]),
                     at<double>(L.terms[which]), term_E};
   }

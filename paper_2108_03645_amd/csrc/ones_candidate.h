@@ -65,11 +65,16 @@ __device__ __forceinline__ uint2 philox_prefix(uint32_t block, uint32_t key1) {
 
 struct WordSource {                                  // what the blocks of one candidate share (wave-uniform)
   uint32_t u0, u2, u3, k0, k1;
-  __device__ __forceinline__ WordSource(const EvolveArgs &a, uint32_t t, uint32_t p) {
+  // counted: the round keys are counted up by the scalar unit for every block.  Otherwise they are kept, and, where there are no
+  // registers for them, reloaded from lanes of a vector register, which takes a vector instruction each: better only for a single
+  // block (a generation of the stress workload, eight blocks, 73.2 -> 71.4 us; a call of 50 of 16384 candidates on two words 866 -> 842; of
+  // 20 of 8192 on one word 148 -> 150).
+  __device__ __forceinline__ WordSource(const EvolveArgs &a, uint32_t t, uint32_t p, bool counted = false) {
     const uint64_t pb = static_cast<uint64_t>(t) * kPhiloxB;
     const uint64_t pa = static_cast<uint64_t>(static_cast<uint32_t>(pb >> 32) ^ p ^ a.key0) * kPhiloxA;
     k0 = a.key0 + 0x9E3779B9u;
     k1 = a.key1 + 0xBB67AE85u;
+    if (counted) asm volatile("" : "+s"(k0), "+s"(k1));
     u0 = static_cast<uint32_t>(pb) ^ k0;
     u2 = static_cast<uint32_t>(pa >> 32) ^ k1;
     u3 = static_cast<uint32_t>(pa);
@@ -190,9 +195,9 @@ struct GpuSum {
 struct Smem {
   // a byte per gene, four rows to a word, word q*64 + lane (like the genomes): codes of the GPU count
   // a waiting job resumes with and of the one at its limit R_j, number of outcomes of a redraw
-  // (0: empty slot), code of the outcome k less k (biased); after a table change also the distance
+  // (0: empty slot), last outcome that gives the former; after a table change also the distance
   // from a stored code to the new one (biased; 0: the slot changed hands) and the arrived jobs (0x7F)
-  uint32_t *start, *most, *draws, *base, *shift, *fresh;
+  uint32_t *start, *most, *draws, *lift, *shift, *fresh;
   uint32_t *bl;      // log2 of the local batch (when the term table does not fit)
   uint2    *prefix;  // [Q][64] Philox prefixes
   double   *abl, *cc, *d, *Y;   // [Q*256] model parameters (when the term table does not fit)
@@ -267,8 +272,8 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.start = reinterpret_cast<uint32_t *>(s.prefix + kWords);
   s.most = s.start + kWords;
   s.draws = s.most + kWords;
-  s.base = s.draws + kWords;
-  s.shift = s.base + kWords;
+  s.lift = s.draws + kWords;
+  s.shift = s.lift + kWords;
   s.fresh = s.shift + kWords;
   s.bl = s.fresh + kWords;
   s.start_at = reinterpret_cast<uint8_t *>(s.bl + kWords);
@@ -334,7 +339,7 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
   load_terms(tid / kLanes);
   const bool by_time = changed && a.new_first && a.time_rank != nullptr;       // the buckets are off: no splitters
   for (uint32_t w = tid; w < kWords; w += threads) {
-    const uint32_t start = tab.start[w], most = tab.most[w], draws = tab.draws[w], base = tab.base[w];
+    const uint32_t start = tab.start[w], most = tab.most[w], draws = tab.draws[w], lift = tab.lift[w];
     s.prefix[w] = philox_prefix(w, a.key1);
     if (changed || E == 0) {
       uint32_t shift = 0, fresh = 0, bl = 0;
@@ -374,7 +379,7 @@ __device__ __forceinline__ void stage_table(const EvolveArgs &a, const Smem &s, 
       }
     }
     s.draws[w] = draws;
-    s.base[w] = base;
+    s.lift[w] = lift;
   }
   store_splits(tid);
   store_terms(tid / kLanes);
@@ -525,9 +530,19 @@ __device__ __forceinline__ uint32_t into_window(uint32_t biased, uint32_t start,
 }
 
 // Redraw of four genes from k in [0, n) each: 0 = the job is pre-empted, else the batch 2^(lo + k - 1)
-// on the GPUs it takes, with the free lift to the per-GPU max batch.
+// on the GPUs it takes, with the free lift to the per-GPU max batch: the code start while k is at most lift, and one more for
+// each outcome beyond (the last one is the batch limit, so nothing has to be cut off above).
 __device__ __forceinline__ uint32_t codes_of_draws(const Smem &s, int w, uint32_t k) {
-  return into_window(s.base[w] + k, s.start[w], s.most[w]) & nonzero_bytes(k);
+  const uint32_t beyond = (k | kTops) - s.lift[w];               // top bits: not below lift
+  return (s.start[w] + (beyond & spread_tops(beyond))) & nonzero_bytes(k);
+}
+
+// k of a mutant's four genes, drawn from the lower halves of their words.  (The products' third bytes: k is below 32.)
+__device__ __forceinline__ uint32_t outcomes_drawn(const Words &w, uint32_t outcomes) {
+  uint32_t product[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) product[u] = (w.w[u] & 0xFFFFu) * ((outcomes >> (8 * u)) & 0xFFu);
+  return __builtin_amdgcn_perm(product[1], product[0], 0x0C0C0602u) | __builtin_amdgcn_perm(product[3], product[2], 0x06020C0Cu);
 }
 
 // Genes stored under another job table: the batch they stood for, pulled inside the new window and
@@ -873,11 +888,31 @@ __device__ __forceinline__ void repair(uint32_t (&c)[Q], const Smem &s, uint32_t
 // Eq. 3: sum over running jobs of T_j c_j = Y_j t_j / (local batch), t = a b + c log2(g) + d.
 // Summation order: a lane's rows top to bottom, then a xor butterfly 32,16,..,1 over lanes.
 // kRows: rows that can hold job slots (the terms of rows beyond the slots are 0).
+// Of tables of few codes (kDirect<Q> at most) a look-up's address is a byte permute of the word of codes: a code's tile of the table
+// takes 2^(8 + kTileShift) bytes, so its address is the code, shifted in its byte, above the low byte of the lane's.  Cut out of
+// the word, scaled and added it takes two instructions and a quarter more.
+template <int Q> constexpr bool kTiled = Q == 1 || Q == 2 || Q == 4 || Q == 8;
+template <int Q> constexpr int kTileShift = Q == 1 ? 3 : Q == 2 ? 4 : Q == 4 ? 5 : 6;
+template <int Q> constexpr uint32_t kDirect = kTiled<Q> ? 256u >> kTileShift<Q> : 0u;
 template <int Q, int kRows = 4 * Q>
 __device__ __forceinline__ double score(const uint32_t (&c)[Q], const Smem &s, uint32_t E, int lane) {
+  using LdsTerms = const __attribute__((address_space(3))) double;
   double acc = 0.0;
   lane = opaque(lane);
-  if (E != 0) {
+  if (kRows > 1 && E != 0 && E <= kDirect<Q>) {
+    const uint32_t column = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsTerms *)(s.terms + lane)));
+    const uint32_t above = (column >> 8) * kOnes;                // below 2^kTileShift: the table lies at the beginning of LDS
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t tiles = (c[q] << kTileShift<Q>) + above;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t at = __builtin_amdgcn_perm(tiles, column, 0x0C0C0000u | static_cast<uint32_t>(4 + k) << 8);
+        acc = acc + ((LdsTerms *)static_cast<uintptr_t>(at))[(4 * q + k) * kLanes];
+      }
+      if (q % 2 == 1) { pin(acc); phase_fence(); }
+    }
+  } else if (E != 0) {
     // the job's term only depends on the code of its GPU count, and the table holds exactly the
     // value the formula below produces
     const double *column = s.terms + lane;

@@ -52,8 +52,8 @@ __host__ __device__ inline uint32_t batch_of_code(uint32_t code, uint32_t bl_exp
 struct JobTable {
   // laid out like a genome row, a byte per slot: code a waiting job resumes with and code at the
   // batch-size limit R_j (0 for an empty slot), number of outcomes of a redraw (hi - lo + 2; 0 for an
-  // empty slot), lo - mu + 31
-  uint32_t *start, *most, *draws, *base;
+  // empty slot), outcomes 1 .. lift of which give the former
+  uint32_t *start, *most, *draws, *lift;
   uint32_t *info;     // bits 0-4 lo, 5-10 (hi-lo+2), 11-15 mu, 16-20 bl_exp, 21 active, 22 arrived with this table
   // info of the table the genomes are stored under: this one, or, between ones_set_jobs and the next
   // generation, an earlier one, where bit 23 marks the slots that have changed hands since (they wait)

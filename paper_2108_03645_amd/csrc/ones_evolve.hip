@@ -60,7 +60,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
     const uint32_t p = first + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(taken));
     if (p >= last) break;
     const uint32_t r = __builtin_amdgcn_readfirstlane(candidate_draw(a, a.t, p).r);
-    const WordSource words(a, a.t, p);
+    const WordSource words(a, a.t, p, Q > 1);
     uint32_t c[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
         phase_fence();
         crossover_over_gpus<Q, kSameTable>(a, a.t, s, coins, p0, lane, c, other);
       } else {
-        const WordSource words(a, a.t, p0);
+        const WordSource words(a, a.t, p0, Q > 1);
         uint32_t swap[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -215,14 +215,11 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
       if (!kSameTable) to_new_table<Q>(s, lane, c);
       if (idx < 2 * n) {
         // uniform mutation: each job redrawn with rate theta (k = 0 pre-empts it)
-        const WordSource words(a, a.t, slot_at(ra, n, i));
+        const WordSource words(a, a.t, slot_at(ra, n, i), Q > 1);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
           const Words w = words.block(s.prefix, q, lane);
-          const uint32_t outcomes = s.draws[q * kLanes + lane];
-          uint32_t k = 0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) k |= (((w.w[u] & 0xFFFFu) * ((outcomes >> (8 * u)) & 0xFFu)) >> 16) << (8 * u);
+          const uint32_t k = outcomes_drawn(w, s.draws[q * kLanes + lane]);
           c[q] = pick(words_below(w, a.T_mut), codes_of_draws(s, q * kLanes + lane, k), c[q]);
           if (q % 2 == 1) { pin(c[q]); phase_fence(); }
         }

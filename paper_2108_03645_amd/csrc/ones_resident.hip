@@ -128,8 +128,8 @@ __device__ __forceinline__ Smem carve_table(unsigned char *at, uint32_t E, bool 
   s.start = reinterpret_cast<uint32_t *>(s.prefix + kWords);
   s.most = s.start + kWords;
   s.draws = s.most + kWords;
-  s.base = s.draws + kWords;
-  s.shift = s.base + kWords;
+  s.lift = s.draws + kWords;
+  s.shift = s.lift + kWords;
   s.fresh = s.shift + kWords;
   s.bl = s.fresh + kWords;
   s.start_at = reinterpret_cast<uint8_t *>(s.bl + kWords);
@@ -168,7 +168,7 @@ __device__ __forceinline__ void draw_genes(const EvolveArgs &a, const Smem &s, u
   if (lane == 0) draws[0] = d.ra | d.rb << 16;
   if (lane < 2) draws[1 + lane] = d.r / R | d.r % R << 16;       // without a pair only the latter counts
   if (child && kOverGpus) return;
-  const WordSource source(a, t, p0);
+  const WordSource source(a, t, p0, Q > 1);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const Words w = source.block(s.prefix, q, lane);
@@ -176,10 +176,7 @@ __device__ __forceinline__ void draw_genes(const EvolveArgs &a, const Smem &s, u
     if (child) {
       out = words_below(w, a.T_x);
     } else {
-      const uint32_t outcomes = s.draws[q * kLanes + lane], redrawn = words_below(w, a.T_mut);
-      uint32_t k = 0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) k |= (((w.w[v] & 0xFFFFu) * ((outcomes >> (8 * v)) & 0xFFu)) >> 16) << (8 * v);
+      const uint32_t k = outcomes_drawn(w, s.draws[q * kLanes + lane]), redrawn = words_below(w, a.T_mut);
       out = redrawn & (codes_of_draws(s, q * kLanes + lane, k) | kTops);
     }
     words[q * kLanes + lane] = out;

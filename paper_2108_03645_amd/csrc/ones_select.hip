@@ -961,7 +961,7 @@ __device__ __forceinline__ void signal_host(const HostSignal &done) {
 }
 
 // What the kernels need of one job slot, derived from the validated raw table.
-struct SlotValues { uint32_t start, most, draws, base, info; double abl, cc, d, Y; };
+struct SlotValues { uint32_t start, most, draws, lift, info; double abl, cc, d, Y; };
 
 __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j) {
   const uint32_t w = raw.rawinfo[j];
@@ -974,7 +974,7 @@ __device__ __forceinline__ SlotValues derive_slot(const RawJobs &raw, uint32_t j
   v.start = static_cast<uint32_t>(max(0, gstart - mu) + 1);
   v.most = static_cast<uint32_t>(max(0, hi - mu) + 1);
   v.draws = static_cast<uint32_t>(hi - lo + 2);
-  v.base = static_cast<uint32_t>(lo - mu + 31);     // code of the batch 2^(lo + k - 1): lo + k - mu, kept above 0
+  v.lift = v.start + static_cast<uint32_t>(mu - lo);     // the batch 2^(lo + k - 1) takes the code lo + k - mu, or, lifted, start (1 .. 31)
   v.info = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo + 2) << 5) | (static_cast<uint32_t>(mu) << 11) |
            (static_cast<uint32_t>(bl) << 16) | (1u << 21) | (((w >> 16) & 1u) << 22);
   v.abl = a * static_cast<double>(1u << bl);
@@ -998,8 +998,8 @@ __global__ __launch_bounds__(kLanes) void table_change_kernel(RawJobs raw, JobTa
   for (uint32_t e = 0; e < E; ++e) tab.terms[(row * E + e) * kLanes + lane] = term_of(v.abl, v.cc, v.d, v.Y, info_blexp(v.info), e);
   remaining[j] = raw_Y;
   uint8_t *arrays[4] = {reinterpret_cast<uint8_t *>(tab.start), reinterpret_cast<uint8_t *>(tab.most),
-                        reinterpret_cast<uint8_t *>(tab.draws), reinterpret_cast<uint8_t *>(tab.base)};
-  const uint32_t values[4] = {v.start, v.most, v.draws, v.base};
+                        reinterpret_cast<uint8_t *>(tab.draws), reinterpret_cast<uint8_t *>(tab.lift)};
+  const uint32_t values[4] = {v.start, v.most, v.draws, v.lift};
   const uint32_t at = gene_byte(j);
 #pragma unroll
   for (int k = 0; k < 4; ++k) arrays[k][at] = static_cast<uint8_t>(values[k]);

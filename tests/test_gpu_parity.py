@@ -1690,3 +1690,19 @@ def test_calls_that_wait_in_quick_succession(ones, ref, n_slots, n_gpus, pop):
     cpu.generation(400)
     assert gpu.best()[2] == cpu.best()[2]
     gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots,widest", [(250, 6), (250, 7), (250, 20), (500, 6), (500, 14), (500, 15), (1000, 6), (1000, 7),
+                                            (2000, 2), (2000, 3), (2000, 6)])
+def test_term_look_ups_at_the_largest_code_of_a_byte_address(ones, ref, n_slots, widest):
+    """The score's look-ups take their addresses by a byte permute while the largest code of the table allows it: 31 at one word a
+    gene column, 15 at two, 7 at four, 3 at eight; that code, the next one, and tables in between."""
+    rng = np.random.default_rng([n_slots, widest])
+    jobs = wide_table(rng, n_slots, widest)
+    cl = cluster(max(n_slots, n_slots << max(0, widest - 3)) % (1 << 20), n_slots, 64, seed=widest)
+    say(f"[parity] term look-ups: slots={n_slots} widest={widest} G={cl.n_gpus}")
+    gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+    for n in (1, 1, 4):
+        gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, f"{n} more generations")
+    gpu.close(); cpu.close()
