@@ -461,9 +461,16 @@ int make_draws(ones_ctx *c, uint32_t t, int least, int ahead) {
   return ONES_OK;
 }
 
+// A launch that is being recorded into a graph must not need a resident grid.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 // scratch: base of the selection's scratch block (the workspace's, or the static array);
 // splitters_valid: that block holds the current survivors' splitters and cleared counters.
-int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid, bool events) {
+// last: of its call, whose winner the last kernel may leave for the host.
+int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid, bool events, bool last) {
   EvolveArgs a;
   const ScratchLayout &S = c->L.S;
   auto sc = [&](size_t off) { return scratch + off; };
@@ -475,6 +482,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.spare = c->at<uint32_t>(c->L.spare);
   a.occupied = c->at<uint32_t>(c->L.occupied[c->occ]);          // set by the last selection, unless it assigned the rows
   a.assigned = c->rows_assigned ? 1u : 0u;
+  c->winner = 0;
   // Under probability sampling this generation is scored with its own place of the ring of
   // remaining-work arrays and term tables: a launch of an earlier generation has filled it
   // already, or the draws of this and the next generations are made now.
@@ -536,10 +544,14 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
     // the launch scored the whole pool (initial population, refresh under a new table, survivors
     // scored again under a new draw): its scores by slot are complete
     const bool all_scored = t == 0 || !same_table || a.rescore != 0;
+    const bool splitters = c->bp.nb != 0 && !sampled && same_table;
+    const uint32_t blocks = last && !splitters ? rank_pool_blocks(c->P) : 0u;
+    const WinnerSource from{a.genes, a.tab.info, c->at<uint32_t>(c->L.fsync) + 1, static_cast<uint32_t>(words_of(static_cast<int>(c->R)) * kLanes)};
     HIP_TRY(launch_select(a.fit_row, all_scored ? a.slot_score : nullptr, rp, c->P, c->K, store,
-                          c->at<int32_t>(c->L.sel), c->stream));
+                          c->at<int32_t>(c->L.sel), from, blocks ? next_winner(c, blocks) : WinnerOut{}, c->stream));
+    if (blocks) c->winner = c->signals;
     splitters_valid = false;
-    if (c->bp.nb != 0 && !sampled && same_table) {
+    if (splitters) {
       // Splitters for the bucketed generations that follow; clears both counter sets.  Under sampling
       // no bucketed generation can follow.  Nor after an initial population or a refresh under a new
       // table: the scores of such survivors say little about where their children will fall (nearly
@@ -562,7 +574,6 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   c->info_stored = c->info_now;     // every genome of the new pool was made under the current table
   c->table_changed = false;
   c->no_schedule = false;
-  c->winner = 0;
   c->profile_tick += 1;
   return ONES_OK;
 }
@@ -670,7 +681,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
   if ((rc = upload_table(c, h)) ||
-      (rc = run_generation(c, 0, c->ws + c->L.scratch, c->splitters_valid, false)))
+      (rc = run_generation(c, 0, c->ws + c->L.scratch, c->splitters_valid, false, false)))
     return rc;
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
@@ -904,12 +915,6 @@ static int poisoned_error() {
   return ONES_E_HIP;
 }
 
-// A launch that is being recorded into a graph must not need a resident grid.
-static bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
-}
-
 static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_scratch) {
   if (!c || n_generations < 0) return ONES_E_INVALID_ARG;
   if (c->t + n_generations > 0xFFFFFFFFll) return ONES_E_INVALID_ARG;
@@ -936,7 +941,8 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   int32_t left = n_generations;
   bool &splitters_valid = in_static_scratch ? static_valid : c->splitters_valid;
   auto launched_generation = [&] {
-    const int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block, splitters_valid, !in_static_scratch);
+    // (a recorded generation's signal would not be the one that is waited for)
+    const int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block, splitters_valid, !in_static_scratch, left == 1 && !capturing(c->stream));
     if (rc) { c->poisoned = true; return rc; }
     c->t += 1;
     left -= 1;

@@ -17,27 +17,32 @@ __device__ __forceinline__ void shared_store(T *p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The winner of a whole call, in genome row `row` (Q words a column), for the host.  Whole workgroup; w lies in the argument block.
-template <int Q, typename Args>
-__device__ __forceinline__ void publish_winner(const Args &w, const uint32_t *genes, uint32_t row, const uint32_t *info, uint64_t score_bits) {
+// All stores and loads of the workgroup are done when one thread goes on, whose fence at system scope then stands for all of
+// them.  (A fence by every wave writes the cache back as often: 16 waves 6 us.)
+__device__ __forceinline__ void all_arrived() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0);
+  asm volatile("" ::: "memory");
+  __syncthreads();
+}
+// The winner of a call, in genome row `row` of so many words, for the host.  Whole workgroup; w lies in the argument block.
+template <typename Args>
+__device__ __forceinline__ void publish_winner(const Args &w, const uint32_t *genes, uint32_t row_words, uint32_t row, const uint32_t *info, uint64_t score_bits) {
   const uint32_t n = w.n_slots;
   int32_t *batch = w.batch, *gpus = w.gpus;
   for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-    const uint32_t at = gene_byte(j), code = (shared_load(genes + static_cast<size_t>(row) * (Q * kLanes) + at / 4) >> (8 * (at % 4))) & 0xFFu;
+    const uint32_t at = gene_byte(j), code = (shared_load(genes + static_cast<size_t>(row) * row_words + at / 4) >> (8 * (at % 4))) & 0xFFu;
     batch[j] = static_cast<int32_t>(batch_of_code(code, info_blexp(info[j])));
     gpus[j] = static_cast<int32_t>((1u << code) >> 1);
   }
-  if (threadIdx.x == 0) {
-    *w.fit = __longlong_as_double(static_cast<long long>(score_bits));
-    *w.of = w.done.value;
-  }
-  __threadfence_system();
+  if (threadIdx.x == 0) *w.fit = __longlong_as_double(static_cast<long long>(score_bits));
 }
 // Tells the host that the call is done: by the thread that knows that all its workgroups are.  err: the two error words.
 template <typename Args>
 __device__ __forceinline__ void signal_call_done(const Args &w, const uint32_t *err) {
   w.err[0] = shared_load(err);
   w.err[1] = shared_load(err + 1);
+  *w.of = w.done.value;                                // (not before: the tickets of a launch that gives up are never all taken)
   __hip_atomic_store(w.done.flag, w.done.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

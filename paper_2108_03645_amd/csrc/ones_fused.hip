@@ -625,8 +625,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedArgs fa) {
       if (kSampled && tid < kLanes) fa.y_out[tid] = rk.ydraw[tid];   // the remaining work the last generation was scored with
       // the other workgroups have published their last and leave, or have left; the argument block is read here, see kernel_args
       const auto *late = (const __attribute__((address_space(4))) FusedArgs *)kernel_args();
-      publish_winner<1>(late->winner, a.genes, rk.srow(nxt)[0], a.tab.info, rk.skey(nxt)[0]);
-      __syncthreads();
+      publish_winner(late->winner, a.genes, kLanes, rk.srow(nxt)[0], a.tab.info, rk.skey(nxt)[0]);
+      all_arrived();
       if (tid == 0) signal_call_done(late->winner, late->sync + 1);
       return;
     }

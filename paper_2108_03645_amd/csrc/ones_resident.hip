@@ -910,15 +910,14 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
       }
       if (deal.me == 0) {
         const uint32_t row = rk.srow[0];
-        publish_winner<Q>(late->winner, a.genes, row, a.tab.info, kSampled ? shared_load(reinterpret_cast<const uint64_t *>(a.fit_row) + row) : rk.ckey[0]);
+        publish_winner(late->winner, a.genes, Q * kLanes, row, a.tab.info, kSampled ? shared_load(reinterpret_cast<const uint64_t *>(a.fit_row) + row) : rk.ckey[0]);
       }
       // The last workgroup tells the host.  Nothing of the workspace is written any more then: what the launch stores there goes
       // to the point of coherence, and has arrived before the ticket is taken.
-      phase_fence();
-      __builtin_amdgcn_s_waitcnt(0);
-      phase_fence();
-      __syncthreads();
-      if (tid == 0 && (deal.groups == 1 || __hip_atomic_fetch_add(late->winner.done.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == late->winner.done.target))
+      all_arrived();
+      if (tid != 0) return;
+      if (deal.me == 0) __threadfence_system();      // the winner
+      if (deal.groups == 1 || __hip_atomic_fetch_add(late->winner.done.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == late->winner.done.target)
         signal_call_done(late->winner, late->sync + 1);
       return;
     }
