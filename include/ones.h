@@ -92,9 +92,9 @@ size_t ones_workspace_bytes(const ones_config *cfg);
  * ranked.  d_workspace: DEVICE pointer, 256-byte aligned, workspace_bytes long.
  * hip_stream: a hipStream_t (NULL = the default stream).  Synchronises the stream
  * before returning.  *out is written only on success.  Besides the context the library
- * allocates one pinned host buffer (a few bytes per slot and per GPU; the size of the whole
- * state where that is at most 256 KB) which the kernels that bring the job table in and the
- * results out read and write themselves; ones_destroy frees both.  The calls that synchronise
+ * allocates one pinned host buffer (a few bytes per slot and per GPU; ones_export one of its own
+ * on first use for states of up to 256 KB) which the kernels that bring the job table in and the
+ * results out read and write themselves; ones_destroy frees them.  The calls that synchronise
  * mostly poll a word of it, for at most 4 ms, and then wait like hipStreamSynchronize.  A
  * context is used by one thread at a time. */
 int ones_init(ones_ctx **out, const ones_config *cfg, const ones_jobs *jobs,

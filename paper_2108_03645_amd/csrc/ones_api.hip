@@ -228,16 +228,16 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
 // that travel together, which lie next to each other in the workspace (every size below is a multiple of the
 // 256-byte alignment except the last of a group).  Behind them HostWords.
 struct HostWords { uint32_t flag, winner, err[2]; double fit; };      // see HostSignal and WinnerOut; behind them its arrays
-// A state of up to so much is exported that way too (a larger one is copied).
+// A state of up to so much is exported that way too, through a buffer of its own that the first export allocates (a larger one
+// is copied).
 constexpr size_t kStagedExport = 256u << 10;
 size_t export_bytes(const Layout &L, uint32_t P, uint32_t Jp) { return L.unpacked + static_cast<size_t>(P) * Jp * 4 - L.export_err; }
-size_t stage_bytes(const Layout &L, uint32_t P, uint32_t Jp, uint32_t G) {
+size_t stage_bytes(const Layout &L, uint32_t Jp, uint32_t G) {
   const size_t table = L.rY + static_cast<size_t>(Jp) * 8 - L.rawinfo;        // rawinfo, a, c, d, Y
   const size_t progress = L.processed + static_cast<size_t>(Jp) * 8 - L.alpha; // alpha, beta, processed
   const size_t best = L.best_err + 8 - L.best_batch;                           // batch, gpus, fitness, error words
   const size_t place = L.place_batch + static_cast<size_t>(G) * 4 - L.place_slot;
-  const size_t all = export_bytes(L, P, Jp);
-  return align_up(std::max({table, progress, best, place, static_cast<size_t>(Jp) * 4, all <= kStagedExport ? all : 0}));
+  return align_up(std::max({table, progress, best, place, static_cast<size_t>(Jp) * 4}));
 }
 
 int check_config(const ones_config *cfg) {
@@ -316,6 +316,7 @@ struct ones_ctx {
   char *stage;                // pinned host staging buffer (stage_bytes), free between calls
   char *stage_dev;            // the same buffer as the device addresses it
   size_t words_at;            // HostWords in it
+  char *export_stage, *export_stage_dev;    // the same for ones_export, once it is used (kStagedExport)
   uint32_t signals, tickets;  // HostSignal: the value of the last one, the tickets of all
   uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0
   Layout L;
@@ -383,6 +384,8 @@ WinnerOut next_winner(ones_ctx *c, uint32_t blocks) {
   return WinnerOut{batch, batch + c->Jp, &words->fit, &words->winner, words->err, c->Jn, next_signal(c, blocks)};
 }
 // Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
+// (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.4 ms
+// that ones_destroy or the next ones_init pays once.  Asked every 16 signals to, an epoch took 5 to 15 us more, every 64 2 to 4.)
 constexpr std::chrono::milliseconds kPollTime(4);
 int wait_signal(ones_ctx *c) {
   const auto from = std::chrono::steady_clock::now();
@@ -619,9 +622,10 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   c->L = L;
   c->stage = nullptr;
   c->stage_dev = nullptr;
+  c->export_stage = c->export_stage_dev = nullptr;
   {
     void *pinned = nullptr;
-    c->words_at = stage_bytes(L, c->P, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
+    c->words_at = stage_bytes(L, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
     HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords) + 8 * static_cast<size_t>(Jp), hipHostMallocDefault));
     c->stage = static_cast<char *>(pinned);
     c->host_words()->flag = c->host_words()->winner = c->signals = c->tickets = c->winner = 0;
@@ -1077,12 +1081,20 @@ static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, i
   const size_t row_bytes = static_cast<size_t>(c->Jp) * 4, genes_bytes = c->P * row_bytes;
   const uint32_t most = unpack_slots(c->P, c->Jp);
   const size_t all_bytes = genes ? L.unpacked + genes_bytes - L.export_err : L.export_fit + fit_bytes - L.export_err;
-  const bool one_copy = all_bytes <= kOneCopyExport && most == c->P, staged = genes && export_bytes(L, c->P, c->Jp) <= kStagedExport;
+  const bool one_copy = all_bytes <= kOneCopyExport && most == c->P;
+  bool staged = genes && export_bytes(L, c->P, c->Jp) <= kStagedExport;
+  if (staged && !c->export_stage) {
+    void *pinned = nullptr, *dev = nullptr;
+    staged = hipHostMalloc(&pinned, export_bytes(L, c->P, c->Jp), hipHostMallocDefault) == hipSuccess;
+    if (staged && hipHostGetDevicePointer(&dev, pinned, 0) != hipSuccess) { (void)hipHostFree(pinned); staged = false; }
+    if (staged) { c->export_stage = static_cast<char *>(pinned); c->export_stage_dev = static_cast<char *>(dev); }
+    else (void)hipGetLastError();                     // copied, then
+  }
   const size_t head_bytes = one_copy ? all_bytes : L.export_sel + sel_bytes - L.export_err;
   std::unique_ptr<char[]> copied;
-  const char *head = c->stage;
+  const char *head = c->export_stage;
   if (staged) {
-    auto mapped = [&](size_t off) { return c->stage_dev + (off - L.export_err); };
+    auto mapped = [&](size_t off) { return c->export_stage_dev + (off - L.export_err); };
     x.fit_out = reinterpret_cast<double *>(mapped(L.export_fit));
     x.sel_out = reinterpret_cast<int32_t *>(mapped(L.export_sel));
     x.err_out = reinterpret_cast<uint32_t *>(mapped(L.export_err));
@@ -1268,6 +1280,7 @@ void ones_destroy(ones_ctx *c) {
   for (auto &e : c->evolve_ev) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
   for (auto &e : c->select_ev) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
   if (c->stage) (void)hipHostFree(c->stage);
+  if (c->export_stage) (void)hipHostFree(c->export_stage);
   delete c;
 }
 
