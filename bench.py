@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published peak
 
 # HBM bytes per evolve launch on the stress workload from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (see profiles/), valid only for the kernel source with this hash.
-MEASURED_TRAFFIC = {"source_sha256": "f746ceb3078edc5d2eb27a1dc272c46ee306501df0044b37c0116a0e2cf23447", "bytes_per_launch": 201885008}
+MEASURED_TRAFFIC = {"source_sha256": "e55f202848fcc790aba0782138a02a1da54c429b7e7843221174a9b4c2c85ac0", "bytes_per_launch": 201939943}
 
 
 def evolve_source_hash() -> str:
