@@ -118,6 +118,12 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
+// v of the lane before this one, `first` for lane 0.  (Two shifts: the one across the wave, wave_shr, does not work here.)
+__device__ __forceinline__ uint32_t from_lane_before(uint32_t v, uint32_t first) {
+  const int rows = __builtin_amdgcn_update_dpp(static_cast<int>(first), static_cast<int>(v), kRowBcast15, 0xE, 0xF, false);
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(rows, static_cast<int>(v), kRowShr + 1, 0xF, 0xF, false));
+}
+
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kLanes - 1);
 }
@@ -228,7 +234,7 @@ inline uint32_t row_groups(uint32_t rows) {
 // kMaxCoinGpus on every cluster, and rounds of 256 ranks, one workgroup was resident where two are: 585 slots,
 // 3767 GPUs, pool 17084, 35 us a generation's launch; now 30.)
 inline uint32_t coin_stride(const EvolveArgs &a) {
-  return a.per_gpu ? std::min<uint32_t>((a.G / 32 + 4) / 4 * 4, kMaxCoinGpus / 32) * 8 : 0u;
+  return a.per_gpu ? (a.G / 32 + 4) / 4 * 4 * 8 : 0u;
 }
 
 // The genes near the job a repair starts from, in visiting order: kSide lanes' columns before that job's lane and
@@ -1021,51 +1027,60 @@ __device__ __forceinline__ void crossover_over_gpus(const EvolveArgs &a, uint32_
         coins[4 * lane + k] = (static_cast<uint64_t>(before) << 32) | w.w[k];
         before += __popc(w.w[k]);
       }
+      if (entries > 4u * kLanes && lane == kLanes - 1) coins[4 * kLanes] = static_cast<uint64_t>(before) << 32;
     }
   }
   // the lanes read each other's entries: one wave, whose LDS operations complete in order
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   phase_fence();
-  // heads among the GPUs below x, x <= G <= kMaxCoinGpus
-  auto heads_below = [&](uint32_t x) {
-    const uint32_t word = min(x >> 5, entries - 1);
-    const uint32_t bits = x - (word << 5);                       // 0 .. 32
+  // From here on a register holds a number for each parent, the second parent's in its upper half: GPUs and heads are at most
+  // kMaxCoinGpus, so that one scan, one shift over the lanes and one subtraction serve both.
+  static_assert(kMaxCoinGpus < 1 << 15, "two counts, and their sum, in 16 bits each");
+  // heads among the GPUs below x: GPU x's word, and of its coins the low x mod 32 (a bit field's width is taken mod 32)
+  auto heads_below = [&](uint32_t word, uint32_t x) {
     const uint64_t e = coins[word];
-    const uint32_t mask = bits >= 32u ? 0xFFFFFFFFu : (1u << bits) - 1u;
-    return static_cast<uint32_t>(e >> 32) + static_cast<uint32_t>(__popc(static_cast<uint32_t>(e) & mask));
+    return static_cast<uint32_t>(e >> 32) + static_cast<uint32_t>(__popc(__builtin_amdgcn_ubfe(static_cast<uint32_t>(e), 0u, x)));
   };
   // A job's first GPU is the GPU after its predecessor's last one (slot order: the lane to the left,
   // or the last lane of the row above), so the heads below a job's range are looked up once, at
   // its end, and its start takes the predecessor's value.
-  uint32_t carry_a = 0, carry_b = 0;                             // GPUs of the rows above (wave-uniform)
-  uint32_t above_a = 0, above_b = 0;                             // heads below the first GPU of the row (wave-uniform)
+  // Bound by the issue of vector instructions, some 40 a row (70 with a register per parent, a clamp of the word's number and a mask
+  // made by shifts: an epoch of eight generations on the stress cluster 1210 us, now 1056).
+  uint32_t carry_a = 0, carry_b = 0;                             // GPUs of the rows above (wave-uniform); kFeasible: carry_a, both parents'
+  uint32_t above = 0;                                            // heads below the first GPU of the row (wave-uniform)
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    uint32_t first = 0, second = 0;                              // the children's codes before the window
+    uint32_t first = 0, second = 0;                              // 31 - the children's codes before the window
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (static_cast<uint32_t>(4 * q + k) >= R) continue;       // no job slots (wave-uniform)
-      const uint32_t ga = (1u << ((cA[q] >> (8 * k)) & 31u)) >> 1, gb = (1u << ((cB[q] >> (8 * k)) & 31u)) >> 1;
-      const uint32_t incl_a = wave_inclusive_scan(ga), incl_b = wave_inclusive_scan(gb);
-      uint32_t end_a = carry_a + incl_a, start_a = end_a - ga;
-      uint32_t end_b = carry_b + incl_b, start_b = end_b - gb;
-      if (!kFeasible) {
-        end_a = min(end_a, a.G); start_a = min(start_a, a.G);
-        end_b = min(end_b, a.G); start_b = min(start_b, a.G);
+      if (static_cast<uint32_t>(4 * q + k) >= R) {               // no job slots (wave-uniform)
+        first |= 31u << (8 * k); second |= 31u << (8 * k);
+        continue;
       }
-      carry_a += __builtin_amdgcn_readlane(incl_a, kLanes - 1);
-      carry_b += __builtin_amdgcn_readlane(incl_b, kLanes - 1);
-      const uint32_t at_end_a = heads_below(end_a), at_end_b = heads_below(end_b);
-      const uint32_t left_a = __shfl_up(at_end_a, 1, kLanes), left_b = __shfl_up(at_end_b, 1, kLanes);
-      const uint32_t heads_a = at_end_a - (lane == 0 ? above_a : left_a);
-      const uint32_t heads_b = at_end_b - (lane == 0 ? above_b : left_b);
-      above_a = __builtin_amdgcn_readlane(at_end_a, kLanes - 1);
-      above_b = __builtin_amdgcn_readlane(at_end_b, kLanes - 1);
-      const uint32_t n1 = heads_a + ((end_b - start_b) - heads_b);
-      const uint32_t n2 = ((end_a - start_a) - heads_a) + heads_b;
-      first |= static_cast<uint32_t>(32 - __clz(static_cast<int>(n1))) << (8 * k);     // 0 GPUs: 0
-      second |= static_cast<uint32_t>(32 - __clz(static_cast<int>(n2))) << (8 * k);
+      const uint32_t ga = (1u << ((cA[q] >> (8 * k)) & 31u)) >> 1, gb = (1u << ((cB[q] >> (8 * k)) & 31u)) >> 1;
+      uint32_t gpus, end;
+      if (kFeasible) {
+        gpus = gb << 16 | ga;
+        const uint32_t incl = wave_inclusive_scan(gpus);
+        end = carry_a + incl;
+        carry_a += __builtin_amdgcn_readlane(incl, kLanes - 1);
+      } else {
+        const uint32_t incl_a = wave_inclusive_scan(ga), incl_b = wave_inclusive_scan(gb);
+        const uint32_t end_a = carry_a + incl_a, end_b = carry_b + incl_b;
+        end = min(end_b, a.G) << 16 | min(end_a, a.G);
+        gpus = end - (min(end_b - gb, a.G) << 16 | min(end_a - ga, a.G));
+        carry_a += __builtin_amdgcn_readlane(incl_a, kLanes - 1);
+        carry_b += __builtin_amdgcn_readlane(incl_b, kLanes - 1);
+      }
+      const uint32_t at_end = heads_below(end >> 21, end >> 16) << 16 | heads_below(__builtin_amdgcn_ubfe(end, 5u, 11u), end);
+      const uint32_t heads = at_end - from_lane_before(at_end, above);
+      above = __builtin_amdgcn_readlane(at_end, kLanes - 1);
+      const uint32_t tails = gpus - heads;
+      const uint32_t n1 = (heads & 0xFFFFu) + (tails >> 16), n2 = (tails & 0xFFFFu) + (heads >> 16);
+      first |= static_cast<uint32_t>(__builtin_clz(2 * n1 + 1)) << (8 * k);            // of 0 GPUs: 31
+      second |= static_cast<uint32_t>(__builtin_clz(2 * n2 + 1)) << (8 * k);
     }
+    first = 31 * kOnes - first; second = 31 * kOnes - second;    // no byte borrows
     const int w = q * kLanes + lane;
     const uint32_t start = s.start[w], most = s.most[w];
     cA[q] = min_bytes(max_bytes(first, start), most) & nonzero_bytes(first);

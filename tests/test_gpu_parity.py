@@ -1365,6 +1365,29 @@ def test_crossover_over_gpus_matches_the_oracle(ones, ref, n_slots, n_gpus, pop,
     gpu.close(); cpu.close()
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(64, 31, 64), (64, 32, 64), (64, 8192, 64), (90, 8192, 2052), (257, 8160, 260),
+                                                (500, 8191, 128), (512, 8192, 4096), (2000, 8192, 64)])
+def test_crossover_over_the_gpus_of_full_clusters(ones, ref, n_slots, n_gpus, pop):
+    """Jobs wide enough to fill the cluster: ranges that end with its last GPU, at the last coin of a word and of all words, and
+    counts of up to the whole cluster for both parents."""
+    cl = cluster(n_gpus, n_slots, pop, seed=n_slots)
+    def jobs(seed):
+        rng = np.random.default_rng(seed)
+        return make_jobs(n_slots, bmin=1, bmax=2 ** rng.integers(8, 29, n_slots), gpu_max_batch=256,
+                         c=rng.uniform(0, 0.05, n_slots), remaining=rng.uniform(1e5, 1e7, n_slots))
+    say(f"[full clusters] G={n_gpus} slots={n_slots} P={pop}")
+    gpu, cpu = ones.Search(cl, jobs(1)), ref.RefSearch(cl, jobs(1))
+    for s in (gpu, cpu):
+        s.set_crossover(per_gpu=True)
+    for n in (1, 4):
+        gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, f"{n} generations")
+    gpu.set_jobs(jobs(2)); cpu.set_jobs(jobs(2))
+    gpu.generation(5); cpu.generation(5)
+    assert_same_state(gpu, cpu, "behind a new table")
+    gpu.close(); cpu.close()
+
+
 def test_crossover_over_gpus_needs_a_small_enough_cluster(ones, ref):
     cl = cluster(8193, 16, 64, seed=1)
     jobs = random_jobs(np.random.default_rng(1), 16)
