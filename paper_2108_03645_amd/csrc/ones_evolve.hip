@@ -270,7 +270,7 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   // the repair walks where what that takes of LDS costs no workgroup its place on the compute unit
   const uint32_t scratch = std::max<uint32_t>(a.coin_stride, window_bytes(words));
   const size_t walking = smem_bytes(words, waves, a.term_lds, rows, scratch, true);
-  a.walk = walking * per_cu <= kLdsBudget ? 1u : 0u;
+  a.walk = walk_pays(a.Jp) && walking * per_cu <= kLdsBudget ? 1u : 0u;
   if (a.walk) { a.coin_stride = scratch; lds = walking; }
   const uint32_t blocks = std::max<uint32_t>(
       1u, std::min<uint32_t>({(items + waves - 1) / waves, static_cast<uint32_t>(n_cus * per_cu), max_blocks}));
