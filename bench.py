@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published peak
 
 # HBM bytes per evolve launch on the stress workload from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (see profiles/), valid only for the kernel source with this hash.
-MEASURED_TRAFFIC = {"source_sha256": "e55f202848fcc790aba0782138a02a1da54c429b7e7843221174a9b4c2c85ac0", "bytes_per_launch": 201939943}
+MEASURED_TRAFFIC = {"source_sha256": "a7cbf167408289e3957629766ad947212c7f4966881ecbc2bac6ea3495297ba3", "bytes_per_launch": 201876425}
 
 
 def evolve_source_hash() -> str:
