@@ -95,8 +95,9 @@ size_t ones_workspace_bytes(const ones_config *cfg);
  * allocates one pinned host buffer (a few bytes per slot and per GPU; ones_export one of its own
  * on first use for states of up to 256 KB) which the kernels that bring the job table in and the
  * results out read and write themselves; ones_destroy frees them.  The calls that synchronise
- * mostly poll a word of it, for at most 4 ms, and then wait like hipStreamSynchronize.  A
- * context is used by one thread at a time. */
+ * mostly poll a word of it, for at most 4 ms, and then wait like hipStreamSynchronize; either way
+ * all that was put on the stream before the call, by the library or by the caller, is done when
+ * they return.  A context is used by one thread at a time. */
 int ones_init(ones_ctx **out, const ones_config *cfg, const ones_jobs *jobs,
               void *d_workspace, size_t workspace_bytes, void *hip_stream);
 

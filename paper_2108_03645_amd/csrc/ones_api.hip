@@ -318,7 +318,7 @@ struct ones_ctx {
   size_t words_at;            // HostWords in it
   char *export_stage, *export_stage_dev;    // the same for ones_export, once it is used (kStagedExport)
   uint32_t signals, tickets;  // HostSignal: the value of the last one, the tickets of all
-  uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0
+  uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0: it does not
   Layout L;
   int cur;                    // the survivors of the current generation are in parent_row[cur ^ 1]
   int occ;                    // which bitmap holds the survivors' rows, unless
@@ -387,18 +387,35 @@ WinnerOut next_winner(ones_ctx *c, uint32_t blocks) {
 // (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.4 ms
 // that ones_destroy or the next ones_init pays once.  Asked every 16 signals to, an epoch took 5 to 15 us more, every 64 2 to 4.)
 constexpr std::chrono::milliseconds kPollTime(4);
-int wait_signal(ones_ctx *c) {
-  const auto from = std::chrono::steady_clock::now();
+using PollClock = std::chrono::steady_clock;
+bool poll_signal(const ones_ctx *c, PollClock::time_point from) {
   do {
     for (int i = 0; i < 256; ++i) {
       if (c->host_words()->flag == c->signals) {
         std::atomic_thread_fence(std::memory_order_acquire);
-        return ONES_OK;
+        return true;
       }
       __builtin_ia32_pause();
     }
-  } while (std::chrono::steady_clock::now() - from < kPollTime);
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  } while (PollClock::now() - from < kPollTime);
+  return false;
+}
+int wait_signal(ones_ctx *c) {
+  if (!poll_signal(c, PollClock::now())) HIP_TRY(hipStreamSynchronize(c->stream));
+  return ONES_OK;
+}
+// Waits for the whole stream where the last signal is that of an earlier call: what the caller has put behind that call's launch
+// is waited for too, and an error of it returned.  Once the signal is there the stream is mostly done within 5 us, which
+// hipStreamQuery tells for less than hipStreamSynchronize (an epoch of 64 candidates 87 us, 98; a kernel of its own that signals,
+// as the calls that launch one anyway do, 95).  Behind an ordinary launch the query is the dearer one (55 against 40).
+int wait_stream(ones_ctx *c) {
+  const auto from = PollClock::now();
+  hipError_t e = hipErrorNotReady;
+  if (poll_signal(c, from)) {
+    while ((e = hipStreamQuery(c->stream)) == hipErrorNotReady && PollClock::now() - from < kPollTime) __builtin_ia32_pause();
+    if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();       // no error of this thread's
+  }
+  if (e != hipSuccess) HIP_TRY(hipStreamSynchronize(c->stream));
   return ONES_OK;
 }
 
@@ -472,8 +489,7 @@ bool capturing(hipStream_t s) {
 
 // scratch: base of the selection's scratch block (the workspace's, or the static array);
 // splitters_valid: that block holds the current survivors' splitters and cleared counters.
-// last: of its call, whose winner the last kernel may leave for the host.
-int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid, bool events, bool last) {
+int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid, bool events) {
   EvolveArgs a;
   const ScratchLayout &S = c->L.S;
   auto sc = [&](size_t off) { return scratch + off; };
@@ -547,14 +563,10 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
     // the launch scored the whole pool (initial population, refresh under a new table, survivors
     // scored again under a new draw): its scores by slot are complete
     const bool all_scored = t == 0 || !same_table || a.rescore != 0;
-    const bool splitters = c->bp.nb != 0 && !sampled && same_table;
-    const uint32_t blocks = last && !splitters ? rank_pool_blocks(c->P) : 0u;
-    const WinnerSource from{a.genes, a.tab.info, c->at<uint32_t>(c->L.fsync) + 1, static_cast<uint32_t>(words_of(static_cast<int>(c->R)) * kLanes)};
     HIP_TRY(launch_select(a.fit_row, all_scored ? a.slot_score : nullptr, rp, c->P, c->K, store,
-                          c->at<int32_t>(c->L.sel), from, blocks ? next_winner(c, blocks) : WinnerOut{}, c->stream));
-    if (blocks) c->winner = c->signals;
+                          c->at<int32_t>(c->L.sel), c->stream));
     splitters_valid = false;
-    if (splitters) {
+    if (c->bp.nb != 0 && !sampled && same_table) {
       // Splitters for the bucketed generations that follow; clears both counter sets.  Under sampling
       // no bucketed generation can follow.  Nor after an initial population or a refresh under a new
       // table: the scores of such survivors say little about where their children will fall (nearly
@@ -685,7 +697,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     if (e != hipSuccess) return hip_fail(e, "launch_zero_words");
   }
   if ((rc = upload_table(c, h)) ||
-      (rc = run_generation(c, 0, c->ws + c->L.scratch, c->splitters_valid, false, false)))
+      (rc = run_generation(c, 0, c->ws + c->L.scratch, c->splitters_valid, false)))
     return rc;
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
@@ -846,7 +858,7 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   fa.winner = next_winner(c, 1);
   if (launch_fused(fa, c->stream) != hipSuccess) return refused(c, c->fused, tickets);
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
-  c->winner = c->signals;
+  c->winner = capturing(c->stream) ? 0 : c->signals;   // (when a recorded launch will run is not known)
   c->fused_generations += n;
   c->fused_changes += c->sampling ? n : fa.first_changed;
   if (c->sampling) {
@@ -945,8 +957,7 @@ static int generation_impl(ones_ctx *c, int32_t n_generations, bool in_static_sc
   int32_t left = n_generations;
   bool &splitters_valid = in_static_scratch ? static_valid : c->splitters_valid;
   auto launched_generation = [&] {
-    // (a recorded generation's signal would not be the one that is waited for)
-    const int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block, splitters_valid, !in_static_scratch, left == 1 && !capturing(c->stream));
+    const int rc = run_generation(c, static_cast<uint32_t>(c->t + 1), block, splitters_valid, !in_static_scratch);
     if (rc) { c->poisoned = true; return rc; }
     c->t += 1;
     left -= 1;
@@ -1014,9 +1025,9 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
     if (fitness_out) memcpy(fitness_out, const_cast<const void *>(fit), 8);
     return ONES_OK;
   };
-  if (c->winner != 0) {
-    // the launch that ran the last call leaves the winner in the pinned buffer
-    if (int rc = wait_signal(c)) return rc;
+  if (c->winner != 0 && c->winner == c->signals) {
+    // the launch that ran the last call, which is this context's last one, leaves the winner in the pinned buffer
+    if (int rc = wait_stream(c)) return rc;
     volatile HostWords *words = c->host_words();
     if (words->winner == c->winner) {
       if (words->err[0]) return wait_gave_up(c);

@@ -148,8 +148,7 @@ struct HostSignal {
   uint32_t *flag;
   uint32_t  target, value;    // the last workgroup's ticket
 };
-// What the last kernel of a call leaves in pinned memory, if it ranks the whole pool and few workgroups have to tell that they are
-// done: the winner, as ones_best hands it out, and the error words.
+// What a launch that runs a whole call leaves in pinned memory: the winner, as ones_best hands it out, and the error words.
 struct WinnerOut {
   int32_t  *batch, *gpus;     // [n_slots]
   double   *fit;
@@ -335,12 +334,9 @@ inline hipError_t launch_evolve(const EvolveArgs &a, int rows, bool same_table, 
 // General selection (any scores).  store: the bucket storage (count, keys, idx and spill arrays,
 // split and split_slot as scratch for the splitters, nb * seg entries of bucket space); used by pools
 // too large for the single launch that ranks a whole pool.  slot_score: the pool's scores by slot
-// when the evolve launch wrote them all, else null (they are then looked up through the rows).  winner: of the pool, to be left by
-// the single launch (rank_pool_blocks workgroups, 0: the pool is larger), or one without a flag.
-struct WinnerSource { const uint32_t *genes, *info, *err; uint32_t row_words; };
-uint32_t rank_pool_blocks(uint32_t P);
+// when the evolve launch wrote them all, else null (they are then looked up through the rows).
 hipError_t launch_select(const double *fit_row, const double *slot_score, const RowPlan &rp, uint32_t P, uint32_t K,
-                         const BucketArgs &store, int32_t *sel, const WinnerSource &from, const WinnerOut &winner, hipStream_t s);
+                         const BucketArgs &store, int32_t *sel, hipStream_t s);
 hipError_t launch_zero_words(uint32_t *words, uint32_t n, hipStream_t s);
 // count_next, ties_next: the other set of counters and bitmaps, cleared for the next generation.
 hipError_t launch_bucket_select(const double *fit_row, const BucketArgs &bk, const RowPlan &rp, uint32_t K,

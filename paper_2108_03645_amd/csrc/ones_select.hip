@@ -64,8 +64,7 @@ __device__ __forceinline__ void keep_child(const RowPlan &rp, uint32_t g, uint32
 constexpr uint32_t kRankPoolMax = ONES_RANK_POOL_MAX;
 constexpr int kRankPoolPer = 64;
 __global__ __launch_bounds__(kSortThreads) void rank_pool_kernel(const double *fit_row, const double *slot_score,
-                                                                RowPlan rp, uint32_t P, uint32_t K, int32_t *sel,
-                                                                WinnerSource from_rows, WinnerOut winner) {
+                                                                RowPlan rp, uint32_t P, uint32_t K, int32_t *sel) {
   const uint32_t *row_of = rp.row_of;
   extern __shared__ __align__(16) uint64_t sk[];       // [padded] scores, then [kRankPoolPer] counters
   constexpr uint32_t kTeam = kSortThreads / kRankPoolPer;
@@ -103,19 +102,6 @@ __global__ __launch_bounds__(kSortThreads) void rank_pool_kernel(const double *f
     if (in) sel[below[t]] = static_cast<int32_t>(mine);
     keep_and_mark(rp, in, below[t], in ? row_of[mine] : 0u);
   }
-  if (winner.done.flag == nullptr) return;
-  // the call's last kernel: the winner for the host (ones_best spares a kernel of its own)
-  __shared__ uint32_t first;
-  if (t == 0) first = ~0u;
-  __syncthreads();
-  if (t < kRankPoolPer && mine < P && below[t] == 0) first = mine;
-  __syncthreads();
-  if (first != ~0u) publish_winner(winner, from_rows.genes, from_rows.row_words, row_of[first], from_rows.info, sk[first]);
-  all_arrived();
-  if (t != 0) return;
-  __threadfence_system();                              // nothing of the workspace is written once the host knows
-  if (gridDim.x == 1 || __hip_atomic_fetch_add(winner.done.tickets, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == winner.done.target)
-    signal_call_done(winner, from_rows.err);
 }
 
 // ----------------------------------------------------------- quantile buckets ------
@@ -1208,16 +1194,16 @@ hipError_t launch_zero_words(uint32_t *words, uint32_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-uint32_t rank_pool_blocks(uint32_t P) { return P <= kRankPoolMax ? (P + kRankPoolPer - 1) / kRankPoolPer : 0u; }
 hipError_t launch_select(const double *fit, const double *slot_score, const RowPlan &rp, uint32_t P, uint32_t K,
-                         const BucketArgs &store, int32_t *sel, const WinnerSource &from, const WinnerOut &winner, hipStream_t s) {
-  if (const uint32_t rank_blocks = rank_pool_blocks(P)) {
+                         const BucketArgs &store, int32_t *sel, hipStream_t s) {
+  if (P <= kRankPoolMax) {
+    const uint32_t rank_blocks = (P + kRankPoolPer - 1) / kRankPoolPer;
     constexpr uint32_t kStep = 8 * (kSortThreads / kRankPoolPer);
     const size_t lds = static_cast<size_t>((P + kStep - 1) / kStep * kStep) * 8 + kRankPoolPer * 4;
     hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(rank_pool_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (rc != hipSuccess) return rc;
-    hipLaunchKernelGGL(rank_pool_kernel, dim3(rank_blocks), dim3(kSortThreads), lds, s, fit, slot_score, rp, P, K, sel, from, winner);
+    hipLaunchKernelGGL(rank_pool_kernel, dim3(rank_blocks), dim3(kSortThreads), lds, s, fit, slot_score, rp, P, K, sel);
     return hipGetLastError();
   }
   // 64 to 127 candidates per bucket (more in pools beyond 2^17), kOversample sample points per

@@ -779,6 +779,70 @@ def test_a_captured_call_is_launched_by_generation(ones, ref, n_slots, n_gpus, p
     gpu.close(); cpu.close()
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop", [(40, 64, 64), (64, 64, 2048)])
+def test_a_captured_call_of_a_one_row_pool(ones, ref, n_slots, n_gpus, pop):
+    """All generations of such a call are one launch, which is recorded as it is.  The graph
+    is launched once; the winner is asked for behind it, and again behind eager calls of either kind."""
+    import torch
+    jobs = random_jobs(np.random.default_rng(91), n_slots)
+    say(f"[captured, one row] slots={n_slots} P={pop}")
+    side = torch.cuda.Stream()
+    gpu = ones.Search(cluster(n_gpus, n_slots, pop, seed=91), jobs, stream=side)
+    cpu = ref.RefSearch(cluster(n_gpus, n_slots, pop, seed=91), jobs)
+
+    def same_winner(what):
+        for x, y in zip(gpu.best(), cpu.best()):
+            assert np.array_equal(x, y), what
+
+    for n in (5, 0, 1):
+        gpu.generation(n); cpu.generation(n)
+        same_winner("before")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        gpu.generation(20)
+    cpu.generation(20)
+    with torch.cuda.stream(side):
+        graph.replay()
+    same_winner("the captured call")
+    for n in (4, 2, 7):
+        gpu.generation(n); cpu.generation(n)
+        same_winner(f"a call of {n} behind it")
+    assert_same_state(gpu, cpu, "at the end")
+    gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots,n_gpus,pop,n,sampled", [
+    (40, 64, 64, 10, False), (64, 64, 2048, 4, True), (40, 64, 64, 1, False), (200, 300, 4096, 8, False),
+    (300, 400, 2052, 12, True), (700, 900, 65536, 2, False)])
+def test_best_waits_for_what_the_caller_put_on_the_stream(ones, n_slots, n_gpus, pop, n, sampled):
+    """ones_best synchronises: work that the caller has put on the stream behind the generations, some 30 ms of it here, and
+    its copy to pinned memory are done when it returns, however the generations ran.  Asked again, and behind a call that
+    launches a kernel, it is the same winner."""
+    import torch
+    say(f"[best waits] slots={n_slots} P={pop} n={n} sampled={sampled}")
+    gpu = ones.Search(cluster(n_gpus, n_slots, pop, seed=92), random_jobs(np.random.default_rng(92), n_slots))
+    if sampled:
+        gpu.set_progress(*W.progress(n_slots, seed=92))
+    x = torch.eye(4096, device="cuda")
+    y = x
+    for _ in range(3):
+        y = x @ y                                                # (the library loads its kernels)
+    there = torch.zeros(1, pin_memory=True)
+    torch.cuda.synchronize()
+    gpu.generation(n)
+    for _ in range(25):
+        y = x @ y
+    there.copy_(y[0, :1], non_blocking=True)
+    first = gpu.best()
+    done = float(there[0])
+    torch.cuda.synchronize()
+    assert done == 1.0
+    gpu.placement()
+    for again in (gpu.best(), gpu.best()):
+        assert all(np.array_equal(a, b) for a, b in zip(first, again))
+    gpu.close()
+
+
 @pytest.mark.parametrize("n_slots,n_gpus,pop,before,n", [
     (200, 300, 4096, [1] * 5, 30), (200, 300, 4096, [7], 4), (1000, 1500, 1024, [2], 37), (130, 90, 128, [1, 2], 9)])
 def test_draws_left_by_an_earlier_call_do_not_decide_how_a_call_runs(ones, ref, n_slots, n_gpus, pop, before, n):
