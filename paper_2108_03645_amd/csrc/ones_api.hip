@@ -317,7 +317,7 @@ struct ones_ctx {
   char *stage_dev;            // the same buffer as the device addresses it
   size_t words_at;            // HostWords in it
   char *export_stage, *export_stage_dev;    // the same for ones_export, once it is used (kStagedExport)
-  uint32_t signals, tickets;  // HostSignal: the value of the last one, the tickets of all
+  uint32_t signals;           // HostSignal: the value of the last one
   uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0: it does not
   Layout L;
   int cur;                    // the survivors of the current generation are in parent_row[cur ^ 1]
@@ -371,17 +371,15 @@ struct ones_ctx {
 
 namespace {
 
-// For a launch of so many workgroups.
-HostSignal next_signal(ones_ctx *c, uint32_t blocks) {
+HostSignal next_signal(ones_ctx *c) {
   c->signals += 1;
-  if (blocks > 1) c->tickets += blocks;
-  return HostSignal{c->at<uint32_t>(c->L.fsync) + 8, &c->host_words_dev()->flag, c->tickets, c->signals};
+  return HostSignal{c->at<uint32_t>(c->L.fsync) + 8, &c->host_words_dev()->flag, c->signals};
 }
 // For a launch that runs a whole call.
-WinnerOut next_winner(ones_ctx *c, uint32_t blocks) {
+WinnerOut next_winner(ones_ctx *c) {
   HostWords *words = c->host_words_dev();
   int32_t *batch = reinterpret_cast<int32_t *>(words + 1);
-  return WinnerOut{batch, batch + c->Jp, &words->fit, &words->winner, words->err, c->Jn, next_signal(c, blocks)};
+  return WinnerOut{batch, batch + c->Jp, &words->fit, &words->winner, words->err, c->Jn, next_signal(c)};
 }
 // Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
 // (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.4 ms
@@ -432,7 +430,7 @@ int upload_table(ones_ctx *c, const HostJobs &h) {
   RawJobs raw{reinterpret_cast<uint32_t *>(mapped(L.rawinfo)), reinterpret_cast<double *>(mapped(L.ra)), reinterpret_cast<double *>(mapped(L.rc)),
               reinterpret_cast<double *>(mapped(L.rd)), reinterpret_cast<double *>(mapped(L.rY))};
   c->term_E = h.term_E;
-  HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(L.rY), c->Jp, next_signal(c, table_change_blocks(c->Jp)), c->stream));
+  HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(L.rY), c->Jp, next_signal(c), c->stream));
   return wait_signal(c);                        // the staging buffer is free again
 }
 
@@ -445,7 +443,7 @@ int fetch_staged(ones_ctx *c, size_t to, size_t bytes) {
     return ONES_OK;
   }
   const uint32_t n = static_cast<uint32_t>(bytes / 16);
-  HIP_TRY(launch_fetch(c->stage_dev, c->ws + to, n, next_signal(c, fetch_blocks(n)), c->stream));
+  HIP_TRY(launch_fetch(c->stage_dev, c->ws + to, n, next_signal(c), c->stream));
   return wait_signal(c);                        // the staging buffer is free again
 }
 
@@ -640,7 +638,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
     c->words_at = stage_bytes(L, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
     HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords) + 8 * static_cast<size_t>(Jp), hipHostMallocDefault));
     c->stage = static_cast<char *>(pinned);
-    c->host_words()->flag = c->host_words()->winner = c->signals = c->tickets = c->winner = 0;
+    c->host_words()->flag = c->host_words()->winner = c->signals = c->winner = 0;
     void *mapped = nullptr;
     HIP_TRY(hipHostGetDevicePointer(&mapped, pinned, 0));
     c->stage_dev = static_cast<char *>(mapped);
@@ -826,10 +824,9 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
 // What run_fused and run_resident return when the runtime refuses the launch: nothing has run and no state has changed,
 // and the kernels of one generation, which any GPU runs, take the call.
 constexpr int kLaunchRefused = 1;
-static int refused(ones_ctx *c, bool &whole_calls, uint32_t tickets) {
+static int refused(ones_ctx *c, bool &whole_calls) {
   whole_calls = false;              // not asked for again by this context
   c->signals -= 1;                  // nor will the signal come
-  c->tickets = tickets;
   (void)hipGetLastError();
   return kLaunchRefused;
 }
@@ -852,11 +849,10 @@ static int run_fused(ones_ctx *c, uint32_t n, bool events) {
   fa.n_generations = n;
   fa.first_changed = c->table_changed ? 1u : 0u;
   fa.spin_limit = c->spin_limit;
-  const uint32_t tickets = c->tickets;
   int rc;
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, true))) return rc;
-  fa.winner = next_winner(c, 1);
-  if (launch_fused(fa, c->stream) != hipSuccess) return refused(c, c->fused, tickets);
+  fa.winner = next_winner(c);
+  if (launch_fused(fa, c->stream) != hipSuccess) return refused(c, c->fused);
   if (events && (rc = timed(c, c->evolve_ev, c->evolve_used, false))) return rc;
   c->winner = capturing(c->stream) ? 0 : c->signals;   // (when a recorded launch will run is not known)
   c->fused_generations += n;
@@ -903,8 +899,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
   ra.spin_limit = c->spin_limit;
   ra.paired = plan.paired; ra.unit_waves = plan.unit_waves; ra.child_items = plan.child_items;
   ra.segment = plan.segment; ra.list = plan.list; ra.table_lds = plan.table_lds;
-  const uint32_t tickets = c->tickets;
-  ra.winner = next_winner(c, plan.groups);
+  ra.winner = next_winner(c);
   hipError_t launched;
   switch (words_of(static_cast<int>(c->R))) {
     case 1: launched = launch_resident_words1(ra, plan, c->stream); break;
@@ -912,7 +907,7 @@ static int run_resident(ones_ctx *c, uint32_t n, const ResidentPlan &plan) {
     case 3: launched = launch_resident_words3(ra, plan, c->stream); break;
     default: launched = launch_resident_words4(ra, plan, c->stream); break;
   }
-  if (launched != hipSuccess) return refused(c, c->resident, tickets);
+  if (launched != hipSuccess) return refused(c, c->resident);
   c->winner = c->signals;
   c->fused_generations += n;
   if (c->sampling) c->y_cur = static_cast<int>((c->t + n) % kDrawRing);
@@ -1047,7 +1042,7 @@ static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double 
                       c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, reinterpret_cast<int32_t *>(mapped(L.best_batch)),
                       reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
                       reinterpret_cast<double *>(mapped(L.best_fit)), c->at<uint32_t>(c->L.fsync) + 1,
-                      reinterpret_cast<uint32_t *>(mapped(L.best_err)), next_signal(c, 1), c->stream));
+                      reinterpret_cast<uint32_t *>(mapped(L.best_err)), next_signal(c), c->stream));
   if (int rc = wait_signal(c)) return rc;
   auto staged = [&](size_t off) { return c->stage + (off - L.best_batch); };   // laid out as in the workspace
   uint32_t words[2] = {0, 0};
@@ -1065,7 +1060,7 @@ static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_g
   auto mapped = [&](size_t off) { return reinterpret_cast<int32_t *>(c->stage_dev + (off - L.place_slot)); };
   HIP_TRY(launch_placement(c->at<uint32_t>(L.genes), survivor_rows(c), c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, c->G, mapped(L.place_slot),
                            mapped(L.place_batch), c->at<uint32_t>(L.fsync) + 1, c->host_words_dev()->err,
-                           next_signal(c, placement_blocks(c->G)), c->stream));
+                           next_signal(c), c->stream));
   if (int rc = wait_signal(c)) return rc;
   if (c->host_words()->err[0]) return wait_gave_up(c);
   if (c->host_words()->err[1]) return row_fault(c);
@@ -1110,7 +1105,7 @@ static int export_impl(ones_ctx *c, int32_t *genes, double *fit, int32_t *sel, i
     x.sel_out = reinterpret_cast<int32_t *>(mapped(L.export_sel));
     x.err_out = reinterpret_cast<uint32_t *>(mapped(L.export_err));
     x.genes_out = reinterpret_cast<int32_t *>(mapped(L.unpacked));
-    x.done = next_signal(c, c->K);
+    x.done = next_signal(c);
     HIP_TRY(launch_export_genes(x, 0, c->P, true, c->stream));
     if (int rc = wait_signal(c)) return rc;
   } else {

@@ -144,9 +144,9 @@ constexpr int kDrawAhead = 8;       // generations drawn at a time for the kerne
 // word of pinned memory that the host polls.  (A kernel and a wait of this kind take 5.9 us alone, with hipStreamSynchronize 9.3; a
 // copy from or to pinned memory is another 5 to 6, so these kernels read and write it themselves.)
 struct HostSignal {
-  uint32_t *tickets;          // of workgroups that are done, over all signals of more than one workgroup
+  uint32_t *arrived;          // workgroups that are done: zero between launches, see last_to_arrive
   uint32_t *flag;
-  uint32_t  target, value;    // the last workgroup's ticket
+  uint32_t  value;
 };
 // What a launch that runs a whole call leaves in pinned memory: the winner, as ones_best hands it out, and the error words.
 struct WinnerOut {
@@ -305,10 +305,8 @@ struct RawJobs {              // uploaded by the host after validation, [Jp] eac
 // launchers (each returns the hipGetLastError of its launch)
 // The per-slot values and the term table from the raw table, and the slots that changed hands marked
 // in tab.stored (unless the genomes are, or will be, stored under this table); one launch.  remaining: the raw table's, kept.
-uint32_t table_change_blocks(uint32_t Jp);
 hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, double *remaining, uint32_t Jp, const HostSignal &done, hipStream_t s);
 // n 16-byte words.
-uint32_t fetch_blocks(uint32_t n);
 hipError_t launch_fetch(const void *from, void *to, uint32_t n, const HostSignal &done, hipStream_t s);
 hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s);
 // ring: the job table with Y and terms pointing at place 0 of a ring of `places`, which lie
@@ -346,7 +344,6 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
                             uint32_t *ties, uint32_t ties_words, hipStream_t s);
 // Eq. 1 for the winner: GPU i runs slot slot_of_gpu[i] (-1 = idle) with batch_of_gpu[i] samples;
 // jobs in slot order on consecutive GPUs.  G entries each.  best: row of the winner.
-uint32_t placement_blocks(uint32_t G);
 hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
                             uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, const uint32_t *err_in, uint32_t *err_out,
                             const HostSignal &done, hipStream_t s);

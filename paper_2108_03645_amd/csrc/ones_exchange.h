@@ -25,6 +25,15 @@ __device__ __forceinline__ void all_arrived() {
   asm volatile("" ::: "memory");
   __syncthreads();
 }
+// Whether this workgroup is the last of the launch to come here; one thread of each asks, behind a fence for what it has stored.  The counter wraps to zero with the last
+// one, so that a launch that was refused, or recorded into a graph and never run, leaves nothing to be made up for.
+__device__ __forceinline__ bool last_to_arrive(uint32_t *arrived) {
+  const uint32_t others = gridDim.x - 1;
+  if (others == 0) return true;
+  if (__builtin_amdgcn_atomic_inc32(arrived, others, __ATOMIC_RELAXED, "agent") != others) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return true;
+}
 // The winner of a call, in genome row `row` of so many words, for the host.  Whole workgroup; w lies in the argument block.
 template <typename Args>
 __device__ __forceinline__ void publish_winner(const Args &w, const uint32_t *genes, uint32_t row_words, uint32_t row, const uint32_t *info, uint64_t score_bits) {
@@ -42,7 +51,7 @@ template <typename Args>
 __device__ __forceinline__ void signal_call_done(const Args &w, const uint32_t *err) {
   w.err[0] = shared_load(err);
   w.err[1] = shared_load(err + 1);
-  *w.of = w.done.value;                                // (not before: the tickets of a launch that gives up are never all taken)
+  *w.of = w.done.value;                                // (not before: the workgroups of a launch that gives up do not all arrive)
   __hip_atomic_store(w.done.flag, w.done.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

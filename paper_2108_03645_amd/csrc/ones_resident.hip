@@ -913,12 +913,11 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
         publish_winner(late->winner, a.genes, Q * kLanes, row, a.tab.info, kSampled ? shared_load(reinterpret_cast<const uint64_t *>(a.fit_row) + row) : rk.ckey[0]);
       }
       // The last workgroup tells the host.  Nothing of the workspace is written any more then: what the launch stores there goes
-      // to the point of coherence, and has arrived before the ticket is taken.
+      // to the point of coherence, and is there before the workgroup counts as arrived.
       all_arrived();
       if (tid != 0) return;
       if (deal.me == 0) __threadfence_system();      // the winner
-      if (deal.groups == 1 || __hip_atomic_fetch_add(late->winner.done.tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == late->winner.done.target)
-        signal_call_done(late->winner, late->sync + 1);
+      if (last_to_arrive(late->winner.done.arrived)) signal_call_done(late->winner, late->sync + 1);
       return;
     }
   }

@@ -957,8 +957,7 @@ __device__ __forceinline__ void signal_host(const HostSignal &done) {
   all_arrived();
   if (threadIdx.x != 0) return;
   __threadfence_system();
-  if (gridDim.x == 1 || __hip_atomic_fetch_add(done.tickets, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == done.target)
-    __hip_atomic_store(done.flag, done.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (last_to_arrive(done.arrived)) __hip_atomic_store(done.flag, done.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // What the kernels need of one job slot, derived from the validated raw table.
@@ -1160,15 +1159,13 @@ hipError_t launch_build_terms(const JobTable &tab, uint32_t Jp, hipStream_t s) {
   return hipGetLastError();
 }
 
-uint32_t table_change_blocks(uint32_t Jp) { return Jp / kLanes; }
 hipError_t launch_table_change(const RawJobs &raw, const JobTable &tab, double *remaining, uint32_t Jp, const HostSignal &done, hipStream_t s) {
-  hipLaunchKernelGGL(table_change_kernel, dim3(table_change_blocks(Jp)), dim3(kLanes), 0, s, raw, tab, remaining, Jp, done);
+  hipLaunchKernelGGL(table_change_kernel, dim3(Jp / kLanes), dim3(kLanes), 0, s, raw, tab, remaining, Jp, done);
   return hipGetLastError();
 }
 
-uint32_t fetch_blocks(uint32_t n) { return (n + kFetchThreads - 1) / kFetchThreads; }
 hipError_t launch_fetch(const void *from, void *to, uint32_t n, const HostSignal &done, hipStream_t s) {
-  hipLaunchKernelGGL(fetch_kernel, dim3(fetch_blocks(n)), dim3(kFetchThreads), 0, s, static_cast<const uint4 *>(from), static_cast<uint4 *>(to),
+  hipLaunchKernelGGL(fetch_kernel, dim3((n + kFetchThreads - 1) / kFetchThreads), dim3(kFetchThreads), 0, s, static_cast<const uint4 *>(from), static_cast<uint4 *>(to),
                      n, done);
   return hipGetLastError();
 }
@@ -1243,11 +1240,11 @@ hipError_t launch_splitters(const double *fit_row, const uint32_t *row_of, const
   return hipGetLastError();
 }
 
-uint32_t placement_blocks(uint32_t G) { return std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u)); }
 hipError_t launch_placement(const uint32_t *genes, const uint32_t *best, const uint32_t *info, uint32_t Jn, uint32_t Jp,
                             uint32_t G, int32_t *slot_of_gpu, int32_t *batch_of_gpu, const uint32_t *err_in, uint32_t *err_out,
                             const HostSignal &done, hipStream_t s) {
-  hipLaunchKernelGGL(placement_kernel, dim3(placement_blocks(G)), dim3(kPlaceThreads), 0, s, genes, best, info, Jn,
+  const uint32_t blocks = std::max<uint32_t>(1u, std::min<uint32_t>((G + kPlaceThreads - 1) / kPlaceThreads, 1024u));
+  hipLaunchKernelGGL(placement_kernel, dim3(blocks), dim3(kPlaceThreads), 0, s, genes, best, info, Jn,
                      static_cast<uint32_t>(words_of(Jp / kLanes) * kLanes), G, slot_of_gpu, batch_of_gpu, err_in, err_out, done);
   return hipGetLastError();
 }

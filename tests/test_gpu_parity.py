@@ -1020,6 +1020,90 @@ def test_a_refused_single_launch_is_run_by_generation(ones, ref, tmp_path):
     assert run.returncode == 0 and "all refused, all right" in run.stdout
 
 
+FAILING_RUNTIME = r"""
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stdio.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3;
+int refuse = 0, pending = 0;
+static void *runtime(const char *name) {
+  static void *lib = 0;
+  if (!lib) {
+    char line[4096];
+    FILE *maps = fopen("/proc/self/maps", "r");
+    while (!lib && fgets(line, sizeof line, maps))
+      if (strstr(line, "libamdhip64")) {
+        line[strcspn(line, "\n")] = 0;
+        lib = dlopen(strchr(line, '/'), RTLD_NOW | RTLD_NOLOAD);
+      }
+    fclose(maps);
+  }
+  return dlsym(lib, name);
+}
+int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
+  if (refuse) { refuse = 0; return pending = 9; }             /* hipErrorInvalidConfiguration */
+  return ((int (*)(const void *, dim3, dim3, void **, size_t, void *))runtime("hipLaunchKernel"))(f, grid, block, args, lds, stream);
+}
+int hipGetLastError(void) {
+  int e = pending;
+  pending = 0;
+  return e ? e : ((int (*)(void))runtime("hipGetLastError"))();
+}
+"""
+
+WITH_FAILED_LAUNCHES = """
+import ctypes, sys, time
+shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)          # found before the runtime's own entry points
+sys.path[:0] = [sys.argv[2], sys.argv[2] + "/tests"]
+import numpy as np
+from test_gpu_parity import assert_same_state, cluster, random_jobs, say, W
+from oracle import ones_ref
+from paper_2108_03645_amd import ones
+refuse = ctypes.c_int.in_dll(shim, "refuse")
+n_slots, n_gpus, pop = 300, 3000, 2052                       # several workgroups in each of the kernels that signal
+jobs = random_jobs(np.random.default_rng(93), n_slots)
+gpu, cpu = ones.Search(cluster(n_gpus, n_slots, pop, seed=93), jobs), ones_ref.RefSearch(cluster(n_gpus, n_slots, pop, seed=93), jobs)
+calls = [lambda s: s.set_jobs(jobs), lambda s: s.set_progress(*W.progress(n_slots, seed=93)), lambda s: (s.generation(1), s.placement()),
+         lambda s: (s.generation(12), s.best())]
+for fails in (gpu.placement, calls[0], calls[1]):
+    say(f"[a failed launch] {fails}")
+    for s in (gpu, cpu):
+        for call in calls:
+            call(s)
+    refuse.value = 1
+    try:
+        fails() if fails == gpu.placement else fails(gpu)
+    except ones.OnesError:
+        pass
+    else:
+        raise AssertionError("not refused")
+    for call in calls:
+        took = []
+        for _ in range(4):
+            start = time.perf_counter()
+            call(gpu)
+            took.append(time.perf_counter() - start)
+            call(cpu)
+        assert min(took) < 3e-3, took
+    assert_same_state(gpu, cpu, "behind it")
+print("as quick as before")
+"""
+
+
+def test_a_failed_launch_does_not_slow_the_calls_behind_it(ones, ref, tmp_path):
+    """A call whose launch fails returns an error, and the context goes on: the kernels of the calls behind it signal that
+    they are done as ever, and none of them sits out the 4 ms after which a call stops polling.  (In a process of its
+    own, which finds an entry point that fails when it is told to before the runtime's.)"""
+    (tmp_path / "fail.c").write_text(FAILING_RUNTIME)
+    shim = str(tmp_path / "libfail.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", shim, str(tmp_path / "fail.c"), "-ldl"], check=True, timeout=60)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-u", "-c", WITH_FAILED_LAUNCHES, shim, root], capture_output=True, text=True, timeout=100)
+    say(run.stdout + run.stderr)
+    assert run.returncode == 0 and "as quick as before" in run.stdout
+
+
 # ---- the five configurations at their stated size and length ----
 
 def host_threads():
