@@ -280,7 +280,9 @@ typedef struct {
 } ones_limit_inputs;
 int ones_update_limits(int32_t n_slots, const ones_limit_inputs *in, double sigma, int32_t *limit);
 
-void ones_destroy(ones_ctx *ctx);           /* NULL is allowed */
+/* Waits for a launch that still writes to the library's pinned memory.  The workspace may be used for something else on
+ * another stream once the context's stream is done.  NULL is allowed. */
+void ones_destroy(ones_ctx *ctx);
 const char *ones_strerror(int code);        /* static or thread-local storage */
 
 #ifdef __cplusplus

@@ -1283,6 +1283,9 @@ int ones_update_limits(int32_t n_slots, const ones_limit_inputs *in, double sigm
 
 void ones_destroy(ones_ctx *c) {
   if (!c) return;
+  // A launch of ones_generation that no call has waited for still writes the winner to the pinned buffer.  (Not on a stream that is
+  // being captured: that would end the capture, and what is recorded writes nothing before it is launched.)
+  if (c->stage && c->host_words()->flag != c->signals && !capturing(c->stream)) (void)hipStreamSynchronize(c->stream);
   for (auto &e : c->evolve_ev) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
   for (auto &e : c->select_ev) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
   if (c->stage) (void)hipHostFree(c->stage);

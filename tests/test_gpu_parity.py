@@ -1830,6 +1830,26 @@ def test_repair_walks_near_its_start(ones, ref, n_slots, share):
     gpu.close(); cpu.close()
 
 
+@pytest.mark.parametrize("n_slots,n_gpus,pop,n", [(64, 64, 2048, 2000), (200, 300, 8192, 400), (200, 300, 300, 1)])
+def test_destroy_waits_for_a_launch_that_writes_the_winner(ones, ref, n_slots, n_gpus, pop, n):
+    """ones_generation is asynchronous, and the launch of a whole call leaves the winner in pinned memory that ones_destroy
+    frees.  A context destroyed while it runs (milliseconds here) leaves nothing running; a search that begins behind it is right."""
+    import torch
+    jobs = random_jobs(np.random.default_rng(94), n_slots)
+    say(f"[destroyed at once] slots={n_slots} P={pop} n={n}")
+    side = torch.cuda.Stream()
+    cl = cluster(n_gpus, n_slots, pop, seed=94)
+    for _ in range(3):
+        gpu = ones.Search(cl, jobs, stream=side)
+        gpu.generation(n)
+        gpu.close()
+        assert n == 1 or side.query()
+    gpu, cpu = ones.Search(cl, jobs, stream=side), ref.RefSearch(cl, jobs)
+    gpu.generation(5); cpu.generation(5)
+    assert_same_state(gpu, cpu, "behind them")
+    gpu.close(); cpu.close()
+
+
 @pytest.mark.parametrize("n_slots,n_gpus,pop", [(1, 0, 8), (64, 64, 64), (130, 90, 260), (2047, 70000, 64), (65, 2000, 1028)])
 def test_calls_that_wait_in_quick_succession(ones, ref, n_slots, n_gpus, pop):
     """Every call that goes through the pinned buffer, one after the other with new values each time: one workgroup or many to a
