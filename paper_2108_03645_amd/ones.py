@@ -131,7 +131,7 @@ def _address(a) -> int:
 def make_jobs(jobs):
     """Returns (struct, keepalive list) for any object carrying the nine job arrays."""
     keep = [np.ascontiguousarray(getattr(jobs, k), dtype=dt) for k, dt in _JOB_DTYPES.items()]
-    return ones_jobs(*map(_address, keep)), keep
+    return ones_jobs(*[_address(a) for a in keep]), keep
 
 
 def workspace_bytes(cluster) -> int:
@@ -204,7 +204,7 @@ class Search:
         arrs = [np.ascontiguousarray(x, np.float64) for x in (alpha, beta, processed)]
         if any(a.shape != (self.n_slots,) for a in arrs):
             raise ValueError("alpha, beta, processed: one entry per slot")
-        self._call(load().ones_set_progress, *map(_address, arrs))
+        self._call(load().ones_set_progress, *[_address(a) for a in arrs])
 
     def set_new_jobs_first(self, on=True):
         _check(load().ones_set_new_jobs_first(self._h, int(bool(on))))

@@ -95,3 +95,30 @@ def test_job_table_validation_needs_no_gpu():
                  lambda: L.ones_generation_static(None, 1), lambda: L.ones_set_wait_limit(None, 5)):
         assert call() == -1
     assert b"static scratch" in L.ones_strerror(-7)
+
+
+def test_calls_leave_nothing_for_the_garbage_collector():
+    """The tables and parameters that an epoch hands over leave no container objects behind: one a call would start a
+    collection every 700 epochs, and once in a while a full one, which takes 40 ms beside torch."""
+    import gc
+
+    import numpy as np
+
+    from paper_2108_03645_amd import ones, workloads
+    if not os.path.exists(ones.library_path()):
+        pytest.skip("libones.so not built here")
+    _, jobs = workloads.paper_scale()
+    search = object.__new__(ones.Search)                           # no GPU: the calls go nowhere
+    search.n_slots, search._call, search._h = 40, lambda function, *args: None, None
+    progress = [np.ones(40) for _ in range(3)]
+    gc.collect()                                                   # empties the interpreter's lists of free objects, too
+    gc.disable()
+    try:
+        before = gc.get_count()[0]
+        for _ in range(300):
+            ones.make_jobs(jobs)
+            search.set_progress(*progress)
+        left = gc.get_count()[0] - before
+    finally:
+        gc.enable()
+    assert left < 100, left
