@@ -811,7 +811,7 @@ __global__ __launch_bounds__(kThreads) void bucket_select_kernel(const double *f
     }
     // the other counter set and bitmaps, for the next generation
     if (tid == 0) count_next[b] = 0;
-    if (b == 0 && tid < static_cast<uint32_t>(kBucketCounters - kMaxBuckets)) count_next[kMaxBuckets + tid] = 0;
+    for (uint32_t c = kMaxBuckets + tid; b == 0 && c < static_cast<uint32_t>(kBucketCounters); c += kThreads) count_next[c] = 0;
     // (only the classes that it was used for: clearing all of them took 0.8 of the kernel's 6 us on the stress workload)
     const uint32_t words = tie_words(K), from = words * b / nb, to = words * (b + 1) / nb;        // 24576 * 1024 fits 32 bits
     const uint32_t *mask = ties_next + kTieClasses * words;
