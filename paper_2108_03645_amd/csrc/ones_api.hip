@@ -79,7 +79,7 @@ struct ScratchLayout {
 
 struct Layout {
   size_t genes, fit_row, slot_score, row_of, parent_row[2], spare, occupied[2], sel, fsync, xkeys, scratch, start, most, draws, lift, info[2], abl, cc, d, Y[kDrawRing], terms[kDrawRing];
-  size_t export_err, export_sel, export_fit, unpacked, rawinfo, ra, rc, rd, rY, alpha, beta, processed, time_rank, best_batch, best_gpus, best_fit, best_err, place_slot, place_batch, total;
+  size_t export_err, export_sel, export_fit, unpacked, rY, alpha, beta, processed, time_rank, total;
   ScratchLayout S;
 };
 
@@ -181,7 +181,7 @@ ScratchLayout make_scratch_layout(uint32_t P) {
 // Pool slots that ones_export unpacks at a time (16 MiB of batch sizes).
 uint32_t unpack_slots(uint32_t P, uint32_t Jp) { return std::min<uint32_t>(P, (16u << 20) / (Jp * 4)); }
 
-Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
+Layout make_layout(uint32_t P, uint32_t Jp) {
   Layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes); return at; };
@@ -214,30 +214,35 @@ Layout make_layout(uint32_t P, uint32_t Jp, uint32_t G) {
   // to the host, next to each other
   L.export_err = take(8); L.export_sel = take(static_cast<size_t>(P / 4) * 4); L.export_fit = take(static_cast<size_t>(P) * 8);
   L.unpacked = take(static_cast<size_t>(unpack_slots(P, Jp)) * Jp * 4);
-  L.rawinfo = take(Jp * 4);
-  L.ra = take(Jp * 8); L.rc = take(Jp * 8); L.rd = take(Jp * 8); L.rY = take(Jp * 8);
+  L.rY = take(Jp * 8);                            // the table's remaining work, for when sampling is switched off
   L.alpha = take(Jp * 8); L.beta = take(Jp * 8); L.processed = take(Jp * 8);
   L.time_rank = take(Jp * 4);
-  L.best_batch = take(Jp * 4); L.best_gpus = take(Jp * 4); L.best_fit = take(8); L.best_err = take(8);
-  L.place_slot = take(static_cast<size_t>(G) * 4); L.place_batch = take(static_cast<size_t>(G) * 4);
   L.total = off;
   return L;
 }
 
-// Host transfers go through one pinned staging buffer, which the kernels read and write themselves: laid out like the arrays
-// that travel together, which lie next to each other in the workspace (every size below is a multiple of the
-// 256-byte alignment except the last of a group).  Behind them HostWords.
-struct HostWords { uint32_t flag, winner, err[2]; double fit; };      // see HostSignal and WinnerOut; behind them its arrays
+// Host transfers go through one pinned staging buffer, which the kernels read and write themselves.  At its beginning lie the
+// arrays of the call that runs: a job table, the parameters of the draws or the ranks of the executed times, as they lie
+// in the workspace, or a placement.  Behind them HostWords and the winner's batch sizes and GPUs.
+struct HostWords { uint32_t flag, winner, err[2]; double fit; };      // see HostSignal and WinnerOut
+struct StageLayout { size_t rawinfo, a, c, d, Y, place_slot, place_batch, words, batch, gpus, total; };
 // A state of up to so much is exported that way too, through a buffer of its own that the first export allocates (a larger one
 // is copied).
 constexpr size_t kStagedExport = 256u << 10;
 size_t export_bytes(const Layout &L, uint32_t P, uint32_t Jp) { return L.unpacked + static_cast<size_t>(P) * Jp * 4 - L.export_err; }
-size_t stage_bytes(const Layout &L, uint32_t Jp, uint32_t G) {
-  const size_t table = L.rY + static_cast<size_t>(Jp) * 8 - L.rawinfo;        // rawinfo, a, c, d, Y
-  const size_t progress = L.processed + static_cast<size_t>(Jp) * 8 - L.alpha; // alpha, beta, processed
-  const size_t best = L.best_err + 8 - L.best_batch;                           // batch, gpus, fitness, error words
-  const size_t place = L.place_batch + static_cast<size_t>(G) * 4 - L.place_slot;
-  return align_up(std::max({table, progress, best, place, static_cast<size_t>(Jp) * 4}));
+StageLayout make_stage_layout(const Layout &L, uint32_t Jp, uint32_t G) {
+  StageLayout S;
+  size_t off = 0, end = 0;
+  auto take = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes); end = std::max(end, off); return at; };
+  S.rawinfo = take(Jp * 4); S.a = take(Jp * 8); S.c = take(Jp * 8); S.d = take(Jp * 8); S.Y = take(Jp * 8);
+  off = 0;
+  S.place_slot = take(static_cast<size_t>(G) * 4); S.place_batch = take(static_cast<size_t>(G) * 4);
+  off = 0;
+  take(std::max(L.processed + static_cast<size_t>(Jp) * 8 - L.alpha, static_cast<size_t>(Jp) * 4));
+  off = end;
+  S.words = take(sizeof(HostWords)); S.batch = take(Jp * 4); S.gpus = take(Jp * 4);
+  S.total = end;
+  return S;
 }
 
 int check_config(const ones_config *cfg) {
@@ -313,9 +318,9 @@ struct ones_ctx {
   uint32_t T_mut, T_x;
   hipStream_t stream;
   char *ws;
-  char *stage;                // pinned host staging buffer (stage_bytes), free between calls
+  char *stage;                // pinned host staging buffer, free between calls
   char *stage_dev;            // the same buffer as the device addresses it
-  size_t words_at;            // HostWords in it
+  StageLayout S;
   char *export_stage, *export_stage_dev;    // the same for ones_export, once it is used (kStagedExport)
   uint32_t signals;           // HostSignal: the value of the last one
   uint32_t winner;            // the last generation's winner comes with this signal (a whole call in one launch), or 0: it does not
@@ -365,8 +370,10 @@ struct ones_ctx {
                     at<double>(L.terms[which]), term_E};
   }
   JobTable table() const { return table(y_cur); }
-  volatile HostWords *host_words() const { return reinterpret_cast<volatile HostWords *>(stage + words_at); }
-  HostWords *host_words_dev() const { return reinterpret_cast<HostWords *>(stage_dev + words_at); }
+  template <typename T> T *staged(size_t off) const { return reinterpret_cast<T *>(stage + off); }
+  template <typename T> T *mapped(size_t off) const { return reinterpret_cast<T *>(stage_dev + off); }     // for kernels
+  volatile HostWords *host_words() const { return staged<volatile HostWords>(S.words); }
+  HostWords *host_words_dev() const { return mapped<HostWords>(S.words); }
 };
 
 namespace {
@@ -378,8 +385,7 @@ HostSignal next_signal(ones_ctx *c) {
 // For a launch that runs a whole call.
 WinnerOut next_winner(ones_ctx *c) {
   HostWords *words = c->host_words_dev();
-  int32_t *batch = reinterpret_cast<int32_t *>(words + 1);
-  return WinnerOut{batch, batch + c->Jp, &words->fit, &words->winner, words->err, c->Jn, next_signal(c)};
+  return WinnerOut{c->mapped<int32_t>(c->S.batch), c->mapped<int32_t>(c->S.gpus), &words->fit, &words->winner, words->err, c->Jn, next_signal(c)};
 }
 // Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
 // (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.4 ms
@@ -419,18 +425,15 @@ int wait_stream(ones_ctx *c) {
 
 int upload_table(ones_ctx *c, const HostJobs &h) {
   const size_t n4 = static_cast<size_t>(c->Jp) * 4, n8 = static_cast<size_t>(c->Jp) * 8;
-  const Layout &L = c->L;
-  auto staged = [&](size_t off) { return c->stage + (off - L.rawinfo); };   // laid out as in the workspace
-  memcpy(staged(L.rawinfo), h.rawinfo.data(), n4);
-  memcpy(staged(L.ra), h.a.data(), n8);
-  memcpy(staged(L.rc), h.c.data(), n8);
-  memcpy(staged(L.rd), h.d.data(), n8);
-  memcpy(staged(L.rY), h.Y.data(), n8);
-  auto mapped = [&](size_t off) { return c->stage_dev + (off - L.rawinfo); };
-  RawJobs raw{reinterpret_cast<uint32_t *>(mapped(L.rawinfo)), reinterpret_cast<double *>(mapped(L.ra)), reinterpret_cast<double *>(mapped(L.rc)),
-              reinterpret_cast<double *>(mapped(L.rd)), reinterpret_cast<double *>(mapped(L.rY))};
+  const StageLayout &S = c->S;
+  memcpy(c->stage + S.rawinfo, h.rawinfo.data(), n4);
+  memcpy(c->stage + S.a, h.a.data(), n8);
+  memcpy(c->stage + S.c, h.c.data(), n8);
+  memcpy(c->stage + S.d, h.d.data(), n8);
+  memcpy(c->stage + S.Y, h.Y.data(), n8);
+  RawJobs raw{c->mapped<uint32_t>(S.rawinfo), c->mapped<double>(S.a), c->mapped<double>(S.c), c->mapped<double>(S.d), c->mapped<double>(S.Y)};
   c->term_E = h.term_E;
-  HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(L.rY), c->Jp, next_signal(c), c->stream));
+  HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(c->L.rY), c->Jp, next_signal(c), c->stream));
   return wait_signal(c);                        // the staging buffer is free again
 }
 
@@ -602,8 +605,7 @@ int32_t ones_padded_jobs(int32_t n_slots) {
 
 size_t ones_workspace_bytes(const ones_config *cfg) {
   if (check_config(cfg) != ONES_OK) return 0;
-  return make_layout(static_cast<uint32_t>(cfg->population), static_cast<uint32_t>(ones_padded_jobs(cfg->n_slots)),
-                     static_cast<uint32_t>(cfg->n_gpus)).total;
+  return make_layout(static_cast<uint32_t>(cfg->population), static_cast<uint32_t>(ones_padded_jobs(cfg->n_slots))).total;
 }
 
 static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jobs, void *d_workspace,
@@ -614,8 +616,7 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   const int Jp = ones_padded_jobs(cfg->n_slots);
   HostJobs h;
   if ((rc = stage_jobs(cfg->n_slots, Jp, jobs, h))) return rc;
-  const Layout L = make_layout(static_cast<uint32_t>(cfg->population), static_cast<uint32_t>(Jp),
-                               static_cast<uint32_t>(cfg->n_gpus));
+  const Layout L = make_layout(static_cast<uint32_t>(cfg->population), static_cast<uint32_t>(Jp));
   if (!d_workspace) return ONES_E_INVALID_ARG;
   if (workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(d_workspace) & 255u) != 0)
     return ONES_E_WORKSPACE_TOO_SMALL;
@@ -635,8 +636,8 @@ static int init_impl(ones_ctx **out, const ones_config *cfg, const ones_jobs *jo
   c->export_stage = c->export_stage_dev = nullptr;
   {
     void *pinned = nullptr;
-    c->words_at = stage_bytes(L, static_cast<uint32_t>(Jp), static_cast<uint32_t>(cfg->n_gpus));
-    HIP_TRY(hipHostMalloc(&pinned, c->words_at + sizeof(HostWords) + 8 * static_cast<size_t>(Jp), hipHostMallocDefault));
+    c->S = make_stage_layout(L, c->Jp, c->G);
+    HIP_TRY(hipHostMalloc(&pinned, c->S.total, hipHostMallocDefault));
     c->stage = static_cast<char *>(pinned);
     c->host_words()->flag = c->host_words()->winner = c->signals = c->winner = 0;
     void *mapped = nullptr;
@@ -749,8 +750,7 @@ static int set_progress_impl(ones_ctx *c, const double *alpha, const double *bet
     if (alpha[j] > ONES_MAX_PARAM || beta[j] > ONES_MAX_PARAM || processed[j] > ONES_MAX_PARAM) return ONES_E_BOUNDS;
   }
   const Layout &L = c->L;
-  auto staged = [&](size_t off) { return reinterpret_cast<double *>(c->stage + (off - L.alpha)); };
-  double *ha = staged(L.alpha), *hb = staged(L.beta), *hp = staged(L.processed);   // laid out as in the workspace
+  double *ha = c->staged<double>(0), *hb = c->staged<double>(L.beta - L.alpha), *hp = c->staged<double>(L.processed - L.alpha);
   for (uint32_t j = 0; j < c->Jp; ++j) {
     const bool real = j < c->Jn;
     ha[j] = real ? alpha[j] : 1.0; hb[j] = real ? beta[j] : 1.0; hp[j] = real ? processed[j] : 0.0;
@@ -783,7 +783,7 @@ static int set_processed_time_impl(ones_ctx *c, const double *t_processed) {
   }
   // position of every slot in ascending (time, slot) order; the padding slots count as time 0
   std::vector<uint32_t> order(c->Jp);
-  uint32_t *rank = reinterpret_cast<uint32_t *>(c->stage);
+  uint32_t *rank = c->staged<uint32_t>(0);
   for (uint32_t j = 0; j < c->Jp; ++j) order[j] = j;
   auto time_of = [&](uint32_t j) { return j < c->Jn ? t_processed[j] : 0.0; };
   std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return time_of(x) < time_of(y); });
@@ -1011,62 +1011,48 @@ static int row_fault(ones_ctx *c) {
 // Rows of the current generation's survivors, best first.
 static const uint32_t *survivor_rows(const ones_ctx *c) { return c->at<uint32_t>(c->L.parent_row[c->cur ^ 1]); }
 
+// What a kernel found wrong, once its error words are there.
+static int check_error_words(ones_ctx *c) {
+  if (c->host_words()->err[0]) return wait_gave_up(c);
+  return c->host_words()->err[1] ? row_fault(c) : ONES_OK;
+}
+
 static int best_impl(ones_ctx *c, int32_t *batch_out, int32_t *gpus_out, double *fitness_out) {
   if (!c) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
-  auto hand_out = [&](const volatile void *batch, const volatile void *gpus, const volatile void *fit) {
-    if (batch_out && c->Jn) memcpy(batch_out, const_cast<const void *>(batch), c->Jn * 4);
-    if (gpus_out && c->Jn) memcpy(gpus_out, const_cast<const void *>(gpus), c->Jn * 4);
-    if (fitness_out) memcpy(fitness_out, const_cast<const void *>(fit), 8);
-    return ONES_OK;
-  };
+  HostWords *words = c->host_words_dev();
+  bool there = false;
   if (c->winner != 0 && c->winner == c->signals) {
     // the launch that ran the last call, which is this context's last one, leaves the winner in the pinned buffer
     if (int rc = wait_stream(c)) return rc;
-    volatile HostWords *words = c->host_words();
-    if (words->winner == c->winner) {
-      if (words->err[0]) return wait_gave_up(c);
-      if (words->err[1]) return row_fault(c);
-      const volatile int32_t *batch = reinterpret_cast<const volatile int32_t *>(words + 1);
-      return hand_out(batch, batch + c->Jp, &words->fit);
-    }
-    c->winner = 0;                  // it has given up
+    there = c->host_words()->winner == c->winner;
+    if (!there) c->winner = 0;      // it has given up
   }
-  // The kernel writes the winner and the two error words straight into the pinned host buffer
-  // (a few hundred bytes to a few kilobytes), laid out as the best_* block of the workspace:
-  // one launch and one wait, no copy.
-  const Layout &L = c->L;
-  auto mapped = [&](size_t off) { return c->stage_dev + (off - L.best_batch); };
-  HIP_TRY(launch_best(c->at<uint32_t>(c->L.genes), c->at<double>(c->L.fit_row), survivor_rows(c),
-                      c->at<uint32_t>(L.info[c->info_stored]),
-                      c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, reinterpret_cast<int32_t *>(mapped(L.best_batch)),
-                      reinterpret_cast<int32_t *>(mapped(L.best_gpus)),
-                      reinterpret_cast<double *>(mapped(L.best_fit)), c->at<uint32_t>(c->L.fsync) + 1,
-                      reinterpret_cast<uint32_t *>(mapped(L.best_err)), next_signal(c), c->stream));
-  if (int rc = wait_signal(c)) return rc;
-  auto staged = [&](size_t off) { return c->stage + (off - L.best_batch); };   // laid out as in the workspace
-  uint32_t words[2] = {0, 0};
-  memcpy(words, staged(L.best_err), 8);
-  if (words[0]) return wait_gave_up(c);
-  if (words[1]) return row_fault(c);
-  return hand_out(staged(L.best_batch), staged(L.best_gpus), staged(L.best_fit));
+  if (!there) {
+    // one launch and one wait, no copy (a few hundred bytes to a few kilobytes)
+    HIP_TRY(launch_best(c->at<uint32_t>(c->L.genes), c->at<double>(c->L.fit_row), survivor_rows(c), c->at<uint32_t>(c->L.info[c->info_stored]),
+                        c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->mapped<int32_t>(c->S.batch), c->mapped<int32_t>(c->S.gpus),
+                        &words->fit, c->at<uint32_t>(c->L.fsync) + 1, words->err, next_signal(c), c->stream));
+    if (int rc = wait_signal(c)) return rc;
+  }
+  if (int rc = check_error_words(c)) return rc;
+  if (batch_out && c->Jn) memcpy(batch_out, c->stage + c->S.batch, c->Jn * 4);
+  if (gpus_out && c->Jn) memcpy(gpus_out, c->stage + c->S.gpus, c->Jn * 4);
+  if (fitness_out) *fitness_out = c->host_words()->fit;
+  return ONES_OK;
 }
 
 static int placement_impl(ones_ctx *c, int32_t *slot_of_gpu, int32_t *batch_of_gpu) {
   if (!c || c->no_schedule) return ONES_E_INVALID_ARG;
   if (c->poisoned) return poisoned_error();
   const size_t n4 = static_cast<size_t>(c->G) * 4;
-  const Layout &L = c->L;
-  auto mapped = [&](size_t off) { return reinterpret_cast<int32_t *>(c->stage_dev + (off - L.place_slot)); };
-  HIP_TRY(launch_placement(c->at<uint32_t>(L.genes), survivor_rows(c), c->at<uint32_t>(L.info[c->info_now]), c->Jn, c->Jp, c->G, mapped(L.place_slot),
-                           mapped(L.place_batch), c->at<uint32_t>(L.fsync) + 1, c->host_words_dev()->err,
-                           next_signal(c), c->stream));
+  HIP_TRY(launch_placement(c->at<uint32_t>(c->L.genes), survivor_rows(c), c->at<uint32_t>(c->L.info[c->info_now]), c->Jn, c->Jp, c->G,
+                           c->mapped<int32_t>(c->S.place_slot), c->mapped<int32_t>(c->S.place_batch), c->at<uint32_t>(c->L.fsync) + 1,
+                           c->host_words_dev()->err, next_signal(c), c->stream));
   if (int rc = wait_signal(c)) return rc;
-  if (c->host_words()->err[0]) return wait_gave_up(c);
-  if (c->host_words()->err[1]) return row_fault(c);
-  auto staged = [&](size_t off) { return c->stage + (off - L.place_slot); };   // laid out as in the workspace
-  if (slot_of_gpu && c->G) memcpy(slot_of_gpu, staged(L.place_slot), n4);
-  if (batch_of_gpu && c->G) memcpy(batch_of_gpu, staged(L.place_batch), n4);
+  if (int rc = check_error_words(c)) return rc;
+  if (slot_of_gpu && c->G) memcpy(slot_of_gpu, c->stage + c->S.place_slot, n4);
+  if (batch_of_gpu && c->G) memcpy(batch_of_gpu, c->stage + c->S.place_batch, n4);
   return ONES_OK;
 }
 

@@ -122,3 +122,14 @@ def test_calls_leave_nothing_for_the_garbage_collector():
     finally:
         gc.enable()
     assert left < 100, left
+
+
+@pytest.mark.parametrize("n_slots,pop", [(1, 4), (700, 2052), (2048, 65536)])
+def test_the_workspace_does_not_grow_with_the_cluster(n_slots, pop):
+    """The search keeps nothing per GPU on the device: a placement is written to the host as it is made."""
+    from paper_2108_03645_amd import ones
+    if not os.path.exists(ones.library_path()):
+        pytest.skip("libones.so not built here")
+    sizes = {ones.load().ones_workspace_bytes(ctypes.byref(ones.ones_config(n_gpus, n_slots, pop, 1, 0.1, 0.5)))
+             for n_gpus in (0, 16, 4096, 1 << 20)}
+    assert len(sizes) == 1 and 0 not in sizes
