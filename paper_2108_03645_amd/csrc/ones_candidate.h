@@ -11,6 +11,7 @@
 // have gained little.
 #pragma once
 
+#include "ones.h"
 #include "ones_device.h"
 
 #include <algorithm>
@@ -219,13 +220,18 @@ struct Smem {
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
   uint64_t *drawn;         // [4 * kRound] the draws of those slots (PackedDraw)
   uint32_t *next_item;     // [1] the next work item of the round that no wave has taken yet
-  uint32_t *tie_count;     // [kTieClasses] children of this workgroup that are copies of a class of survivors (see kTieRun)
-  uint32_t *tie_bucket;    // [kTieClasses] ... and the bucket they belong to
+  // Children of this workgroup that are copies of a class of survivors (see kTieRun), and the bucket they belong to, [kTieClasses]
+  // each.  Under the table that the genes are stored under only, and so in the place of shift and fresh (and, of one word, of bl,
+  // which is for larger tables).  (In a place of their own, 1 KB, they cost shapes at the edge of a compute unit's LDS a workgroup or
+  // the table of terms: six generations of 32768 candidates, 1516 slots, jobs of up to 512 GPUs 446 us, 338 here; 492, 4096, over 2304
+  // GPUs 328 and 279; 1004, 32 GPUs 268 and 257.)
+  uint32_t *tie_count;
+  uint16_t *tie_bucket;
 };
 
 constexpr uint32_t kRound = 128;                     // survivors' ranks a workgroup covers between two barriers
 
-inline uint32_t row_groups(uint32_t rows) {
+constexpr uint32_t row_groups(uint32_t rows) {
   return ((rows + 31) / 32 + kRowGroupWords - 1) / kRowGroupWords;
 }
 
@@ -259,11 +265,17 @@ inline bool walk_pays(uint32_t Jp) { return Jp > 2 * kLanes; }
 constexpr size_t walk_table_bytes(uint32_t Q) { return 2 * (static_cast<size_t>(Q) * 4 * kLanes + kWindowAhead); }
 
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
-inline size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride, bool walk = false) {
+constexpr size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride, bool walk = false) {
   const size_t words = static_cast<size_t>(Q) * kLanes;
   return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 + (walk ? walk_table_bytes(Q) : 0) +
-         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16 + 2 * kTieClasses * 4;
+         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16;
 }
+// A compute unit hands LDS out in pieces of so much.
+constexpr size_t kLdsPiece = 1280;
+constexpr size_t lds_taken(size_t bytes) { return (bytes + kLdsPiece - 1) / kLdsPiece * kLdsPiece; }
+static_assert(kTieClasses * 6 <= 3 * kLanes * 4, "the copies' counts fit in the place of three arrays of one word");
+static_assert(smem_bytes(1, 8, kMaxTermEntries, ONES_MAX_POPULATION / 4 * 5, (kMaxCoinGpus / 32 + 4) / 4 * 4 * 8) <= kLdsBudget,
+              "of one word the third of them, bl, is not used: the term table always fits");
 
 template <int Q>
 __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t waves, uint32_t stride, bool walk = false) {
@@ -291,9 +303,9 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.coins = s.start_at + (walk ? walk_table_bytes(Q) : 0);
   s.rows = reinterpret_cast<uint32_t *>(s.coins + static_cast<size_t>(waves) * stride);
   s.next_item = s.rows + 4 * kRound;
-  s.tie_count = s.next_item + 4;
-  s.tie_bucket = s.tie_count + kTieClasses;
-  s.free_in_group = s.tie_bucket + kTieClasses;
+  s.free_in_group = s.next_item + 4;
+  s.tie_count = s.shift;
+  s.tie_bucket = reinterpret_cast<uint16_t *>(s.tie_count + kTieClasses);
   return s;
 }
 
@@ -978,7 +990,7 @@ __device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double
       KernelArgs *ka = kernel_args();
       const uint32_t c = (b - 1) / kTieRun, q = p - ka->K;
       atomicAdd(&s.tie_count[c], 1u);
-      s.tie_bucket[c] = b;
+      s.tie_bucket[c] = static_cast<uint16_t>(b);
       atomicOr(&ka->bk.ties[static_cast<size_t>(c) * tie_words(ka->K) + q / 32], 1u << (q % 32));
     }
     return;

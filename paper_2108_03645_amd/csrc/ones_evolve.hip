@@ -136,7 +136,10 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
   if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing, a.walk != 0);
-  if (kSameTable && threadIdx.x < static_cast<uint32_t>(kTieClasses)) s.tie_count[threadIdx.x] = 0;
+  if (kSameTable) {
+    if (a.term_lds == 0) __syncthreads();            // without a table of terms something has been staged in their place
+    if (threadIdx.x < static_cast<uint32_t>(kTieClasses)) s.tie_count[threadIdx.x] = 0;
+  }
   if (a.occupied_other != nullptr)
     for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < (a.P + K + 31) / 32; w += gridDim.x * blockDim.x)
       a.occupied_other[w] = 0;
@@ -261,19 +264,26 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
                    ? a.tab.term_E : 0u;
   size_t lds = smem_bytes(words, waves, a.term_lds, rows, a.coin_stride);
   if (lds > kLdsBudget) return hipErrorInvalidValue;
-  // as many workgroups as can be resident (LDS- and wave-limited), at most one wave per item.  Of eight waves
+  // as many workgroups as can be resident (limited by LDS and registers), at most one wave per item.  Of eight waves
   // three, though a fourth has room: what it costs to stage its tables is more than its waves hide
   // (epochs of 10 sampled generations, 130 slots, pool 16384: 526 us with four, 485 with three, 492 with
-  // two; pool 65536: 845, 799, 841; unsampled 512 slots, 16384: 19 us a generation's launch with four, 16.5 with three)
-  const size_t resident = waves == 8 ? 3 : 32 / waves;
-  const size_t per_cu = std::max<size_t>(1, std::min<size_t>(kLdsBudget / lds, resident));
-  // the repair walks where what that takes of LDS costs no workgroup its place on the compute unit
+  // two; pool 65536: 845, 799, 841; unsampled 512 slots, 16384: 19 us a generation's launch with four, 16.5 with three).
+  // Of sixteen, whose waves take 71 to 128 registers, one: a second would come after it and stage the tables again (six generations of
+  // 32768 candidates, jobs of one GPU at most: 1260 slots 227 us with two workgroups to a compute unit, 200 with one; 2028 299
+  // and 259; crossover over 3072 GPUs 311 and 259, 433 and 360).
+  const size_t resident = waves == 8 ? 3 : 1;
+  auto places = [&](size_t bytes) { return std::max<size_t>(1, std::min<size_t>(kLdsBudget / lds_taken(bytes), resident)); };
+  // The repair walks where it fits beside that, with two workgroups in place of three if need be (six generations of 32768
+  // candidates: 492 slots, jobs of up to 32 GPUs, crossover over 2816: 225 us walking, 237 with three workgroups; 748 slots, 8 GPUs, over
+  // 768: 231 and 287), but not with one in place of two (492 slots, 4096 GPUs, over 2304: 325 and 275; 748, 64, over 5376: 338 and 306),
+  // unless the items need no two.
   const uint32_t scratch = std::max<uint32_t>(a.coin_stride, window_bytes(words));
   const size_t walking = smem_bytes(words, waves, a.term_lds, rows, scratch, true);
-  a.walk = walk_pays(a.Jp) && walking * per_cu <= kLdsBudget ? 1u : 0u;
+  const uint32_t groups = std::max<uint32_t>(1u, std::min<uint32_t>((items + waves - 1) / waves, max_blocks));
+  const size_t needed = std::min<size_t>({places(lds), (groups + n_cus - 1) / n_cus, 2});
+  a.walk = walk_pays(a.Jp) && walking <= kLdsBudget && places(walking) >= needed ? 1u : 0u;
   if (a.walk) { a.coin_stride = scratch; lds = walking; }
-  const uint32_t blocks = std::max<uint32_t>(
-      1u, std::min<uint32_t>({(items + waves - 1) / waves, static_cast<uint32_t>(n_cus * per_cu), max_blocks}));
+  const uint32_t blocks = std::min<uint32_t>(groups, static_cast<uint32_t>(n_cus * places(lds)));
   hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                       static_cast<int>(lds));
   if (rc != hipSuccess) return rc;

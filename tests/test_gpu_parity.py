@@ -196,6 +196,43 @@ def test_children_that_copy_many_survivors(ones, ref, n_slots, n_gpus, pop, seed
         ref.set_threads(1)
 
 
+@pytest.mark.parametrize("n_slots,pop,seed,gens", [(200, 4356, 1, 12), (500, 4356, 2, 12), (1300, 4356, 3, 12), (2048, 8192, 4, 10)])
+def test_copies_where_a_job_may_take_a_million_gpus(ones, ref, n_slots, pop, seed, gens):
+    """Copies are counted in LDS in the place of what a new table needs of every slot.  With a table of terms of the largest width,
+    which fits at 200 and 500 slots and does not beyond, and tables that change in between.  (By the oracle: as above.)"""
+    rng = np.random.default_rng(seed)
+    jobs = random_jobs(rng, n_slots)
+    on = rng.permutation(n_slots)[:20]                     # a few jobs, so that copies come early
+    jobs.active = np.zeros(n_slots, np.uint8)
+    jobs.active[on] = 1
+    jobs.bmin[on[0]], jobs.bmax[on[0]], jobs.gpu_max_batch[on[0]] = 1, 1 << 20, 1
+    K, cl = pop // 4, cluster(30, n_slots, pop, seed=seed)
+    nb = min(1024, K // 16)
+    bounds = np.arange(1, nb) * K // nb
+    say(f"[parity] copies beside wide jobs: slots={n_slots} P={pop} seed={seed}")
+    ref.set_threads(8)
+    try:
+        gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+        seen = 0
+        for gen in range(gens):
+            _, fit, sel, _ = cpu.export(genes=False)
+            split, worst = fit[sel[bounds]], fit[sel[-1]]
+            gpu.generation(1); cpu.generation(1)
+            assert_same_state(gpu, cpu, f"generation {gen + 1}", genes=gen % 4 == 3)
+            children = cpu.export(genes=False)[1][K:]
+            seen += np.isin(children[children < worst], split[7:][split[7:] == split[:-7]]).sum()
+        assert seen > 0
+        jobs.remaining[on] *= 0.9
+        for s in (gpu, cpu):
+            s.set_jobs(jobs)
+            for _ in range(3):
+                s.generation(1)
+        assert_same_state(gpu, cpu, "under another table")
+        gpu.close(); cpu.close()
+    finally:
+        ref.set_threads(1)
+
+
 @pytest.mark.parametrize("pop", [4100, 8192, 20000, 40004])
 def test_bucketed_selection_and_table_changes(ones, ref, pop):
     """Pools above one sort chunk select through survivor-quantile buckets while the job table
