@@ -23,10 +23,10 @@ constexpr int kGroupFirst = 2 * ONES_ROW_GROUP + 1;   // words per lane kGroupFi
 // ----------------------------------------------------------------- kernels ---------
 template <int Q> struct Shape { static constexpr int kWaves = Q > 4 ? 16 : 8; };
 
-template <int Q, Genes kGenes, bool kArrivals>
+template <int Q, Genes kGenes, bool kArrivals, bool kWalk>
 __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uint32_t dst_row, uint32_t lr, uint32_t ir,
                                          uint32_t (&c)[Q], int lane, uint8_t *window) {
-  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, kArrivals && a.time_rank != nullptr, window, a.walk != 0);
+  repair<Q, kGenes, kArrivals>(c, s, a.G, lr, ir, lane, a.Jp, kArrivals && a.time_rank != nullptr, window, kWalk && a.walk != 0);
   phase_fence();
   const double f = score<Q>(c, s, a.term_lds, lane);
   phase_fence();
@@ -39,11 +39,11 @@ __device__ __forceinline__ double finish(const EvolveArgs &a, const Smem &s, uin
 
 // Initial population G_0: every gene uniform over {waiting, bmin..bmax}.
 // (Argument block: one EvolveArgs by value, see kernel_args.)
-template <int Q, Genes kGenes>
+template <int Q, Genes kGenes, bool kWalk>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, a.walk != 0);
-  stage_table<Q>(a, s, a.term_lds, false, threadIdx.x, blockDim.x, a.walk != 0);
+  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, kWalk && a.walk != 0);
+  stage_table<Q>(a, s, a.term_lds, false, threadIdx.x, blockDim.x, kWalk && a.walk != 0);
   uint8_t *window = s.coins + static_cast<size_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * a.coin_stride;
   if (threadIdx.x == 0) *s.next_item = 0;
   __syncthreads();
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
       c[q] = codes_of_draws(s, q * kLanes + lane, k);
     }
     phase_fence();
-    const double f = finish<Q, kGenes, false>(a, s, p, r / R, r % R, c, lane, window);   // slot p starts in row p
+    const double f = finish<Q, kGenes, false, kWalk>(a, s, p, r / R, r % R, c, lane, window);   // slot p starts in row p
     note_slot_score(p, f, lane);
     if (lane == 0) a.row_of[p] = p;
   }
@@ -86,11 +86,11 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void init_kernel(EvolveAr
 // jobs that arrived with it are served first.  kOverGpus: the uniform crossover scans the GPUs instead of the jobs.
 // (Argument block: one EvolveArgs by value, see kernel_args.)
 enum Table { kSame, kChanged, kArrivals };
-template <int Q, Table kTable, bool kOverGpus, Genes kGenes>
+template <int Q, Table kTable, bool kOverGpus, Genes kGenes, bool kWalk>
 __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(EvolveArgs a) {
   constexpr bool kSameTable = kTable == kSame;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, a.walk != 0);
+  const Smem s = carve<Q>(smem_raw, a.term_lds, Shape<Q>::kWaves, a.coin_stride, kWalk && a.walk != 0);
   const int lane0 = threadIdx.x & (kLanes - 1);
   const bool assigned = a.assigned != 0;
   if (!assigned) {
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     }
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
-  if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing, a.walk != 0);
+  if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing, kWalk && a.walk != 0);
   if (kSameTable) {
     if (a.term_lds == 0) __syncthreads();            // without a table of terms something has been staged in their place
     if (threadIdx.x < static_cast<uint32_t>(kTieClasses)) s.tie_count[threadIdx.x] = 0;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
     phase_fence();
     for (;;) {
       const uint32_t p = slot_at(ra, n, i);
-      const double f = finish<Q, kGenes, kTable == kArrivals>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane, window);
+      const double f = finish<Q, kGenes, kTable == kArrivals, kWalk>(a, s, row_at(s, i, a), d.lane(), d.row(), c, lane, window);
       if (kSameTable && a.bk.nb != 0) drop_in_bucket(s, p, f, lane); else note_slot_score(p, f, lane);
       if (--children == 0) break;
       phase_fence();
@@ -291,18 +291,26 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   return hipGetLastError();
 }
 
-template <int Q, Genes kGenes>
-hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
+template <int Q, Genes kGenes, bool kWalk>
+hipError_t launch_words_of(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
   constexpr int kWaves = Shape<Q>::kWaves;
-  if (a.t == 0) return launch_persistent(init_kernel<Q, kGenes>, a, Q, kWaves, a.P, a.P, n_cus, s);
+  if (a.t == 0) return launch_persistent(init_kernel<Q, kGenes, kWalk>, a, Q, kWaves, a.P, a.P, n_cus, s);
   const uint32_t items = (!same_table || a.rescore ? 3 : 2) * a.K;       // a share of the ranks each
   const Table table = same_table ? kSame : a.new_first ? kArrivals : kChanged;
   auto launch = [&](auto kernel) { return launch_persistent(kernel, a, Q, kWaves, items, a.K, n_cus, s); };
   switch (table) {
-    case kSame: return a.per_gpu ? launch(evolve_kernel<Q, kSame, true, kGenes>) : launch(evolve_kernel<Q, kSame, false, kGenes>);
-    case kChanged: return a.per_gpu ? launch(evolve_kernel<Q, kChanged, true, kGenes>) : launch(evolve_kernel<Q, kChanged, false, kGenes>);
-    default: return a.per_gpu ? launch(evolve_kernel<Q, kArrivals, true, kGenes>) : launch(evolve_kernel<Q, kArrivals, false, kGenes>);
+    case kSame: return a.per_gpu ? launch(evolve_kernel<Q, kSame, true, kGenes, kWalk>) : launch(evolve_kernel<Q, kSame, false, kGenes, kWalk>);
+    case kChanged: return a.per_gpu ? launch(evolve_kernel<Q, kChanged, true, kGenes, kWalk>) : launch(evolve_kernel<Q, kChanged, false, kGenes, kWalk>);
+    default: return a.per_gpu ? launch(evolve_kernel<Q, kArrivals, true, kGenes, kWalk>) : launch(evolve_kernel<Q, kArrivals, false, kGenes, kWalk>);
   }
+}
+
+template <int Q, Genes kGenes>
+hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
+  if constexpr (Q == 1) {
+    if (!walk_pays(a.Jp)) return launch_words_of<Q, kGenes, false>(a, same_table, n_cus, s);
+  }
+  return launch_words_of<Q, kGenes, true>(a, same_table, n_cus, s);
 }
 
 template <int Q>
