@@ -279,6 +279,7 @@ struct HostJobs {                     // validated, padded staging copy of a job
   std::vector<double> a, c, d, Y;
   std::vector<int64_t> id;
   uint32_t term_E = 2;                // waiting + GPU-count codes up to the largest bmax / gpu_max_batch
+  uint64_t demand = 0;                // GPUs that all jobs together take at their limits
 };
 
 int stage_jobs(int Jn, int Jp, const ones_jobs *jobs, HostJobs &h) {
@@ -286,6 +287,7 @@ int stage_jobs(int Jn, int Jp, const ones_jobs *jobs, HostJobs &h) {
   h.a.assign(Jp, 0.0); h.c.assign(Jp, 0.0); h.d.assign(Jp, 0.0); h.Y.assign(Jp, 0.0);
   h.id.assign(Jp, 0);
   h.term_E = 2;
+  h.demand = 0;
   if (Jn > 0 && (!jobs || !jobs->job_id || !jobs->active || !jobs->bmin || !jobs->bmax ||
                  !jobs->gpu_max_batch || !jobs->a || !jobs->c || !jobs->d || !jobs->remaining))
     return ONES_E_INVALID_ARG;
@@ -304,6 +306,7 @@ int stage_jobs(int Jn, int Jp, const ones_jobs *jobs, HostJobs &h) {
                    (static_cast<uint32_t>(mu) << 10) | (1u << 15);
     h.a[j] = jobs->a[j]; h.c[j] = jobs->c[j]; h.d[j] = jobs->d[j]; h.Y[j] = jobs->remaining[j];
     h.term_E = std::max<uint32_t>(h.term_E, static_cast<uint32_t>(std::max(0, hi - mu)) + 2);
+    h.demand += 1u << std::max(0, hi - mu);
   }
   return ONES_OK;
 }
@@ -354,6 +357,7 @@ struct ones_ctx {
   char *static_scratch;       // this device's copy of the library's static scratch array
   int n_cus;
   uint32_t term_E;            // entries per job of the term table
+  uint64_t demand;            // GPUs that the table's jobs take at their limits
   int64_t t;                  // generation counter
   std::vector<int64_t> ids;   // job identity per slot, to detect slots that change hands
   // measurement
@@ -433,6 +437,7 @@ int upload_table(ones_ctx *c, const HostJobs &h) {
   memcpy(c->stage + S.Y, h.Y.data(), n8);
   RawJobs raw{c->mapped<uint32_t>(S.rawinfo), c->mapped<double>(S.a), c->mapped<double>(S.c), c->mapped<double>(S.d), c->mapped<double>(S.Y)};
   c->term_E = h.term_E;
+  c->demand = h.demand;
   HIP_TRY(launch_table_change(raw, c->table(), c->at<double>(c->L.rY), c->Jp, next_signal(c), c->stream));
   return wait_signal(c);                        // the staging buffer is free again
 }
@@ -519,7 +524,8 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.rescore = same_table && sampled ? 1u : 0u;
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;   // the table's "arrived" marks are fresh
   a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.coin_stride = a.walk = 0;                                    // the launcher sets them
+  a.coin_stride = 0;                                             // the launcher sets it
+  a.walk = walk_pays(c->Jp, c->G, c->demand) ? 1u : 0u;
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   a.slot_score = c->at<double>(c->L.slot_score);
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
@@ -817,6 +823,7 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
   a.per_gpu = c->per_gpu ? 1u : 0u;
+  a.walk = walk_pays(c->Jp, c->G, c->demand) ? 1u : 0u;
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   return a;
 }

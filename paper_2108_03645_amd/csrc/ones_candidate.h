@@ -258,10 +258,6 @@ static_assert(Window<1>::kBytes == window_bytes(1) && Window<2>::kBytes == windo
 static_assert(Window<2>::kPositions <= kWindowAhead && Window<4>::kPositions <= kWindowAhead && Window<8>::kPositions <= kWindowAhead,
               "start_at and most_at reach as far as the window");
 // Their LDS beside the wave's scratch.
-// Whole genomes of one or two rows of slots are shed and filled in fewer instructions than it takes to lay a window out and walk it
-// (17 slots, pool 7676, sampled: an epoch of 44 generations 1037 us walking, 994 not; 103 slots, pool 15844, 4 generations 115 and 111;
-// three rows: 130 slots, pool 260, 8 generations 106 and 110; four: 212 slots, pool 15848, 40 generations 893 and 923).
-inline bool walk_pays(uint32_t Jp) { return Jp > 2 * kLanes; }
 constexpr size_t walk_table_bytes(uint32_t Q) { return 2 * (static_cast<size_t>(Q) * 4 * kLanes + kWindowAhead); }
 
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.

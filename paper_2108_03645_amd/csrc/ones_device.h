@@ -158,6 +158,16 @@ struct WinnerOut {
   HostSignal done;
 };
 
+// Whether the repair is faster if it walks along the genes near its start (see Window), on G GPUs, with jobs that would take `demand`
+// of them at their limits.  Whole genomes of one or two rows of slots are shed and filled in fewer instructions than it takes
+// to lay a window out and walk it (17 slots, pool 7676, sampled: an epoch of 44 generations 1037 us walking, 994 not; 103 slots, pool
+// 15844, 4 generations 115 and 111; three rows: 130 slots, pool 260, 8 generations 106 and 110; four: 212 slots, pool 15848, 40
+// generations 893 and 923).  And where the GPUs are enough for nearly all jobs, few of them ask for more, and the walk leaves its
+// window: 1004 slots, pool 32768, six generations on 0.7, 0.9, 1 and 1.05 times the demand 206, 230, 213 and 244 us walking, 227, 227,
+// 187 and 203 not; 200 slots 139, 144, 135 and 151, 140, 136, 122 and 129; 2028, whose genomes take longer, 276, 303, 274 and 287, 311,
+// 310, 250 and 271.
+inline bool walk_pays(uint32_t Jp, uint32_t G, uint64_t demand) { return Jp > 2 * kLanes && 20ull * G <= (Jp > 1024 ? 19 : 17) * demand; }
+
 // Genomes live in physical rows; a candidate keeps its row for as long as it survives, so a
 // survivor is never copied.  The pool of P slots uses P + K rows.  While a generation is computed
 // the K survivors hold theirs (parent_row); 3K rows are for the new children and mutants, by slot
@@ -190,7 +200,8 @@ struct EvolveArgs {
   uint32_t       rescore;     // the survivors' scores are stale (remaining work redrawn): score them again
   uint32_t       per_gpu;     // the uniform crossover scans the GPUs (Eq. 1) instead of the jobs; needs G <= kMaxCoinGpus
   uint32_t       coin_stride; // set by the launcher: bytes of LDS scratch per wave
-  uint32_t       walk;        // set by the launcher: LDS holds what the repair needs to walk along the genes near its start
+  uint32_t       walk;        // the repair walks along the genes near its start: walk_pays, and then whether the launcher finds
+                              // room in LDS for what it needs
   uint32_t       term_lds;    // set by the launcher: entries per job of the term table in LDS, 0 = none
   uint32_t       *fault;      // [1] raised when a row index had to be pulled back into the genome array
   double         *slot_score; // [P] the score of every candidate this launch scores, by pool slot (written when

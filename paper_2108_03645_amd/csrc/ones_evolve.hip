@@ -281,7 +281,7 @@ hipError_t launch_persistent(Kernel k, EvolveArgs a, int words, int waves, uint3
   const size_t walking = smem_bytes(words, waves, a.term_lds, rows, scratch, true);
   const uint32_t groups = std::max<uint32_t>(1u, std::min<uint32_t>((items + waves - 1) / waves, max_blocks));
   const size_t needed = std::min<size_t>({places(lds), (groups + n_cus - 1) / n_cus, 2});
-  a.walk = walk_pays(a.Jp) && walking <= kLdsBudget && places(walking) >= needed ? 1u : 0u;
+  a.walk = a.walk != 0 && walking <= kLdsBudget && places(walking) >= needed ? 1u : 0u;
   if (a.walk) { a.coin_stride = scratch; lds = walking; }
   const uint32_t blocks = std::min<uint32_t>(groups, static_cast<uint32_t>(n_cus * places(lds)));
   hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -308,7 +308,7 @@ hipError_t launch_words_of(const EvolveArgs &a, bool same_table, int n_cus, hipS
 template <int Q, Genes kGenes>
 hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
   if constexpr (Q == 1) {
-    if (!walk_pays(a.Jp)) return launch_words_of<Q, kGenes, false>(a, same_table, n_cus, s);
+    if (a.walk == 0) return launch_words_of<Q, kGenes, false>(a, same_table, n_cus, s);
   }
   return launch_words_of<Q, kGenes, true>(a, same_table, n_cus, s);
 }

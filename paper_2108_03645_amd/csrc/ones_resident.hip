@@ -970,7 +970,7 @@ bool resident_plan(const EvolveArgs &ev, bool sampled, int n_cus, ResidentPlan &
   plan.segment = (plan.paired ? 2 : 1) * plan.child_items;
   plan.list = kResLeastList;
   size_t least = 0;
-  for (plan.walk = walk_pays(ev.Jp);; plan.walk = 0) {  // the repair walks where there is room for it
+  for (plan.walk = ev.walk;; plan.walk = 0) {  // the repair walks where there is room for it
     plan.coin_stride = plan.walk ? std::max<uint32_t>(coin_stride(ev), window_bytes(Q)) : coin_stride(ev);
     plan.table_lds = static_cast<uint32_t>((table_bytes(Q, ev.tab.term_E, plan.coin_stride, plan.walk != 0) + 15) & ~size_t(15));
     least = plan.table_lds + ranking_bytes(Q, ev.P, plan);

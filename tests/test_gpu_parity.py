@@ -1,6 +1,7 @@
 """GPU parity: libones (HIP, through the C ABI) against the CPU oracle on the same seeded
 inputs.  Genomes and survivor lists must match bit for bit every generation; scores within
 1e-12 relative (they are expected to be bit-identical too, which is asserted separately)."""
+import copy
 import os
 import subprocess
 import sys
@@ -1864,6 +1865,28 @@ def test_repair_walks_near_its_start(ones, ref, n_slots, share):
     for n in (1, 1, 4):                                # launched by generation, then, up to 1024 slots, in one launch
         gpu.generation(n); cpu.generation(n)
         assert_same_state(gpu, cpu, f"generation {gpu.export(genes=False)[3]}")
+    gpu.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n_slots", [130, 256, 700, 1024, 1030, 2048])
+@pytest.mark.parametrize("share", [0.845, 0.855, 0.945, 0.955])
+def test_repair_where_the_walk_begins_to_pay(ones, ref, n_slots, share):
+    """Clusters on either side of the shares of what the jobs could take, 0.85 and beyond 1024 slots 0.95, up to which the
+    repair walks; with a table in between under which it is the other way."""
+    test_repair_walks_near_its_start(ones, ref, n_slots, share)
+    rng = np.random.default_rng(n_slots)
+    jobs = wide_table(rng, n_slots, 3)
+    most = int(np.where(jobs.active != 0, np.maximum(jobs.bmax // jobs.gpu_max_batch, 1), 0).sum())
+    cl = cluster(int(share * most), n_slots, 260, seed=n_slots)
+    gpu, cpu = ones.Search(cl, jobs), ref.RefSearch(cl, jobs)
+    for active in (0.5, 1.0):                              # half of the jobs leave and come back
+        now = copy.deepcopy(jobs)
+        now.active = jobs.active & (rng.random(n_slots) < active).astype(np.uint8)
+        for s in (gpu, cpu):
+            s.set_jobs(now)
+        for n in (1, 1, 5):
+            gpu.generation(n); cpu.generation(n)
+        assert_same_state(gpu, cpu, f"{active} of the jobs")
     gpu.close(); cpu.close()
 
 
