@@ -525,7 +525,7 @@ int run_generation(ones_ctx *c, uint32_t t, char *scratch, bool &splitters_valid
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;   // the table's "arrived" marks are fresh
   a.per_gpu = c->per_gpu ? 1u : 0u;
   a.coin_stride = 0;                                             // the launcher sets it
-  a.walk = walk_pays(c->Jp, c->G, c->demand) ? 1u : 0u;
+  a.walk = walk_pays(c->Jp, c->G, c->demand, false) ? 1u : 0u;
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   a.slot_score = c->at<double>(c->L.slot_score);
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
@@ -823,7 +823,7 @@ static EvolveArgs whole_call_args(const ones_ctx *c) {
   a.new_first = c->new_jobs_first && c->no_schedule ? 1u : 0u;
   a.time_rank = c->has_times ? c->at<uint32_t>(c->L.time_rank) : nullptr;
   a.per_gpu = c->per_gpu ? 1u : 0u;
-  a.walk = walk_pays(c->Jp, c->G, c->demand) ? 1u : 0u;
+  a.walk = walk_pays(c->Jp, c->G, c->demand, true) ? 1u : 0u;
   a.fault = c->at<uint32_t>(c->L.fsync) + 2;
   return a;
 }

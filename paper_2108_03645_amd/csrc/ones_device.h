@@ -162,11 +162,18 @@ struct WinnerOut {
 // of them at their limits.  Whole genomes of one or two rows of slots are shed and filled in fewer instructions than it takes
 // to lay a window out and walk it (17 slots, pool 7676, sampled: an epoch of 44 generations 1037 us walking, 994 not; 103 slots, pool
 // 15844, 4 generations 115 and 111; three rows: 130 slots, pool 260, 8 generations 106 and 110; four: 212 slots, pool 15848, 40
-// generations 893 and 923).  And where the GPUs are enough for nearly all jobs, few of them ask for more, and the walk leaves its
-// window: 1004 slots, pool 32768, six generations on 0.7, 0.9, 1 and 1.05 times the demand 206, 230, 213 and 244 us walking, 227, 227,
-// 187 and 203 not; 200 slots 139, 144, 135 and 151, 140, 136, 122 and 129; 2028, whose genomes take longer, 276, 303, 274 and 287, 311,
-// 310, 250 and 271.
-inline bool walk_pays(uint32_t Jp, uint32_t G, uint64_t demand) { return Jp > 2 * kLanes && 20ull * G <= (Jp > 1024 ? 19 : 17) * demand; }
+// generations 893 and 923).  And where the GPUs are enough for most jobs, few of them ask for more, and the walk leaves its window, the
+// sooner the shorter the genome (six generations on 0.7, 0.9, 1 and 1.05 of the demand: 1004 slots, pool 32768 206, 230, 213 and
+// 244 us walking, 227, 227, 187 and 203 not; 200 slots 139, 144, 135 and 151, 140, 136, 122 and 129; 2028 276, 303, 274 and 287,
+// 311, 310, 250 and 271; speed of walking on 0.5, 0.6, 0.7 and 0.8, jobs of up to 16 GPUs: 140 slots, pool 20000 0.96, 0.95, 0.96 and 0.97, 200,
+// pool 32768 1.08, 1.03, 1.01 and 0.96, 1004 1.18, 1.11, 1.07 and 1.08).  A launch that runs whole calls (whole_call) waits for its
+// slowest wave in every generation, and there it pays less (200 slots, pool 8192 1.01, 0.98, 0.95 and 0.93; 500 1.05, 0.97, 0.90 and
+// 0.87; 1000, pool 4096 1.02, 0.95, 0.95 and 0.91; jobs of up to 4 GPUs 1.01, 1.04, 1.02 and 0.99; 1.05, 1.03, 1.00 and 0.97; 1.08, 1.05,
+// 0.99 and 0.89).
+inline bool walk_pays(uint32_t Jp, uint32_t G, uint64_t demand, bool whole_call) {
+  const uint32_t twentieths = whole_call ? 11 : Jp <= 256 ? 13 : Jp <= 1024 ? 17 : 19;
+  return Jp > 2 * kLanes && 20ull * G <= twentieths * demand;
+}
 
 // Genomes live in physical rows; a candidate keeps its row for as long as it survives, so a
 // survivor is never copied.  The pool of P slots uses P + K rows.  While a generation is computed

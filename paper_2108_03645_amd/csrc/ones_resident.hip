@@ -193,7 +193,7 @@ __device__ __forceinline__ void load_shared_genes(const uint32_t *genes, uint32_
 
 // One item of generation t: composed, repaired and scored, its genomes stored; done(slot, which child of the item, row,
 // score) takes note of each candidate.  rows: of the item's children.
-template <int Q, Genes kGenes, bool kOverGpus, bool kSameTable, typename Done>
+template <int Q, Genes kGenes, bool kOverGpus, bool kSameTable, bool kWalk, typename Done>
 __device__ __forceinline__ void compose_item(const EvolveArgs &a, uint32_t t, const Smem &s, const Ranking &rk, const Deal &deal, uint32_t i,
                                              bool new_first, uint64_t *coins, const uint32_t *draws, const uint32_t *words,
                                              const uint16_t *rows, int lane, Done done) {
@@ -245,8 +245,8 @@ __device__ __forceinline__ void compose_item(const EvolveArgs &a, uint32_t t, co
     phase_fence();
     const uint32_t lr = start & 0xFFFFu, ir = start >> 16;
     uint8_t *window = reinterpret_cast<uint8_t *>(coins);
-    if (!kSameTable && new_first) repair<Q, kGenes, true>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank != nullptr, window, a.walk != 0);
-    else repair<Q, kGenes, false>(c, s, a.G, lr, ir, lane, a.Jp, false, window, a.walk != 0);
+    if (!kSameTable && new_first) repair<Q, kGenes, true>(c, s, a.G, lr, ir, lane, a.Jp, a.time_rank != nullptr, window, kWalk);
+    else repair<Q, kGenes, false>(c, s, a.G, lr, ir, lane, a.Jp, false, window, kWalk);
     phase_fence();
     const double f = score<Q>(c, s, a.term_lds, lane);
     uint32_t *at = a.genes + static_cast<size_t>(row) * (Q * kLanes) + lane;
@@ -419,13 +419,13 @@ __device__ __forceinline__ void count_all_below(const Ranking &rk, uint32_t n, u
 static_assert(offsetof(ResidentArgs, ev) == 0, "kernel_args() reads the EvolveArgs at the start of the argument block");
 // kSampled: the remaining work is drawn anew for every generation (Alg. 1, Eq. 7) and the whole pool, survivors
 // included, is scored with the draw; the draws and their term tables have been made ahead (a ring in memory).
-template <int Q, Genes kGenes, bool kOverGpus, bool kSampled>
+template <int Q, Genes kGenes, bool kOverGpus, bool kSampled, bool kWalk>
 __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const EvolveArgs &a = ra.ev;
   const uint32_t P = a.P, K = a.K, tid = threadIdx.x, E = a.term_lds;
   const Deal deal{K, gridDim.x, blockIdx.x, ra.paired, (ra.paired ? 2u : 3u) * K};
-  const Smem s = carve_table<Q>(smem_raw, E, a.walk != 0);
+  const Smem s = carve_table<Q>(smem_raw, E, kWalk);
   const Ranking rk = carve_ranking(smem_raw + ra.table_lds, Q, P, deal.groups, ra.list, ra.child_items);
   const int lane0 = tid & (kLanes - 1);
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
     }
   };
 
-  stage_table<Q>(a, s, E, ra.first_changed != 0, tid, kResThreads, a.walk != 0);
+  stage_table<Q>(a, s, E, ra.first_changed != 0, tid, kResThreads, kWalk);
   // the state the last selection left: the survivors' rows and scores, the rows of the units
   for (uint32_t e = tid; e < K; e += kResThreads) {
     const uint32_t row = checked_row(ra.parent_rows[e], P + K);
@@ -516,10 +516,10 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
         load_shared_genes<Q>(a.genes, row, lane, c);
         done(e, 0u, row, score<Q>(c, s, E, lane));
       } else if (changed) {
-        compose_item<Q, kGenes, kOverGpus, false>(a, t, s, rk, deal, i, new_first, coins, rk.draws + 3 * m, rk.words + m * Q * kLanes,
+        compose_item<Q, kGenes, kOverGpus, false, kWalk>(a, t, s, rk, deal, i, new_first, coins, rk.draws + 3 * m, rk.words + m * Q * kLanes,
                                                   rk.rows + 2 * m, lane, done);
       } else {
-        compose_item<Q, kGenes, kOverGpus, true>(a, t, s, rk, deal, i, false, coins, rk.draws + 3 * m, rk.words + m * Q * kLanes,
+        compose_item<Q, kGenes, kOverGpus, true, kWalk>(a, t, s, rk, deal, i, false, coins, rk.draws + 3 * m, rk.words + m * Q * kLanes,
                                                  rk.rows + 2 * m, lane, done);
       }
       uint32_t taken = 0;
@@ -923,13 +923,17 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs ra) 
   }
 }
 
+template <int Q, Genes kGenes, bool kOverGpus, bool kSampled>
+const void *kernel_of(const ResidentPlan &plan) {
+  return plan.walk ? reinterpret_cast<const void *>(resident_kernel<Q, kGenes, kOverGpus, kSampled, true>)
+                   : reinterpret_cast<const void *>(resident_kernel<Q, kGenes, kOverGpus, kSampled, false>);
+}
+
 template <int Q, Genes kGenes>
 hipError_t launch_genes(const ResidentArgs &args, const ResidentPlan &plan, hipStream_t stream) {
   const bool over = args.ev.per_gpu != 0, sampled = args.sampled != 0;
-  const void *fn = over ? (sampled ? reinterpret_cast<const void *>(resident_kernel<Q, kGenes, true, true>)
-                                   : reinterpret_cast<const void *>(resident_kernel<Q, kGenes, true, false>))
-                        : (sampled ? reinterpret_cast<const void *>(resident_kernel<Q, kGenes, false, true>)
-                                   : reinterpret_cast<const void *>(resident_kernel<Q, kGenes, false, false>));
+  const void *fn = over ? (sampled ? kernel_of<Q, kGenes, true, true>(plan) : kernel_of<Q, kGenes, true, false>(plan))
+                        : (sampled ? kernel_of<Q, kGenes, false, true>(plan) : kernel_of<Q, kGenes, false, false>(plan));
   const hipError_t rc = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(plan.lds));
   if (rc != hipSuccess) return rc;
   ResidentArgs ra = args;

@@ -1869,10 +1869,10 @@ def test_repair_walks_near_its_start(ones, ref, n_slots, share):
 
 
 @pytest.mark.parametrize("n_slots", [130, 256, 700, 1024, 1030, 2048])
-@pytest.mark.parametrize("share", [0.845, 0.855, 0.945, 0.955])
+@pytest.mark.parametrize("share", [0.545, 0.555, 0.645, 0.655, 0.845, 0.855, 0.945, 0.955])
 def test_repair_where_the_walk_begins_to_pay(ones, ref, n_slots, share):
-    """Clusters on either side of the shares of what the jobs could take, 0.85 and beyond 1024 slots 0.95, up to which the
-    repair walks; with a table in between under which it is the other way."""
+    """Clusters on either side of the shares of what the jobs could take up to which the repair walks, 0.55 in one launch and, by
+    generation, 0.65 up to 256 slots, 0.85 up to 1024 and 0.95 beyond; with a table in between under which it is the other way."""
     test_repair_walks_near_its_start(ones, ref, n_slots, share)
     rng = np.random.default_rng(n_slots)
     jobs = wide_table(rng, n_slots, 3)
