@@ -307,7 +307,7 @@ hipError_t launch_words_of(const EvolveArgs &a, bool same_table, int n_cus, hipS
 
 template <int Q, Genes kGenes>
 hipError_t launch_words(const EvolveArgs &a, bool same_table, int n_cus, hipStream_t s) {
-  if constexpr (Q == 1) {
+  if constexpr (Q <= 4) {
     if (a.walk == 0) return launch_words_of<Q, kGenes, false>(a, same_table, n_cus, s);
   }
   return launch_words_of<Q, kGenes, true>(a, same_table, n_cus, s);
