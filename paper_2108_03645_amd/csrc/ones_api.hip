@@ -392,7 +392,7 @@ WinnerOut next_winner(ones_ctx *c) {
   return WinnerOut{c->mapped<int32_t>(c->S.batch), c->mapped<int32_t>(c->S.gpus), &words->fit, &words->winner, words->err, c->Jn, next_signal(c)};
 }
 // Waits for the last signal.  The poll leaves a longer wait to the runtime, which reports what goes wrong on the device.
-// (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.4 ms
+// (The runtime clears up after launches as they come, and after the last some hundred when it is next asked to wait: 0.1 to 0.6 ms
 // that ones_destroy or the next ones_init pays once.  Asked every 16 signals to, an epoch took 5 to 15 us more, every 64 2 to 4.)
 constexpr std::chrono::milliseconds kPollTime(4);
 using PollClock = std::chrono::steady_clock;

@@ -683,8 +683,8 @@ __device__ __forceinline__ uint32_t accept_prefix(const uint32_t (&v)[Q], uint32
 // of it are laid out in LDS in visiting order, and the wave walks along them, a gene per lane, 64 positions a step of some 25
 // instructions; a cut and a fill round over whole genomes are 150 and 270 at eight words.
 // The kernels are bound by the issue of vector instructions: a generation of the stress workload issued 5.0e7 with whole genomes
-// and issues 3.8e7 now (86 -> 74 us in a search's first 300 generations); epochs: 200 slots, pool 8192 205 -> 192 us, 512 slots,
-// pool 16384 820 -> 779, stress 1771 -> 1679.  A window that the walk leaves (few asks, or many idle GPUs) costs it some 100
+// and 3.8e7 walking (86 and 74 us in a search's first 300 generations; other steps have taken both down since); epochs: 200 slots, pool 8192
+// 205 -> 192 us, 512 slots, pool 16384 820 -> 779, stress 1771 -> 1679.  A window that the walk leaves (few asks, or many idle GPUs) costs it some 100
 // instructions; the round then goes on over whole genomes.  Where more than kPositions GPUs are idle it is not tried.
 template <int Q>
 __device__ __forceinline__ bool in_window(uint32_t lr, int lane, uint32_t &at) {
