@@ -220,13 +220,6 @@ struct Smem {
   uint32_t *rows;          // [4 * kRound] rows of the slots this workgroup fills in the current round
   uint64_t *drawn;         // [4 * kRound] the draws of those slots (PackedDraw)
   uint32_t *next_item;     // [1] the next work item of the round that no wave has taken yet
-  // Children of this workgroup that are copies of a class of survivors (see kTieRun), and the bucket they belong to, [kTieClasses]
-  // each.  Under the table that the genes are stored under only, and so in the place of shift and fresh (and, of one word, of bl,
-  // which is for larger tables).  (In a place of their own, 1 KB, they cost shapes at the edge of a compute unit's LDS a workgroup or
-  // the table of terms: six generations of 32768 candidates, 1516 slots, jobs of up to 512 GPUs 446 us, 338 here; 492, 4096, over 2304
-  // GPUs 328 and 279; 1004, 32 GPUs 268 and 257.)
-  uint32_t *tie_count;
-  uint16_t *tie_bucket;
 };
 
 constexpr uint32_t kRound = 128;                     // survivors' ranks a workgroup covers between two barriers
@@ -260,18 +253,24 @@ static_assert(Window<2>::kPositions <= kWindowAhead && Window<4>::kPositions <= 
 // Their LDS beside the wave's scratch.
 constexpr size_t walk_table_bytes(uint32_t Q) { return 2 * (static_cast<size_t>(Q) * 4 * kLanes + kWindowAhead); }
 
+constexpr uint32_t kTieBytes = kTieClasses * 6;
+static_assert(kTieBytes <= 3 * kLanes * 4, "the copies' counts fit in the place of three arrays of one word");
 // E = entries per job of the term table kept in LDS, 0 = keep the four model parameters.
 constexpr size_t smem_bytes(uint32_t Q, int waves, uint32_t E, uint32_t rows, uint32_t stride, bool walk = false) {
   const size_t words = static_cast<size_t>(Q) * kLanes;
   return words * 4 * 8 * (E ? E : 4) + (kMaxBuckets + 1) * 8 + 4 * kRound * 8 + words * 8 + words * 4 * 7 + (walk ? walk_table_bytes(Q) : 0) +
-         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16;
+         static_cast<size_t>(waves) * stride + static_cast<size_t>(row_groups(rows)) * 4 + 4 * kRound * 4 + 16 + (E ? 0 : kTieBytes);
 }
+// Children of this workgroup that are copies of a class of survivors (see kTieRun), [kTieClasses], and, 16 bits each behind them, the
+// bucket they belong to.  Only counted under the table that the genes are stored under, and so in the place of shift, fresh and bl,
+// unless the term table does not fit, when all three are staged.  (In a place of their own, 1 KB, they cost shapes at the edge of a
+// compute unit's LDS a workgroup or the table of terms: six generations of 32768 candidates, 1516 slots, jobs of up to 512 GPUs 446 us,
+// 338 here; 492, 4096, over 2304 GPUs 328 and 279; 1004, 32 GPUs 268 and 257.)
+__device__ __forceinline__ uint32_t *tie_counts(const Smem &s, uint32_t E) { return E ? s.shift : s.next_item + 4; }
+__device__ __forceinline__ uint16_t *tie_buckets(uint32_t *counts) { return reinterpret_cast<uint16_t *>(counts + kTieClasses); }
 // A compute unit hands LDS out in pieces of so much.
 constexpr size_t kLdsPiece = 1280;
 constexpr size_t lds_taken(size_t bytes) { return (bytes + kLdsPiece - 1) / kLdsPiece * kLdsPiece; }
-static_assert(kTieClasses * 6 <= 3 * kLanes * 4, "the copies' counts fit in the place of three arrays of one word");
-static_assert(smem_bytes(1, 8, kMaxTermEntries, ONES_MAX_POPULATION / 4 * 5, (kMaxCoinGpus / 32 + 4) / 4 * 4 * 8) <= kLdsBudget,
-              "of one word the third of them, bl, is not used: the term table always fits");
 
 template <int Q>
 __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t waves, uint32_t stride, bool walk = false) {
@@ -299,9 +298,7 @@ __device__ __forceinline__ Smem carve(unsigned char *at, uint32_t E, uint32_t wa
   s.coins = s.start_at + (walk ? walk_table_bytes(Q) : 0);
   s.rows = reinterpret_cast<uint32_t *>(s.coins + static_cast<size_t>(waves) * stride);
   s.next_item = s.rows + 4 * kRound;
-  s.free_in_group = s.next_item + 4;
-  s.tie_count = s.shift;
-  s.tie_bucket = reinterpret_cast<uint16_t *>(s.tie_count + kTieClasses);
+  s.free_in_group = s.next_item + 4 + (E ? 0 : kTieBytes / 4);
   return s;
 }
 
@@ -985,8 +982,9 @@ __device__ __forceinline__ void drop_in_bucket(const Smem &s, uint32_t p, double
     if (lane == 0) {
       KernelArgs *ka = kernel_args();
       const uint32_t c = (b - 1) / kTieRun, q = p - ka->K;
-      atomicAdd(&s.tie_count[c], 1u);
-      s.tie_bucket[c] = static_cast<uint16_t>(b);
+      uint32_t *counts = tie_counts(s, ka->term_lds);
+      atomicAdd(&counts[c], 1u);
+      tie_buckets(counts)[c] = static_cast<uint16_t>(b);
       atomicOr(&ka->bk.ties[static_cast<size_t>(c) * tie_words(ka->K) + q / 32], 1u << (q % 32));
     }
     return;

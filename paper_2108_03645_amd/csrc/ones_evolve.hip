@@ -136,10 +136,7 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   };
   if (first < last) prepare_round(first, min(kRound, last - first));
   if (threadIdx.x >= listing) stage_table<Q>(a, s, a.term_lds, !kSameTable, threadIdx.x - listing, blockDim.x - listing, kWalk && a.walk != 0);
-  if (kSameTable) {
-    if (a.term_lds == 0) __syncthreads();            // without a table of terms something has been staged in their place
-    if (threadIdx.x < static_cast<uint32_t>(kTieClasses)) s.tie_count[threadIdx.x] = 0;
-  }
+  if (kSameTable && threadIdx.x < static_cast<uint32_t>(kTieClasses)) tie_counts(s, a.term_lds)[threadIdx.x] = 0;
   if (a.occupied_other != nullptr)
     for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < (a.P + K + 31) / 32; w += gridDim.x * blockDim.x)
       a.occupied_other[w] = 0;
@@ -245,10 +242,11 @@ __global__ __launch_bounds__(Shape<Q>::kWaves *kLanes) void evolve_kernel(Evolve
   }
   if (kSameTable && a.bk.nb != 0) {                  // one count a workgroup and class of copies, not one a child
     __syncthreads();
-    const uint32_t copies = threadIdx.x < static_cast<uint32_t>(kTieClasses) ? s.tie_count[threadIdx.x] : 0u;
+    uint32_t *counts = tie_counts(s, a.term_lds);
+    const uint32_t copies = threadIdx.x < static_cast<uint32_t>(kTieClasses) ? counts[threadIdx.x] : 0u;
     if (copies != 0) {
       atomicAdd(&a.bk.count[kTieCount + threadIdx.x], copies);
-      a.bk.count[kTieBucket + threadIdx.x] = s.tie_bucket[threadIdx.x];
+      a.bk.count[kTieBucket + threadIdx.x] = tie_buckets(counts)[threadIdx.x];
       a.bk.count[kTieFlag] = 1;
     }
   }
