@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published peak
 
 # HBM bytes per evolve launch on the stress workload from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (see profiles/), valid only for the kernel source with this hash.
-MEASURED_TRAFFIC = {"source_sha256": "a7cbf167408289e3957629766ad947212c7f4966881ecbc2bac6ea3495297ba3", "bytes_per_launch": 201876425}
+MEASURED_TRAFFIC = {"source_sha256": "c24745a4a00a7922779ad113cb13ded0f7962e97ee65980ca6c3661dbbb6aaca", "bytes_per_launch": 201937086}
 
 
 def evolve_source_hash() -> str:
